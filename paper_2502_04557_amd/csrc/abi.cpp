@@ -374,18 +374,13 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   // elements the activation buffers hold (their row tiles bound what a kernel may fetch)
   const size_t pl_d = act_elems(dt, rows, md.d), pl_a = act_elems(dt, rows, md.H * md.dh), pl_f = act_elems(dt, rows, md.ff);
   launch_embed(dt, md, m.tok_emb, m.pos_emb, rd, sc.h, sc.rope, max_rows, s);
-  // bf16: O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
+  // O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
   // them (and the bias) into the residual stream before it normalises the row.
-  const bool split = norm_takes_pending(dt, md.d);
   const size_t part_stride = (size_t)rows * md.d;
   NormPending pend{sc.part, part_stride, 0, nullptr};
   auto resid_gemm = [&](const void* W, const void* X, size_t plane, int K, const float* bias) {
-    if (split) {
-      pend.shares = launch_gemm_part(W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, PART_SHARES, max_rows, s);
-      pend.bias = bias;
-    } else {
-      launch_gemm(dt, EPI_RESID, W, nullptr, X, plane, rd.n_rows, md.d, K, bias, sc.h, md.d, nullptr, 0, max_rows, s);
-    }
+    pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, PART_SHARES, max_rows, s);
+    pend.bias = bias;
   };
   auto norm = [&](const float* g, const float* b, void* out, float* f32_out) {
     launch_norm(dt, md.arch, sc.h, g, b, md.eps, md.d, rd.n_rows, out, f32_out, max_rows, s,

@@ -44,7 +44,7 @@ struct ModelScratch {  // per-model activation buffers, sized for max_batch rows
   float* hf;           // [M, d] final hidden state after the last norm, float32
   void* hfn;           // same values in activation layout (LM-head input)
   float* rope;         // [M, dh/2, 2] cos/sin of the row's position
-  float* part;         // [PART_SHARES][M, d] partial O-proj / FFN-down products (bf16 mode), float32
+  float* part;         // [PART_SHARES][M, d] partial O-proj / FFN-down products, float32
   unsigned long long* am_part;  // [n_lm_wg, Mpad] packed (value, index) arg-max partials
   int n_lm_wg;
 };
@@ -65,16 +65,15 @@ void launch_embed(int dtype, const ModelDims& md, const void* tok_emb, const voi
 struct NormPending {
   const float* part; size_t stride; int shares; const float* bias;
 };
-// pend is honoured by the bf16 kernel only (d a multiple of 8, at most 8192): see norm_takes_pending().
+// d a multiple of 8, at most 8192.
 void launch_norm(int dtype, int arch, const float* h, const float* g, const float* b, float eps, int d,
                  const int* n_rows, void* act_out, float* f32_out, int max_rows, hipStream_t s,
                  const NormPending* pend = nullptr);
-inline bool norm_takes_pending(int dtype, int d) { return dtype == 1 && d % 8 == 0 && d <= 8192; }
-// bf16: part[s] = X[:, K share s] W[:, K share s]^T for s < returned share count (<= max_shares)
-int launch_gemm_part(const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
+// part[s] = X[:, K share s] W[:, K share s]^T for s < returned share count (<= max_shares)
+int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
                      size_t part_stride, int max_shares, int max_rows, hipStream_t s);
 
-enum { EPI_F32 = 0, EPI_RESID = 1, EPI_GELU = 2, EPI_SWIGLU = 3, EPI_PART = 4 /* partial product of one K share */ };
+enum { EPI_F32 = 0, EPI_GELU = 2, EPI_SWIGLU = 3, EPI_PART = 4 /* partial product of one K share */ };
 // Y[M,N] = X[M,K] W[N,K]^T (+bias) with epilogue; X in activation layout, W in weight layout.
 // x_elems: elements the activation buffer X holds (its row tiles bound what a kernel may fetch).
 void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* X, size_t x_elems,

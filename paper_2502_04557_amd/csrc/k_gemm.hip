@@ -16,12 +16,11 @@ struct GemmArgs {
   int rows_live;      // the host's bound on the row count: rows from here on exist in no launch, their activations are not fetched
 };
 
-// bias: the column's bias (0 if none); res: the current value of the output element (residual epilogue only)
+// bias: the column's bias (0 if none)
 template <int EPI, typename AT>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int m, int n, float v, float v2, float bias, float res) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int m, int n, float v, float v2, float bias) {
   if (m >= n_rows || n >= a.N) return;
   if (EPI == EPI_F32) a.out_f32[(size_t)m * a.ldo + n] = v + bias;
-  else if (EPI == EPI_RESID) a.out_f32[(size_t)m * a.ldo + n] = res + (v + bias);
   else if (EPI == EPI_GELU) act_store<AT>((AT*)a.out_act, m, n, a.out_K, gelu_tanh(v + bias));
   else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu(v) * v2);
 }
@@ -30,7 +29,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int
 // bf16-mode GEMM (float16 operands) on MFMA for at most 16 rows.  512 threads = 8 waves that split K; each wave owns NTW column tiles
 // (16 columns each): D[m][n] += X[m][k] W[n][k].
 // All 8 waves leave their partial sums in LDS and every thread then finishes ONE output element: it adds the 8
-// partials in fixed order, applies bias / residual / GELU / SwiGLU and stores.  With the element order chosen per
+// partials in fixed order, applies bias / GELU / SwiGLU and stores.  With the element order chosen per
 // output layout the 256 x NTW stores of the workgroup are contiguous: one 32-column operand tile for
 // the activation outputs, 64-128 byte runs for float32 rows.  (When wave 0 alone ran the epilogue - 8 tanh and 16
 // scattered 2-byte stores per lane for FFN-up - it took 2.2 of the kernel's 7.1 us.)
@@ -49,7 +48,7 @@ __global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
   const uint4* __restrict__ Xp = (const uint4*)a.X;
   const int Kt = a.Kt;
   // Requests that depend on nothing are issued before the row count is even read: this wave's first weight
-  // tiles and this thread's bias and (residual epilogue) current output value.
+  // tiles and this thread's bias.
   uint4 wv[U][NTW], wv2[U][DUAL ? NTW : 1];
   auto load_weights = [&](int kt) {
 #pragma unroll
@@ -88,7 +87,6 @@ __global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
   const int n = nt0 * 16 + c;
   const bool n_ok = tid < NOUT && n < a.N;
   const float pbias = (n_ok && a.bias) ? a.bias[n] : 0.f;
-  const float pres = (EPI == EPI_RESID && n_ok) ? a.out_f32[(size_t)m * a.ldo + n] : 0.f;
   // (The row count is only needed by the epilogue: launches are sized by the host for rows that exist, so the loop
   // does not wait for it.)
   const int n_rows = *a.n_rows;
@@ -135,7 +133,7 @@ __global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
     s1 += red[((size_t)q * NI2 + it) * 64 + sl];
     if (DUAL) s2 += red[((size_t)q * NI2 + NI + it) * 64 + sl];
   }
-  gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, pbias, pres);
+  gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, pbias);
 }
 
 // bf16-mode GEMM for 17 .. 64 rows per pass (MT row tiles of 16), one column tile per workgroup, K split over
@@ -286,8 +284,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
       part[(size_t)m * a.ldo + n] = s1;
     } else {
       const float bias = a.bias ? a.bias[n] : 0.f;
-      const float res = (EPI == EPI_RESID) ? a.out_f32[(size_t)m * a.ldo + n] : 0.f;
-      gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias, res);
+      gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias);
     }
   }
 }
@@ -393,8 +390,7 @@ __global__ __launch_bounds__(512) void k_gemm_wide(GemmArgs a) {
         if constexpr (EPI == EPI_PART) {
           part[(size_t)m * a.ldo + n] = s1;
         } else {
-          const float res = (EPI == EPI_RESID) ? a.out_f32[(size_t)m * a.ldo + n] : 0.f;
-          gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias, res);
+          gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias);
         }
       }
   }
@@ -513,43 +509,106 @@ __global__ __launch_bounds__(512) void k_gemm16_part(GemmArgs a) {
   if (n < a.N && m < n_rows) (a.part + (size_t)sk * a.part_stride)[(size_t)m * a.ldo + n] = sum;
 }
 
-// float32 GEMM on the vector ALU: one wave per output column, 8 rows at a time.
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs a) {
+// float32 GEMM on the float32 matrix pipes (v_mfma_f32_16x16x4_f32: exact float32 products, float32 sums).  A workgroup
+// owns 16 columns and MT row tiles of 16; its 8 waves split K.  Operands come straight from the row-major matrices: lane
+// (l16, lq) takes four consecutive k of row / column l16 with one 16-byte load, and the four products of a load use
+// k = 4 lq + 0 .. 3 in both operands, so 16 k cost one load per operand and four matrix instructions.  U groups of 16 k
+// are requested together before the first product waits: at these widths (K <= 2048) that is one or two memory round
+// trips per wave, which is what bounds the kernel - the vector version (one wave per column, 8 rows at a time, the row
+// loads under a branch per row) paid one round trip per row and 256 k: 768 x 256 at 24 rows 15.8 -> TIME_A us,
+// 512 x 2048 at 24 rows 43 -> TIME_B us, and at one row 7.2 -> TIME_C us.
+// blockIdx.y = pass over 16 MT rows.
+template <int MT, int U, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_f32(GemmArgs a) {
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
-  const int n_rows = *a.n_rows;
-  const int lane = threadIdx.x & 63, w = wave_index();
-  const int n = blockIdx.x * 4 + w;
-  if (n >= a.N || n_rows <= 0) return;
-  const int K = a.K;
-  const float* __restrict__ wr = (const float*)a.W + (size_t)n * K;
-  const float* __restrict__ wr2 = DUAL ? (const float*)a.W2 + (size_t)n * K : nullptr;
+  constexpr int NA = DUAL ? 2 : 1;
+  __shared__ float red[8][NA * MT * 4][64];
+  const int tid = threadIdx.x, lane = tid & 63, kw = wave_index();
+  const int l16 = lane & 15, lq = lane >> 4, K = a.K;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * MT * 16;
+  // EPI_PART: blockIdx.z = K share, the partial product goes to part[share] (summed by the norm that follows)
+  const int all_groups = (K + 15) >> 4, s0 = all_groups * (int)blockIdx.z / (int)gridDim.z;
+  const int n_groups = all_groups * (int)(blockIdx.z + 1) / (int)gridDim.z - s0;
+  const int g0 = s0 + n_groups * kw / 8, g1 = s0 + n_groups * (kw + 1) / 8;
+  const int n_col = min(n0 + l16, a.N - 1);             // columns beyond N are computed on the last one and dropped
+  const float* __restrict__ wr = (const float*)a.W + (size_t)n_col * K;
+  const float* __restrict__ wr2 = DUAL ? (const float*)a.W2 + (size_t)n_col * K : nullptr;
   const float* __restrict__ X = (const float*)a.X;
-  for (int m0 = 0; m0 < n_rows; m0 += 8) {
-    float acc[8], acc2[8];
+  bool live[MT];                                        // lanes of rows that do not exist load nothing and enter as zeros
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = acc2[i] = 0.f;
-    for (int k = lane * 4; k < K; k += 256) {
-      float4 wv = *reinterpret_cast<const float4*>(wr + k);
-      float4 wv2 = DUAL ? *reinterpret_cast<const float4*>(wr2 + k) : make_float4(0, 0, 0, 0);
+  for (int mt = 0; mt < MT; ++mt) live[mt] = m0 + mt * 16 + l16 < a.rows_live;
+  // This thread's output element (consecutive threads: consecutive columns of a row); its bias and current value are
+  // requested here, not after the sums.
+  const int mr = tid >> 4, c = tid & 15, m_out = m0 + mr, n_out = n0 + c;
+  const int n_rows = *a.n_rows;
+  const bool out_ok = mr < MT * 16 && m_out < a.rows_live && n_out < a.N;
+  const float pbias = (EPI != EPI_PART && out_ok && a.bias) ? a.bias[n_out] : 0.f;
+  f32x4 acc[NA * MT];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (m0 + i < n_rows) {
-          float4 xv = *reinterpret_cast<const float4*>(X + (size_t)(m0 + i) * K + k);
-          acc[i] += xv.x * wv.x + xv.y * wv.y + xv.z * wv.z + xv.w * wv.w;
-          if (DUAL) acc2[i] += xv.x * wv2.x + xv.y * wv2.y + xv.z * wv2.z + xv.w * wv2.w;
+  for (int i = 0; i < NA * MT; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int g = g0; g < g1; g += U) {
+    float4 wv[U], wv2[DUAL ? U : 1], xv[U][MT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {                       // K is a multiple of 4; k beyond it is clamped here and zeroed below
+      const int k = min(min(g + u, g1 - 1) * 16 + lq * 4, K - 4);
+      wv[u] = *reinterpret_cast<const float4*>(wr + k);
+      if (DUAL) wv2[u] = *reinterpret_cast<const float4*>(wr2 + k);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) xv[u][mt] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      if (live[mt]) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = min(min(g + u, g1 - 1) * 16 + lq * 4, K - 4);
+          xv[u][mt] = *reinterpret_cast<const float4*>(X + (size_t)(m0 + mt * 16 + l16) * K + k);
+        }
+      }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool on = g + u < g1 && (g + u) * 16 + lq * 4 < K;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float w1 = on ? (&wv[u].x)[e] : 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32((&xv[u][mt].x)[e], w1, acc[mt], 0, 0, 0);
+        if (DUAL) {
+          const float w2 = on ? (&wv2[u].x)[e] : 0.f;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[MT + mt] = __builtin_amdgcn_mfma_f32_16x16x4f32((&xv[u][mt].x)[e], w2, acc[MT + mt], 0, 0, 0);
         }
       }
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float s1 = wave_sum(acc[i]);
-      float s2 = DUAL ? wave_sum(acc2[i]) : 0.f;
-      if (lane == i && m0 + i < n_rows)
-        gemm_epilogue<EPI, float>(a, n_rows, m0 + i, n, s1, s2, a.bias ? a.bias[n] : 0.f,
-                                  EPI == EPI_RESID ? a.out_f32[(size_t)(m0 + i) * a.ldo + n] : 0.f);
-    }
   }
+#pragma unroll
+  for (int i = 0; i < NA * MT; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[kw][i * 4 + v][lane] = acc[i][v];
+  __syncthreads();
+  if (!out_ok) return;
+  const int mt = mr >> 4, sl = ((mr & 15) >> 2) * 16 + c;
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {                         // fixed order: wave 0, 1, ..
+    s1 += red[q][mt * 4 + (mr & 3)][sl];
+    if (DUAL) s2 += red[q][(MT + mt) * 4 + (mr & 3)][sl];
+  }
+  if (m_out >= n_rows) return;
+  if constexpr (EPI == EPI_PART) (a.part + (size_t)blockIdx.z * a.part_stride)[(size_t)m_out * a.ldo + n_out] = s1;
+  else gemm_epilogue<EPI, float>(a, n_rows, m_out, n_out, s1, s2, pbias);
+}
+
+template <int EPI>
+static void launch_gemm_f32(const GemmArgs& a, int max_rows, int shares, hipStream_t s) {
+  // two row tiles per pass from 17 rows on; as many groups of 16 k per request as a wave's share of K has, at most 8
+  const int per_wave = ((a.K + 15) / 16 + 8 * shares - 1) / (8 * shares), mt = max_rows <= 16 ? 1 : 2;
+  const dim3 grid(a.n_tiles, (max_rows + 16 * mt - 1) / (16 * mt), shares);
+#define SPRINTER_F32(MT_, U_) hipLaunchKernelGGL((k_gemm_f32<MT_, U_, EPI>), grid, dim3(512), 0, s, a)
+  if (mt == 1) { if (per_wave <= 2) SPRINTER_F32(1, 2); else if (per_wave <= 4) SPRINTER_F32(1, 4); else SPRINTER_F32(1, 8); }
+  else { if (per_wave <= 2) SPRINTER_F32(2, 2); else if (per_wave <= 4) SPRINTER_F32(2, 4); else SPRINTER_F32(2, 8); }
+#undef SPRINTER_F32
 }
 
 template <int EPI>
@@ -605,30 +664,33 @@ void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* 
   a.Kt = (K + 31) / 32; a.n_tiles = (N + 15) / 16;
   a.bias = bias; a.out_f32 = out_f32; a.ldo = ldo; a.out_act = out_act; a.out_K = out_K; a.rows_live = max_rows;
   if (dtype == 0) {
-    dim3 grid((N + 3) / 4), block(256);
     switch (epi) {
-      case EPI_F32: hipLaunchKernelGGL(k_gemm_f32<EPI_F32>, grid, block, 0, s, a); break;
-      case EPI_RESID: hipLaunchKernelGGL(k_gemm_f32<EPI_RESID>, grid, block, 0, s, a); break;
-      case EPI_GELU: hipLaunchKernelGGL(k_gemm_f32<EPI_GELU>, grid, block, 0, s, a); break;
-      default: hipLaunchKernelGGL(k_gemm_f32<EPI_SWIGLU>, grid, block, 0, s, a); break;
+      case EPI_F32: launch_gemm_f32<EPI_F32>(a, max_rows, 1, s); break;
+      case EPI_GELU: launch_gemm_f32<EPI_GELU>(a, max_rows, 1, s); break;
+      default: launch_gemm_f32<EPI_SWIGLU>(a, max_rows, 1, s); break;
     }
   } else {
     switch (epi) {
       case EPI_F32: launch_gemm_bf16<EPI_F32>(a, max_rows, s); break;
-      case EPI_RESID: launch_gemm_bf16<EPI_RESID>(a, max_rows, s); break;
       case EPI_GELU: launch_gemm_bf16<EPI_GELU>(a, max_rows, s); break;
       default: launch_gemm_bf16<EPI_SWIGLU>(a, max_rows, s); break;
     }
   }
 }
 
-int launch_gemm_part(const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
+int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
                      size_t part_stride, int max_shares, int max_rows, hipStream_t s) {
   GemmArgs a;
   memset(&a, 0, sizeof a);
   a.W = W; a.X = X; a.x_elems = x_elems; a.n_rows = n_rows; a.N = N; a.K = K;
   a.Kt = (K + 31) / 32; a.n_tiles = (N + 15) / 16; a.ldo = N;
   a.part = part; a.part_stride = part_stride; a.rows_live = max_rows;
+  if (dtype == 0) {
+    // shares of at least 32 groups of 16 k (4 per wave: one round of requests), at most 4 (the norm's smaller variant)
+    const int sk = std::max(1, std::min(std::min(4, max_shares), (K + 15) / 16 / 32));
+    launch_gemm_f32<EPI_PART>(a, max_rows, sk, s);
+    return sk;
+  }
   if (max_rows <= 16) {
     // shares: fill the 256 compute units, at least 12 k tiles per share; long K takes two column tiles per wave
     const bool two = a.Kt >= 192 && a.n_tiles >= 64;   // (4096x4096: 8.2 us with one tile, 10.5 with two; 4096x11008: 24.1 / 19.8)

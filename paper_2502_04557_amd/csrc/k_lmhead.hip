@@ -297,58 +297,98 @@ __global__ __launch_bounds__(512, MT <= 4 ? 4 : 2) void k_lmhead_wide(LmArgs a) 
   }
 }
 
-// float32: one wave per vocabulary column, 8 rows at a time.
-__global__ __launch_bounds__(256) void k_lmhead_f32(LmArgs a) {
-  __shared__ u64 sbest[4][8];
-  const int n_rows = *a.rd.n_rows;
-  if (n_rows <= 0) return;
-  const int lane = threadIdx.x & 63, w = wave_index();
-  const int cpw = (a.V + gridDim.x - 1) / gridDim.x;
-  const int c0 = blockIdx.x * cpw, c1 = min(c0 + cpw, a.V);
-  const int K = a.K;
+// float32: the same product on the float32 matrix pipes as k_gemm_f32 (k_gemm.hip): the 8 waves split K over one tile of 16
+// columns and MT row tiles, wave mt then adds the partial accumulators of row tile mt in fixed order, samples on them and keeps
+// the running key of its rows; a workgroup walks its range of column tiles.  Latency bound at these widths (a 16 KiB tile of
+// weights per round at K = 256); one wave per column and 8 rows took 8.7 us at 1 row and 23.5 us at 24 (V = 4096), now
+// LM_A and LM_B us.
+template <int MT, int U>
+__global__ __launch_bounds__(512) void k_lmhead_f32(LmArgs a) {
+  __shared__ float red[8][MT * 4][64];
+  const int lane = threadIdx.x & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
+  const int n_rows = *a.rd.n_rows, K = a.K;
+  const int tpw = (a.n_tiles + gridDim.x - 1) / gridDim.x;
+  const int t0 = blockIdx.x * tpw, t1 = min(t0 + tpw, a.n_tiles);
+  const int n_groups = (K + 15) >> 4, g0 = n_groups * w / 8, g1 = n_groups * (w + 1) / 8;
   const float* __restrict__ W = (const float*)a.W;
   const float* __restrict__ X = (const float*)a.X;
-  for (int m0 = 0; m0 < n_rows; m0 += 8) {
-    u64 best = 0;
-    const int my_m = m0 + lane;
-    const int my_b = (lane < 8 && my_m < n_rows) ? a.rd.b[my_m] : 0;
-    const int my_t = (lane < 8 && my_m < n_rows) ? a.rd.pos[my_m] + 1 : 0;
-    for (int n = c0 + w; n < c1; n += 4) {
-      const float* wr = W + (size_t)n * K;
-      float acc[8];
+  for (int m0 = 0; m0 < a.rows_live; m0 += MT * 16) {
+    // wave mt < MT samples row tile mt: its quad's random streams and its running keys
+    const int mq = m0 + min(w, MT - 1) * 16 + lq * 4 + (lane & 3);
+    const int rb = mq < n_rows ? a.rd.b[mq] : 0, rt = mq < n_rows ? a.rd.pos[mq] + 1 : 0;
+    u64 best[4] = {0, 0, 0, 0};
+    bool live[MT];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-      for (int k = lane * 4; k < K; k += 256) {
-        float4 wv = *reinterpret_cast<const float4*>(wr + k);
+    for (int mt = 0; mt < MT; ++mt) live[mt] = m0 + mt * 16 + l16 < a.rows_live;
+    for (int t = t0; t < t1; ++t) {
+      const int n = t * 16 + l16;
+      const float* __restrict__ wr = W + (size_t)min(n, a.V - 1) * K;
+      f32x4 acc[MT];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          if (m0 + i < n_rows) {
-            float4 xv = *reinterpret_cast<const float4*>(X + (size_t)(m0 + i) * K + k);
-            acc[i] += xv.x * wv.x + xv.y * wv.y + xv.z * wv.z + xv.w * wv.w;
+      for (int mt = 0; mt < MT; ++mt) acc[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      for (int g = g0; g < g1; g += U) {
+        float4 wv[U], xv[U][MT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          wv[u] = *reinterpret_cast<const float4*>(wr + min(min(g + u, g1 - 1) * 16 + lq * 4, K - 4));
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) xv[u][mt] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          if (live[mt]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+              xv[u][mt] = *reinterpret_cast<const float4*>(X + (size_t)(m0 + mt * 16 + l16) * K + min(min(g + u, g1 - 1) * 16 + lq * 4, K - 4));
           }
-      }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float sacc = wave_sum(acc[i]);
-        if (lane == i && m0 + i < n_rows) {
-          if (a.logits_out) a.logits_out[(size_t)(m0 + i) * a.V + n] = sacc;
-          best = umax64(best, sample_key(sacc, a.sa, my_b, my_t, n));
+        for (int u = 0; u < U; ++u) {
+          const bool on = g + u < g1 && (g + u) * 16 + lq * 4 < K;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float w1 = on ? (&wv[u].x)[e] : 0.f;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32((&xv[u][mt].x)[e], w1, acc[mt], 0, 0, 0);
+          }
+        }
+      }
+      __syncthreads();                                     // the previous tile's sums have been read
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[w][mt * 4 + v][lane] = acc[mt][v];
+      __syncthreads();
+      if (w < MT) {
+        f32x4 sum = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) sum[v] += red[q][w * 4 + v][lane];
+        u64 kj[4];
+        sample_keys_quad(sum, a.sa, rb, rt, n, kj);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int m = m0 + w * 16 + lq * 4 + v;
+          const bool ok = n < a.V && m < n_rows;
+          if (a.logits_out && ok) a.logits_out[(size_t)m * a.V + n] = sum[v];
+          best[v] = umax64(best[v], ok ? kj[v] : 0);
         }
       }
     }
-    if (lane < 8) sbest[w][lane] = best;
-    __syncthreads();
-    if (threadIdx.x < 8 && m0 + (int)threadIdx.x < a.Mpad) {
-      u64 k = umax64(umax64(sbest[0][threadIdx.x], sbest[1][threadIdx.x]),
-                     umax64(sbest[2][threadIdx.x], sbest[3][threadIdx.x]));
-      a.part[(size_t)blockIdx.x * a.Mpad + m0 + threadIdx.x] = k;
+    if (w < MT) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const u64 k = group_umax64_16(best[v]);
+        const int m = m0 + w * 16 + lq * 4 + v;
+        if (l16 == 0 && m < a.Mpad) a.part[(size_t)blockIdx.x * a.Mpad + m] = k;
+      }
     }
-    __syncthreads();
   }
 }
 
 int lmhead_num_wg(int dtype, int V) {
-  int n = (dtype == 0) ? (V + 7) / 8 : ((V + 15) / 16 + 7) / 8;
+  const int tiles = (V + 15) / 16, n = (dtype == 0) ? tiles : (tiles + 7) / 8;
   return n < 512 ? n : 512;
 }
 
@@ -360,7 +400,11 @@ void launch_lmhead(int dtype, const void* W, const void* X, size_t x_elems, cons
   a.W = W; a.X = X; a.rd = rd; a.V = V; a.K = K; a.Kt = (K + 31) / 32; a.n_tiles = (V + 15) / 16;
   a.sa = sa; a.part = part; a.Mpad = Mpad; a.logits_out = logits_out; a.m_tiles = 0; a.rows_live = max_rows;
   if (dtype == 0) {
-    hipLaunchKernelGGL(k_lmhead_f32, dim3(n_wg), dim3(256), 0, s, a);
+    const int per_wave = ((K + 15) / 16 + 7) / 8;            // groups of 16 k in a wave's share of K, at most 4 requested at a time
+#define SPRINTER_LMF(MT, U) hipLaunchKernelGGL((k_lmhead_f32<MT, U>), dim3(n_wg), dim3(512), 0, s, a)
+    if (max_rows <= 16) { if (per_wave <= 2) SPRINTER_LMF(1, 2); else SPRINTER_LMF(1, 4); }
+    else { if (per_wave <= 2) SPRINTER_LMF(2, 2); else SPRINTER_LMF(2, 4); }
+#undef SPRINTER_LMF
   } else if (max_rows <= 16) {
     hipLaunchKernelGGL(k_lmhead_bf16<1>, dim3(n_wg), dim3(512), 0, s, a);
   } else {

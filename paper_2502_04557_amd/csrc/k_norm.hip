@@ -96,57 +96,17 @@ void launch_embed(int dtype, const ModelDims& md, const void* tok_emb, const voi
 }
 
 // =================================================================== norm
-// LayerNorm (arch 0) / RMSNorm (arch 1) of one row per workgroup; two-pass statistics.
-template <typename AT, int ARCH>
-__global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g,
-                                              const float* __restrict__ b, float eps, int d,
-                                              const int* __restrict__ n_rows, AT* __restrict__ act_out,
-                                              float* __restrict__ f32_out) {
-  __shared__ float s4[4];
-  int r = blockIdx.x;
-  if (r >= *n_rows) return;
-  const float* x = h + (size_t)r * d;
-  float v[32];
-  float sum = 0.f;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    int k = threadIdx.x + i * 256;
-    v[i] = k < d ? x[k] : 0.f;
-    sum += v[i];
-  }
-  float mean = 0.f;
-  if (ARCH == 0) mean = block_sum256(sum, s4) / (float)d;
-  float sq = 0.f;
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    int k = threadIdx.x + i * 256;
-    float c = k < d ? v[i] - mean : 0.f;
-    sq += c * c;
-  }
-  float var = block_sum256(sq, s4) / (float)d;
-  float rstd = 1.0f / sqrtf(var + eps);
-#pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    int k = threadIdx.x + i * 256;
-    if (k < d) {
-      float o = (v[i] - mean) * rstd * g[k];
-      if (ARCH == 0) o += b[k];
-      act_store<AT>(act_out, r, k, d, o);
-      if (f32_out) f32_out[(size_t)r * d + k] = o;
-    }
-  }
-}
-// bf16 output: one row per workgroup, one thread per 8 consecutive columns (= one 16-byte slot of an
-// operand tile), so the row, gain and offset are requested with six 16-byte loads per thread
-// before anything is waited for and the result leaves as one 16-byte store of float16.  d <= 8192.
+// LayerNorm (arch 0) / RMSNorm (arch 1), two-pass statistics: one row per workgroup, one thread per 8 consecutive columns
+// (bf16 mode: one 16-byte slot of a float16 operand tile), so the row, gain and offset are requested with six 16-byte
+// loads per thread before anything is waited for and the result leaves as one or two 16-byte stores.  d <= 8192.
 // NI = 2048-column blocks per row (1, 2 or 4); SH = 0, or the most partial products a pending update of the
 // residual stream may consist of (4 or 8): the row is then h + bias + share 0 + share 1 + ..., added in that
 // order, written back and normalised.  The partial loads are issued with the others, before the row count
 // is known, with clamped share indices and the surplus selected away - no branch, no second memory round.
-template <int ARCH, int NI, int SH>
-__global__ __launch_bounds__(256) void k_norm_bf16(const float* __restrict__ h, const float* __restrict__ g,
+template <typename AT, int ARCH, int NI, int SH>
+__global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g,
                                                    const float* __restrict__ b, float eps, int d,
-                                                   const int* __restrict__ n_rows, bf16_t* __restrict__ act_out,
+                                                   const int* __restrict__ n_rows, AT* __restrict__ act_out,
                                                    float* __restrict__ f32_out, NormPending pend) {
   __shared__ float s4[4];
   const int r = blockIdx.x, tid = threadIdx.x;
@@ -224,10 +184,15 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const float* __restrict__ h, 
         o[e] = (x[i][e] - mean) * rstd * gg[i][e];
         if (ARCH == 0) o[e] += bb[i][e];
       }
-      const uint4 ov = make_uint4(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]), pk_f16(o[4], o[5]), pk_f16(o[6], o[7]));
       const int k = c * 8;
-      const size_t slot = ((size_t)(r >> 4) * Kt + (k >> 5)) * 512 + ((((k & 31) >> 3) << 4) + (r & 15)) * 8;
-      *reinterpret_cast<uint4*>(act_out + slot) = ov;
+      if constexpr (sizeof(AT) == 2) {
+        const uint4 ov = make_uint4(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]), pk_f16(o[4], o[5]), pk_f16(o[6], o[7]));
+        const size_t slot = ((size_t)(r >> 4) * Kt + (k >> 5)) * 512 + ((((k & 31) >> 3) << 4) + (r & 15)) * 8;
+        *reinterpret_cast<uint4*>(act_out + slot) = ov;
+      } else {
+        *reinterpret_cast<float4*>(act_out + (size_t)r * d + k) = make_float4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<float4*>(act_out + (size_t)r * d + k + 4) = make_float4(o[4], o[5], o[6], o[7]);
+      }
       if (f32_out) {
         *reinterpret_cast<float4*>(f32_out + (size_t)r * d + k) = make_float4(o[0], o[1], o[2], o[3]);
         *reinterpret_cast<float4*>(f32_out + (size_t)r * d + k + 4) = make_float4(o[4], o[5], o[6], o[7]);
@@ -236,14 +201,21 @@ __global__ __launch_bounds__(256) void k_norm_bf16(const float* __restrict__ h, 
   }
 }
 
-template <int ARCH, int NI>
-static void launch_norm_bf16(const float* h, const float* g, const float* b, float eps, int d, const int* n_rows,
-                             bf16_t* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np) {
-#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm_bf16<ARCH, NI, SH>), dim3(max_rows), dim3(256), 0, s, h, g, b, eps, d, n_rows, act_out, f32_out, np)
+template <typename AT, int ARCH, int NI>
+static void launch_norm_ni(const float* h, const float* g, const float* b, float eps, int d, const int* n_rows,
+                           void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np) {
+#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out, np)
   if (np.shares <= 0) SPRINTER_NORM(0);
   else if (np.shares <= 4) SPRINTER_NORM(4);
   else SPRINTER_NORM(8);
 #undef SPRINTER_NORM
+}
+template <typename AT, int ARCH>
+static void launch_norm_arch(const float* h, const float* g, const float* b, float eps, int d, const int* n_rows,
+                             void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np) {
+  if (d <= 2048) launch_norm_ni<AT, ARCH, 1>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np);
+  else if (d <= 4096) launch_norm_ni<AT, ARCH, 2>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np);
+  else launch_norm_ni<AT, ARCH, 4>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np);
 }
 
 void launch_norm(int dtype, int arch, const float* h, const float* g, const float* b, float eps, int d,
@@ -252,21 +224,8 @@ void launch_norm(int dtype, int arch, const float* h, const float* g, const floa
   NormPending np;
   memset(&np, 0, sizeof np);
   if (pend) np = *pend;
-#define NORM_CASE(AT, ARCH) \
-  hipLaunchKernelGGL((k_norm<AT, ARCH>), dim3(max_rows), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out)
+#define NORM_CASE(AT, ARCH) launch_norm_arch<AT, ARCH>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np)
   if (dtype == 0) { if (arch == 0) NORM_CASE(float, 0); else NORM_CASE(float, 1); }
-  else if (d % 8 == 0 && d <= 8192) {
-    bf16_t* out = (bf16_t*)act_out;
-    if (arch == 0) {
-      if (d <= 2048) launch_norm_bf16<0, 1>(h, g, b, eps, d, n_rows, out, f32_out, max_rows, s, np);
-      else if (d <= 4096) launch_norm_bf16<0, 2>(h, g, b, eps, d, n_rows, out, f32_out, max_rows, s, np);
-      else launch_norm_bf16<0, 4>(h, g, b, eps, d, n_rows, out, f32_out, max_rows, s, np);
-    } else {
-      if (d <= 2048) launch_norm_bf16<1, 1>(h, g, b, eps, d, n_rows, out, f32_out, max_rows, s, np);
-      else if (d <= 4096) launch_norm_bf16<1, 2>(h, g, b, eps, d, n_rows, out, f32_out, max_rows, s, np);
-      else launch_norm_bf16<1, 4>(h, g, b, eps, d, n_rows, out, f32_out, max_rows, s, np);
-    }
-  }
   else            { if (arch == 0) NORM_CASE(bf16_t, 0); else NORM_CASE(bf16_t, 1); }
 #undef NORM_CASE
 }

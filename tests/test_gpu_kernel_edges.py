@@ -1,0 +1,49 @@
+"""Kernel variants at the edges of the sizes their launchers choose them for: row counts around a row tile and a pass,
+widths that leave a half-filled last k tile or column tile, K shares, small and ragged vocabularies.  Logits, hidden states,
+scores and tokens of every step against the oracle replayed on the GPU's history, with the tolerances of parity_util."""
+import numpy as np
+import pytest
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_min=2, n_gen=3, tau=0.5, max_seq=48, seed=7):
+    """Decode steps of one configuration; returns the rejected rows per step."""
+    from parity_util import Pair, compare_replay, close_enough, eps_of
+    cfg = W.SprinterCfg(draft, target, ver_hidden, dtype, B, max_seq, tau=tau, seed=seed, name="edges", batch=B, prompt_len=prompt_len,
+                        prompt_len_min=prompt_len_min, n_gen=n_gen, prompt_dist="uniform", weight_seed=500 + seed, prompt_seed=600 + seed)
+    p = Pair(cfg, ver_scale=8.0)
+    eps = eps_of(cfg)
+    outs, _ = p.gpu_steps(n_gen)
+    g = {k: np.stack([o[k2] for o in outs], axis=1) for k, k2 in
+         (("tok", "committed_tok"), ("accept", "accept"), ("score", "score"), ("draft_tok", "draft_tok"))}
+    rec = p.oracle(n_gen, forced=dict(tok=g["tok"], accept=g["accept"]), keep_logits=True)
+    print(B, dtype, compare_replay(cfg, g, rec), flush=True)
+    for s, o in enumerate(outs):
+        R = int(o["n_rej"][0])
+        assert list(o["rej_idx"][:R]) == list(np.flatnonzero(o["accept"] == 0))
+        assert close_enough(o["draft_logits"], rec["draft_logits"][s], eps).all()
+        assert close_enough(o["draft_hidden"], rec["draft_hidden"][s], eps).all()
+        if R:
+            assert close_enough(o["target_logits"][:R], rec["target_logits"][s], eps).all()
+            assert close_enough(o["target_hidden"][:R], rec["target_hidden"][s], eps).all()
+    p.close()
+    return [int(o["n_rej"][0]) for o in outs]
+
+
+def _gpt(L, d, ff, V):
+    return W.ModelCfg(W.ARCH_GPT, L, d, d // 64, d // 64, ff, V, 48)
+
+
+def _llama(L, d, H, KVH, ff, V):
+    return W.ModelCfg(W.ARCH_LLAMA, L, d, H, KVH, ff, V, 48, 1e-5, 10000.0)
+
+
+@pytest.mark.parametrize("B", [1, 16, 17, 33])
+@pytest.mark.parametrize("ff", [72, 1096])
+def test_float32_matrix_kernels(B, ff):
+    """Float32 matrix kernels: one and two row tiles, a second pass over the rows; K = 64 (fewer groups of 16 k than waves), 72
+    (half a group at the end), 192, 512 and 1096 (two K shares); both FFN kinds; a vocabulary with a ragged last column tile."""
+    _check(_gpt(1, 64, ff, 331), _llama(1, 512, 8, 4, ff, 331), B, W.DT_F32)
+    _check(_llama(1, 192, 3, 3, ff, 35), _gpt(1, 256, ff, 35), B, W.DT_F32)
