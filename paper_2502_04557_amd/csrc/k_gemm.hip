@@ -513,10 +513,10 @@ __global__ __launch_bounds__(512) void k_gemm16_part(GemmArgs a) {
 // owns 16 columns and MT row tiles of 16; its 8 waves split K.  Operands come straight from the row-major matrices: lane
 // (l16, lq) takes four consecutive k of row / column l16 with one 16-byte load, and the four products of a load use
 // k = 4 lq + 0 .. 3 in both operands, so 16 k cost one load per operand and four matrix instructions.  U groups of 16 k
-// are requested together before the first product waits: at these widths (K <= 2048) that is one or two memory round
-// trips per wave, which is what bounds the kernel - the vector version (one wave per column, 8 rows at a time, the row
-// loads under a branch per row) paid one round trip per row and 256 k: 768 x 256 at 24 rows 15.8 -> TIME_A us,
-// 512 x 2048 at 24 rows 43 -> TIME_B us, and at one row 7.2 -> TIME_C us.
+// are requested together before the first product waits: at these widths (K <= 2048) that is one or two memory round trips
+// per wave, which is what bounds the kernel - the vector version (one wave per column, 8 rows at a time, the row loads
+// under a branch per row) paid one round trip per row and 256 k: 768 x 256 at 24 rows 15.8 -> 4.2 us; O-proj and FFN-down
+// of a 512-wide model (K = 512 and 2048) at 6 - 32 rows 28 -> 4 - 6 us with K shares, at one row 7.2 -> 3.8 us.
 // blockIdx.y = pass over 16 MT rows.
 template <int MT, int U, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_f32(GemmArgs a) {

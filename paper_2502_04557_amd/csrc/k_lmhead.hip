@@ -300,8 +300,8 @@ __global__ __launch_bounds__(512, MT <= 4 ? 4 : 2) void k_lmhead_wide(LmArgs a) 
 // float32: the same product on the float32 matrix pipes as k_gemm_f32 (k_gemm.hip): the 8 waves split K over one tile of 16
 // columns and MT row tiles, wave mt then adds the partial accumulators of row tile mt in fixed order, samples on them and keeps
 // the running key of its rows; a workgroup walks its range of column tiles.  Latency bound at these widths (a 16 KiB tile of
-// weights per round at K = 256); one wave per column and 8 rows took 8.7 us at 1 row and 23.5 us at 24 (V = 4096), now
-// LM_A and LM_B us.
+// weights per round at K = 256); one wave per column and 8 rows at a time took 8.7 us at 1 row and 23.5 us at 24
+// (V = 4096), this 5.1 and 5.8 us.
 template <int MT, int U>
 __global__ __launch_bounds__(512) void k_lmhead_f32(LmArgs a) {
   __shared__ float red[8][MT * 4][64];
