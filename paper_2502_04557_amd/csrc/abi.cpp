@@ -218,6 +218,7 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
   sc.hf = (float*)bump.take((size_t)rows * md.d * 4);
   sc.hfn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.rope = (float*)bump.take((size_t)rows * md.dh * 4);
+  sc.rope_table = md.arch == SPRINTER_ARCH_LLAMA ? (float*)bump.take((size_t)c.max_seq * md.dh * 4) : nullptr;
   sc.part = (float*)bump.take((size_t)PART_SHARES * rows * md.d * 4);
   sc.n_lm_wg = lmhead_num_wg(c.dtype, md.V);
   sc.am_part = (unsigned long long*)bump.take((size_t)sc.n_lm_wg * rows * 8);
@@ -364,8 +365,9 @@ size_t carve(const sprinter_cfg& c, void* base, sprinter_ctx* ctx, size_t* scrat
 // shared_caches: several rows of rd may belong to one batch row (consecutive positions): every layer appends all
 // new keys / values first and attends in a second launch.  long_runs: those entries come in long runs of
 // consecutive positions (prefill), so the attending launch lets 8 queries share one pass over the row's cache.
+// ver: the verifier's work, done by the LM head's launch.
 void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool want_head, unsigned stream_id,
-             float* logits_out, bool shared_caches = false, bool long_runs = false) {
+             float* logits_out, bool shared_caches = false, bool long_runs = false, const VerifierArgs* ver = nullptr) {
   const int dt = ctx->cfg.dtype;
   const ModelDims& md = m.md;
   hipStream_t s = ctx->stream;
@@ -373,7 +375,7 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   const int rows = ctx->rows_alloc;
   // elements the activation buffers hold (their row tiles bound what a kernel may fetch)
   const size_t pl_d = act_elems(dt, rows, md.d), pl_a = act_elems(dt, rows, md.H * md.dh), pl_f = act_elems(dt, rows, md.ff);
-  launch_embed(dt, md, m.tok_emb, m.pos_emb, rd, sc.h, sc.rope, max_rows, s);
+  const EmbedSource emb{m.tok_emb, m.pos_emb, rd, sc.rope_table, sc.rope, md.V, md.max_pos, ctx->cfg.max_seq, md.dh};
   // O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
   // them (and the bias) into the residual stream before it normalises the row.
   const size_t part_stride = (size_t)rows * md.d;
@@ -382,14 +384,14 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
     pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, PART_SHARES, max_rows, s);
     pend.bias = bias;
   };
-  auto norm = [&](const float* g, const float* b, void* out, float* f32_out) {
+  auto norm = [&](const float* g, const float* b, void* out, float* f32_out, const EmbedSource* src = nullptr) {
     launch_norm(dt, md.arch, sc.h, g, b, md.eps, md.d, rd.n_rows, out, f32_out, max_rows, s,
-                pend.shares > 0 ? &pend : nullptr);
+                pend.shares > 0 ? &pend : nullptr, src);
     pend.shares = 0;
   };
   for (int i = 0; i < md.n_layer; ++i) {
     const LayerW& L = m.layers[i];
-    norm(L.n1g, L.n1b, sc.xn, nullptr);
+    norm(L.n1g, L.n1b, sc.xn, nullptr, i == 0 ? &emb : nullptr);
     launch_gemm(dt, EPI_F32, L.wqkv, nullptr, sc.xn, pl_d, rd.n_rows, md.dqkv, md.d, L.bqkv, sc.y, md.dqkv, nullptr, 0,
                 max_rows, s);
     if (shared_caches) {
@@ -419,8 +421,8 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   sa.seed_hi = (unsigned)(ctx->cfg.seed >> 32);
   sa.stream = stream_id;
   sa.inv_temperature = ctx->cfg.temperature > 0.f ? 1.0f / ctx->cfg.temperature : 0.f;
-  launch_lmhead(dt, m.lm_head, sc.hfn, pl_d, rd, md.V, md.d, sa, sc.am_part, sc.n_lm_wg, ctx->rows_alloc, logits_out,
-                max_rows, s);
+  launch_lmhead(dt, m.lm_head, sc.hfn, pl_d, rd, md.V, md.d, sa, sc.am_part, sc.n_lm_wg, lm_row_pad(max_rows),
+                logits_out, max_rows, s, ver);
 }
 
 int check_ready(sprinter_ctx* ctx) {
@@ -473,13 +475,13 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
   const int B = ctx->B;
   Model &dq = ctx->draft, &tp = ctx->target;
   const bool sd = ctx->cfg.reject_mode == 1;
-  forward(ctx, dq, dq.rd(), B, true, 0u, sd ? ctx->dl : (out ? out->draft_logits : nullptr));
+  const VerifierArgs ver{dq.sc.hf, dq.md.d, ctx->cfg.ver_d_hidden, (const float*)ctx->v_w1, (const float*)ctx->v_b1,
+                         (const float*)ctx->v_w2, ctx->ver_part, B, ctx->ver_chunks};
+  forward(ctx, dq, dq.rd(), B, true, 0u, sd ? ctx->dl : (out ? out->draft_logits : nullptr), false, false, &ver);
   if (sd && out && out->draft_logits) launch_copy_f32(ctx->dl, out->draft_logits, dq.rd_n, dq.md.V, B, s);
   if (out && out->draft_hidden) launch_copy_f32(dq.sc.hf, out->draft_hidden, dq.rd_n, dq.md.d, B, s);
-  launch_verifier_part(dq.sc.hf, dq.md.d, ctx->cfg.ver_d_hidden, (const float*)ctx->v_w1, (const float*)ctx->v_b1,
-                       (const float*)ctx->v_w2, dq.rd_n, ctx->ver_part, B, s);
   DecideArgs da;
-  da.am_part = dq.sc.am_part; da.n_lm_wg = dq.sc.n_lm_wg; da.Mpad = ctx->rows_alloc;
+  da.am_part = dq.sc.am_part; da.n_lm_wg = dq.sc.n_lm_wg; da.Mpad = lm_row_pad(B);
   da.ver_part = ctx->ver_part; da.n_chunks = ctx->ver_chunks; da.b2 = (const float*)ctx->v_b2; da.tau_ptr = ctx->tau_dev;
   da.B = B; da.st = ctx->st;
   da.draft_tok = ctx->draft_tok; da.score = ctx->score; da.accept = ctx->accept; da.rej_idx = ctx->rej_idx;
@@ -492,7 +494,15 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
   da.ctx_mode = mode; da.ent_off = ctx->ent_off;
   da.host_word = ctx->kernel_word; da.ticket = ++ctx->ticket;
   if (da.ticket == 0) da.ticket = ++ctx->ticket;   // 0 is the word's initial value
-  launch_draft_decide(da, s);
+  FinishArgs fa;
+  fa.am_part = tp.sc.am_part; fa.n_lm_wg = tp.sc.n_lm_wg; fa.Mpad = 0; fa.B = B; fa.st = ctx->st;
+  fa.draft_tok = ctx->draft_tok; fa.score = ctx->score; fa.accept = ctx->accept; fa.rej_idx = ctx->rej_idx;
+  fa.n_rej = ctx->n_rej; fa.committed = ctx->committed;
+  fa.d_n_rows = dq.rd_n; fa.d_b = dq.rd_b; fa.d_tok = dq.rd_tok; fa.d_pos = dq.rd_pos; fa.d_slot = dq.rd_slot;
+  fa.o_committed = out ? out->committed_tok : nullptr;
+  fa.ctx_mode = mode; fa.pre_merged = (mode == 1 || sd) ? 1 : 0;
+  fa.n_tokens = n_tokens; fa.g_tok = g_tok; fa.g_accept = g_accept; fa.g_score = g_score; fa.g_draft_tok = g_draft_tok;
+  launch_draft_decide(da, fa, s);
   // The host waits for the number of rejected rows R: the target's kernels are then launched for exactly R
   // rows (row-tile count and K split follow R, not the batch size), and not at all when every row accepted.
   // The decide kernel stores (ticket, R) into pinned memory and the host polls that word, which costs a few
@@ -503,6 +513,8 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
     if (rc) return rc;
   }
   if (R < 0 || R > B) return fail(ctx, SPRINTER_E_HIP, "device reported %d rejected rows of %d", R, B);
+  if (R == 0) return SPRINTER_OK;                  // (the decide kernel has committed the step)
+  fa.Mpad = lm_row_pad(R);
   SdArgs sa;
   memset(&sa, 0, sizeof sa);
   if (sd) {
@@ -511,14 +523,14 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
     sa.seed_lo = (unsigned)(ctx->cfg.seed & 0xFFFFFFFFull); sa.seed_hi = (unsigned)(ctx->cfg.seed >> 32);
     sa.committed = ctx->committed; sa.coin_kept = ctx->coin_kept;
   }
-  if (R > 0 && mode == 0) {
+  if (mode == 0) {
     forward(ctx, tp, tp.rd(), R, true, 1u, sd ? ctx->tl : (out ? out->target_logits : nullptr));
     if (sd) {
       launch_sd_correct(sa, R, s);
       if (out && out->target_logits) launch_copy_f32(ctx->tl, out->target_logits, tp.rd_n, tp.md.V, R, s);
     }
     if (out && out->target_hidden) launch_copy_f32(tp.sc.hf, out->target_hidden, tp.rd_n, tp.md.d, R, s);
-  } else if (R > 0) {
+  } else {
     // full prefix: the work list (E entries, at least one per rejected row) goes through the target in chunks of
     // at most rows_alloc entries, in list order, so that a later entry of a row finds the earlier ones cached
     const long long E = (long long)((volatile unsigned long long*)ctx->host_counts)[1];
@@ -536,19 +548,11 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
         sa.t_last = ctx->t_last;
         launch_sd_correct(sa, n, s);
       } else {
-        launch_catchup_collect(tp.sc.am_part, tp.sc.n_lm_wg, ctx->rows_alloc, tp.rd_n, tp.rd_b, ctx->t_last,
+        launch_catchup_collect(tp.sc.am_part, tp.sc.n_lm_wg, lm_row_pad(n), tp.rd_n, tp.rd_b, ctx->t_last,
                                ctx->committed, n, s);
       }
     }
   }
-  FinishArgs fa;
-  fa.am_part = tp.sc.am_part; fa.n_lm_wg = tp.sc.n_lm_wg; fa.Mpad = ctx->rows_alloc; fa.B = B; fa.st = ctx->st;
-  fa.draft_tok = ctx->draft_tok; fa.score = ctx->score; fa.accept = ctx->accept; fa.rej_idx = ctx->rej_idx;
-  fa.n_rej = ctx->n_rej; fa.committed = ctx->committed;
-  fa.d_n_rows = dq.rd_n; fa.d_b = dq.rd_b; fa.d_tok = dq.rd_tok; fa.d_pos = dq.rd_pos; fa.d_slot = dq.rd_slot;
-  fa.o_committed = out ? out->committed_tok : nullptr;
-  fa.ctx_mode = mode; fa.pre_merged = (mode == 1 || sd) ? 1 : 0;
-  fa.n_tokens = n_tokens; fa.g_tok = g_tok; fa.g_accept = g_accept; fa.g_score = g_score; fa.g_draft_tok = g_draft_tok;
   launch_step_finish(fa, s);
   return SPRINTER_OK;
 }
@@ -589,6 +593,7 @@ int create_common(const sprinter_cfg* cfg, void* dev_workspace, void* hip_stream
     launch_fill_zero(m->sc.ao, act_elems(cfg->dtype, rows, m->md.H * m->md.dh) * es, ctx->stream);
     launch_fill_zero(m->sc.mid, act_elems(cfg->dtype, rows, m->md.ff) * es, ctx->stream);
     launch_fill_zero(m->sc.hfn, act_elems(cfg->dtype, rows, m->md.d) * es, ctx->stream);
+    if (m->sc.rope_table) launch_rope_table(m->sc.rope_table, cfg->max_seq, m->md.dh, m->md.theta, ctx->stream);
   }
   launch_set_f32(ctx->tau_dev, cfg->tau, ctx->stream);
   launch_fill_zero(ctx->dev_counts, 256, ctx->stream);
@@ -877,13 +882,13 @@ int sprinter_sd_generate(sprinter_ctx* ctx, int gamma, int n_rounds, int32_t* de
       const int n = std::min(rows, E0 - start);
       launch_sd_take_chunk(sd, start, n, D[0], ctx->t_last, s);
       forward(ctx, dq, ro(D[0]), n, true, 0u, sd.dlw + (size_t)start * Vd, E0 > B);
-      launch_sd_draft_next(sd, 0, dq.sc.am_part, dq.sc.n_lm_wg, rows, ro(D[0]), ctx->t_last, start, D[1], n, s);
+      launch_sd_draft_next(sd, 0, dq.sc.am_part, dq.sc.n_lm_wg, lm_row_pad(n), ro(D[0]), ctx->t_last, start, D[1], n, s);
     }
     for (int j = 1; j < gamma; ++j) {
       const RowDescW &in = D[j & 1], &out = D[(j + 1) & 1];
       const int base = 2 * B + (j - 1) * B;
       forward(ctx, dq, ro(in), B, true, 0u, sd.dlw + (size_t)base * Vd, false);
-      launch_sd_draft_next(sd, j, dq.sc.am_part, dq.sc.n_lm_wg, rows, ro(in), nullptr, base, out, B, s);
+      launch_sd_draft_next(sd, j, dq.sc.am_part, dq.sc.n_lm_wg, lm_row_pad(B), ro(in), nullptr, base, out, B, s);
     }
     // 2. the target over gamma + 1 positions of every row, 3. coin / residual / extra token per entry
     const int E = B * (gamma + 1);
@@ -891,7 +896,7 @@ int sprinter_sd_generate(sprinter_ctx* ctx, int gamma, int n_rounds, int32_t* de
       const int n = std::min(rows, E - start);
       launch_sd_target_list(sd, start, n, T, s);
       forward(ctx, tp, tp.rd(), n, true, 1u, sd.tlw + (size_t)start * Vt, true);
-      launch_sd_window_check(sd, start, n, tp.sc.am_part, tp.sc.n_lm_wg, rows, s);
+      launch_sd_window_check(sd, start, n, tp.sc.am_part, tp.sc.n_lm_wg, lm_row_pad(n), s);
     }
     // 4. commit
     SdFinishArgs fa;

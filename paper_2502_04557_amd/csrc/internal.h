@@ -44,6 +44,7 @@ struct ModelScratch {  // per-model activation buffers, sized for max_batch rows
   float* hf;           // [M, d] final hidden state after the last norm, float32
   void* hfn;           // same values in activation layout (LM-head input)
   float* rope;         // [M, dh/2, 2] cos/sin of the row's position
+  float* rope_table;   // [max_seq, dh/2, 2] the same for every position (LLaMA; else NULL)
   float* part;         // [PART_SHARES][M, d] partial O-proj / FFN-down products, float32
   unsigned long long* am_part;  // [n_lm_wg, Mpad] packed (value, index) arg-max partials
   int n_lm_wg;
@@ -58,8 +59,12 @@ struct SamplerArgs {
 void launch_pack_bf16(const void* w, void* out, int N, int K, hipStream_t s);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
-void launch_embed(int dtype, const ModelDims& md, const void* tok_emb, const void* pos_emb,
-                  const RowDesc& rd, float* h, float* rope, int max_rows, hipStream_t s);
+void launch_rope_table(float* out, int max_seq, int dh, float theta, hipStream_t s);
+// The first norm of a forward reads its rows from the embedding tables (dtype elements) and starts the residual stream; with
+// a rotary table it also leaves each row's factors in rope[M, dh].
+struct EmbedSource {
+  const void *tok_emb, *pos_emb; RowDesc rd; const float* rope_table; float* rope; int V, max_pos, max_seq, dh;
+};
 // An update of the residual stream that is still in pieces (launch_gemm_part): the norm kernel adds
 // bias + share 0 + share 1 + ... to the row, writes the row back and normalises the sum.
 struct NormPending {
@@ -68,7 +73,7 @@ struct NormPending {
 // d a multiple of 8, at most 8192.
 void launch_norm(int dtype, int arch, const float* h, const float* g, const float* b, float eps, int d,
                  const int* n_rows, void* act_out, float* f32_out, int max_rows, hipStream_t s,
-                 const NormPending* pend = nullptr);
+                 const NormPending* pend = nullptr, const EmbedSource* emb = nullptr);
 // part[s] = X[:, K share s] W[:, K share s]^T for s < returned share count (<= max_shares)
 int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
                      size_t part_stride, int max_shares, int max_rows, hipStream_t s);
@@ -87,14 +92,19 @@ void launch_attention(int dtype, const ModelDims& md, const float* y, const floa
 // phase 0: append the row's new key / value to the cache and attend (rows of one launch own different caches);
 // phase 1: append only; phase 2: attend only (the pair serves launches where several rows share a cache).
 
+// The verifier's hidden layer over the rows of the draft pass; part[chunk][row] receives each chunk's share of the logit.
+struct VerifierArgs {
+  const float* hf; int d, d_hidden; const float *w1, *b1, *w2; float* part; int part_stride, chunks;
+};
+int verifier_num_chunks(int d_hidden);
+
 int lmhead_num_wg(int dtype, int V);
+// part: [n_wg][Mpad] partial arg-max keys; Mpad = lm_row_pad(max_rows), so that the keys of a small pass lie together.
+// ver: the verifier's work, which rides along with the draft's head (NULL: none).
+inline int lm_row_pad(int max_rows) { return round_up(max_rows, 16); }
 void launch_lmhead(int dtype, const void* W, const void* X, size_t x_elems, const RowDesc& rd, int V, int K,
                    const SamplerArgs& sa, unsigned long long* part, int n_wg, int Mpad,
-                   float* logits_out, int max_rows, hipStream_t s);
-
-int verifier_num_chunks(int d_hidden);
-void launch_verifier_part(const float* hf, int d, int d_hidden, const float* w1, const float* b1,
-                          const float* w2, const int* n_rows, float* part, int max_rows, hipStream_t s);
+                   float* logits_out, int max_rows, hipStream_t s, const VerifierArgs* ver = nullptr);
 
 struct State {           // device-resident per-batch state
   int* last_tok;         // [B] last committed token
@@ -125,7 +135,6 @@ struct DecideArgs {
   // cache has not seen, then the step's own input); ent_off[0 .. R] = exclusive prefix sums of those counts
   int ctx_mode; int* ent_off;
 };
-void launch_draft_decide(const DecideArgs& a, hipStream_t s);
 
 struct FinishArgs {
   const unsigned long long* am_part; int n_lm_wg; int Mpad;
@@ -143,6 +152,8 @@ struct FinishArgs {
   int pre_merged;   // 1: committed[] already holds the rejected rows' tokens (full-prefix collect / p-over-q correction)
 };
 void launch_step_finish(const FinishArgs& a, hipStream_t s);
+// f: what launch_step_finish would get: a step that rejects no row is committed by the decide kernel itself.
+void launch_draft_decide(const DecideArgs& a, const FinishArgs& f, hipStream_t s);
 
 // Full-prefix target context: entries [start, start + n) of the step's work list become the target's row
 // descriptors (several entries may belong to one batch row; entry order = ascending row, ascending position).

@@ -6,44 +6,82 @@
 
 namespace sprinter {
 
+// ===================================================== commit of a step
+// Thread b commits row b's token c: token history, cache lengths, outputs, and the next step's draft row descriptors.
+__device__ __forceinline__ void commit_row(const FinishArgs& a, int b, int c, bool acc, int draft_tok, float score, long long g) {
+  a.committed[b] = c;
+  a.st.last_tok[b] = c;
+  const int lq = a.st.len_q[b] + 1;
+  a.st.len_q[b] = lq;
+  if (!acc) {
+    a.st.len_p[b] = a.ctx_mode == 1 ? lq : a.st.len_p[b] + 1;
+    a.st.n_target_calls[b] += 1;
+  }
+  a.st.hist[(size_t)b * a.st.hist_stride + lq] = c;
+  if (a.o_committed) a.o_committed[b] = c;
+  if (a.n_tokens > 0 && g < a.n_tokens) {
+    const size_t o = (size_t)b * a.n_tokens + (size_t)g;
+    if (a.g_tok) a.g_tok[o] = c;
+    if (a.g_accept) a.g_accept[o] = acc ? 1 : 0;
+    if (a.g_score) a.g_score[o] = score;
+    if (a.g_draft_tok) a.g_draft_tok[o] = draft_tok;
+  }
+  a.d_b[b] = b;                                      // the next step's draft forward: every row, its last token at the next position
+  a.d_tok[b] = c;
+  a.d_pos[b] = lq;
+  a.d_slot[b] = lq;
+}
+__device__ __forceinline__ void commit_counters(const FinishArgs& a, int R, long long g) {
+  *a.d_n_rows = a.B;
+  a.st.counters[0] += 1;
+  a.st.counters[1] += (R > 0) ? 1 : 0;
+  a.st.counters[2] += R;
+  a.st.counters[3] = g + 1;
+}
+
 // ====================================== decide: arg-max merge, threshold, compaction
 // Single workgroup of 1024 threads (B <= 1024).  accept <=> sigmoid(logit) >= tau in float32.
 // Rejected rows are listed in ascending order: ballot + popcount inside each wave,
-// wave totals prefix-summed through LDS.
-__global__ __launch_bounds__(1024) void k_draft_decide(DecideArgs a) {
+// wave totals prefix-summed through LDS.  A step without rejections is committed right here (f), so its chain ends with
+// this launch.
+__global__ __launch_bounds__(1024) void k_draft_decide(DecideArgs a, FinishArgs f, int row_lanes) {
   __shared__ int s_tok[1024];
   __shared__ int s_wave_cnt[16];
   __shared__ int s_rej[1024];
   __shared__ u64 s_key[16][64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int B = a.B;
-  // Arg-max merge over the LM head's per-workgroup partials part[workgroup][row]: a lane takes one row of a block
-  // of 64, a wave every 16th workgroup, so that a load covers 64 consecutive rows of one workgroup (512 contiguous
-  // bytes; with a lane per workgroup every 8-byte load hit its own cache line: 37 us at 64 rows and 512 workgroups),
-  // then the 16 waves' results meet in LDS.
+  // Arg-max merge over the LM head's per-workgroup partials part[workgroup][row]: row_lanes (a power of two, min(B, 64)
+  // rounded up) lanes of a wave take consecutive rows of one workgroup (with a lane per workgroup every 8-byte load hit its
+  // own cache line: 37 us at 64 rows and 512 workgroups), the wave's 64 / row_lanes groups and the 16 waves different
+  // workgroups, eight loads in flight per lane; then shuffles and LDS merge them.  At one row the whole merge is a single
+  // round of loads (with one active lane per wave it took four rounds, and with keys 32 KiB apart as many TLB misses:
+  // kernel 7.6 us at one row and 393 workgroups, now DECIDE_US).
   float z = 0.f;                                     // the verifier's output logit: offset + the hidden chunks' shares, in order
   if (tid < B) {                                     // (requested ahead of the merge below)
     z = a.b2[0];
 #pragma unroll 8
     for (int c = 0; c < a.n_chunks; ++c) z += a.ver_part[(size_t)c * B + tid];
   }
-  for (int rb = 0; rb < B; rb += 64) {
-    const int m = rb + lane;
+  const int rl = lane & (row_lanes - 1), subs = 64 / row_lanes, first = w * subs + lane / row_lanes, stride = 16 * subs;
+  for (int rb = 0; rb < B; rb += row_lanes) {
+    const int m = rb + rl;
     u64 k = 0;
     if (m < B)
-      for (int i0 = w; i0 < a.n_lm_wg; i0 += 128) {            // eight loads in flight per lane, not a chain of single ones
+      for (int i0 = first; i0 < a.n_lm_wg; i0 += 8 * stride) {
         u64 v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-          const int i = i0 + 16 * u;
+          const int i = i0 + stride * u;
           v[u] = i < a.n_lm_wg ? a.am_part[(size_t)i * a.Mpad + m] : 0;
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) k = umax64(k, v[u]);
       }
+    for (int o = row_lanes; o < 64; o <<= 1) k = umax64(k, shfl_xor_u64(k, o));
     s_key[w][lane] = k;
     __syncthreads();
-    if (w == 0 && m < B) {
+    if (tid < row_lanes && m < B) {
       u64 kk = s_key[0][lane];
 #pragma unroll
       for (int q = 1; q < 16; ++q) kk = umax64(kk, s_key[q][lane]);
@@ -69,9 +107,13 @@ __global__ __launch_bounds__(1024) void k_draft_decide(DecideArgs a) {
     if (q < w) off += c;
     total += c;
   }
+  if (tid == 0 && total == 0 && a.host_word) {       // the host may queue the next step while this kernel commits
+    if (a.ctx_mode == 1) a.host_word[1] = 0;
+    __hip_atomic_store(a.host_word, (unsigned long long)a.ticket << 32, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
   if (rej) s_rej[off + rank] = tid;
+  const int dt = active ? s_tok[tid] : 0;
   if (active) {
-    int dt = s_tok[tid];
     a.draft_tok[tid] = dt;
     a.score[tid] = score;
     a.accept[tid] = acc ? 1 : 0;
@@ -79,6 +121,18 @@ __global__ __launch_bounds__(1024) void k_draft_decide(DecideArgs a) {
     if (a.o_draft_tok) a.o_draft_tok[tid] = dt;
     if (a.o_score) a.o_score[tid] = score;
     if (a.o_accept) a.o_accept[tid] = acc ? 1 : 0;
+  }
+  if (total == 0) {
+    const long long g = a.st.counters[3];
+    __syncthreads();                                 // (everybody has read the generation index)
+    if (active) commit_row(f, tid, dt, true, dt, score, g);
+    if (tid == 0) {
+      *a.n_rej = 0;
+      *a.t_n_rows = 0;
+      if (a.o_n_rej) *a.o_n_rej = 0;
+      commit_counters(f, 0, g);
+    }
+    return;
   }
   __syncthreads();
   if (tid < total) {
@@ -117,8 +171,10 @@ __global__ __launch_bounds__(1024) void k_draft_decide(DecideArgs a) {
                          __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
-void launch_draft_decide(const DecideArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_draft_decide, dim3(1), dim3(1024), 0, s, a);
+void launch_draft_decide(const DecideArgs& a, const FinishArgs& f, hipStream_t s) {
+  int row_lanes = 1;
+  while (row_lanes < a.B && row_lanes < 64) row_lanes <<= 1;
+  hipLaunchKernelGGL(k_draft_decide, dim3(1), dim3(1024), 0, s, a, f, row_lanes);
 }
 
 // ===================== finish: target arg-max merge, scatter back, advance state
@@ -134,41 +190,10 @@ __global__ __launch_bounds__(1024) void k_step_finish(FinishArgs a) {
       if (lane == 0) s_commit[a.rej_idx[i]] = key_index(k);
     }
   }
-  __syncthreads();
   const long long g = a.st.counters[3];
-  if (tid < B) {
-    int c = s_commit[tid];
-    bool acc = a.accept[tid] != 0;
-    a.committed[tid] = c;
-    a.st.last_tok[tid] = c;
-    int lq = a.st.len_q[tid] + 1;
-    a.st.len_q[tid] = lq;
-    if (!acc) {
-      a.st.len_p[tid] = a.ctx_mode == 1 ? lq : a.st.len_p[tid] + 1;
-      a.st.n_target_calls[tid] += 1;
-    }
-    a.st.hist[(size_t)tid * a.st.hist_stride + lq] = c;
-    if (a.o_committed) a.o_committed[tid] = c;
-    if (a.n_tokens > 0 && g < a.n_tokens) {
-      size_t o = (size_t)tid * a.n_tokens + (size_t)g;
-      if (a.g_tok) a.g_tok[o] = c;
-      if (a.g_accept) a.g_accept[o] = acc ? 1 : 0;
-      if (a.g_score) a.g_score[o] = a.score[tid];
-      if (a.g_draft_tok) a.g_draft_tok[o] = a.draft_tok[tid];
-    }
-    // the next step's draft forward: every row, its last token at the next position
-    a.d_b[tid] = tid;
-    a.d_tok[tid] = c;
-    a.d_pos[tid] = lq;
-    a.d_slot[tid] = lq;
-  }
-  if (tid == 0) {
-    *a.d_n_rows = B;
-    a.st.counters[0] += 1;
-    a.st.counters[1] += (R > 0) ? 1 : 0;
-    a.st.counters[2] += R;
-    a.st.counters[3] = g + 1;
-  }
+  __syncthreads();
+  if (tid < B) commit_row(a, tid, s_commit[tid], a.accept[tid] != 0, a.draft_tok[tid], a.score[tid], g);
+  if (tid == 0) commit_counters(a, R, g);
 }
 void launch_step_finish(const FinishArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_step_finish, dim3(1), dim3(1024), 0, s, a);

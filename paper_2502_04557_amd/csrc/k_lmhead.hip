@@ -6,11 +6,80 @@
 
 namespace sprinter {
 
+// =============================================================== verifier
+// Hidden layer of the verifier MLP (Sec. 3.2; the paper's single linear layer when d_hidden == 0) in float32.
+// With a hidden layer it is a small matrix product, hidden = relu(hf W1^T + b1), done on the float32 matrix
+// pipes: a workgroup owns 16 rows x 16 hidden units, its 8 waves split K; lane (l16, lq) holds four consecutive k of
+// row l16 and of unit l16 per 16-byte load, and the four 16x16x4 products of a load take k = 4 lq + 0 .. 3 (any
+// assignment of k to products is a valid order of the sum as long as both operands use the same one).  The waves'
+// accumulators are added in fixed order through LDS, then relu(. + b1) * w2 is summed over the 16 units and the
+// workgroup leaves its share of each row's output logit in part[chunk][row]; the consumer adds the chunks in order.
+// (One wave per hidden unit re-read the whole hidden-state matrix per wave - 268 MB through L2 at d = 2048,
+// 512 units and 64 rows, 81 us; this form reads 32 MB.)
+// The verifier and the LM head read the same hidden states and nothing of each other, so its workgroups ride at the end
+// of the draft's LM-head launch (blockIdx.x >= LmArgs.n_wg): as a launch of its own it was 4.0 - 5.7 us of the step's chain.
+int verifier_num_chunks(int d_hidden) { return d_hidden > 0 ? (d_hidden + 15) / 16 : 1; }
+
+__device__ __forceinline__ void verifier_block(const VerifierArgs& a, int n_rows, int block) {
+  __shared__ float red[8][4][64];
+  const int lane = threadIdx.x & 63, w = wave_index(), d = a.d, d_hidden = a.d_hidden;
+  if (d_hidden == 0) {                               // (one workgroup)
+    for (int m = w; m < n_rows; m += 8) {
+      float acc = 0.f;
+      for (int k = lane; k < d; k += 64) acc += a.w2[k] * a.hf[(size_t)m * d + k];
+      acc = wave_sum(acc);
+      if (lane == 0) a.part[m] = acc;
+    }
+    return;
+  }
+  const int chunk = block % a.chunks, m0 = block / a.chunks * 16;
+  if (m0 >= n_rows) return;
+  const int l16 = lane & 15, lq = lane >> 4, j = chunk * 16 + l16;
+  // rows beyond the row count and units beyond the layer are read at the last valid one and dropped below
+  const float4* __restrict__ hrow = reinterpret_cast<const float4*>(a.hf + (size_t)min(m0 + l16, n_rows - 1) * d) + lq;
+  const float4* __restrict__ wrow = reinterpret_cast<const float4*>(a.w1 + (size_t)min(j, d_hidden - 1) * d) + lq;
+  const int n16 = d >> 4, g0 = n16 * w / 8, g1 = n16 * (w + 1) / 8;   // this wave's groups of 16 k (d is a multiple of 16)
+  f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int g = g0; g < g1; g += 8) {
+    float4 av[8], bv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int gi = min(g + i, g1 - 1);
+      av[i] = hrow[gi * 4];
+      bv[i] = wrow[gi * 4];
+    }
+    __builtin_amdgcn_sched_barrier(0);               // all sixteen loads go out before the first product waits
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const bool on = g + i < g1;                    // (scalar) a group beyond the share contributes zeros
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].x, on ? bv[i].x : 0.f, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].y, on ? bv[i].y : 0.f, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].z, on ? bv[i].z : 0.f, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].w, on ? bv[i].w : 0.f, acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) red[w][v][lane] = acc[v];
+  __syncthreads();
+  if (w < 4) {                                       // wave v finishes accumulator register v: row m0 + lq * 4 + v, unit j
+    float sum = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) sum += red[q][w][lane];
+    const bool unit = j < d_hidden;
+    const float t = unit ? fmaxf(sum + a.b1[min(j, d_hidden - 1)], 0.f) * a.w2[min(j, d_hidden - 1)] : 0.f;
+    const float tot = group_sum<16>(t);
+    const int m = m0 + lq * 4 + w;
+    if (l16 == 0 && m < n_rows) a.part[(size_t)chunk * a.part_stride + m] = tot;
+  }
+}
+
 // ======================================================= LM head + sample
 struct LmArgs {
   const void* W; const void* X; RowDesc rd; int V, K, Kt, n_tiles;
   SamplerArgs sa; u64* part; int Mpad; float* logits_out; size_t x_elems; int m_tiles;
   int rows_live;   // the host's bound on the row count: lanes of rows from here on skip their activation loads
+  int n_wg;        // workgroups of the LM head; those from here on are the verifier's
+  VerifierArgs ver;
 };
 
 // bf16, at most 16 rows (launched with MT = 1): each workgroup owns a contiguous range of column tiles; its 8 waves
@@ -20,10 +89,11 @@ struct LmArgs {
 // beyond the row count are dropped when the logits are sampled.
 template <int MT>
 __global__ __launch_bounds__(512) void k_lmhead_bf16(LmArgs a) {
+  if ((int)blockIdx.x >= a.n_wg) { verifier_block(a.ver, *a.rd.n_rows, (int)blockIdx.x - a.n_wg); return; }
   __shared__ u64 sbest[8][MT * 16];
   __shared__ int s_rb[MT * 16], s_rt[MT * 16];
   const int lane = threadIdx.x & 63, w = wave_index();
-  const int tpw = (a.n_tiles + gridDim.x - 1) / gridDim.x;
+  const int tpw = (a.n_tiles + a.n_wg - 1) / a.n_wg;
   const int t0 = blockIdx.x * tpw, t1 = min(t0 + tpw, a.n_tiles);
   const uint4* __restrict__ Wp = (const uint4*)a.W + lane;
   const uint4* __restrict__ Xp = (const uint4*)a.X + lane;
@@ -148,13 +218,14 @@ __global__ __launch_bounds__(512) void k_lmhead_bf16(LmArgs a) {
 // tiles are clamped to the m_tiles the activation buffer holds.  More than 16 MT rows take further passes.
 template <int MT, int NTW, int KS>
 __global__ __launch_bounds__(512, MT <= 4 ? 4 : 2) void k_lmhead_wide(LmArgs a) {
+  if ((int)blockIdx.x >= a.n_wg) { verifier_block(a.ver, *a.rd.n_rows, (int)blockIdx.x - a.n_wg); return; }
   constexpr int NF = KS * MT, F = (NF + 7) / 8;             // fragments per stage, per wave (with fewer than 8 the last waves stage none)
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   __shared__ u32x4 xs[2][NF][64];
   __shared__ u64 sbest[8][MT * 16];
   __shared__ int s_rb[MT * 16], s_rt[MT * 16];
   const int lane = threadIdx.x & 63, w = wave_index();
-  const int tpw = (a.n_tiles + gridDim.x - 1) / gridDim.x;
+  const int tpw = (a.n_tiles + a.n_wg - 1) / a.n_wg;
   const int t0 = blockIdx.x * tpw, t1 = min(t0 + tpw, a.n_tiles);
   const uint4* __restrict__ Wp = (const uint4*)a.W + lane;
   const int Kt = a.Kt;
@@ -304,10 +375,11 @@ __global__ __launch_bounds__(512, MT <= 4 ? 4 : 2) void k_lmhead_wide(LmArgs a) 
 // (V = 4096), this 5.1 and 5.8 us.
 template <int MT, int U>
 __global__ __launch_bounds__(512) void k_lmhead_f32(LmArgs a) {
+  if ((int)blockIdx.x >= a.n_wg) { verifier_block(a.ver, *a.rd.n_rows, (int)blockIdx.x - a.n_wg); return; }
   __shared__ float red[8][MT * 4][64];
   const int lane = threadIdx.x & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
   const int n_rows = *a.rd.n_rows, K = a.K;
-  const int tpw = (a.n_tiles + gridDim.x - 1) / gridDim.x;
+  const int tpw = (a.n_tiles + a.n_wg - 1) / a.n_wg;
   const int t0 = blockIdx.x * tpw, t1 = min(t0 + tpw, a.n_tiles);
   const int n_groups = (K + 15) >> 4, g0 = n_groups * w / 8, g1 = n_groups * (w + 1) / 8;
   const float* __restrict__ W = (const float*)a.W;
@@ -394,105 +466,36 @@ int lmhead_num_wg(int dtype, int V) {
 
 void launch_lmhead(int dtype, const void* W, const void* X, size_t x_elems, const RowDesc& rd, int V, int K,
                    const SamplerArgs& sa, unsigned long long* part, int n_wg, int Mpad, float* logits_out, int max_rows,
-                   hipStream_t s) {
+                   hipStream_t s, const VerifierArgs* ver) {
   LmArgs a;
   a.x_elems = x_elems;
   a.W = W; a.X = X; a.rd = rd; a.V = V; a.K = K; a.Kt = (K + 31) / 32; a.n_tiles = (V + 15) / 16;
   a.sa = sa; a.part = part; a.Mpad = Mpad; a.logits_out = logits_out; a.m_tiles = 0; a.rows_live = max_rows;
+  a.n_wg = n_wg;
+  memset(&a.ver, 0, sizeof a.ver);
+  if (ver) a.ver = *ver;
+  const dim3 grid(n_wg + (!ver ? 0 : ver->d_hidden > 0 ? ver->chunks * ((max_rows + 15) / 16) : 1));
   if (dtype == 0) {
     const int per_wave = ((K + 15) / 16 + 7) / 8;            // groups of 16 k in a wave's share of K, at most 4 requested at a time
-#define SPRINTER_LMF(MT, U) hipLaunchKernelGGL((k_lmhead_f32<MT, U>), dim3(n_wg), dim3(512), 0, s, a)
+#define SPRINTER_LMF(MT, U) hipLaunchKernelGGL((k_lmhead_f32<MT, U>), grid, dim3(512), 0, s, a)
     if (max_rows <= 16) { if (per_wave <= 2) SPRINTER_LMF(1, 2); else SPRINTER_LMF(1, 4); }
     else { if (per_wave <= 2) SPRINTER_LMF(2, 2); else SPRINTER_LMF(2, 4); }
 #undef SPRINTER_LMF
   } else if (max_rows <= 16) {
-    hipLaunchKernelGGL(k_lmhead_bf16<1>, dim3(n_wg), dim3(512), 0, s, a);
+    hipLaunchKernelGGL(k_lmhead_bf16<1>, grid, dim3(512), 0, s, a);
   } else {
     a.m_tiles = (int)(x_elems / ((size_t)a.Kt * 512));      // row tiles the activation buffer holds
     const int tpw = (a.n_tiles + n_wg - 1) / n_wg;           // tiles per workgroup
 #define SPRINTER_LM(MT, KS1, KS2)                                                                       \
   do {                                                                                                  \
-    if (tpw <= 8) hipLaunchKernelGGL((k_lmhead_wide<MT, 1, KS1>), dim3(n_wg), dim3(512), 0, s, a);      \
-    else hipLaunchKernelGGL((k_lmhead_wide<MT, 2, KS2>), dim3(n_wg), dim3(512), 0, s, a);               \
+    if (tpw <= 8) hipLaunchKernelGGL((k_lmhead_wide<MT, 1, KS1>), grid, dim3(512), 0, s, a);      \
+    else hipLaunchKernelGGL((k_lmhead_wide<MT, 2, KS2>), grid, dim3(512), 0, s, a);               \
   } while (0)
     if (max_rows <= 32) SPRINTER_LM(2, 2, 2);
     else if (max_rows <= 64) SPRINTER_LM(4, 2, 2);
     else SPRINTER_LM(8, 2, 1);                               // more than 128 rows: further passes inside the kernel
 #undef SPRINTER_LM
   }
-}
-
-// =============================================================== verifier
-// Hidden layer of the verifier MLP (Sec. 3.2; the paper's single linear layer when d_hidden == 0) in float32.
-// With a hidden layer it is a small matrix product, hidden = relu(hf W1^T + b1), done on the float32 matrix
-// pipes: a workgroup owns 16 rows x 16 hidden units, its 8 waves split K; lane (l16, lq) holds four consecutive k of
-// row l16 and of unit l16 per 16-byte load, and the four 16x16x4 products of a load take k = 4 lq + 0 .. 3 (any
-// assignment of k to products is a valid order of the sum as long as both operands use the same one).  The waves'
-// accumulators are added in fixed order through LDS, then relu(. + b1) * w2 is summed over the 16 units and the
-// workgroup leaves its share of each row's output logit in part[chunk][row]; the consumer adds the chunks in order.
-// (One wave per hidden unit re-read the whole hidden-state matrix per wave - 268 MB through L2 at d = 2048,
-// 512 units and 64 rows, 81 us; this form reads 32 MB.)
-__global__ __launch_bounds__(512) void k_verifier_part(const float* __restrict__ hf, int d, int d_hidden,
-                                                       const float* __restrict__ w1, const float* __restrict__ b1,
-                                                       const float* __restrict__ w2, const int* __restrict__ n_rows_p,
-                                                       float* __restrict__ part, int max_rows) {
-  __shared__ float red[8][4][64];
-  const int n_rows = *n_rows_p;
-  const int lane = threadIdx.x & 63, w = wave_index();
-  if (d_hidden == 0) {                               // (one workgroup)
-    for (int m = w; m < n_rows; m += 8) {
-      float acc = 0.f;
-      for (int k = lane; k < d; k += 64) acc += w2[k] * hf[(size_t)m * d + k];
-      acc = wave_sum(acc);
-      if (lane == 0) part[m] = acc;
-    }
-    return;
-  }
-  const int m0 = blockIdx.y * 16;
-  if (m0 >= n_rows) return;
-  const int l16 = lane & 15, lq = lane >> 4, j = blockIdx.x * 16 + l16;
-  // rows beyond the row count and units beyond the layer are read at the last valid one and dropped below
-  const float4* __restrict__ hrow = reinterpret_cast<const float4*>(hf + (size_t)min(m0 + l16, n_rows - 1) * d) + lq;
-  const float4* __restrict__ wrow = reinterpret_cast<const float4*>(w1 + (size_t)min(j, d_hidden - 1) * d) + lq;
-  const int n16 = d >> 4, g0 = n16 * w / 8, g1 = n16 * (w + 1) / 8;   // this wave's groups of 16 k (d is a multiple of 16)
-  f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
-  for (int g = g0; g < g1; g += 8) {
-    float4 av[8], bv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int gi = min(g + i, g1 - 1);
-      av[i] = hrow[gi * 4];
-      bv[i] = wrow[gi * 4];
-    }
-    __builtin_amdgcn_sched_barrier(0);               // all sixteen loads go out before the first product waits
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bool on = g + i < g1;                    // (scalar) a group beyond the share contributes zeros
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].x, on ? bv[i].x : 0.f, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].y, on ? bv[i].y : 0.f, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].z, on ? bv[i].z : 0.f, acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i].w, on ? bv[i].w : 0.f, acc, 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v) red[w][v][lane] = acc[v];
-  __syncthreads();
-  if (w < 4) {                                       // wave v finishes accumulator register v: row m0 + lq * 4 + v, unit j
-    float sum = 0.f;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) sum += red[q][w][lane];
-    const bool unit = j < d_hidden;
-    const float t = unit ? fmaxf(sum + b1[min(j, d_hidden - 1)], 0.f) * w2[min(j, d_hidden - 1)] : 0.f;
-    const float tot = group_sum<16>(t);
-    const int m = m0 + lq * 4 + w;
-    if (l16 == 0 && m < n_rows) part[(size_t)blockIdx.x * max_rows + m] = tot;
-  }
-}
-int verifier_num_chunks(int d_hidden) { return d_hidden > 0 ? (d_hidden + 15) / 16 : 1; }
-void launch_verifier_part(const float* hf, int d, int d_hidden, const float* w1, const float* b1, const float* w2,
-                          const int* n_rows, float* part, int max_rows, hipStream_t s) {
-  const dim3 grid = d_hidden > 0 ? dim3(verifier_num_chunks(d_hidden), (max_rows + 15) / 16) : dim3(1);
-  hipLaunchKernelGGL(k_verifier_part, grid, dim3(512), 0, s, hf, d, d_hidden, w1, b1, w2, n_rows, part, max_rows);
 }
 
 }  // namespace sprinter

@@ -59,40 +59,21 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_zero, dim3(grid), dim3(256), 0, s, (uint4*)p, n16);
 }
 
-// ================================================================== embed
-template <typename T>
-__global__ __launch_bounds__(256) void k_embed(const T* __restrict__ E, const T* __restrict__ P, RowDesc rd,
-                                               float* __restrict__ h, float* __restrict__ rope, int d, int dh,
-                                               float theta, int use_rope, int V, int max_pos) {
-  int r = blockIdx.x;
-  if (r >= *rd.n_rows) return;
-  int tok = rd.tok[r], pos = rd.pos[r];
-  tok = min(max(tok, 0), V - 1);            // an out-of-vocabulary id must not become a wild read
-  if (P) pos = min(max(pos, 0), max_pos - 1);
-  const T* e = E + (size_t)tok * d;
-  const T* p = P ? P + (size_t)pos * d : nullptr;
-  for (int k = threadIdx.x; k < d; k += 256) {
-    float v = to_f<T>(e[k]);
-    if (p) v += to_f<T>(p[k]);
-    h[(size_t)r * d + k] = v;
-  }
-  if (use_rope && (int)threadIdx.x < dh / 2) {
-    // angle = pos * theta^(-2i/dh), evaluated in double so that large positions stay accurate
-    double inv = pow((double)theta, -2.0 * (double)threadIdx.x / (double)dh);
-    double ang = (double)pos * inv;
-    rope[(size_t)r * dh + 2 * threadIdx.x] = (float)cos(ang);
-    rope[(size_t)r * dh + 2 * threadIdx.x + 1] = (float)sin(ang);
-  }
+// ============================================================ rotary table
+// cos / sin of every position a cache can hold, [max_seq][dh / 2][2]; angle = pos * theta^(-2i/dh), evaluated in double so
+// that large positions stay accurate.  Written once per context: the double-precision pow / cos / sin took 2.5 of the 4.8 us
+// of a one-row embedding launch.
+__global__ __launch_bounds__(256) void k_rope_table(float2* __restrict__ out, int max_seq, int half, float theta) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (size_t)max_seq * half) return;
+  const int pos = (int)(i / half), k = (int)(i % half);
+  const double inv = pow((double)theta, -2.0 * (double)k / (double)(2 * half));
+  const double ang = (double)pos * inv;
+  out[i] = make_float2((float)cos(ang), (float)sin(ang));
 }
-void launch_embed(int dtype, const ModelDims& md, const void* tok_emb, const void* pos_emb, const RowDesc& rd,
-                  float* h, float* rope, int max_rows, hipStream_t s) {
-  int use_rope = md.arch == 1;
-  if (dtype == 0)
-    hipLaunchKernelGGL(k_embed<float>, dim3(max_rows), dim3(256), 0, s, (const float*)tok_emb,
-                       (const float*)pos_emb, rd, h, rope, md.d, md.dh, md.theta, use_rope, md.V, md.max_pos);
-  else
-    hipLaunchKernelGGL(k_embed<bf16_t>, dim3(max_rows), dim3(256), 0, s, (const bf16_t*)tok_emb,
-                       (const bf16_t*)pos_emb, rd, h, rope, md.d, md.dh, md.theta, use_rope, md.V, md.max_pos);
+void launch_rope_table(float* out, int max_seq, int dh, float theta, hipStream_t s) {
+  const size_t n = (size_t)max_seq * (dh / 2);
+  hipLaunchKernelGGL(k_rope_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (float2*)out, max_seq, dh / 2, theta);
 }
 
 // =================================================================== norm
@@ -103,11 +84,23 @@ void launch_embed(int dtype, const ModelDims& md, const void* tok_emb, const voi
 // residual stream may consist of (4 or 8): the row is then h + bias + share 0 + share 1 + ..., added in that
 // order, written back and normalised.  The partial loads are issued with the others, before the row count
 // is known, with clamped share indices and the surplus selected away - no branch, no second memory round.
+// SH = -1: the first norm of a forward; the row is the token's embedding (+ the position's), it starts the residual stream,
+// and the position's rotary factors are copied from the table (an embedding launch of its own cost 1.9 - 4.8 us).
+__device__ __forceinline__ void load8(const float* p, float (&x)[8]) {
+  *reinterpret_cast<float4*>(&x[0]) = *reinterpret_cast<const float4*>(p);
+  *reinterpret_cast<float4*>(&x[4]) = *reinterpret_cast<const float4*>(p + 4);
+}
+__device__ __forceinline__ void load8(const bf16_t* p, float (&x)[8]) {
+  const uint4 v = *reinterpret_cast<const uint4*>(p);
+  const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) { x[2 * k] = __uint_as_float(w[k] << 16); x[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u); }
+}
 template <typename AT, int ARCH, int NI, int SH>
 __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g,
                                                    const float* __restrict__ b, float eps, int d,
                                                    const int* __restrict__ n_rows, AT* __restrict__ act_out,
-                                                   float* __restrict__ f32_out, NormPending pend) {
+                                                   float* __restrict__ f32_out, NormPending pend, EmbedSource emb) {
   __shared__ float s4[4];
   const int r = blockIdx.x, tid = threadIdx.x;
   const float4* __restrict__ x4 = reinterpret_cast<const float4*>(h + (size_t)r * d);
@@ -118,11 +111,31 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
     const int c = min(tid + i * 256, n_chunks - 1);  // clamped: no branch around the loads
-    *reinterpret_cast<float4*>(&x[i][0]) = x4[2 * c]; *reinterpret_cast<float4*>(&x[i][4]) = x4[2 * c + 1];
+    if (SH >= 0) { *reinterpret_cast<float4*>(&x[i][0]) = x4[2 * c]; *reinterpret_cast<float4*>(&x[i][4]) = x4[2 * c + 1]; }
     *reinterpret_cast<float4*>(&gg[i][0]) = g4[2 * c]; *reinterpret_cast<float4*>(&gg[i][4]) = g4[2 * c + 1];
     if (ARCH == 0) { *reinterpret_cast<float4*>(&bb[i][0]) = b4[2 * c]; *reinterpret_cast<float4*>(&bb[i][4]) = b4[2 * c + 1]; }
   }
-  if (SH > 0) {
+  if constexpr (SH < 0) {
+    const int tok = min(max(emb.rd.tok[r], 0), emb.V - 1);   // (an out-of-vocabulary id must not become a wild read)
+    const int pos = max(emb.rd.pos[r], 0);
+    const AT* __restrict__ e = (const AT*)emb.tok_emb + (size_t)tok * d;
+    const AT* __restrict__ p = emb.pos_emb ? (const AT*)emb.pos_emb + (size_t)min(pos, emb.max_pos - 1) * d : nullptr;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int c = min(tid + i * 256, n_chunks - 1);
+      load8(e + c * 8, x[i]);
+      if (p) {
+        float pv[8];
+        load8(p + c * 8, pv);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[i][k] += pv[k];
+      }
+    }
+    if (emb.rope_table && tid < (emb.dh >> 1))
+      reinterpret_cast<float2*>(emb.rope + (size_t)r * emb.dh)[tid] =
+          reinterpret_cast<const float2*>(emb.rope_table + (size_t)min(pos, emb.max_seq - 1) * emb.dh)[tid];
+  }
+  if constexpr (SH > 0) {
     const float4* __restrict__ pb4 = reinterpret_cast<const float4*>(pend.bias ? pend.bias : g);
     const bool has_bias = pend.bias != nullptr;
 #pragma unroll
@@ -144,7 +157,7 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
     }
   }
   if (r >= *n_rows) return;
-  if (SH > 0) {
+  if (SH != 0) {
     float* hrow = const_cast<float*>(h) + (size_t)r * d;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -203,28 +216,31 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
 
 template <typename AT, int ARCH, int NI>
 static void launch_norm_ni(const float* h, const float* g, const float* b, float eps, int d, const int* n_rows,
-                           void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np) {
-#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out, np)
-  if (np.shares <= 0) SPRINTER_NORM(0);
+                           void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np, const EmbedSource* emb) {
+#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out, np, es)
+  EmbedSource es;
+  memset(&es, 0, sizeof es);
+  if (emb) { es = *emb; SPRINTER_NORM(-1); }
+  else if (np.shares <= 0) SPRINTER_NORM(0);
   else if (np.shares <= 4) SPRINTER_NORM(4);
   else SPRINTER_NORM(8);
 #undef SPRINTER_NORM
 }
 template <typename AT, int ARCH>
 static void launch_norm_arch(const float* h, const float* g, const float* b, float eps, int d, const int* n_rows,
-                             void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np) {
-  if (d <= 2048) launch_norm_ni<AT, ARCH, 1>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np);
-  else if (d <= 4096) launch_norm_ni<AT, ARCH, 2>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np);
-  else launch_norm_ni<AT, ARCH, 4>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np);
+                             void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np, const EmbedSource* emb) {
+  if (d <= 2048) launch_norm_ni<AT, ARCH, 1>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np, emb);
+  else if (d <= 4096) launch_norm_ni<AT, ARCH, 2>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np, emb);
+  else launch_norm_ni<AT, ARCH, 4>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np, emb);
 }
 
 void launch_norm(int dtype, int arch, const float* h, const float* g, const float* b, float eps, int d,
                  const int* n_rows, void* act_out, float* f32_out, int max_rows, hipStream_t s,
-                 const NormPending* pend) {
+                 const NormPending* pend, const EmbedSource* emb) {
   NormPending np;
   memset(&np, 0, sizeof np);
   if (pend) np = *pend;
-#define NORM_CASE(AT, ARCH) launch_norm_arch<AT, ARCH>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np)
+#define NORM_CASE(AT, ARCH) launch_norm_arch<AT, ARCH>(h, g, b, eps, d, n_rows, act_out, f32_out, max_rows, s, np, emb)
   if (dtype == 0) { if (arch == 0) NORM_CASE(float, 0); else NORM_CASE(float, 1); }
   else            { if (arch == 0) NORM_CASE(bf16_t, 0); else NORM_CASE(bf16_t, 1); }
 #undef NORM_CASE
