@@ -211,6 +211,7 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
   void* vc = bump.take(layer_stride * md.n_layer * es);
   ModelScratch sc;
   sc.h = (float*)bump.take((size_t)rows * md.d * 4);
+  sc.h2 = (float*)bump.take((size_t)4 * md.d * 4);
   sc.xn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.y = (float*)bump.take((size_t)rows * md.dqkv * 4);
   sc.ao = bump.take(act_elems(c.dtype, rows, md.H * md.dh) * es);
@@ -379,21 +380,35 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   // O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
   // them (and the bias) into the residual stream before it normalises the row.
   const size_t part_stride = (size_t)rows * md.d;
+  // a few rows: the norms before QKV and FFN-up are part of those launches
+  const bool fused = !shared_caches && gemm_takes_norm(md.d, max_rows);
+  float *h = sc.h, *h_other = sc.h2;
   NormPending pend{sc.part, part_stride, 0, nullptr};
   auto resid_gemm = [&](const void* W, const void* X, size_t plane, int K, const float* bias) {
-    pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, PART_SHARES, max_rows, s);
+    pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, fused ? 4 : PART_SHARES, max_rows, s);
     pend.bias = bias;
   };
   auto norm = [&](const float* g, const float* b, void* out, float* f32_out, const EmbedSource* src = nullptr) {
-    launch_norm(dt, md.arch, sc.h, g, b, md.eps, md.d, rd.n_rows, out, f32_out, max_rows, s,
+    launch_norm(dt, md.arch, h, g, b, md.eps, md.d, rd.n_rows, out, f32_out, max_rows, s,
                 pend.shares > 0 ? &pend : nullptr, src);
     pend.shares = 0;
   };
+  // xn = norm(residual stream), out = epilogue(xn W^T): in one launch or two
+  auto norm_gemm = [&](const float* g, const float* b, int epi, const void* W, const void* W2, int N, const float* bias, float* out_f32,
+                       void* out_act, const EmbedSource* src = nullptr) {
+    if (fused) {
+      NormFusion nf{h, h_other, g, b, md.eps, md.arch, pend, src ? *src : EmbedSource{}};
+      launch_gemm_norm(dt, epi, nf, W, W2, N, md.d, bias, out_f32, N, out_act, N, max_rows, s);
+      std::swap(h, h_other);
+      pend.shares = 0;
+    } else {
+      norm(g, b, sc.xn, nullptr, src);
+      launch_gemm(dt, epi, W, W2, sc.xn, pl_d, rd.n_rows, N, md.d, bias, out_f32, N, out_act, N, max_rows, s);
+    }
+  };
   for (int i = 0; i < md.n_layer; ++i) {
     const LayerW& L = m.layers[i];
-    norm(L.n1g, L.n1b, sc.xn, nullptr, i == 0 ? &emb : nullptr);
-    launch_gemm(dt, EPI_F32, L.wqkv, nullptr, sc.xn, pl_d, rd.n_rows, md.dqkv, md.d, L.bqkv, sc.y, md.dqkv, nullptr, 0,
-                max_rows, s);
+    norm_gemm(L.n1g, L.n1b, EPI_F32, L.wqkv, nullptr, md.dqkv, L.bqkv, sc.y, nullptr, i == 0 ? &emb : nullptr);
     if (shared_caches) {
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
                        kv_slots(ctx->cfg), sc.ao, max_rows, s, 1);
@@ -405,13 +420,8 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
     }
     if (!want_head && i + 1 == md.n_layer) break;   // a prefill position only has to fill the caches
     resid_gemm(L.wo, sc.ao, pl_a, md.H * md.dh, L.bo);
-    norm(L.n2g, L.n2b, sc.xn, nullptr);
-    if (md.arch == SPRINTER_ARCH_GPT)
-      launch_gemm(dt, EPI_GELU, L.w1, nullptr, sc.xn, pl_d, rd.n_rows, md.ff, md.d, L.b1, nullptr, 0, sc.mid, md.ff,
-                  max_rows, s);
-    else
-      launch_gemm(dt, EPI_SWIGLU, L.wg, L.wu, sc.xn, pl_d, rd.n_rows, md.ff, md.d, nullptr, nullptr, 0, sc.mid, md.ff,
-                  max_rows, s);
+    if (md.arch == SPRINTER_ARCH_GPT) norm_gemm(L.n2g, L.n2b, EPI_GELU, L.w1, nullptr, md.ff, L.b1, nullptr, sc.mid);
+    else norm_gemm(L.n2g, L.n2b, EPI_SWIGLU, L.wg, L.wu, md.ff, nullptr, nullptr, sc.mid);
     resid_gemm(L.w2, sc.mid, pl_f, md.ff, L.b2);
   }
   if (!want_head) return;

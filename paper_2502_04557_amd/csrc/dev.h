@@ -72,6 +72,23 @@ __device__ __forceinline__ void split2(float a, float b, unsigned& hi, unsigned&
   hi = pk_bf16(a, b);
   lo = pk_bf16(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
 }
+// N consecutive embedding elements (float32 or bf16) as floats, one or two wide loads.
+__device__ __forceinline__ void load_row(const float* p, float (&x)[4]) { *reinterpret_cast<float4*>(x) = *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ void load_row(const float* p, float (&x)[8]) {
+  *reinterpret_cast<float4*>(&x[0]) = *reinterpret_cast<const float4*>(p);
+  *reinterpret_cast<float4*>(&x[4]) = *reinterpret_cast<const float4*>(p + 4);
+}
+__device__ __forceinline__ void load_row(const bf16_t* p, float (&x)[4]) {
+  const uint2 v = *reinterpret_cast<const uint2*>(p);
+  x[0] = __uint_as_float(v.x << 16); x[1] = __uint_as_float(v.x & 0xffff0000u);
+  x[2] = __uint_as_float(v.y << 16); x[3] = __uint_as_float(v.y & 0xffff0000u);
+}
+__device__ __forceinline__ void load_row(const bf16_t* p, float (&x)[8]) {
+  const uint4 v = *reinterpret_cast<const uint4*>(p);
+  const unsigned w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) { x[2 * k] = __uint_as_float(w[k] << 16); x[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u); }
+}
 __device__ __forceinline__ float gelu_tanh(float x) {
   const float c = 0.7978845608028654f;   // sqrt(2/pi)
   return 0.5f * x * (1.0f + tanhf(c * (x + 0.044715f * x * x * x)));
@@ -219,6 +236,15 @@ __device__ __forceinline__ float group_sum(float v) {
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));   // row_half_mirror
   if (LANES == 16) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, true));   // row_mirror
+  return v;
+}
+
+// Sum over the whole wave, in lane 63 only: the DPP row sums, then the row broadcasts (lane 15 of rows 0 and 2 into rows 1
+// and 3, lane 31 into rows 2 and 3).
+__device__ __forceinline__ float wave_total(float v) {
+  v = group_sum<16>(v);
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xA, 0xF, false));   // row_bcast:15
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x143, 0xC, 0xF, false));   // row_bcast:31
   return v;
 }
 

@@ -37,6 +37,7 @@ struct ModelDims {
 constexpr int PART_SHARES = 8;   // most K shares launch_gemm_part may use
 struct ModelScratch {  // per-model activation buffers, sized for max_batch rows
   float* h;            // [M, d] residual stream, float32
+  float* h2;           // [4, d] a few rows' residual stream: launch_gemm_norm alternates between h and h2
   void* xn;            // [M, d] normalised GEMM input (activation layout)
   float* y;            // [M, dqkv] QKV projection output, float32
   void* ao;            // [M, H*dh] attention output (activation layout)
@@ -84,6 +85,15 @@ enum { EPI_F32 = 0, EPI_GELU = 2, EPI_SWIGLU = 3, EPI_PART = 4 /* partial produc
 void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* X, size_t x_elems,
                  const int* n_rows, int N, int K, const float* bias, float* out_f32, int ldo, void* out_act,
                  int out_K, int max_rows, hipStream_t s);
+
+// QKV / FFN-up of a few rows with the norm before it in the same launch (k_gemm_norm.hip): X = norm(h_in + pending) or
+// norm(embedding); the updated residual rows go to h_out (a buffer other than h_in).  At most 4 pending shares.
+struct NormFusion {
+  const float* h_in; float* h_out; const float *g, *b; float eps; int arch; NormPending pend; EmbedSource emb;   // emb.tok_emb NULL: h_in
+};
+bool gemm_takes_norm(int d, int rows);
+void launch_gemm_norm(int dtype, int epi, const NormFusion& f, const void* W, const void* W2, int N, int K, const float* bias,
+                      float* out_f32, int ldo, void* out_act, int out_K, int rows, hipStream_t s);
 
 void launch_attention(int dtype, const ModelDims& md, const float* y, const float* rope, const RowDesc& rd,
                       void* kcache, void* vcache, size_t layer_off, int ctx_bound /* upper bound of the rows' cache lengths */,

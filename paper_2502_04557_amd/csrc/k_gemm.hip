@@ -1,30 +1,10 @@
 // HIP kernels of the batched SPRINTER decode step for gfx950: the projection / FFN GEMMs
 // (Alg. 2: the draft's and the target's forward passes).
-#include "dev.h"
+#include "gemm.h"
 #include <algorithm>
 #include <cstring>
 
 namespace sprinter {
-
-// =================================================================== GEMM
-struct GemmArgs {
-  const void* W; const void* W2; const void* X; const int* n_rows;
-  int N, K, Kt, n_tiles;
-  const float* bias; float* out_f32; int ldo; void* out_act; int out_K;
-  size_t x_elems;     // elements the activation buffer X holds (bf16 mode)
-  int SK; float* part; size_t part_stride;   // k_gemm16_part: K shares, partial outputs [SK][rows][N], floats per share
-  int rows_live;      // the host's bound on the row count: rows from here on exist in no launch, their activations are not fetched
-};
-
-// bias: the column's bias (0 if none)
-template <int EPI, typename AT>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int m, int n, float v, float v2, float bias) {
-  if (m >= n_rows || n >= a.N) return;
-  if (EPI == EPI_F32) a.out_f32[(size_t)m * a.ldo + n] = v + bias;
-  else if (EPI == EPI_GELU) act_store<AT>((AT*)a.out_act, m, n, a.out_K, gelu_tanh(v + bias));
-  else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu(v) * v2);
-}
-
 
 // bf16-mode GEMM (float16 operands) on MFMA for at most 16 rows.  512 threads = 8 waves that split K; each wave owns NTW column tiles
 // (16 columns each): D[m][n] += X[m][k] W[n][k].

@@ -1,0 +1,214 @@
+// HIP kernel of the batched SPRINTER decode step for gfx950: QKV projection and FFN-up for a few rows, with the layer norm
+// (and the residual update or embedding before it) folded into the same launch.
+#include "gemm.h"
+#include <algorithm>
+#include <cstring>
+
+namespace sprinter {
+
+// At a handful of rows a step is a chain of short dependent launches, and the norm is two of a layer's seven: 3 - 4 us each
+// for a few KiB of work.  Here every workgroup of the product that follows normalises the rows for itself: it requests the
+// weight tiles of its first k tiles, then reads the residual rows and the pending partial products (or the embeddings), adds
+// them in the order of k_norm, takes the statistics in two passes, and leaves the normalised rows in LDS, from where the
+// matrix instructions take them.  Workgroup 0 also writes the updated residual rows - to the other of two buffers, since its
+// neighbours are still reading this one.  What it costs is R d (1 + shares) floats per workgroup through L2 next to its own
+// weights, so it is taken only while that stays small (gemm_takes_norm): norm + product as two launches against one, at 1 / 2 / 4 rows
+// and 4 shares: d = 1600, N = 4800: 9.0 / 9.1 / 9.1 -> 6.4 / 7.2 / 8.8 us; N = 6400: 9.5 -> 7.2 / 8.0 / 9.5; d = 2048 (RMS),
+// N = 3072: 8.0 -> 5.4 / 6.0 / 7.4; N = 2 x 8192: 17.3 -> 14.6 / 15.1 / 16.4; at 8 rows 2 - 3 us slower than two launches.
+// R rows; thread t takes float4 t of every row (d <= 2048), so gain, offset and bias are fetched once.
+template <typename AT, int R, int NTW, int EPI>
+__global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
+  constexpr bool BF = sizeof(AT) == 2;                  // bf16 mode: float16 operand tiles; else float32 rows
+  constexpr bool DUAL = (EPI == EPI_SWIGLU), ACT_OUT = BF && (EPI == EPI_GELU || EPI == EPI_SWIGLU);
+  constexpr int NW = NTW * (DUAL ? 2 : 1), NI4 = NW * 4, U = 8;   // weight tiles per k tile; k tiles (16-k groups) in flight
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ float s_stat[2][R][8];
+  __shared__ float red[8 * NI4 * 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
+  const int nt0 = blockIdx.x * NTW, d = a.K;
+  // ---- this wave's share of K: k tiles w, w + 8, .. (bf16) or 16-k groups [g0, g1) (float32); first weights requested
+  const int n_k = BF ? a.Kt : d >> 4;
+  const int g0 = BF ? w : n_k * w / 8, g1 = BF ? n_k : n_k * (w + 1) / 8, gs = BF ? 8 : 1;
+  const uint4* wp[NW];
+#pragma unroll
+  for (int j = 0; j < NW; ++j) {
+    const void* W = DUAL && j >= NTW ? a.W2 : a.W;
+    const int nt = min(nt0 + (j % NTW), a.n_tiles - 1);
+    wp[j] = BF ? (const uint4*)W + (size_t)nt * a.Kt * 64 + lane
+               : (const uint4*)((const float*)W + (size_t)min(nt * 16 + l16, a.N - 1) * d + lq * 4);
+  }
+  uint4 wv[U][NW];
+  auto load_weights = [&](int g) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g + u * gs < g1) {                            // (scalar; the tiles beyond the share are skipped below too)
+#pragma unroll
+        for (int j = 0; j < NW; ++j) wv[u][j] = wp[j][(size_t)(g + u * gs) * (BF ? 64 : 4)];
+      }
+  };
+  load_weights(g0);
+  // this thread's output element: (row m, column c of the workgroup's 16 NTW columns), as in k_gemm16 / k_gemm_f32
+  int m, c;
+  if (ACT_OUT) { m = (tid >> 3) & 15; c = (tid >> 7) * 8 + (tid & 7); }
+  else { m = tid / (16 * NTW); c = tid % (16 * NTW); }
+  const int n = nt0 * 16 + c;
+  const bool out_ok = tid < NTW * 256 && m < a.rows_live && n < a.N;
+  const float pbias = (out_ok && a.bias) ? a.bias[n] : 0.f;
+  // ---- residual rows
+  const int n4 = d >> 2, q4 = min(tid, n4 - 1);
+  const bool mine = tid < n4;
+  const float4 gg = reinterpret_cast<const float4*>(f.g)[q4];
+  float4 bb = make_float4(0.f, 0.f, 0.f, 0.f), pb = bb, x[R];
+  if (f.b) bb = reinterpret_cast<const float4*>(f.b)[q4];
+  if (f.emb.tok_emb) {                                  // first norm of a forward: the token's (and the position's) embedding
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int tok = min(max(f.emb.rd.tok[r], 0), f.emb.V - 1), pos = max(f.emb.rd.pos[r], 0);
+      const AT* __restrict__ e = (const AT*)f.emb.tok_emb + (size_t)tok * d;
+      const AT* __restrict__ p = f.emb.pos_emb ? (const AT*)f.emb.pos_emb + (size_t)min(pos, f.emb.max_pos - 1) * d : nullptr;
+      float ev[4], pv[4] = {0.f, 0.f, 0.f, 0.f};
+      load_row(e + q4 * 4, ev);
+      if (p) load_row(p + q4 * 4, pv);
+      x[r] = make_float4(ev[0] + pv[0], ev[1] + pv[1], ev[2] + pv[2], ev[3] + pv[3]);
+      if (blockIdx.x == 0 && f.emb.rope_table && tid < (f.emb.dh >> 1))
+        reinterpret_cast<float2*>(f.emb.rope + (size_t)r * f.emb.dh)[tid] =
+            reinterpret_cast<const float2*>(f.emb.rope_table + (size_t)min(pos, f.emb.max_seq - 1) * f.emb.dh)[tid];
+    }
+  } else {
+    if (f.pend.bias) pb = reinterpret_cast<const float4*>(f.pend.bias)[q4];
+    float4 p[R][4];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const size_t q = (size_t)r * n4 + q4;
+      x[r] = reinterpret_cast<const float4*>(f.h_in)[q];
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (s < f.pend.shares) p[r][s] = reinterpret_cast<const float4*>(f.pend.part + (size_t)s * f.pend.stride)[q];   // (scalar test)
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {                       // fixed order: bias, share 0, share 1, ...
+      x[r].x += pb.x; x[r].y += pb.y; x[r].z += pb.z; x[r].w += pb.w;
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (s < f.pend.shares) { x[r].x += p[r][s].x; x[r].y += p[r][s].y; x[r].z += p[r][s].z; x[r].w += p[r][s].w; }
+    }
+  }
+  if (blockIdx.x == 0 && mine) {
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      reinterpret_cast<float4*>(f.h_out)[(size_t)r * n4 + tid] = x[r];
+  }
+  // ---- statistics: the wave (DPP only), then every thread adds the 8 waves' sums.  No shuffles through LDS and one store
+  // block for all rows: a wave-wide butterfly per row, each waited for on its own, was 0.3 us a row.
+  float part[R];
+  auto row_sums = [&](int slot) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) part[r] = wave_total(part[r]);
+    if (lane == 63) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) s_stat[slot][r][w] = part[r];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float4 u = *reinterpret_cast<const float4*>(&s_stat[slot][r][0]), v = *reinterpret_cast<const float4*>(&s_stat[slot][r][4]);
+      part[r] = (((u.x + u.y) + (u.z + u.w)) + ((v.x + v.y) + (v.z + v.w)));
+    }
+  };
+  if (f.arch == 0) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) part[r] = mine ? (x[r].x + x[r].y) + (x[r].z + x[r].w) : 0.f;
+    row_sums(0);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float mean = part[r] / (float)d;
+      x[r].x -= mean; x[r].y -= mean; x[r].z -= mean; x[r].w -= mean;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r) part[r] = mine ? (x[r].x * x[r].x + x[r].y * x[r].y) + (x[r].z * x[r].z + x[r].w * x[r].w) : 0.f;
+  row_sums(1);
+  // ---- normalised rows to LDS: float16 operand slots [k / 8][row] of 16 bytes, or float32 rows (4 floats of padding)
+  if (mine) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const float rstd = 1.0f / sqrtf(part[r] / (float)d + f.eps);
+      const float o0 = x[r].x * rstd * gg.x + bb.x, o1 = x[r].y * rstd * gg.y + bb.y;
+      const float o2 = x[r].z * rstd * gg.z + bb.z, o3 = x[r].w * rstd * gg.w + bb.w;
+      if (BF) *reinterpret_cast<uint2*>(smem + ((size_t)(tid >> 1) * R + r) * 16 + (tid & 1) * 8) = make_uint2(pk_f16(o0, o1), pk_f16(o2, o3));
+      else *reinterpret_cast<float4*>(smem + ((size_t)r * (d + 4) + tid * 4) * 4) = make_float4(o0, o1, o2, o3);
+    }
+  }
+  __syncthreads();
+  // ---- product
+  const int xrow = min(l16, R - 1);                  // (lanes of absent rows repeat the last one; their outputs are dropped)
+  f32x4 acc[NW];
+#pragma unroll
+  for (int j = 0; j < NW; ++j) acc[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int g = g0; g < g1; g += U * gs) {
+    if (g != g0) load_weights(g);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g + u * gs < g1) {                            // (scalar)
+        if constexpr (BF) {
+          const uint4 xv = *reinterpret_cast<const uint4*>(smem + ((size_t)((g + u * 8) * 4 + lq) * R + xrow) * 16);
+#pragma unroll
+          for (int j = 0; j < NW; ++j) acc[j] = mfma_f16(xv, wv[u][j], acc[j]);
+        } else {
+          const float4 xv = *reinterpret_cast<const float4*>(smem + ((size_t)xrow * (d + 4) + (g + u) * 16 + lq * 4) * 4);
+#pragma unroll
+          for (int j = 0; j < NW; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32((&xv.x)[e], __uint_as_float((&wv[u][j].x)[e]), acc[j], 0, 0, 0);
+        }
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < NW; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[((size_t)w * NI4 + j * 4 + v) * 64 + lane] = acc[j][v];
+  __syncthreads();
+  if (!out_ok) return;
+  const int it = (c >> 4) * 4 + (m & 3), sl = (m >> 2) * 16 + (c & 15);
+  float s1 = 0.f, sg = 0.f;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {                         // fixed order: wave 0, 1, ..
+    s1 += red[((size_t)q * NI4 + it) * 64 + sl];
+    if (DUAL) sg += red[((size_t)q * NI4 + NTW * 4 + it) * 64 + sl];
+  }
+  gemm_epilogue<EPI, AT>(a, a.rows_live, m, n, s1, sg, pbias);
+}
+
+// The line: a row costs about 0.75 us of a 1600-wide launch, and a launch saves 3.3 - 3.5 us less the 1 us the prologue takes
+// at any row count.  Wider rows (4096: 896 workgroups for FFN-up) lose already at one: 45.6 -> 48.4 us.
+bool gemm_takes_norm(int d, int rows) { return rows <= 4 && d <= 2048; }
+
+template <typename AT, int NTW, int EPI>
+static void launch_gemm_norm_epi(const GemmArgs& a, const NormFusion& f, int rows, hipStream_t s) {
+  const dim3 grid((a.n_tiles + NTW - 1) / NTW);
+  const size_t lds = sizeof(AT) == 2 ? (size_t)rows * a.K * 2 : (size_t)rows * (a.K + 4) * 4;
+#define SPRINTER_FUSED(R_) hipLaunchKernelGGL((k_gemm_norm<AT, R_, NTW, EPI>), grid, dim3(512), lds, s, a, f)
+  if (rows == 1) SPRINTER_FUSED(1); else if (rows == 2) SPRINTER_FUSED(2); else if (rows == 3) SPRINTER_FUSED(3); else SPRINTER_FUSED(4);
+#undef SPRINTER_FUSED
+}
+
+void launch_gemm_norm(int dtype, int epi, const NormFusion& f, const void* W, const void* W2, int N, int K, const float* bias,
+                      float* out_f32, int ldo, void* out_act, int out_K, int rows, hipStream_t s) {
+  GemmArgs a;
+  memset(&a, 0, sizeof a);
+  a.W = W; a.W2 = W2; a.N = N; a.K = K; a.Kt = (K + 31) / 32; a.n_tiles = (N + 15) / 16;
+  a.bias = bias; a.out_f32 = out_f32; a.ldo = ldo; a.out_act = out_act; a.out_K = out_K; a.rows_live = rows;
+#define SPRINTER_EPI(AT, NTW)                                                                 \
+  do {                                                                                        \
+    if (epi == EPI_F32) launch_gemm_norm_epi<AT, NTW, EPI_F32>(a, f, rows, s);                \
+    else if (epi == EPI_GELU) launch_gemm_norm_epi<AT, NTW, EPI_GELU>(a, f, rows, s);         \
+    else launch_gemm_norm_epi<AT, NTW, EPI_SWIGLU>(a, f, rows, s);                            \
+  } while (0)
+  if (dtype == 0) SPRINTER_EPI(float, 1);
+  else if (a.n_tiles >= 256 && a.Kt < 100) SPRINTER_EPI(bf16_t, 2);   // two column tiles per wave, as k_gemm16
+  else SPRINTER_EPI(bf16_t, 1);
+#undef SPRINTER_EPI
+}
+
+}  // namespace sprinter

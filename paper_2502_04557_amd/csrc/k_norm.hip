@@ -86,16 +86,6 @@ void launch_rope_table(float* out, int max_seq, int dh, float theta, hipStream_t
 // is known, with clamped share indices and the surplus selected away - no branch, no second memory round.
 // SH = -1: the first norm of a forward; the row is the token's embedding (+ the position's), it starts the residual stream,
 // and the position's rotary factors are copied from the table (an embedding launch of its own cost 1.9 - 4.8 us).
-__device__ __forceinline__ void load8(const float* p, float (&x)[8]) {
-  *reinterpret_cast<float4*>(&x[0]) = *reinterpret_cast<const float4*>(p);
-  *reinterpret_cast<float4*>(&x[4]) = *reinterpret_cast<const float4*>(p + 4);
-}
-__device__ __forceinline__ void load8(const bf16_t* p, float (&x)[8]) {
-  const uint4 v = *reinterpret_cast<const uint4*>(p);
-  const unsigned w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) { x[2 * k] = __uint_as_float(w[k] << 16); x[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u); }
-}
 template <typename AT, int ARCH, int NI, int SH>
 __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g,
                                                    const float* __restrict__ b, float eps, int d,
@@ -123,10 +113,10 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int c = min(tid + i * 256, n_chunks - 1);
-      load8(e + c * 8, x[i]);
+      load_row(e + c * 8, x[i]);
       if (p) {
         float pv[8];
-        load8(p + c * 8, pv);
+        load_row(p + c * 8, pv);
 #pragma unroll
         for (int k = 0; k < 8; ++k) x[i][k] += pv[k];
       }

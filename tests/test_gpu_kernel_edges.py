@@ -47,3 +47,13 @@ def test_float32_matrix_kernels(B, ff):
     (half a group at the end), 192, 512 and 1096 (two K shares); both FFN kinds; a vocabulary with a ragged last column tile."""
     _check(_gpt(1, 64, ff, 331), _llama(1, 512, 8, 4, ff, 331), B, W.DT_F32)
     _check(_llama(1, 192, 3, 3, ff, 35), _gpt(1, 256, ff, 35), B, W.DT_F32)
+
+
+@pytest.mark.parametrize("dtype", [W.DT_F32, W.DT_BF16])
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 5])
+def test_norm_inside_the_product(B, dtype):
+    """A few rows: the norm folded into QKV / FFN-up, at its row counts and just beyond, with
+    both norms, gate + up and GELU, column tiles in pairs (>= 256 of them) and ragged; deep enough that both residual
+    buffers and K shares are used.  tau > 1: the target sees the same rows."""
+    _check(_gpt(2, 128, 200, 83), _llama(3, 512, 4, 2, 4104, 83), B, dtype, tau=1.5)
+    _check(_llama(3, 640, 10, 5, 136, 83), _gpt(2, 2048 if B == 2 else 1024, 4232, 83), B, dtype, tau=1.5)
