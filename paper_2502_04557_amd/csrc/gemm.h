@@ -1,4 +1,5 @@
-// What the GEMM kernels (k_gemm.hip, k_gemm_norm.hip) share: launch arguments and the epilogue of one output element.
+// What the GEMM kernels (k_gemm.hip, k_gemm_norm.hip, k_gemm_tile.hip) share: launch arguments and the epilogue of one output
+// element.
 #pragma once
 #include "dev.h"
 
@@ -22,5 +23,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int
   else if (EPI == EPI_GELU) act_store<AT>((AT*)a.out_act, m, n, a.out_K, gelu_tanh(v + bias));
   else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu(v) * v2);
 }
+
+// The kernel for many rows (k_gemm_tile.hip): whether a shape takes it, and its launch (returns the K shares of EPI_PART).
+bool gemm_takes_tile(int epi, const GemmArgs& a, int rows, int max_shares);
+int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipStream_t s);
 
 }  // namespace sprinter

@@ -269,150 +269,6 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   }
 }
 
-// bf16-mode GEMM for 128+ rows (prefill chunks, long work lists): the 8 waves of a workgroup split the COLUMNS (NTW
-// column tiles each; SwiGLU: one gate + one up tile) and share the activations of 8 row tiles (128 rows) through LDS,
-// so a k tile costs the workgroup 8 KiB of activations (once) + 8 * NWT KiB of weights for
-// 8 * NWT * 8 MFMAs - far fewer bytes per MFMA than the K-split kernel above, which reads every operand per wave.
-// Two k tiles per stage (one with four weight tiles per wave), two LDS stages: the global loads of stage c + 1 (the activation fragments a thread stages, into
-// registers, and the wave's own weight tiles) are in flight while the MFMAs of stage c run; one barrier per stage.
-// blockIdx.y = group of 128 rows, blockIdx.z = K share (EPI_PART).  The activation buffer must hold every row
-// tile the grid covers (the launcher checks it against the buffer's size).
-template <int NTW, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_wide(GemmArgs a) {
-  constexpr bool DUAL = (EPI == EPI_SWIGLU);
-  constexpr int NWT = NTW * (DUAL ? 2 : 1), MT = 8;
-  constexpr int KU = NWT >= 4 ? 1 : 2;                 // k tiles per stage (four weight tiles per wave leave registers for one)
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  __shared__ u32x4 xs[2][KU][MT][64];                   // [stage][k tile][row tile][lane]: 16 KiB per k tile of a stage
-  const int lane = threadIdx.x & 63, w = wave_index();
-  const int Kt = a.Kt, mtile0 = blockIdx.y * MT, nt0 = (blockIdx.x * 8 + w) * NTW;
-  const int sk = (EPI == EPI_PART) ? blockIdx.z : 0, SK = (EPI == EPI_PART) ? gridDim.z : 1;
-  const int k0 = (int)((long long)Kt * sk / SK), k1 = (int)((long long)Kt * (sk + 1) / SK);
-  const uint4* __restrict__ Wp = (const uint4*)a.W + lane;
-  const uint4* __restrict__ W2p = DUAL ? (const uint4*)a.W2 + lane : nullptr;
-  // staging: wave w fetches row tile w of every k tile of the stage
-  const u32x4* __restrict__ Xh = (const u32x4*)a.X + (size_t)(mtile0 + w) * Kt * 64 + lane;
-  size_t wrow[NTW];
-#pragma unroll
-  for (int j = 0; j < NTW; ++j) wrow[j] = (size_t)min(nt0 + j, a.n_tiles - 1) * Kt * 64;
-  struct Regs { u32x4 x[KU]; uint4 w[KU][NWT]; };
-  auto gload = [&](Regs& r, int kt) {
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int kc = min(kt + u, k1 - 1);                // clamped: always a tile of this share
-      r.x[u] = Xh[(size_t)kc * 64];
-#pragma unroll
-      for (int j = 0; j < NTW; ++j) {
-        r.w[u][j] = Wp[wrow[j] + (size_t)kc * 64];
-        if (DUAL) r.w[u][NTW + j] = W2p[wrow[j] + (size_t)kc * 64];
-      }
-    }
-  };
-  auto sstore = [&](int stage, const Regs& r) {
-#pragma unroll
-    for (int i = 0; i < KU; ++i) xs[stage][i][w][lane] = r.x[i];
-  };
-  f32x4 acc[NWT][MT];
-#pragma unroll
-  for (int j = 0; j < NWT; ++j)
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[j][mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int stage, const Regs& r, int kt) {
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const bool in_k = kt + u < k1;
-      uint4 wv[NWT];
-#pragma unroll
-      for (int j = 0; j < NWT; ++j) wv[j] = in_k ? r.w[u][j] : make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const u32x4 h = xs[stage][u][mt][lane];
-        const uint4 xh = make_uint4(h.x, h.y, h.z, h.w);
-#pragma unroll
-        for (int j = 0; j < NWT; ++j) {
-          acc[j][mt] = mfma_f16(xh, wv[j], acc[j][mt]);
-        }
-      }
-    }
-  };
-  Regs A, B;
-  gload(A, k0);
-  sstore(0, A);
-  const int n_rows = *a.n_rows;                          // only the epilogue needs it
-  __syncthreads();
-  for (int kt = k0; kt < k1; kt += 2 * KU) {
-    gload(B, kt + KU);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(0, A, kt);
-    sstore(1, B);
-    __syncthreads();
-    gload(A, kt + 2 * KU);
-    __builtin_amdgcn_sched_barrier(0);
-    compute(1, B, kt + KU);
-    sstore(0, A);
-    __syncthreads();
-  }
-  // every wave stores its own 128 x 16 NTW block straight from the accumulators (lane l, register v: column l % 16,
-  // row (l / 16) * 4 + v)
-  float* part = (EPI == EPI_PART) ? a.part + (size_t)sk * a.part_stride : nullptr;
-#pragma unroll
-  for (int j = 0; j < NTW; ++j) {
-    const int n = (nt0 + j) * 16 + (lane & 15);
-    if (n >= a.N) continue;
-    const float bias = (EPI != EPI_PART && a.bias) ? a.bias[n] : 0.f;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int m = (mtile0 + mt) * 16 + (lane >> 4) * 4 + v;
-        if (m >= n_rows) continue;
-        const float s1 = acc[j][mt][v], s2 = DUAL ? acc[NTW + j][mt][v] : 0.f;
-        if constexpr (EPI == EPI_PART) {
-          part[(size_t)m * a.ldo + n] = s1;
-        } else {
-          gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias);
-        }
-      }
-  }
-}
-
-// Launches k_gemm_wide if the row count calls for it and the activation buffer holds every row tile of the grid.
-// min_rows: 128 for outputs that need the whole K in one workgroup; 97 for partial products, where K shares bring the
-// workgroup count back up (c4's shapes at 100 rows: FFN-down 4096 x 11008 50.8 -> 42.2 us, O-proj 25.5 -> 18.3 us with one
-// 128-row group, while FFN-up and QKV, left with 86 - 96 workgroups, lose: 95 -> 115 us and 56 -> 77 us; at 72 - 88 rows
-// FFN-down loses too, 42 -> 46 us, against two passes of 3 row tiles).
-template <int EPI>
-static bool try_gemm_wide(const GemmArgs& a, int max_rows, int sk, hipStream_t s, int min_rows = 128) {
-  if (max_rows < min_rows) return false;
-  const int row_groups = (max_rows + 127) / 128;
-  if ((size_t)row_groups * 128 * a.Kt * 32 > a.x_elems) return false;
-  constexpr bool DUAL = EPI == EPI_SWIGLU;
-  const int g2 = (a.n_tiles + 15) / 16, g1 = (a.n_tiles + 7) / 8;
-  // too few workgroups for the chip (a 128-row decode batch on a narrow model: 18 column groups): the K-split
-  // kernels, which put every column tile in a workgroup of its own, do better there
-  if (g1 * row_groups * sk < 128) return false;
-  // four weight tiles per wave (SwiGLU: two gate + two up) halve the LDS reads per MFMA, which at two tiles take as
-  // long as the MFMAs themselves; two or one tile per wave where that would leave too few workgroups
-  const int g4 = (a.n_tiles + 31) / 32;
-  if constexpr (DUAL) {
-    if (g2 * row_groups * sk >= 160) {
-      hipLaunchKernelGGL((k_gemm_wide<2, EPI>), dim3(g2, row_groups, sk), dim3(512), 0, s, a);
-      return true;
-    }
-  } else {
-    if (g4 * row_groups * sk >= 160) {
-      hipLaunchKernelGGL((k_gemm_wide<4, EPI>), dim3(g4, row_groups, sk), dim3(512), 0, s, a);
-      return true;
-    }
-    if (g2 * row_groups * sk >= 160) {
-      hipLaunchKernelGGL((k_gemm_wide<2, EPI>), dim3(g2, row_groups, sk), dim3(512), 0, s, a);
-      return true;
-    }
-  }
-  hipLaunchKernelGGL((k_gemm_wide<1, EPI>), dim3(g1, row_groups, sk), dim3(512), 0, s, a);
-  return true;
-}
-
 // bf16-mode GEMM for at most 16 rows whose output only has to exist as a sum: O-proj and FFN-down add into the
 // residual stream, and the layer norm that follows reads the whole row anyway.  K is split into SK shares
 // over workgroups (workgroup = NTW column tiles x one share), each share leaves its partial product in
@@ -605,7 +461,7 @@ static void launch_gemm_bf16(const GemmArgs& a, int max_rows, hipStream_t s) {
   if (max_rows <= 16 && a.n_tiles >= 256 && a.Kt < 100)
     hipLaunchKernelGGL((k_gemm16<2, EPI>), dim3((a.n_tiles + 1) / 2), dim3(512), 0, s, a);
   else if (max_rows <= 16) hipLaunchKernelGGL((k_gemm16<1, EPI>), dim3(a.n_tiles), dim3(512), 0, s, a);
-  else if (try_gemm_wide<EPI>(a, max_rows, 1, s)) return;
+  else if (gemm_takes_tile(EPI, a, max_rows, 1)) launch_gemm_tile(EPI, a, max_rows, 1, s);
   else {
     // column tiles per wave that share the activation fragments: as many as leave about 192 workgroups
     // as few passes over the weights as 4 row tiles per pass allow, the row tiles spread evenly over them
@@ -687,17 +543,7 @@ int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, co
   // 17+ rows: the workgroup's activation traffic (1 KiB per k tile and 16 rows) is what costs, so a wave takes
   // four column tiles (two if that leaves too few workgroups) and K is split until about 256 workgroups exist,
   // with at least two k tiles per wave and share
-  if (max_rows >= 97) {            // 97+ rows: column-split workgroups, K shares until about 256 of them exist
-    const int row_groups = (max_rows + 127) / 128, s_lim = std::max(1, std::min(max_shares, a.Kt / 16));
-    // first with four column tiles per wave (the shares make up for the fewer column groups), then with two
-    for (int per_group : {32, 16}) {
-      const int groups = (a.n_tiles + per_group - 1) / per_group * row_groups;
-      const int sk = std::max(1, std::min(s_lim, (256 + groups - 1) / groups));
-      if (per_group == 32 && groups * sk < 160) continue;
-      a.SK = sk;
-      if (try_gemm_wide<EPI_PART>(a, max_rows, sk, s, 97)) return sk;
-    }
-  }
+  if (gemm_takes_tile(EPI_PART, a, max_rows, max_shares)) return launch_gemm_tile(EPI_PART, a, max_rows, max_shares, s);
   const int row_tiles = (max_rows + 15) / 16;
   const int s_max = std::max(1, std::min(max_shares, a.Kt / 16));
 #define SPRINTER_PART(MT_, NTW_) hipLaunchKernelGGL((k_gemm_rows<MT_, NTW_, EPI_PART>), grid, dim3(512), 0, s, a)

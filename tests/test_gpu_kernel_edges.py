@@ -8,7 +8,7 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_min=2, n_gen=3, tau=0.5, max_seq=48, seed=7):
+def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_min=2, n_gen=3, tau=0.5, max_seq=48, seed=7, whole_prompt=False):
     """Decode steps of one configuration; returns the rejected rows per step."""
     from parity_util import Pair, compare_replay, close_enough, eps_of
     cfg = W.SprinterCfg(draft, target, ver_hidden, dtype, B, max_seq, tau=tau, seed=seed, name="edges", batch=B, prompt_len=prompt_len,
@@ -18,7 +18,7 @@ def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_m
     outs, _ = p.gpu_steps(n_gen)
     g = {k: np.stack([o[k2] for o in outs], axis=1) for k, k2 in
          (("tok", "committed_tok"), ("accept", "accept"), ("score", "score"), ("draft_tok", "draft_tok"))}
-    rec = p.oracle(n_gen, forced=dict(tok=g["tok"], accept=g["accept"]), keep_logits=True)
+    rec = p.oracle(n_gen, forced=dict(tok=g["tok"], accept=g["accept"]), keep_logits=True, whole_prompt_prefill=whole_prompt)
     print(B, dtype, compare_replay(cfg, g, rec), flush=True)
     for s, o in enumerate(outs):
         R = int(o["n_rej"][0])
@@ -57,3 +57,14 @@ def test_norm_inside_the_product(B, dtype):
     buffers and K shares are used.  tau > 1: the target sees the same rows."""
     _check(_gpt(2, 128, 200, 83), _llama(3, 512, 4, 2, 4104, 83), B, dtype, tau=1.5)
     _check(_llama(3, 640, 10, 5, 136, 83), _gpt(2, 2048 if B == 2 else 1024, 4232, 83), B, dtype, tau=1.5)
+
+
+@pytest.mark.parametrize("B, prompt_len", [(7, 20), (9, 59), (8, 114)])
+def test_tiles_of_many_rows(B, prompt_len):
+    """Prefill passes of 133, 522 and 904 rows (none a multiple of a tile): the 64-row tile with K shares, the 128-row tile and
+    the 256-row tile (FFN-up of the target at 522 and 904 rows), a last k tile that is a quarter and a whole one too many for
+    pairs of k tiles (FFN-down, K = 3080 and 5128), column tiles beyond the last one, GELU and SwiGLU.  The prefilled caches
+    carry every position, so the first steps' logits depend on all of them."""
+    draft = W.ModelCfg(W.ARCH_GPT, 2, 768, 12, 12, 3080, 331, 128)
+    target = W.ModelCfg(W.ARCH_LLAMA, 2, 1024, 16, 16, 5128, 331, 128, 1e-5, 10000.0)
+    _check(draft, target, B, W.DT_BF16, prompt_len=prompt_len, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=128, whole_prompt=True)
