@@ -203,19 +203,19 @@ void launch_step_finish(const FinishArgs& a, hipStream_t s) {
 // Chunked prefill: the prompts go into the token history, every row's caches count as empty and every row is
 // listed, so that the full-prefix work-list kernel (k_catchup_chunk) enumerates the prompt positions 0 .. P_b-2
 // in row-major order from the prefix sums the host uploaded.
-__global__ __launch_bounds__(1024) void k_prefill_begin(const int* __restrict__ prompt, int max_prompt, int B, State st,
-                                                        int* rej_idx, int* n_rej) {
-  const int tid = threadIdx.x;
-  if (tid < B) {
-    const int P = st.prompt_len[tid];
-    for (int j = 0; j < P; ++j) st.hist[(size_t)tid * st.hist_stride + j] = prompt[(size_t)tid * max_prompt + j];
-    st.len_p[tid] = 0;
-    rej_idx[tid] = tid;
+// One workgroup per row (one thread per row copied its prompt token after token: 1.1 ms for 2000 tokens).
+__global__ __launch_bounds__(256) void k_prefill_begin(const int* __restrict__ prompt, int max_prompt, int B, State st,
+                                                       int* rej_idx, int* n_rej) {
+  const int b = blockIdx.x, P = st.prompt_len[b];
+  for (int j = threadIdx.x; j < P; j += 256) st.hist[(size_t)b * st.hist_stride + j] = prompt[(size_t)b * max_prompt + j];
+  if (threadIdx.x == 0) {
+    st.len_p[b] = 0;
+    rej_idx[b] = b;
+    if (b == 0) *n_rej = B;
   }
-  if (tid == 0) *n_rej = B;
 }
 void launch_prefill_begin(const int* prompt, int max_prompt, int B, State st, int* rej_idx, int* n_rej, hipStream_t s) {
-  hipLaunchKernelGGL(k_prefill_begin, dim3(1), dim3(1024), 0, s, prompt, max_prompt, B, st, rej_idx, n_rej);
+  hipLaunchKernelGGL(k_prefill_begin, dim3(B), dim3(256), 0, s, prompt, max_prompt, B, st, rej_idx, n_rej);
 }
 
 __global__ __launch_bounds__(1024) void k_prefill_finish(const int* __restrict__ prompt, int max_prompt, int B,
@@ -229,7 +229,6 @@ __global__ __launch_bounds__(1024) void k_prefill_finish(const int* __restrict__
     st.len_q[tid] = P - 1;
     st.len_p[tid] = P - 1;
     st.n_target_calls[tid] = 0;
-    for (int j = 0; j < P; ++j) st.hist[(size_t)tid * st.hist_stride + j] = prompt[(size_t)tid * max_prompt + j];
     d_b[tid] = tid;
     d_tok[tid] = last;
     d_pos[tid] = P - 1;
