@@ -420,214 +420,275 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
 }
 
 // Append-only launch of a multi-entry pass: rotate the new key, round key and value to bf16 and write them to the
-// entry's cache slot - what k_attn_dec_bf16 does in its prologue, without the attention around it.  One 64-lane
-// workgroup per (entry, KV head): the first DH / 8 lanes take the key, the next DH / 8 the value, 8 elements each.
+// entry's cache slot - what k_attn_dec_bf16 does in its prologue, without the attention around it.  One wave per
+// (8 entries, KV head).  The value cache keeps 8 consecutive slots of a column in 16 bytes (vt_index): where 8 entries in a row
+// are such a block of slots of one batch row - all but the ends of a prefill run - the wave in whose window the block begins
+// gathers a column's 8 values from the 8 rows per lane and stores 16 bytes; the other entries of the window go 2 bytes per
+// entry and column, as in the attention kernel.  (One entry per wave with 2-byte stores: 125 us for 4096 entries x 32 heads
+// x 128 columns, now 49, of which 30 are its 192 MB at the rate of a copy.)
 template <int DH>
 __global__ __launch_bounds__(64) void k_kv_append_bf16(AttnArgs a) {
-  constexpr int LPK = DH / 8;
-  const int r = blockIdx.y, lane = threadIdx.x;
-  if (r >= *a.rd.n_rows || lane >= 2 * LPK) return;
-  const int kvh = blockIdx.x, b = a.rd.b[r], slot = a.rd.slot[r], S = a.max_seq;
-  const bool is_v = lane >= LPK;
+  constexpr int LPK = DH / 8, KEYS = 64 / LPK;                   // lanes per key, keys per wave and round
+  const int n_rows = *a.rd.n_rows, r0 = blockIdx.y * 8;
+  if (r0 >= n_rows) return;
+  const int lane = threadIdx.x, kvh = blockIdx.x, S = a.max_seq, n_here = min(8, n_rows - r0);
+  // lane i: the descriptor of entry r0 - 7 + i, so that lanes 7 .. 14 hold the window and its blocks lie in lanes 0 .. 21
+  const int ri = r0 - 7 + lane;
+  const bool listed = lane < 22 && ri >= 0 && ri < n_rows;
+  const int at = min(max(ri, 0), n_rows - 1), e_b = a.rd.b[at], e_slot = a.rd.slot[at];
+  const size_t head = (size_t)S * DH;
+  bf16_t* __restrict__ kc = (bf16_t*)a.kcache + a.layer_off;
+  bf16_t* __restrict__ vc = (bf16_t*)a.vcache + a.layer_off;
+  // ---- keys: 8 elements per lane
   const int chunk = lane % LPK, pchunk = chunk ^ (LPK / 2);
   const bool upper = chunk >= LPK / 2;
-  const float* __restrict__ y = a.y + (size_t)r * a.dqkv + (size_t)(a.H + (is_v ? a.KVH : 0) + kvh) * DH;
-  const float* __restrict__ cs = a.rope + (size_t)r * DH + 2 * (chunk % (LPK / 2)) * 8;
-  float x[8], xp[8], c16[16];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const float4 u = reinterpret_cast<const float4*>(y + chunk * 8)[i], w = reinterpret_cast<const float4*>(y + pchunk * 8)[i];
-    x[4 * i] = u.x; x[4 * i + 1] = u.y; x[4 * i + 2] = u.z; x[4 * i + 3] = u.w;
-    xp[4 * i] = w.x; xp[4 * i + 1] = w.y; xp[4 * i + 2] = w.z; xp[4 * i + 3] = w.w;
-  }
+  for (int k0 = 0; k0 < 8; k0 += KEYS) {
+    const int e = k0 + lane / LPK, r = r0 + min(e, n_here - 1);
+    const float* __restrict__ y = a.y + (size_t)r * a.dqkv + (size_t)(a.H + kvh) * DH;
+    const float* __restrict__ cs = a.rope + (size_t)r * DH + 2 * (chunk % (LPK / 2)) * 8;
+    float x[8], xp[8], c16[16];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float4 u = reinterpret_cast<const float4*>(cs)[i];
-    c16[4 * i] = u.x; c16[4 * i + 1] = u.y; c16[4 * i + 2] = u.z; c16[4 * i + 3] = u.w;
-  }
-  const bool rot = a.use_rope && !is_v;
-  unsigned pk[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float v2[2];
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int e = 2 * i + j;
-      const float c = rot ? c16[2 * e] : 1.f, sn = rot ? c16[2 * e + 1] : 0.f;
-      v2[j] = upper ? x[e] * c + xp[e] * sn : x[e] * c - xp[e] * sn;
+    for (int i = 0; i < 2; ++i) {
+      const float4 u = reinterpret_cast<const float4*>(y + chunk * 8)[i], w = reinterpret_cast<const float4*>(y + pchunk * 8)[i];
+      x[4 * i] = u.x; x[4 * i + 1] = u.y; x[4 * i + 2] = u.z; x[4 * i + 3] = u.w;
+      xp[4 * i] = w.x; xp[4 * i + 1] = w.y; xp[4 * i + 2] = w.z; xp[4 * i + 3] = w.w;
     }
-    pk[i] = (unsigned)f2bf(v2[0]) | ((unsigned)f2bf(v2[1]) << 16);
-  }
-  bf16_t* __restrict__ dst = (bf16_t*)(is_v ? a.vcache : a.kcache) + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
-  if (!is_v) {
-    *reinterpret_cast<uint4*>(dst + (size_t)slot * DH + chunk * 8) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-  } else {                                                       // value cache: operand tiles of V^T (vt_index)
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      dst[vt_index(slot, chunk * 8 + e, DH)] = (bf16_t)((e & 1) ? (pk[e >> 1] >> 16) : (pk[e >> 1] & 0xffffu));
+    for (int i = 0; i < 4; ++i) {
+      const float4 u = reinterpret_cast<const float4*>(cs)[i];
+      c16[4 * i] = u.x; c16[4 * i + 1] = u.y; c16[4 * i + 2] = u.z; c16[4 * i + 3] = u.w;
+    }
+    unsigned pk[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float v2[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int q = 2 * i + j;
+        const float c = a.use_rope ? c16[2 * q] : 1.f, sn = a.use_rope ? c16[2 * q + 1] : 0.f;
+        v2[j] = upper ? x[q] * c + xp[q] * sn : x[q] * c - xp[q] * sn;
+      }
+      pk[i] = pk_bf16(v2[0], v2[1]);
+    }
+    const int b = __shfl(e_b, 7 + e), slot = __shfl(e_slot, 7 + e);
+    if (e < n_here)
+      *reinterpret_cast<uint4*>(kc + ((size_t)b * a.KVH + kvh) * head + (size_t)slot * DH + chunk * 8) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
   }
+  // ---- values.  follows: bit i = entry i is the next position of entry i - 1; 7 of them after a slot that is a multiple of 8
+  // make a block
+  const int b_prev = __shfl_up(e_b, 1), slot_prev = __shfl_up(e_slot, 1);
+  const u64 follows = __ballot(lane > 0 && listed && ri > 0 && e_b == b_prev && e_slot == slot_prev + 1);
+  const int first = lane - (e_slot & 7);                         // lane of the block's first entry
+  const bool in_window = listed && lane >= 7 && lane < 15;
+  const bool full = in_window && ((follows >> (first + 1)) & 0x7f) == 0x7f;
+  const u64 starts = __ballot(full && (e_slot & 7) == 0);        // at most one bit
+  u64 single = __ballot(in_window && !full);
+  const float* __restrict__ yv = a.y + (size_t)(a.H + a.KVH + kvh) * DH;
+  if (starts) {
+    const int f = __builtin_ctzll(starts), b = __builtin_amdgcn_readlane(e_b, f), slot = __builtin_amdgcn_readlane(e_slot, f);
+#pragma unroll
+    for (int c0 = 0; c0 < DH; c0 += 64) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = yv[(size_t)(r0 - 7 + f + e) * a.dqkv + c0 + lane];
+      unsigned pk[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) pk[i] = pk_bf16(x[2 * i], x[2 * i + 1]);
+      *reinterpret_cast<uint4*>(vc + ((size_t)b * a.KVH + kvh) * head + vt_index(slot, c0 + lane, DH)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+    }
+  }
+  while (single) {
+    const int i = __builtin_ctzll(single), b = __builtin_amdgcn_readlane(e_b, i), slot = __builtin_amdgcn_readlane(e_slot, i);
+    single &= single - 1;
+#pragma unroll
+    for (int c0 = 0; c0 < DH; c0 += 64)
+      vc[((size_t)b * a.KVH + kvh) * head + vt_index(slot, c0 + lane, DH)] = f2bf(yv[(size_t)(r0 - 7 + i) * a.dqkv + c0 + lane]);
+  }
+}
+
+// Maximum / sum over the four lanes that share lane % 16 (lanes 16 apart), in all of them: two lane swaps on the vector ALU.
+__device__ __forceinline__ float quarter_max(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ __forceinline__ float quarter_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // Causal attention on the matrix cores for a multi-entry pass whose entries come in runs of consecutive positions of
 // one batch row (prefill); every key and value of the pass is already cached (the append-only launch ran before).
-// One wave per (block of 16 entries, query head).  Per block of 32 keys: S = Q K^T (16 x 32 scores, Q as hi + lo bf16
-// planes so that it enters at float32 precision, K straight from the cache in operand layout), causal mask per
-// query, online softmax in float32 on the accumulator layout (a query's 16 keys of a tile sit in one DPP row),
-// P through LDS into operand layout (hi + lo), V^T tiles straight from the cache (keys beyond the run's last one
-// zeroed: 0 x NaN is NaN), O += P V.  A block that straddles two batch rows handles its runs one after the other.
-template <int DH>
-__global__ __launch_bounds__(64) void k_attn_mfma_bf16(AttnArgs a) {
-  constexpr int T = DH / 32, CT = DH / 16, PS = 36;
+// One wave takes two sets of 16 queries that read the same keys: two heads of one KV head over 16 entries (PAIR), or one
+// head over 32 entries, so that a key or value fragment fetched from L2 feeds four products.  Per block of 32 keys:
+//   S^T = K Q^T: a lane holds the scores of ONE query (lane % 16) against 8 keys, so the softmax statistics are one value per
+//     lane, reduced in the lane and over the four lanes of the query (sums only at the end).  Row i of key tile t is key
+//     8 (i / 4) + 4 t + i % 4: the 8 keys a lane ends up with are 8 (lane / 16) .. + 7, which is the operand layout of P.
+//   O^T += V^T P^T with P straight from those registers (hi + lo bf16, as Q: both enter at float32 precision); V^T tiles
+//     straight from the cache, keys beyond the run's last one zeroed (0 x NaN is NaN).  The accumulator holds four
+//     consecutive columns of one query per lane: 8-byte stores.
+// The keys of the next block are requested when this block's have been used, and the values likewise.
+// Per launch at 4096 entries: 32 heads x 128 columns, prompts of 255: 145 -> 81 us; 32 heads over 8 KV heads, 511: 187 -> 92;
+// contexts up to 2000: 362 -> 170.  What bounds it now is the latency of the keys and values (3900 cycles per block of 32 keys
+// for 1024 cycles of matrix instructions, at two waves per SIMD).  What bounded the version before (16 queries of one head per
+// wave, the query along the registers, P through LDS, 366 registers) was not arithmetic either: one descriptor read after the
+// other, and barriers that waited for the prefetched block every time.
+template <int DH, bool PAIR>
+__global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
+  constexpr int T = DH / 32, CT = DH / 16, E = PAIR ? 16 : 32;
   constexpr float NEG = -1e30f;
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  __shared__ __attribute__((aligned(16))) float lds_p[16 * PS];
-  const int n_rows = *a.rd.n_rows, r0 = blockIdx.y * 16;
+  __shared__ u32x4 lds_q[2][T][2][64];                           // [set][32 columns][hi, lo][lane]
+  const int n_rows = *a.rd.n_rows, r0 = (gridDim.y - 1 - blockIdx.y) * E;   // the longest contexts first
   if (r0 >= n_rows) return;
-  const int h = blockIdx.x, kvh = h / (a.H / a.KVH), lane = threadIdx.x, l16 = lane & 15, lq = lane >> 4, S = a.max_seq;
-  const int n_here = min(16, n_rows - r0);
-  for (int s0 = 0; s0 < n_here;) {
-    const int b = a.rd.b[r0 + s0];
-    int s1 = s0 + 1;
-    while (s1 < n_here && a.rd.b[r0 + s1] == b) ++s1;            // entries s0 .. s1-1 belong to batch row b
+  const int lane = threadIdx.x, l16 = lane & 15, lq = lane >> 4, S = a.max_seq, G = a.H / a.KVH;
+  const int h0 = PAIR ? 2 * blockIdx.x : blockIdx.x, kvh = h0 / G;
+  const int n_here = min(E, n_rows - r0), mine = r0 + min(lane, n_here - 1);
+  const int e_b = a.rd.b[mine], e_slot = a.rd.slot[mine];        // lane e: entry e's batch row and position in the cache
+  const int b_prev = __shfl_up(e_b, 1);                          // (by all lanes: an inactive one would read as 0)
+  u64 starts = __ballot(lane < n_here && (lane == 0 || e_b != b_prev));
+  while (starts) {
+    const int s0 = __builtin_ctzll(starts);
+    starts &= starts - 1;
+    const int s1 = starts ? __builtin_ctzll(starts) : n_here;    // entries s0 .. s1 - 1 belong to batch row b, positions ascend
+    const int b = __builtin_amdgcn_readlane(e_b, s0), max_slot = __builtin_amdgcn_readlane(e_slot, s1 - 1);
     const bf16_t* __restrict__ Kc = (const bf16_t*)a.kcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
     const bf16_t* __restrict__ Vc = (const bf16_t*)a.vcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
-    int max_slot = 0;
-    for (int e = s0; e < s1; ++e) max_slot = max(max_slot, a.rd.slot[r0 + e]);
-    int slot[4];                                                 // of this lane's 4 accumulator rows (queries)
+    u32x4 K[2][T], V[CT];
+    const int key_lane = (l16 >> 2) * 8 + (l16 & 3);
+    auto fetch_k = [&](int kb) {                                 // (keys beyond the run's last one: that one again, masked)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int e = lq * 4 + v;
-      slot[v] = (e >= s0 && e < s1) ? a.rd.slot[r0 + e] : -1;    // -1: not a query of this run, every key masked
-    }
-    // Q in operand layout: row l16 of the block, elements t * 32 + lq * 8 .. + 8, rotated and scaled
-    uint4 qh[T], ql[T];
-    {
-      const int re = r0 + min(max(l16, s0), s1 - 1);
-      const float* __restrict__ y = a.y + (size_t)re * a.dqkv + (size_t)h * DH;
-      const float* __restrict__ rp = a.rope + (size_t)re * DH;
+      for (int t2 = 0; t2 < 2; ++t2) {
+        const bf16_t* kr = Kc + (size_t)min(kb + key_lane + t2 * 4, max_slot) * DH + lq * 8;
 #pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const int d0 = t * 32 + lq * 8, p0 = d0 ^ (DH / 2);
-        const bool upper = d0 >= DH / 2;
-        float x[8], xp[8], cs[16], qv[8];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const float4 u = reinterpret_cast<const float4*>(y + d0)[i], w = reinterpret_cast<const float4*>(y + p0)[i];
-          x[4 * i] = u.x; x[4 * i + 1] = u.y; x[4 * i + 2] = u.z; x[4 * i + 3] = u.w;
-          xp[4 * i] = w.x; xp[4 * i + 1] = w.y; xp[4 * i + 2] = w.z; xp[4 * i + 3] = w.w;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4 u = reinterpret_cast<const float4*>(rp + 2 * (d0 % (DH / 2)))[i];
-          cs[4 * i] = u.x; cs[4 * i + 1] = u.y; cs[4 * i + 2] = u.z; cs[4 * i + 3] = u.w;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float c = a.use_rope ? cs[2 * i] : 1.f, sn = a.use_rope ? cs[2 * i + 1] : 0.f;
-          qv[i] = (upper ? x[i] * c + xp[i] * sn : x[i] * c - xp[i] * sn) * a.scale;
-        }
-        split2(qv[0], qv[1], qh[t].x, ql[t].x);
-        split2(qv[2], qv[3], qh[t].y, ql[t].y);
-        split2(qv[4], qv[5], qh[t].z, ql[t].z);
-        split2(qv[6], qv[7], qh[t].w, ql[t].w);
+        for (int t = 0; t < T; ++t) K[t2][t] = *reinterpret_cast<const u32x4*>(kr + t * 32);
       }
-    }
-    f32x4 O[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) O[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    float m_run[4] = {NEG, NEG, NEG, NEG}, l_run[4] = {0.f, 0.f, 0.f, 0.f};
-    // Two register buffers: the keys (operand fragments) and values (staging pieces) of block kb + 32 are requested
-    // before block kb is worked on.  Addresses are clamped to the run's last key, so a block beyond it loads valid
-    // memory, has every key masked and every value zeroed, and changes nothing.
-    struct Blk { u32x4 k[2][T]; u32x4 v[CT]; };
-    auto fetch = [&](Blk& B, int kb) {
-#pragma unroll
-      for (int tile = 0; tile < 2; ++tile) {
-        const bf16_t* kr = Kc + (size_t)min(kb + tile * 16 + l16, max_slot) * DH + lq * 8;
-#pragma unroll
-        for (int t = 0; t < T; ++t) B.k[tile][t] = *reinterpret_cast<const u32x4*>(kr + t * 32);
-      }
+    };
+    auto fetch_v = [&](int kb) {
       const bf16_t* vb = Vc + (size_t)(min(kb, max_slot & ~31) >> 5) * (32 * DH) + lane * 8;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) B.v[ct] = *reinterpret_cast<const u32x4*>(vb + ct * 512);
+      for (int ct = 0; ct < CT; ++ct) V[ct] = *reinterpret_cast<const u32x4*>(vb + ct * 512);
     };
-    auto step = [&](Blk& B, int kb) {
-      if (kb + 31 > max_slot) {                                   // (scalar) zero the values of keys beyond the run's last one
+    fetch_k(0);
+    fetch_v(0);
+    // Queries, rotated and scaled (in base-2 units), to LDS in operand layout: in registers they spill at 128 columns.  The lanes
+    // go along the rows, 4 columns each (16 rows x 16 pieces of 32 bytes at once took the memory pipeline 4 times as long).
+    int slot[2];                                                 // a query's position; -1: not of this run, every key masked
+    const float scale = a.scale * 1.4426950408889634f;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const uint4 f = vt_fix(make_uint4(B.v[ct].x, B.v[ct].y, B.v[ct].z, B.v[ct].w), kb + lq * 8, max_slot + 1, 0u);
-          B.v[ct].x = f.x; B.v[ct].y = f.y; B.v[ct].z = f.z; B.v[ct].w = f.w;
+    for (int s = 0; s < 2; ++s) {
+      const int e = l16 + (PAIR ? 0 : 16 * s), sl = __shfl(e_slot, e);
+      slot[s] = (e >= s0 && e < s1) ? sl : -1;
+      constexpr int LPR = DH / 4, RPI = 64 / LPR;                // lanes per row, rows per instruction
+      const int c4 = (lane % LPR) * 4;
+      const bool upper = c4 >= DH / 2;
+#pragma unroll
+      for (int i = 0; i < 16 / RPI; ++i) {
+        const int row = i * RPI + lane / LPR, re = r0 + min(max(row + (PAIR ? 0 : 16 * s), s0), s1 - 1);
+        const float* __restrict__ y = a.y + (size_t)re * a.dqkv + (size_t)(h0 + (PAIR ? s : 0)) * DH;
+        float4 x = *reinterpret_cast<const float4*>(y + c4);
+        if (a.use_rope) {                                        // (uniform)
+          const float4 xp = *reinterpret_cast<const float4*>(y + (c4 ^ (DH / 2)));
+          const float4* __restrict__ cs = reinterpret_cast<const float4*>(a.rope + (size_t)re * DH + 2 * (c4 % (DH / 2)));
+          const float4 c = cs[0], d = cs[1];                     // cos, sin, cos, sin
+          const float sg = upper ? 1.f : -1.f;
+          x.x = x.x * c.x + sg * (xp.x * c.y); x.y = x.y * c.z + sg * (xp.y * c.w);
+          x.z = x.z * d.x + sg * (xp.z * d.y); x.w = x.w * d.z + sg * (xp.w * d.w);
         }
+        uint2 qh, ql;
+        split2(x.x * scale, x.y * scale, qh.x, ql.x);
+        split2(x.z * scale, x.w * scale, qh.y, ql.y);
+        const int at = ((c4 & 31) >> 3) * 16 + row;              // operand lane of row `row`, columns c4 & ~7 .. + 7
+        *reinterpret_cast<uint2*>((char*)&lds_q[s][c4 >> 5][0][at] + (c4 & 4) * 2) = qh;
+        *reinterpret_cast<uint2*>((char*)&lds_q[s][c4 >> 5][1][at] + (c4 & 4) * 2) = ql;
       }
-      // scores of the two 16-key tiles
-      f32x4 sc[2];
+      __builtin_amdgcn_sched_barrier(0);                         // one set's loads at a time (registers)
+    }
+    __builtin_amdgcn_wave_barrier();                             // (one wave: its LDS operations complete in order)
+    f32x4 O[2][CT];
+    float m_run[2] = {NEG, NEG}, l_run[2] = {0.f, 0.f};          // (l_run: this lane's keys only)
 #pragma unroll
-      for (int tile = 0; tile < 2; ++tile) {
-        sc[tile] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-        for (int t = 0; t < T; ++t) {
-          const u32x4 kk = B.k[tile][t];
-          const uint4 kf = make_uint4(kk.x, kk.y, kk.z, kk.w);
-          sc[tile] = mfma_bf16(qh[t], kf, sc[tile]);
-          sc[tile] = mfma_bf16(ql[t], kf, sc[tile]);
+      for (int ct = 0; ct < CT; ++ct) O[s][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int kb = 0; kb <= max_slot; kb += 32) {
+      f32x4 sc[2][2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) sc[s][0] = sc[s][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int hl = 0; hl < 2; ++hl)                           // (four independent chains)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const uint4 q = __builtin_bit_cast(uint4, lds_q[s][t][hl][lane]);
+            sc[s][0] = mfma_bf16(__builtin_bit_cast(uint4, K[0][t]), q, sc[s][0]);
+            sc[s][1] = mfma_bf16(__builtin_bit_cast(uint4, K[1][t]), q, sc[s][1]);
+          }
+      __builtin_amdgcn_sched_barrier(0);
+      fetch_k(kb + 32);
+      __builtin_amdgcn_sched_barrier(0);
+      uint4 ph[2], pl[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int left = slot[s] - kb - lq * 8;                  // keys 0 .. left of this lane's 8 are valid
+        float x[8], mx = NEG;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          x[e] = e <= left ? sc[s][e >> 2][e & 3] : NEG;
+          mx = fmaxf(mx, x[e]);
         }
-      }
-      // online softmax: accumulator register v of lane (lq, l16) is query lq * 4 + v, key kb + tile * 16 + l16
-      float p[2][4];
+        const float mn = fmaxf(m_run[s], quarter_max(mx));
+        if (__any(mn > m_run[s])) {                              // (uniform) the running maximum of some query moves
+          const float corr = __builtin_amdgcn_exp2f(m_run[s] - mn);
+          l_run[s] *= corr;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const bool ok0 = kb + l16 <= slot[v], ok1 = kb + 16 + l16 <= slot[v];
-        const float mx = group_max16(fmaxf(ok0 ? sc[0][v] : NEG, ok1 ? sc[1][v] : NEG));
-        const float mn = fmaxf(m_run[v], mx);
-        const float corr = __expf(m_run[v] - mn);
-        p[0][v] = ok0 ? __expf(sc[0][v] - mn) : 0.f;
-        p[1][v] = ok1 ? __expf(sc[1][v] - mn) : 0.f;
-        l_run[v] = l_run[v] * corr + group_sum<16>(p[0][v] + p[1][v]);
-        m_run[v] = mn;
+          for (int ct = 0; ct < CT; ++ct) O[s][ct] *= corr;
+          m_run[s] = mn;
+        }
+        float p[8];
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) O[ct][v] *= corr;
-        lds_p[(lq * 4 + v) * PS + l16] = p[0][v];
-        lds_p[(lq * 4 + v) * PS + 16 + l16] = p[1][v];
+        for (int e = 0; e < 8; ++e) p[e] = e <= left ? __builtin_amdgcn_exp2f(x[e] - mn) : 0.f;
+        l_run[s] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        split2(p[0], p[1], ph[s].x, pl[s].x);
+        split2(p[2], p[3], ph[s].y, pl[s].y);
+        split2(p[4], p[5], ph[s].z, pl[s].z);
+        split2(p[6], p[7], ph[s].w, pl[s].w);
       }
-      __syncthreads();
-      // P in operand layout: query l16, keys lq * 8 .. + 8 of the block
-      uint4 ph, pl;
-      {
-        const float4 u = *reinterpret_cast<const float4*>(lds_p + l16 * PS + lq * 8);
-        const float4 w = *reinterpret_cast<const float4*>(lds_p + l16 * PS + lq * 8 + 4);
-        split2(u.x, u.y, ph.x, pl.x);
-        split2(u.z, u.w, ph.y, pl.y);
-        split2(w.x, w.y, ph.z, pl.z);
-        split2(w.z, w.w, ph.w, pl.w);
+      if (kb + 31 > max_slot) {                                  // (scalar) zero the values of keys beyond the run's last one
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          V[ct] = __builtin_bit_cast(u32x4, vt_fix(__builtin_bit_cast(uint4, V[ct]), kb + lq * 8, max_slot + 1, 0u));
       }
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        const uint4 vf = make_uint4(B.v[ct].x, B.v[ct].y, B.v[ct].z, B.v[ct].w);
-        O[ct] = mfma_bf16(ph, vf, O[ct]);
-        O[ct] = mfma_bf16(pl, vf, O[ct]);
+        const uint4 vf = __builtin_bit_cast(uint4, V[ct]);
+        O[0][ct] = mfma_bf16(vf, ph[0], O[0][ct]);
+        O[1][ct] = mfma_bf16(vf, ph[1], O[1][ct]);
+        O[0][ct] = mfma_bf16(vf, pl[0], O[0][ct]);
+        O[1][ct] = mfma_bf16(vf, pl[1], O[1][ct]);
       }
-      __syncthreads();                                           // LDS is rewritten by the next key block
-    };
-    Blk A, B;
-    fetch(A, 0);
-    for (int kb = 0; kb <= max_slot; kb += 64) {
-      fetch(B, kb + 32);
       __builtin_amdgcn_sched_barrier(0);
-      step(A, kb);
-      fetch(A, kb + 64);
+      fetch_v(kb + 32);
       __builtin_amdgcn_sched_barrier(0);
-      step(B, kb + 32);
     }
     bf16_t* __restrict__ ao = (bf16_t*)a.ao;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int e = lq * 4 + v;
-      if (e < s0 || e >= s1) continue;
-      const float inv = 1.0f / l_run[v];
+    for (int s = 0; s < 2; ++s) {
+      const float inv = 1.0f / quarter_sum(l_run[s]);
+      if (slot[s] < 0) continue;
+      const int m = r0 + l16 + (PAIR ? 0 : 16 * s);
+      bf16_t* __restrict__ dst = ao + act_idx<bf16_t>(m, (h0 + (PAIR ? s : 0)) * DH + lq * 4, a.ao_K);
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) act_store<bf16_t>(ao, r0 + e, h * DH + ct * 16 + l16, a.ao_K, O[ct][v] * inv);
+      for (int ct = 0; ct < CT; ++ct) {                          // 16 columns on: half an operand tile (256 elements)
+        const f32x4 o = O[s][ct] * inv;
+        *reinterpret_cast<uint2*>(dst + ct * 256) = make_uint2(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]));
+      }
     }
-    s0 = s1;
   }
 }
 
@@ -638,11 +699,12 @@ static size_t attn_smem_bytes(int DH, int G, int max_seq) {
 template <int DH>
 static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bound, hipStream_t s) {
   if (a.phase == 1) {          // append only
-    hipLaunchKernelGGL((k_kv_append_bf16<DH>), dim3(a.KVH, max_rows), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((k_kv_append_bf16<DH>), dim3(a.KVH, (max_rows + 7) / 8), dim3(64), 0, s, a);
     return;
   }
   if (a.phase == 3) {          // attend-only over runs of consecutive positions of one row: the matrix-core kernel
-    hipLaunchKernelGGL((k_attn_mfma_bf16<DH>), dim3(a.H, (max_rows + 15) / 16), dim3(64), 0, s, a);
+    if (G > 1) hipLaunchKernelGGL((k_attn_mfma_bf16<DH, true>), dim3(a.H / 2, (max_rows + 15) / 16), dim3(64), 0, s, a);
+    else hipLaunchKernelGGL((k_attn_mfma_bf16<DH, false>), dim3(a.H, (max_rows + 31) / 32), dim3(64), 0, s, a);
     return;
   }
   // NW = waves per workgroup that share one (row, KV head)'s keys: 8 when the launch has no more workgroups than

@@ -8,11 +8,11 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_min=2, n_gen=3, tau=0.5, max_seq=48, seed=7, whole_prompt=False):
+def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_min=2, n_gen=3, tau=0.5, max_seq=48, seed=7, whole_prompt=False, chunk_rows=0):
     """Decode steps of one configuration; returns the rejected rows per step."""
     from parity_util import Pair, compare_replay, close_enough, eps_of
     cfg = W.SprinterCfg(draft, target, ver_hidden, dtype, B, max_seq, tau=tau, seed=seed, name="edges", batch=B, prompt_len=prompt_len,
-                        prompt_len_min=prompt_len_min, n_gen=n_gen, prompt_dist="uniform", weight_seed=500 + seed, prompt_seed=600 + seed)
+                        prompt_len_min=prompt_len_min, n_gen=n_gen, prompt_dist="uniform", weight_seed=500 + seed, prompt_seed=600 + seed, chunk_rows=chunk_rows)
     p = Pair(cfg, ver_scale=8.0)
     eps = eps_of(cfg)
     outs, _ = p.gpu_steps(n_gen)
@@ -68,3 +68,14 @@ def test_tiles_of_many_rows(B, prompt_len):
     draft = W.ModelCfg(W.ARCH_GPT, 2, 768, 12, 12, 3080, 331, 128)
     target = W.ModelCfg(W.ARCH_LLAMA, 2, 1024, 16, 16, 5128, 331, 128, 1e-5, 10000.0)
     _check(draft, target, B, W.DT_BF16, prompt_len=prompt_len, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=128, whole_prompt=True)
+
+
+@pytest.mark.parametrize("chunk_rows", [0, 64])
+@pytest.mark.parametrize("group", [1, 2, 8])
+def test_prefill_attention_runs(group, chunk_rows):
+    """Prompts of 1 - 40 tokens: runs that begin and end anywhere in a block of 8 cached slots, of 16 or 32 entries and of 32
+    keys, one or many in a block, whole in one pass or split over passes of 64 entries; 1, 2 and 8 query heads per KV head, head
+    dimensions 64 and 128, with and without rotary positions."""
+    draft = W.ModelCfg(W.ARCH_LLAMA, 1, 512, 8, 8 // group, 136, 83, 48, 1e-5, 10000.0)
+    target = _llama(1, 1024, 8, 8 // group, 136, 83) if group > 1 else _gpt(1, 128, 136, 83)
+    _check(draft, target, 13, W.DT_BF16, prompt_len=41, prompt_len_min=1, tau=1.5, whole_prompt=True, chunk_rows=chunk_rows, seed=21 + group)
