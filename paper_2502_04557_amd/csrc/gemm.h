@@ -24,8 +24,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int
   else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu(v) * v2);
 }
 
-// The kernel for many rows (k_gemm_tile.hip): whether a shape takes it, and its launch (returns the K shares of EPI_PART).
-bool gemm_takes_tile(int epi, const GemmArgs& a, int rows, int max_shares);
+// The kernel for 17 and more rows (k_gemm_tile.hip): whether a shape takes it, and its launch (returns the K shares of EPI_PART).
+bool gemm_takes_tile(int epi, const GemmArgs& a, int rows);
 int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipStream_t s);
 
 }  // namespace sprinter

@@ -116,13 +116,13 @@ __global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
   gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, pbias);
 }
 
-// bf16-mode GEMM for 17 .. 64 rows per pass (MT row tiles of 16), one column tile per workgroup, K split over
-// the 8 waves.  At these row counts a workgroup pulls the whole activation matrix (MT x 1 KiB per k tile,
+// bf16-mode GEMM for 17 .. 64 rows (MT row tiles of 16) of outputs too narrow for k_gemm_tile, NTW column tiles per workgroup,
+// K split over the 8 waves.  At these row counts a workgroup pulls the whole activation matrix (MT x 1 KiB per k tile,
 // from L2) for 1 KiB of weights per k tile, so the kernel lives on memory-level parallelism: two register
 // buffers, the loads of chunk c + 1 (weights and all MT row tiles) are in flight while the
 // MFMAs of chunk c run, and there is no branch inside the loop.  Row tiles beyond the row count are
 // computed on whatever the buffers hold and dropped by the epilogue; k tiles beyond K are clamped on load
-// and their weight operand zeroed.  blockIdx.y = pass over 16 * MT rows.
+// and their weight operand zeroed.
 template <int MT, int NTW, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
@@ -131,13 +131,10 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   constexpr int NI = MT * NWT * 4;
   __shared__ float red[4 * NI * 64];
   const int lane = threadIdx.x & 63, kw = wave_index();
-  const int nt0 = blockIdx.x * NTW, mtile0 = blockIdx.y * MT, Kt = a.Kt;
-  // EPI_PART: blockIdx.z = K share, the partial product goes to part[share] (summed by the consumer)
-  const int sk = (EPI == EPI_PART) ? blockIdx.z : 0, SK = (EPI == EPI_PART) ? gridDim.z : 1;
-  const int k0 = (int)((long long)Kt * sk / SK), k1 = (int)((long long)Kt * (sk + 1) / SK);
+  const int nt0 = blockIdx.x * NTW, Kt = a.Kt;
   const uint4* __restrict__ Wp = (const uint4*)a.W + lane;
   const uint4* __restrict__ W2p = DUAL ? (const uint4*)a.W2 + lane : nullptr;
-  const uint4* __restrict__ Xp = (const uint4*)a.X + (size_t)mtile0 * Kt * 64 + lane;
+  const uint4* __restrict__ Xp = (const uint4*)a.X + lane;
   size_t wrow[NTW];
 #pragma unroll
   for (int j = 0; j < NTW; ++j) wrow[j] = (size_t)min(nt0 + j, a.n_tiles - 1) * Kt * 64;
@@ -146,11 +143,11 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   // rows the second row tile costs an eighth of its bytes)
   bool row_live[MT];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) row_live[mt] = (mtile0 + mt) * 16 + (lane & 15) < a.rows_live;
+  for (int mt = 0; mt < MT; ++mt) row_live[mt] = mt * 16 + (lane & 15) < a.rows_live;
   auto load = [&](Buf& b, int kt) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int kc = min(kt + u * 8, k1 - 1);
+      const int kc = min(kt + u * 8, Kt - 1);
 #pragma unroll
       for (int j = 0; j < NTW; ++j) {
         b.w[u][j] = Wp[wrow[j] + (size_t)kc * 64];
@@ -162,7 +159,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
       if (row_live[mt]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int kc = min(kt + u * 8, k1 - 1);
+          const int kc = min(kt + u * 8, Kt - 1);
           b.xh[u][mt] = Xp[((size_t)mt * Kt + kc) * 64];
         }
       }
@@ -176,7 +173,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   auto compute = [&](const Buf& b, int kt) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool in_k = kt + u * 8 < k1;
+      const bool in_k = kt + u * 8 < Kt;
 #pragma unroll
       for (int j = 0; j < NWT; ++j) {
         const uint4 w1 = in_k ? b.w[u][j] : make_uint4(0u, 0u, 0u, 0u);
@@ -192,10 +189,10 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) A.xh[u][mt] = B.xh[u][mt] = make_uint4(0u, 0u, 0u, 0u);
-  load(A, min(k0 + kw, k1 - 1));
+  load(A, min(kw, Kt - 1));
   const int n_rows = *a.n_rows;                               // only the epilogue needs it (passes are sized by the host)
   // (the scheduling barriers keep the compiler from sinking a buffer's loads down to their first use)
-  for (int kt = k0 + kw; kt < k1; kt += 2 * STEP) {
+  for (int kt = kw; kt < Kt; kt += 2 * STEP) {
     load(B, kt + STEP);
     __builtin_amdgcn_sched_barrier(0);
     compute(A, kt);
@@ -242,7 +239,6 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   }
   __syncthreads();
   constexpr bool ACT_OUT = (EPI == EPI_GELU || EPI == EPI_SWIGLU);
-  float* part = (EPI == EPI_PART) ? a.part + (size_t)sk * a.part_stride : nullptr;
 #pragma unroll
   for (int i = 0; i < (MT * NTW + 1) / 2; ++i) {
     const int o = i * 512 + (int)threadIdx.x;        // element index among the MT*16 x NTW*16 outputs
@@ -255,17 +251,13 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
       const int m_all = o / (16 * NTW);
       c = o % (16 * NTW); mt = m_all >> 4; m16 = m_all & 15;
     }
-    const int j = c >> 4, n = nt0 * 16 + c, m = (mtile0 + mt) * 16 + m16;
+    const int j = c >> 4, n = nt0 * 16 + c, m = mt * 16 + m16;
     const int sl = (m16 >> 2) * 16 + (c & 15), v = m16 & 3;
     const float s1 = red[((j * MT + mt) * 4 + v) * 64 + sl];
     const float s2 = DUAL ? red[(((NTW + j) * MT + mt) * 4 + v) * 64 + sl] : 0.f;
     if (m >= n_rows || n >= a.N) continue;
-    if constexpr (EPI == EPI_PART) {
-      part[(size_t)m * a.ldo + n] = s1;
-    } else {
-      const float bias = a.bias ? a.bias[n] : 0.f;
-      gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias);
-    }
+    const float bias = a.bias ? a.bias[n] : 0.f;
+    gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias);
   }
 }
 
@@ -455,37 +447,22 @@ static void launch_gemm_bf16(const GemmArgs& a, int max_rows, hipStream_t s) {
   // d = 1600 - and splitting K over workgroups with a last-arriver reduction - its two device-scope fences
   // cost more than the 4 us they save; and a variant that requests all of a wave's weight and activation
   // tiles up front (K <= 2048) - no faster.)
-  // 17 .. 64 rows: 2, 3 or 4 row tiles per pass with double-buffered loads; more rows take further passes.
   // wide outputs with a short K: two column tiles per wave share the activation fragments (at K = 4096 one tile per
   // workgroup is faster: QKV 12288x4096 26 against 32 us, FFN-up 2x11008x4096 40 against 48 us)
   if (max_rows <= 16 && a.n_tiles >= 256 && a.Kt < 100)
     hipLaunchKernelGGL((k_gemm16<2, EPI>), dim3((a.n_tiles + 1) / 2), dim3(512), 0, s, a);
   else if (max_rows <= 16) hipLaunchKernelGGL((k_gemm16<1, EPI>), dim3(a.n_tiles), dim3(512), 0, s, a);
-  else if (gemm_takes_tile(EPI, a, max_rows, 1)) launch_gemm_tile(EPI, a, max_rows, 1, s);
+  else if (gemm_takes_tile(EPI, a, max_rows)) launch_gemm_tile(EPI, a, max_rows, 1, s);
   else {
-    // column tiles per wave that share the activation fragments: as many as leave about 192 workgroups
-    // as few passes over the weights as 4 row tiles per pass allow, the row tiles spread evenly over them
-    // (80 rows: 2 passes of 3 tiles, not 4 + 1)
-    const int row_tiles = (max_rows + 15) / 16;
+    // 17 .. 64 rows; column tiles per wave that share the activation fragments: as many as leave about 192 workgroups
     constexpr bool DUAL = EPI == EPI_SWIGLU;
 #define SPRINTER_ROWS(MT_, NTW_) hipLaunchKernelGGL((k_gemm_rows<MT_, NTW_, EPI>), grid, dim3(512), 0, s, a)
-    if (row_tiles >= 5 && row_tiles <= 7 && (long long)a.n_tiles * a.Kt <= 24576) {
-      // 65 .. 112 rows of a matrix under 24 MiB in ONE pass over the weights (5-7 row tiles per workgroup; the
-      // registers allow two column tiles per wave, one for SwiGLU's two matrices) instead of two passes of 3-4 tiles:
-      // the fixed cost per pass weighs more than the activation traffic there (an SD round of 80 entries at c2
-      // 7.4 -> 6.5 ms; at c4's 4096-wide matrices the single pass is slower, 13.3 -> 14.4 ms per step)
-      constexpr int ntw = DUAL ? 1 : 2;
-      const dim3 grid((a.n_tiles + ntw - 1) / ntw, 1, 1);
-      if (row_tiles == 5) SPRINTER_ROWS(5, ntw); else if (row_tiles == 6) SPRINTER_ROWS(6, ntw); else SPRINTER_ROWS(7, ntw);
-      return;
+    const int mt = (max_rows + 15) / 16, ntw = !DUAL && a.n_tiles >= 256 ? 2 : 1;
+    const dim3 grid((a.n_tiles + ntw - 1) / ntw);
+    if constexpr (!DUAL) {
+      if (ntw == 2) { if (mt == 2) SPRINTER_ROWS(2, 2); else if (mt == 3) SPRINTER_ROWS(3, 2); else SPRINTER_ROWS(4, 2); }
     }
-    const int passes = (row_tiles + 3) / 4;
-    const int mt = std::max(2, (row_tiles + passes - 1) / passes);
-    const int ntw = (!DUAL && mt > 2 && a.n_tiles / 4 >= 192) ? 4 : (a.n_tiles / 2 >= (DUAL ? 256 : 128)) ? 2 : 1;
-    const dim3 grid((a.n_tiles + ntw - 1) / ntw, passes, 1);
-    if (ntw == 4) { if (mt == 3) SPRINTER_ROWS(3, 4); else SPRINTER_ROWS(4, 4); }
-    else if (ntw == 2) { if (mt == 2) SPRINTER_ROWS(2, 2); else if (mt == 3) SPRINTER_ROWS(3, 2); else SPRINTER_ROWS(4, 2); }
-    else { if (mt == 2) SPRINTER_ROWS(2, 1); else if (mt == 3) SPRINTER_ROWS(3, 1); else SPRINTER_ROWS(4, 1); }
+    if (ntw == 1) { if (mt == 2) SPRINTER_ROWS(2, 1); else if (mt == 3) SPRINTER_ROWS(3, 1); else SPRINTER_ROWS(4, 1); }
 #undef SPRINTER_ROWS
   }
 }
@@ -540,30 +517,7 @@ int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, co
     else hipLaunchKernelGGL((k_gemm16_part<1>), dim3(groups * sk), dim3(512), 0, s, a);
     return sk;
   }
-  // 17+ rows: the workgroup's activation traffic (1 KiB per k tile and 16 rows) is what costs, so a wave takes
-  // four column tiles (two if that leaves too few workgroups) and K is split until about 256 workgroups exist,
-  // with at least two k tiles per wave and share
-  if (gemm_takes_tile(EPI_PART, a, max_rows, max_shares)) return launch_gemm_tile(EPI_PART, a, max_rows, max_shares, s);
-  const int row_tiles = (max_rows + 15) / 16;
-  const int s_max = std::max(1, std::min(max_shares, a.Kt / 16));
-#define SPRINTER_PART(MT_, NTW_) hipLaunchKernelGGL((k_gemm_rows<MT_, NTW_, EPI_PART>), grid, dim3(512), 0, s, a)
-  if (row_tiles >= 5 && row_tiles <= 7 && (long long)a.n_tiles * a.Kt <= 24576) {   // small matrix: one pass of 5-7 row tiles
-    const int groups = (a.n_tiles + 1) / 2, sk = std::min(s_max, std::max(1, 256 / groups));
-    a.SK = sk;
-    const dim3 grid(groups, 1, sk);
-    if (row_tiles == 5) SPRINTER_PART(5, 2); else if (row_tiles == 6) SPRINTER_PART(6, 2); else SPRINTER_PART(7, 2);
-    return sk;
-  }
-  const int passes = (row_tiles + 3) / 4;
-  const int mt = std::max(2, (row_tiles + passes - 1) / passes);
-  int ntw = 4, groups = (a.n_tiles + 3) / 4, sk = std::min(s_max, std::max(1, 256 / groups));
-  if (groups * sk < 192 || mt == 4) { ntw = 2; groups = (a.n_tiles + 1) / 2; sk = std::min(s_max, std::max(1, 256 / groups)); }
-  a.SK = sk;
-  const dim3 grid(groups, passes, sk);
-  if (ntw == 4) { if (mt == 2) SPRINTER_PART(2, 4); else if (mt == 3) SPRINTER_PART(3, 4); else SPRINTER_PART(4, 4); }
-  else { if (mt == 2) SPRINTER_PART(2, 2); else if (mt == 3) SPRINTER_PART(3, 2); else SPRINTER_PART(4, 2); }
-#undef SPRINTER_PART
-  return sk;
+  return launch_gemm_tile(EPI_PART, a, max_rows, max_shares, s);
 }
 
 }  // namespace sprinter

@@ -1,5 +1,5 @@
-// HIP kernel of the batched SPRINTER decode step for gfx950: the GEMMs of many rows (prefill chunks, long work lists,
-// large batches).
+// HIP kernel of the batched SPRINTER decode step for gfx950: the GEMMs of 17 and more rows (prefill chunks, work lists, larger
+// batches).
 #include "gemm.h"
 #include <algorithm>
 #include <cstring>
@@ -28,6 +28,8 @@ struct GemmTile {                                       // WM x WN waves, MT x N
 using TileL = GemmTile<4, 2, 4, 8, 4>;                  // 256 x 256, 128 KiB: one workgroup per compute unit
 using TileM = GemmTile<2, 2, 4, 4, 5>;                  // 128 x 128, 80 KiB: two
 using TileS = GemmTile<2, 2, 2, 4, 6>;                  // 64 x 128, 72 KiB: two
+using TileX = GemmTile<2, 2, 2, 2, 8>;                  // 64 x 64, 64 KiB: two
+using TileN = GemmTile<1, 2, 2, 2, 8>;                  // 32 x 64, 48 KiB: three
 
 template <typename T, int EPI>
 __global__ __launch_bounds__(T::waves * 64, 2) void k_gemm_tile(GemmArgs a, int x_tiles, int gm, int gn) {
@@ -169,48 +171,61 @@ __global__ __launch_bounds__(T::waves * 64, 2) void k_gemm_tile(GemmArgs a, int 
 }
 
 // Which tile, and how many K shares (partial products), for a shape: the one with the smallest estimate of
-//   max(rounds of workgroups x cycles of a workgroup, padded products / rate) + the shares' way through memory,
-// with the measured cycles per k tile of a workgroup that has its compute unit for itself / shares it with another, and the
-// rate (PFLOP/s) that the tile reaches on a full chip.  Over 60 shapes of 100 - 4096 rows (K 768 - 14336, N 768 - 14336) the
-// pick is within 10 % of the best of the three tiles and 1 / 2 / 4 / 8 shares, in 50 of them within 4 %.
-struct TileCost { int tm, tn, per_cu; float alone, shared, rate; };
-static float tile_us(const TileCost& c, int rows, int N, int Kt, bool dual, int sk) {
-  const int cols = c.tn / (dual ? 2 : 1), slots = 256 * c.per_cu;
-  const int wgs = (rows + c.tm - 1) / c.tm * ((N + cols - 1) / cols) * sk;
-  const float kt = (float)Kt / sk, start = 5500.f;      // cycles before the first product and after the last
-  const int full = wgs / slots, rest = wgs % slots;
-  const float cycles = full * (start + c.shared * kt) + (rest > 256 ? start + c.shared * kt : rest > 0 ? start + c.alone * kt : 0.f);
-  return std::max(cycles / 2400.f, 2.f * wgs * c.tm * c.tn * kt * 32 / c.rate * 1e-9f);
+//   start + max(rounds of workgroups x cycles, padded products / rate, weights and shares / HBM rate) + the shares' way into the norm.
+// Per tile: workgroups a compute unit holds, microseconds before the first product and after the last, cycles per k tile of a
+// workgroup that has its compute unit for itself and what each further one adds, PFLOP/s on a full chip.  The constants are a
+// fit to 1050 timings of 113 shapes (20 - 4096 rows, K 768 - 14336, N 768 - 14336, 1 - 8 shares; the fits are 7 - 11 % off in
+// the mean); the pick is 1 % slower than the best tile and share count in the mean, at worst 13 %.
+struct TileCost { int tm, tn, per_cu; float start_us, cycles, shared, rate; };
+static float tile_us(const TileCost& c, int epi, int rows, int N, int Kt, int sk) {
+  const int mats = epi == EPI_SWIGLU ? 2 : 1, cols = c.tn / mats, slots = 256 * c.per_cu;
+  const int wgs = (rows + c.tm - 1) / c.tm * ((N + cols - 1) / cols) * sk, full = wgs / slots, rest = wgs % slots;
+  const float kt = (float)Kt / sk, part = epi == EPI_PART ? 4.f * rows * N * sk : 0.f;
+  float cycles = full * (c.cycles + c.shared * (c.per_cu - 1)) * kt;
+  if (rest) cycles += (c.cycles + c.shared * ((rest + 255) / 256 - 1)) * kt;
+  const float product = 2.f * wgs * c.tm * c.tn * kt * 32 / c.rate * 1e-9f, memory = (64.f * N * Kt * mats + part) / 6.3e6f;
+  // the norm reads the shares at 4.5 TB/s; more than 4 take its larger variant
+  return c.start_us + std::max(cycles / 2400.f, std::max(product, memory)) + part / 4.5e6f + (epi == EPI_PART && sk > 4 ? 0.3f : 0.f);
+}
+
+template <typename T, int EPI>
+static void launch_tile(const GemmArgs& a, int rows, int sk, hipStream_t s) {
+  constexpr int tm = T::wm * T::mt * 16, cols = T::wn * T::nt * 16 / (EPI == EPI_SWIGLU ? 2 : 1);
+  const int x_tiles = (int)(a.x_elems / ((size_t)a.Kt * 512)), gm = (rows + tm - 1) / tm, gn = (a.N + cols - 1) / cols;
+  hipLaunchKernelGGL((k_gemm_tile<T, EPI>), dim3(gm * gn, sk), dim3(T::waves * 64), 0, s, a, x_tiles, gm, gn);
 }
 
 template <int EPI>
-static int launch_tile_epi(GemmArgs a, int rows, int max_shares, hipStream_t s) {
-  constexpr bool DUAL = EPI == EPI_SWIGLU;
-  static const TileCost cost[3] = {{256, 256, 1, 1247.f, 1247.f, 1.33f}, {128, 128, 2, 530.f, 800.f, 1.16f}, {64, 128, 2, 340.f, 520.f, 0.92f}};
+static int launch_tile_epi(const GemmArgs& a, int rows, int max_shares, hipStream_t s) {
+  static const TileCost cost[5] = {{256, 256, 1, 8.0f, 1355.f, 0.f, 1.22f}, {128, 128, 2, 5.4f, 608.f, 465.f, 1.10f},
+                                   {64, 128, 2, 4.2f, 478.f, 200.f, 0.83f}, {64, 64, 2, 3.7f, 327.f, 517.f, 0.64f},
+                                   {32, 64, 3, 3.4f, 290.f, 293.f, 1.23f}};
   int best = 0, sk = 1;
   float best_us = 1e30f;
-  for (int i = 0; i < 3; ++i)
-    for (int k = 1; k <= max_shares && (k == 1 || a.Kt / k >= 8); ++k) {
-      // a share is written once and read once by the norm: 4.5 TB/s each way, half of the write hidden
-      const float us = tile_us(cost[i], rows, a.N, a.Kt, DUAL, k) + (EPI == EPI_PART ? 1.5f * rows * a.N * 4.f * k / 4.5e6f : 0.f);
+  for (int i = 0; i < 5; ++i)
+    for (int k = 1; k <= max_shares && (k == 1 || a.Kt / k >= 3); ++k) {
+      const float us = tile_us(cost[i], EPI, rows, a.N, a.Kt, k);
       if (us < best_us) { best_us = us; best = i; sk = k; }
     }
-  const int x_tiles = (int)(a.x_elems / ((size_t)a.Kt * 512));
-  const int gm = (rows + cost[best].tm - 1) / cost[best].tm, cols = cost[best].tn / (DUAL ? 2 : 1), gn = (a.N + cols - 1) / cols;
-  const dim3 grid(gm * gn, sk);
-  if (best == 0) hipLaunchKernelGGL((k_gemm_tile<TileL, EPI>), grid, dim3(TileL::waves * 64), 0, s, a, x_tiles, gm, gn);
-  else if (best == 1) hipLaunchKernelGGL((k_gemm_tile<TileM, EPI>), grid, dim3(TileM::waves * 64), 0, s, a, x_tiles, gm, gn);
-  else hipLaunchKernelGGL((k_gemm_tile<TileS, EPI>), grid, dim3(TileS::waves * 64), 0, s, a, x_tiles, gm, gn);
+  switch (best) {
+    case 0: launch_tile<TileL, EPI>(a, rows, sk, s); break;
+    case 1: launch_tile<TileM, EPI>(a, rows, sk, s); break;
+    case 2: launch_tile<TileS, EPI>(a, rows, sk, s); break;
+    case 3: launch_tile<TileX, EPI>(a, rows, sk, s); break;
+    default: launch_tile<TileN, EPI>(a, rows, sk, s); break;
+  }
   return sk;
 }
 
-// Under 128 workgroups of the smallest tile the K-split kernels of k_gemm.hip, which put every column tile in a workgroup of
-// its own, are ahead: QKV 6144 x 4096 at 128 rows (96 workgroups) 20.6 against 24.3 us, 3072 x 2048 at 256 rows (96) 13.3
-// against 14.6; 6144 x 4096 at 200 rows (192) 29.7 against 26.3, 12288 x 4096 at 100 rows (192) 35.7 against 26.4.
-bool gemm_takes_tile(int epi, const GemmArgs& a, int rows, int max_shares) {
-  if (rows < 97) return false;
-  const int cols = epi == EPI_SWIGLU ? 64 : 128, shares = epi == EPI_PART ? std::max(1, std::min(max_shares, a.Kt / 8)) : 1;
-  return (rows + 63) / 64 * ((a.N + cols - 1) / cols) * shares >= 128;
+// 17 - 64 rows of an output that cannot be left in K shares: under 160 workgroups of the narrowest tile the K-split kernel of
+// k_gemm.hip, whose 8 waves share a column tile, is ahead (6144 x 4096 at 20 / 40 / 64 rows, 96 workgroups: 13.9 / 17.9 / 20.4
+// against 18.9 / 21.2 / 21.1 us; 6400 x 1600, 100: 9.7 against 12.0 at 20); with 192 and more this one is (12288 x 4096: 26.2 /
+// 27.1 / 31.3 against 23.2 / 28.4 / 28.8; 2 x 8192 x 2048: 18.6 against 15.2 at 64).  Partial products are ahead at any size:
+// 4096 x 4096 12.2 -> 8.8 at 20 rows, 1600 x 6400 9.7 -> 6.9, 4096 x 14336 33.9 -> 24.7 at 64; and so is everything from 65 rows
+// on, where that kernel takes two passes (4800 x 1600 at 80 rows 12.2 -> 9.0, 2 x 3072 x 768 9.1 -> 6.8; 12288 x 4096 36.9 / 37.4).
+bool gemm_takes_tile(int epi, const GemmArgs& a, int rows) {
+  const int cols = epi == EPI_SWIGLU ? 32 : 64;
+  return rows > 64 || (rows > 16 && (epi == EPI_PART || (a.N + cols - 1) / cols >= 160));
 }
 
 int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipStream_t s) {
