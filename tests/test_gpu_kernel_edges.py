@@ -79,3 +79,29 @@ def test_prefill_attention_runs(group, chunk_rows):
     draft = W.ModelCfg(W.ARCH_LLAMA, 1, 512, 8, 8 // group, 136, 83, 48, 1e-5, 10000.0)
     target = _llama(1, 1024, 8, 8 // group, 136, 83) if group > 1 else _gpt(1, 128, 136, 83)
     _check(draft, target, 13, W.DT_BF16, prompt_len=41, prompt_len_min=1, tau=1.5, whole_prompt=True, chunk_rows=chunk_rows, seed=21 + group)
+
+
+@pytest.mark.parametrize("B", [17, 40, 65, 80])
+def test_small_tiles(B):
+    """17 - 80 rows of one step, all rejected: the 32- and 64-row tiles with K shares down to three k tiles each, a row count
+    just beyond a tile and beyond two, a half-filled last k tile, the wide gate + up product (FFN 5128: 161 workgroups of 32
+    columns) next to the K-split kernel for the narrow ones."""
+    _check(_gpt(1, 192, 712, 83), _llama(1, 512, 8, 2, 5128, 83), B, W.DT_BF16, tau=1.5, prompt_len=3, n_gen=2)
+
+
+@pytest.mark.parametrize("group", [1, 2, 8])
+def test_short_runs_share_a_pass(group):
+    """Full-prefix work lists: runs of 1 to 40 entries that begin and end anywhere in a group of 16 / G positions (the first
+    pass over a prompt-free cache is long, later ones follow the rejections), contexts beyond one block of keys per wave."""
+    from parity_util import Pair, compare_replay
+    draft = W.ModelCfg(W.ARCH_GPT, 1, 128, 2, 2, 136, 83, 160)
+    target = W.ModelCfg(W.ARCH_LLAMA, 2, 1024, 8, 8 // group, 136, 83, 160, 1e-5, 10000.0)
+    cfg = W.SprinterCfg(draft, target, 24, W.DT_BF16, 5, 160, tau=0.5, seed=31 + group, name="runs", batch=5, prompt_len=110,
+                        prompt_len_min=3, n_gen=24, prompt_dist="uniform", weight_seed=531, prompt_seed=631, target_ctx_mode=W.CTX_FULL_PREFIX)
+    p = Pair(cfg, ver_scale=8.0)
+    g, _ = p.gpu_generate(cfg.n_gen)
+    rec = p.oracle(cfg.n_gen, forced=dict(tok=g["tok"], accept=g["accept"]))
+    rep = compare_replay(cfg, g, rec)
+    print(group, rep, flush=True)
+    assert 0 < rep["reject_rate"] < 1
+    p.close()
