@@ -1,6 +1,6 @@
 // HIP kernels of standard speculative decoding (Sec. 2 with Eq. (1)) for gfx950: work lists of the draft window
 // and of the target's parallel pass, the p/q coin with the residual draw, and the commit of a round.
-#include "dev.h"
+#include "coin.h"
 
 namespace sprinter {
 
@@ -71,62 +71,31 @@ void launch_sd_target_list(const SdBase& a, int start, int n, RowDescW out, hipS
   hipLaunchKernelGGL(k_sd_target_list, dim3(1), dim3(1024), 0, s, a, start, n, out);
 }
 
-// q = softmax(draft logits / T), p = softmax(target logits / T); sweeps over the vocabulary for the maxima, the
-// sums of exponentials and - only where the coin fails - the Gumbel-max draw from max(0, p - q), taken on
-// ln(p - q) + noise of the target stream.  float32 throughout.
-__global__ __launch_bounds__(256) void k_sd_window_check(SdBase a, int start, const u64* __restrict__ am_part, int n_lm_wg,
-                                                         int Mpad) {
-  __shared__ float s4[4];
-  __shared__ u64 s_key[4];
-  const int i = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = wave_index();
+// One workgroup per entry of the target pass: the coin of a window token and, where it fails, its replacement; the last entry
+// of a window gives the extra token.
+__global__ __launch_bounds__(COIN_THREADS) void k_sd_window_check(SdBase a, int start, const u64* __restrict__ am_part, int n_lm_wg,
+                                                                  int Mpad) {
+  const int i = blockIdx.x, tid = threadIdx.x;
   const int per = a.gamma + 1, e = start + i, b = e / per, j = e - b * per, V = a.V;
   if (j == a.gamma) {                                    // the extra token: the target's own sample of this entry
-    if (w == 0) {
-      const u64 k = merge_partials(am_part, n_lm_wg, Mpad, i, lane);
-      if (lane == 0) a.alt[b * per + j] = key_index(k);
+    if (wave_index() == 0) {
+      const u64 k = merge_partials(am_part, n_lm_wg, Mpad, i, tid & 63);
+      if (tid == 0) a.alt[b * per + j] = key_index(k);
     }
     return;
   }
   const int t = a.st.len_q[b] + j + 1;                   // sequence position of the checked token
-  const int x = a.win[b * a.gamma + j];
-  const float* __restrict__ lq = a.dlw + (size_t)a.qrow[b * a.gamma + j] * V;
-  const float* __restrict__ lp = a.tlw + (size_t)e * V;
-  const float it = a.inv_temperature;
-  float mq = -INFINITY, mp = -INFINITY;
-  for (int v = tid; v < V; v += 256) { mq = fmaxf(mq, lq[v] * it); mp = fmaxf(mp, lp[v] * it); }
-  mq = block_max256(mq, s4);
-  mp = block_max256(mp, s4);
-  float sq = 0.f, sp = 0.f;
-  for (int v = tid; v < V; v += 256) { sq += expf(lq[v] * it - mq); sp += expf(lp[v] * it - mp); }
-  sq = block_sum256(sq, s4);
-  sp = block_sum256(sp, s4);
-  const float lse_q = mq + logf(sq), lse_p = mp + logf(sp);
-  const float log_ratio = (lp[x] * it - lse_p) - (lq[x] * it - lse_q);
-  const unsigned cw = philox_word(a.seed_lo, a.seed_hi, 2u, (unsigned)b, (unsigned)t, 0u);
-  const float coin = ((float)(cw >> 9) + 0.5f) * 1.1920928955078125e-07f;
-  const bool kept = coin <= fminf(1.0f, expf(log_ratio));        // uniform over the workgroup
-  if (tid == 0) a.kept[b * a.gamma + j] = kept ? 1 : 0;
-  if (kept) return;
-  u64 best = 0;
-  for (int v = tid; v < V; v += 256) {
-    const float r = expf(lp[v] * it - lse_p) - expf(lq[v] * it - lse_q);
-    if (r > 0.f) {
-      const float z = logf(r) + gumbel_from_word(philox_word(a.seed_lo, a.seed_hi, 1u, (unsigned)b, (unsigned)t, (unsigned)v));
-      best = umax64(best, pack_key(z, (unsigned)v));
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) best = umax64(best, shfl_xor_u64(best, o));
-  if (lane == 0) s_key[w] = best;
-  __syncthreads();
+  int drawn = 0;
+  const bool kept = coin_or_residual(a.dlw + (size_t)a.qrow[b * a.gamma + j] * V, a.tlw + (size_t)e * V, V, a.inv_temperature,
+                                     a.seed_lo, a.seed_hi, b, t, a.win[b * a.gamma + j], &drawn);
   if (tid == 0) {
-    best = umax64(umax64(s_key[0], s_key[1]), umax64(s_key[2], s_key[3]));
-    a.alt[b * per + j] = best ? key_index(best) : x;     // (an empty residual cannot occur when the coin fails)
+    a.kept[b * a.gamma + j] = kept ? 1 : 0;
+    if (!kept) a.alt[b * per + j] = drawn;
   }
 }
 void launch_sd_window_check(const SdBase& a, int start, int n, const unsigned long long* am_part, int n_lm_wg, int Mpad,
                             hipStream_t s) {
-  hipLaunchKernelGGL(k_sd_window_check, dim3(n), dim3(256), 0, s, a, start, am_part, n_lm_wg, Mpad);
+  hipLaunchKernelGGL(k_sd_window_check, dim3(n), dim3(COIN_THREADS), 0, s, a, start, am_part, n_lm_wg, Mpad);
 }
 
 // Single workgroup, one thread per row: the first failed coin ends the window; commit, advance the state, and
