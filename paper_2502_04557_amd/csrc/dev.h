@@ -248,6 +248,14 @@ __device__ __forceinline__ float wave_total(float v) {
   return v;
 }
 
+// Sum over a workgroup of 256, in every thread.  s4: LDS that nothing else uses (no barrier before the store).
+__device__ __forceinline__ float block_total256(float v, float* s4) {
+  v = wave_total(v);
+  if ((threadIdx.x & 63) == 63) s4[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return ((s4[0] + s4[1]) + s4[2]) + s4[3];
+}
+
 // Maximum over an aligned group of 16 consecutive lanes (one DPP row), in every lane of the group.
 __device__ __forceinline__ float group_max16(float v) {
   v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true)));

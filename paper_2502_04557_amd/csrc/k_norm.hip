@@ -81,7 +81,7 @@ void launch_rope_table(float* out, int max_seq, int dh, float theta, hipStream_t
 // (bf16 mode: one 16-byte slot of a float16 operand tile), so the row, gain and offset are requested with six 16-byte
 // loads per thread before anything is waited for and the result leaves as one or two 16-byte stores.  d <= 8192.
 // NI = 2048-column blocks per row (1, 2 or 4); SH = 0, or the most partial products a pending update of the
-// residual stream may consist of (4 or 8): the row is then h + bias + share 0 + share 1 + ..., added in that
+// residual stream may consist of (1, 4 or 8): the row is then h + bias + share 0 + share 1 + ..., added in that
 // order, written back and normalised.  The partial loads are issued with the others, before the row count
 // is known, with clamped share indices and the surplus selected away - no branch, no second memory round.
 // SH = -1: the first norm of a forward; the row is the token's embedding (+ the position's), it starts the residual stream,
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
                                                    const float* __restrict__ b, float eps, int d,
                                                    const int* __restrict__ n_rows, AT* __restrict__ act_out,
                                                    float* __restrict__ f32_out, NormPending pend, EmbedSource emb) {
-  __shared__ float s4[4];
+  __shared__ float s_sum[4], s_sq[4];
   const int r = blockIdx.x, tid = threadIdx.x;
   const float4* __restrict__ x4 = reinterpret_cast<const float4*>(h + (size_t)r * d);
   const float4* __restrict__ g4 = reinterpret_cast<const float4*>(g);
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
     for (int e = 0; e < 8; ++e) { x[i][e] = ok ? x[i][e] : 0.f; sum += x[i][e]; }
   }
   float mean = 0.f;
-  if (ARCH == 0) mean = block_sum256(sum, s4) / (float)d;
+  if (ARCH == 0) mean = block_total256(sum, s_sum) / (float)d;
   float sq = 0.f;
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
 #pragma unroll
     for (int e = 0; e < 8; ++e) { const float c = ok ? x[i][e] - mean : 0.f; sq += c * c; }
   }
-  const float var = block_sum256(sq, s4) / (float)d;
+  const float var = block_total256(sq, s_sq) / (float)d;
   const float rstd = 1.0f / sqrtf(var + eps);
   const int Kt = (d + 31) >> 5;
 #pragma unroll
@@ -212,6 +212,7 @@ static void launch_norm_ni(const float* h, const float* g, const float* b, float
   memset(&es, 0, sizeof es);
   if (emb) { es = *emb; SPRINTER_NORM(-1); }
   else if (np.shares <= 0) SPRINTER_NORM(0);
+  else if (np.shares == 1) SPRINTER_NORM(1);
   else if (np.shares <= 4) SPRINTER_NORM(4);
   else SPRINTER_NORM(8);
 #undef SPRINTER_NORM
