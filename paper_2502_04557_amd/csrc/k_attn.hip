@@ -480,7 +480,7 @@ __global__ __launch_bounds__(64) void k_kv_append_bf16(AttnArgs a) {
   const bool in_window = listed && lane >= 7 && lane < 15;
   const bool full = in_window && ((follows >> (first + 1)) & 0x7f) == 0x7f;
   const u64 starts = __ballot(full && (e_slot & 7) == 0);        // at most one bit
-  u64 single = __ballot(in_window && !full);
+  const u64 single = __ballot(in_window && !full);
   const float* __restrict__ yv = a.y + (size_t)(a.H + a.KVH + kvh) * DH;
   if (starts) {
     const int f = __builtin_ctzll(starts), b = __builtin_amdgcn_readlane(e_b, f), slot = __builtin_amdgcn_readlane(e_slot, f);
@@ -495,12 +495,20 @@ __global__ __launch_bounds__(64) void k_kv_append_bf16(AttnArgs a) {
       *reinterpret_cast<uint4*>(vc + ((size_t)b * a.KVH + kvh) * head + vt_index(slot, c0 + lane, DH)) = make_uint4(pk[0], pk[1], pk[2], pk[3]);
     }
   }
-  while (single) {
-    const int i = __builtin_ctzll(single), b = __builtin_amdgcn_readlane(e_b, i), slot = __builtin_amdgcn_readlane(e_slot, i);
-    single &= single - 1;
+  if (single) {                                                  // all of the window's values requested together
+    float x[8][DH / 64];
 #pragma unroll
-    for (int c0 = 0; c0 < DH; c0 += 64)
-      vc[((size_t)b * a.KVH + kvh) * head + vt_index(slot, c0 + lane, DH)] = f2bf(yv[(size_t)(r0 - 7 + i) * a.dqkv + c0 + lane]);
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int c = 0; c < DH / 64; ++c) x[e][c] = yv[(size_t)(r0 + min(e, n_here - 1)) * a.dqkv + c * 64 + lane];
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if ((single >> (7 + e)) & 1) {                             // (scalar)
+        const int b = __builtin_amdgcn_readlane(e_b, 7 + e), slot = __builtin_amdgcn_readlane(e_slot, 7 + e);
+#pragma unroll
+        for (int c = 0; c < DH / 64; ++c)
+          vc[((size_t)b * a.KVH + kvh) * head + vt_index(slot, c * 64 + lane, DH)] = f2bf(x[e][c]);
+      }
   }
 }
 
