@@ -411,12 +411,12 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
     norm_gemm(L.n1g, L.n1b, EPI_F32, L.wqkv, nullptr, md.dqkv, L.bqkv, sc.y, nullptr, i == 0 ? &emb : nullptr);
     if (shared_caches) {
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
-                       kv_slots(ctx->cfg), sc.ao, max_rows, s, 1);
+                       kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, 1);
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
-                       kv_slots(ctx->cfg), sc.ao, max_rows, s, long_runs ? 3 : 2);
+                       kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, long_runs ? 3 : 2);
     } else {
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
-                       kv_slots(ctx->cfg), sc.ao, max_rows, s);
+                       kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s);
     }
     if (!want_head && i + 1 == md.n_layer) break;   // a prefill position only has to fill the caches
     resid_gemm(L.wo, sc.ao, pl_a, md.H * md.dh, L.bo);

@@ -98,8 +98,9 @@ void launch_gemm_norm(int dtype, int epi, const NormFusion& f, const void* W, co
 void launch_attention(int dtype, const ModelDims& md, const float* y, const float* rope, const RowDesc& rd,
                       void* kcache, void* vcache, size_t layer_off, int ctx_bound /* upper bound of the rows' cache lengths */,
                       int max_seq /* slots per (row, KV head) of the caches; bf16: a multiple of 32 */,
-                      void* ao, int max_rows, hipStream_t s, int phase = 0);
-// phase 0: append the row's new key / value to the cache and attend (rows of one launch own different caches);
+                      void* ao, int max_rows, float* split, hipStream_t s, int phase = 0);
+// split: scratch, the partial products' buffer (free between a layer's first norm and its O-projection; its PART_SHARES x rows x d
+// floats hold the at most 256 / KVH x H / KVH x (dh + 2) of a split launch); phase 0: append the row's new key / value to the cache and attend (rows of one launch own different caches);
 // phase 1: append only; phase 2: attend only (the pair serves launches where several rows share a cache).
 
 // The verifier's hidden layer over the rows of the draft pass; part[chunk][row] receives each chunk's share of the logit.

@@ -14,6 +14,7 @@ struct AttnArgs {
   void* kcache; void* vcache; size_t layer_off;
   int H, KVH, dqkv, max_seq, use_rope; float scale;
   void* ao; int ao_K;
+  float* split;   // k_attn_dec_bf16 with gridDim.z > 1: partial results [row][KV head][z][query head][DH + 2]
   int phase;   // 0 append + attend, 1 append only, 2 attend only, 3 attend only over long runs of one row (launcher only)
 };
 
@@ -199,7 +200,8 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // buffers; the query operand is kept in LDS to make room); nothing in the loop synchronises waves.  The row's own key and value
 // (the token being processed) are computed in the prologue, appended to the cache by wave 0 and patched into the
 // operands of the block that holds slot `slot`, which is the row's last block; keys beyond it are masked.
-// The waves' partial results are merged through LDS at the end.
+// The waves' partial results are merged through LDS at the end.  gridDim.z > 1: that many workgroups share the keys (their waves
+// count on), each leaves its unnormalised result, maximum and sum in a.split, and k_attn_merge puts them together.
 template <int DH, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
   constexpr int T = DH / 32, CT = DH / 16, PS = 36, HALF = DH / 2, GMAX = 8;
@@ -248,7 +250,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
   const int b = a.rd.b[r], slot = a.rd.slot[r], S = a.max_seq;
   bf16_t* __restrict__ Kc = (bf16_t*)a.kcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
   bf16_t* __restrict__ Vc = (bf16_t*)a.vcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
-  const int n_steps = (slot + 32 * NW) / (32 * NW);             // blocks 0 .. slot / 32, NW per step
+  const int wz = blockIdx.z * NW + w, NZ = gridDim.z * NW;      // this wave among all that share the keys
+  const int n_steps = (slot + 32 * NZ) / (32 * NZ);             // blocks 0 .. slot / 32, NZ per step
   // Two register buffers: a block's key fragments and value tiles are requested a whole step ahead (the query
   // operand lives in LDS to make room for them).
   // A block beyond the row's last one is read at the last one's address (scalar clamp) and fully masked; inside a
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
     for (int ct = 0; ct < CT; ++ct) B.v[ct] = *reinterpret_cast<const u32x4*>(v_lane + off + ct * 512);
   };
   Blk A, B;
-  fetch(A, w * 32);
+  fetch(A, wz * 32);
   {
     const bool upper = d0 >= HALF;
     float qv[8], kn[8];
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
       lds_q[1][tq][lane] = ql;
       if (l16 == 0) {                                            // the new key: into LDS for the row's last block, and into the cache
         *reinterpret_cast<u32x4*>(lds_kn + d0) = knew;
-        *reinterpret_cast<u32x4*>(Kc + (size_t)slot * DH + d0) = knew;
+        if (blockIdx.z == 0) *reinterpret_cast<u32x4*>(Kc + (size_t)slot * DH + d0) = knew;
       }
     }
   }
@@ -301,7 +304,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
     const unsigned h = f2bf(vraw[ct]);
-    if (w == 0 && lq == 0) Vc[vt_index(slot, ct * 16 + l16, DH)] = (bf16_t)h;
+    if (wz == 0 && lq == 0) Vc[vt_index(slot, ct * 16 + l16, DH)] = (bf16_t)h;
     if (ct & 1) vnew[ct >> 1] |= h << 16; else vnew[ct >> 1] = h;
   }
   lds_barrier();                                                 // the query operand and the new key are in LDS for every wave
@@ -376,15 +379,15 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
     }
   };
   for (int i = 0; i < n_steps; i += 2) {
-    const int kb = (i * NW + w) * 32;
-    fetch(B, kb + 32 * NW);
+    const int kb = (i * NZ + wz) * 32;
+    fetch(B, kb + 32 * NZ);
     __builtin_amdgcn_sched_barrier(0);
     step(A, kb);
     __builtin_amdgcn_sched_barrier(0);
     if (i + 1 < n_steps) {                                       // (scalar condition)
-      fetch(A, kb + 64 * NW);
+      fetch(A, kb + 64 * NZ);
       __builtin_amdgcn_sched_barrier(0);
-      step(B, kb + 32 * NW);
+      step(B, kb + 32 * NZ);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -412,8 +415,38 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
       den += c * s_ml[q][g][1];
       num += c * s_o[q][g][i];
     }
-    act_store<bf16_t>(ao, r, kvh * G * DH + idx, a.ao_K, num / den);
+    if (gridDim.z > 1) {                                         // (uniform)
+      float* __restrict__ o = a.split + ((((size_t)r * a.KVH + kvh) * gridDim.z + blockIdx.z) * G + g) * (DH + 2);
+      o[i] = num;
+      if (i == 0) { o[DH] = mn; o[DH + 1] = den; }
+    } else {
+      act_store<bf16_t>(ao, r, kvh * G * DH + idx, a.ao_K, num / den);
+    }
   }
+}
+
+// One workgroup per (query head, row): the n <= 8 partial results of k_attn_dec_bf16, in their order.
+template <int DH>
+__global__ __launch_bounds__(DH) void k_attn_merge(AttnArgs a, int n) {
+  const int h = blockIdx.x, r = blockIdx.y, G = a.H / a.KVH, kvh = h / G, g = h % G, i = threadIdx.x;
+  const float* __restrict__ p = a.split + (((size_t)r * a.KVH + kvh) * n * G + g) * (DH + 2);
+  float m[8], l[8], o[8];
+#pragma unroll
+  for (int z = 0; z < 8; ++z) {                                  // (requested together; beyond n: the last one again, dropped)
+    const float* q = p + (size_t)min(z, n - 1) * G * (DH + 2);
+    m[z] = q[DH]; l[z] = q[DH + 1]; o[z] = q[i];
+  }
+  if (r >= *a.rd.n_rows) return;
+  float mn = -1e30f, den = 0.f, num = 0.f;
+#pragma unroll
+  for (int z = 0; z < 8; ++z) mn = fmaxf(mn, m[z]);
+#pragma unroll
+  for (int z = 0; z < 8; ++z) {
+    const float c = z < n ? __expf(m[z] - mn) : 0.f;
+    den += c * l[z];
+    num += z < n ? c * o[z] : 0.f;
+  }
+  act_store<bf16_t>((bf16_t*)a.ao, r, h * DH + i, a.ao_K, num / den);
 }
 
 // Append-only launch of a multi-entry pass: rotate the new key, round key and value to bf16 and write them to the
@@ -869,6 +902,16 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
     else hipLaunchKernelGGL((k_attn_runs_bf16<DH, 4>), grid, dim3(256), 0, s, a);
     return;
   }
+  // A compute unit pulls at most 48 KB/us, so one workgroup needs 21 us for 2000 keys of 128 columns: few rows with long
+  // contexts share the keys over several workgroups, at the price of a merge launch (3 rows x 8 KV heads, 1500 - 2000 keys of
+  // 128 columns: 29.6 -> 10.3 + 4.6 us; 4 rows, 64 columns: 16.6 -> 7.5 + 3.3).  400 KB a workgroup are where the two meet.
+  const int split = std::min(8, 256 / (a.KVH * max_rows));
+  if (wide && split > 1 && (size_t)ctx_bound * DH * 4 >= 400 * 1024) {
+    grid.z = split;
+    hipLaunchKernelGGL((k_attn_dec_bf16<DH, 8>), grid, dim3(512), 0, s, a);
+    hipLaunchKernelGGL((k_attn_merge<DH>), dim3(a.H, max_rows), dim3(DH), 0, s, a, split);
+    return;
+  }
   if (wide) hipLaunchKernelGGL((k_attn_dec_bf16<DH, 8>), grid, dim3(512), 0, s, a);
   else hipLaunchKernelGGL((k_attn_dec_bf16<DH, 4>), grid, dim3(256), 0, s, a);
 }
@@ -887,13 +930,13 @@ static void launch_attn_g(const AttnArgs& a, int G, int max_rows, hipStream_t s)
 
 void launch_attention(int dtype, const ModelDims& md, const float* y, const float* rope, const RowDesc& rd,
                       void* kcache, void* vcache, size_t layer_off, int ctx_bound, int max_seq, void* ao,
-                      int max_rows, hipStream_t s, int phase) {
+                      int max_rows, float* split, hipStream_t s, int phase) {
   AttnArgs a;
   a.phase = (phase == 3 && dtype == 0) ? 2 : phase;      // the run-sharing kernel exists for bf16 only
   a.y = y; a.rope = rope; a.rd = rd; a.kcache = kcache; a.vcache = vcache; a.layer_off = layer_off;
   a.H = md.H; a.KVH = md.KVH; a.dqkv = md.dqkv; a.max_seq = max_seq; a.use_rope = md.arch == 1;
   a.scale = 1.0f / sqrtf((float)md.dh);
-  a.ao = ao; a.ao_K = md.H * md.dh;
+  a.ao = ao; a.ao_K = md.H * md.dh; a.split = split;
   int G = md.H / md.KVH;
   if (dtype == 0) {
     if (md.dh == 64) launch_attn_g<float, 64>(a, G, max_rows, s); else launch_attn_g<float, 128>(a, G, max_rows, s);

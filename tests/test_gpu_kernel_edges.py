@@ -105,3 +105,12 @@ def test_short_runs_share_a_pass(group):
     print(group, rep, flush=True)
     assert 0 < rep["reject_rate"] < 1
     p.close()
+
+
+@pytest.mark.parametrize("B", [1, 3])
+def test_keys_shared_by_several_workgroups(B):
+    """Few rows with contexts long enough that several workgroups share a row's keys: 8 and 4 of them, one or two query heads per
+    KV head, head dimension 128 (from 800 positions) and 64 (from 1600), the new key in the last block of another workgroup's."""
+    draft = W.ModelCfg(W.ARCH_LLAMA, 1, 256, 4, 4, 136, 83, 1700, 1e-5, 10000.0)
+    target = W.ModelCfg(W.ARCH_LLAMA, 1, 1024, 8, 8 if B == 3 else 4, 136, 83, 1700, 1e-5, 10000.0)
+    _check(draft, target, B, W.DT_BF16, prompt_len=1630, prompt_len_min=810, tau=1.5, n_gen=3, max_seq=1664, whole_prompt=True)
