@@ -211,7 +211,7 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
   void* vc = bump.take(layer_stride * md.n_layer * es);
   ModelScratch sc;
   sc.h = (float*)bump.take((size_t)rows * md.d * 4);
-  sc.h2 = (float*)bump.take((size_t)4 * md.d * 4);
+  sc.h2 = sc.h + (size_t)4 * md.d;       // (rows >= 16; only passes of at most 4 rows use it)
   sc.xn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.y = (float*)bump.take((size_t)rows * md.dqkv * 4);
   sc.ao = bump.take(act_elems(c.dtype, rows, md.H * md.dh) * es);
@@ -219,7 +219,6 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
   sc.hf = (float*)bump.take((size_t)rows * md.d * 4);
   sc.hfn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.rope = (float*)bump.take((size_t)rows * md.dh * 4);
-  sc.rope_table = md.arch == SPRINTER_ARCH_LLAMA ? (float*)bump.take((size_t)c.max_seq * md.dh * 4) : nullptr;
   sc.part = (float*)bump.take((size_t)PART_SHARES * rows * md.d * 4);
   sc.n_lm_wg = lmhead_num_wg(c.dtype, md.V);
   sc.am_part = (unsigned long long*)bump.take((size_t)sc.n_lm_wg * rows * 8);
@@ -376,7 +375,7 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   const int rows = ctx->rows_alloc;
   // elements the activation buffers hold (their row tiles bound what a kernel may fetch)
   const size_t pl_d = act_elems(dt, rows, md.d), pl_a = act_elems(dt, rows, md.H * md.dh), pl_f = act_elems(dt, rows, md.ff);
-  const EmbedSource emb{m.tok_emb, m.pos_emb, rd, sc.rope_table, sc.rope, md.V, md.max_pos, ctx->cfg.max_seq, md.dh};
+  const EmbedSource emb{m.tok_emb, m.pos_emb, rd, md.arch == SPRINTER_ARCH_LLAMA ? sc.rope : nullptr, md.theta, md.V, md.max_pos, md.dh};
   // O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
   // them (and the bias) into the residual stream before it normalises the row.
   const size_t part_stride = (size_t)rows * md.d;
@@ -603,7 +602,6 @@ int create_common(const sprinter_cfg* cfg, void* dev_workspace, void* hip_stream
     launch_fill_zero(m->sc.ao, act_elems(cfg->dtype, rows, m->md.H * m->md.dh) * es, ctx->stream);
     launch_fill_zero(m->sc.mid, act_elems(cfg->dtype, rows, m->md.ff) * es, ctx->stream);
     launch_fill_zero(m->sc.hfn, act_elems(cfg->dtype, rows, m->md.d) * es, ctx->stream);
-    if (m->sc.rope_table) launch_rope_table(m->sc.rope_table, cfg->max_seq, m->md.dh, m->md.theta, ctx->stream);
   }
   launch_set_f32(ctx->tau_dev, cfg->tau, ctx->stream);
   launch_fill_zero(ctx->dev_counts, 256, ctx->stream);

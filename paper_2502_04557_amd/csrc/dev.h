@@ -89,6 +89,13 @@ __device__ __forceinline__ void load_row(const bf16_t* p, float (&x)[8]) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) { x[2 * k] = __uint_as_float(w[k] << 16); x[2 * k + 1] = __uint_as_float(w[k] & 0xffff0000u); }
 }
+// cos / sin of rotary pair k at row r's position; angle = pos * theta^(-2k/dh), evaluated in double so that large positions
+// stay accurate.
+__device__ __forceinline__ void rope_factors(const EmbedSource& e, int r, int k) {
+  const double inv = pow((double)e.theta, -2.0 * (double)k / (double)e.dh);
+  const double ang = (double)e.rd.pos[r] * inv;
+  reinterpret_cast<float2*>(e.rope + (size_t)r * e.dh)[k] = make_float2((float)cos(ang), (float)sin(ang));
+}
 __device__ __forceinline__ float gelu_tanh(float x) {
   const float c = 0.7978845608028654f;   // sqrt(2/pi)
   return 0.5f * x * (1.0f + tanhf(c * (x + 0.044715f * x * x * x)));

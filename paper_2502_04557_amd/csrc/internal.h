@@ -37,7 +37,7 @@ struct ModelDims {
 constexpr int PART_SHARES = 8;   // most K shares launch_gemm_part may use
 struct ModelScratch {  // per-model activation buffers, sized for max_batch rows
   float* h;            // [M, d] residual stream, float32
-  float* h2;           // [4, d] a few rows' residual stream: launch_gemm_norm alternates between h and h2
+  float* h2;           // [4, d] a few rows' residual stream: launch_gemm_norm alternates between rows 0 .. 3 of h and this, its rows 4 .. 7
   void* xn;            // [M, d] normalised GEMM input (activation layout)
   float* y;            // [M, dqkv] QKV projection output, float32
   void* ao;            // [M, H*dh] attention output (activation layout)
@@ -45,7 +45,6 @@ struct ModelScratch {  // per-model activation buffers, sized for max_batch rows
   float* hf;           // [M, d] final hidden state after the last norm, float32
   void* hfn;           // same values in activation layout (LM-head input)
   float* rope;         // [M, dh/2, 2] cos/sin of the row's position
-  float* rope_table;   // [max_seq, dh/2, 2] the same for every position (LLaMA; else NULL)
   float* part;         // [PART_SHARES][M, d] partial O-proj / FFN-down products, float32
   unsigned long long* am_part;  // [n_lm_wg, Mpad] packed (value, index) arg-max partials
   int n_lm_wg;
@@ -60,11 +59,10 @@ struct SamplerArgs {
 void launch_pack_bf16(const void* w, void* out, int N, int K, hipStream_t s);
 void launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
-void launch_rope_table(float* out, int max_seq, int dh, float theta, hipStream_t s);
 // The first norm of a forward reads its rows from the embedding tables (dtype elements) and starts the residual stream; with
-// a rotary table it also leaves each row's factors in rope[M, dh].
+// rope (NULL: no rotary positions) workgroups of its own also leave each row's factors in rope[M, dh].
 struct EmbedSource {
-  const void *tok_emb, *pos_emb; RowDesc rd; const float* rope_table; float* rope; int V, max_pos, max_seq, dh;
+  const void *tok_emb, *pos_emb; RowDesc rd; float* rope; float theta; int V, max_pos, dh;
 };
 // An update of the residual stream that is still in pieces (launch_gemm_part): the norm kernel adds
 // bias + share 0 + share 1 + ... to the row, writes the row back and normalises the sum.

@@ -26,6 +26,11 @@ __global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
   __shared__ float red[8 * NI4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
   const int nt0 = blockIdx.x * NTW, d = a.K;
+  if (nt0 >= a.n_tiles) {                               // one workgroup more with rotary positions: the rows' factors
+    const int half = f.emb.dh >> 1;
+    if (tid < R * half) rope_factors(f.emb, tid / half, tid % half);
+    return;
+  }
   // ---- this wave's share of K: k tiles w, w + 8, .. (bf16) or 16-k groups [g0, g1) (float32); first weights requested
   const int n_k = BF ? a.Kt : d >> 4;
   const int g0 = BF ? w : n_k * w / 8, g1 = BF ? n_k : n_k * (w + 1) / 8, gs = BF ? 8 : 1;
@@ -70,9 +75,6 @@ __global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
       load_row(e + q4 * 4, ev);
       if (p) load_row(p + q4 * 4, pv);
       x[r] = make_float4(ev[0] + pv[0], ev[1] + pv[1], ev[2] + pv[2], ev[3] + pv[3]);
-      if (blockIdx.x == 0 && f.emb.rope_table && tid < (f.emb.dh >> 1))
-        reinterpret_cast<float2*>(f.emb.rope + (size_t)r * f.emb.dh)[tid] =
-            reinterpret_cast<const float2*>(f.emb.rope_table + (size_t)min(pos, f.emb.max_seq - 1) * f.emb.dh)[tid];
     }
   } else {
     if (f.pend.bias) pb = reinterpret_cast<const float4*>(f.pend.bias)[q4];
@@ -186,7 +188,7 @@ bool gemm_takes_norm(int d, int rows) { return rows <= 4 && d <= 2048; }
 
 template <typename AT, int NTW, int EPI>
 static void launch_gemm_norm_epi(const GemmArgs& a, const NormFusion& f, int rows, hipStream_t s) {
-  const dim3 grid((a.n_tiles + NTW - 1) / NTW);
+  const dim3 grid((a.n_tiles + NTW - 1) / NTW + (f.emb.rope ? 1 : 0));   // (4 rows x 64 pairs at most: one workgroup)
   const size_t lds = sizeof(AT) == 2 ? (size_t)rows * a.K * 2 : (size_t)rows * (a.K + 4) * 4;
 #define SPRINTER_FUSED(R_) hipLaunchKernelGGL((k_gemm_norm<AT, R_, NTW, EPI>), grid, dim3(512), lds, s, a, f)
   if (rows == 1) SPRINTER_FUSED(1); else if (rows == 2) SPRINTER_FUSED(2); else if (rows == 3) SPRINTER_FUSED(3); else SPRINTER_FUSED(4);

@@ -59,23 +59,6 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_zero, dim3(grid), dim3(256), 0, s, (uint4*)p, n16);
 }
 
-// ============================================================ rotary table
-// cos / sin of every position a cache can hold, [max_seq][dh / 2][2]; angle = pos * theta^(-2i/dh), evaluated in double so
-// that large positions stay accurate.  Written once per context: the double-precision pow / cos / sin took 2.5 of the 4.8 us
-// of a one-row embedding launch.
-__global__ __launch_bounds__(256) void k_rope_table(float2* __restrict__ out, int max_seq, int half, float theta) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)max_seq * half) return;
-  const int pos = (int)(i / half), k = (int)(i % half);
-  const double inv = pow((double)theta, -2.0 * (double)k / (double)(2 * half));
-  const double ang = (double)pos * inv;
-  out[i] = make_float2((float)cos(ang), (float)sin(ang));
-}
-void launch_rope_table(float* out, int max_seq, int dh, float theta, hipStream_t s) {
-  const size_t n = (size_t)max_seq * (dh / 2);
-  hipLaunchKernelGGL(k_rope_table, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (float2*)out, max_seq, dh / 2, theta);
-}
-
 // =================================================================== norm
 // LayerNorm (arch 0) / RMSNorm (arch 1), two-pass statistics: one row per workgroup, one thread per 8 consecutive columns
 // (bf16 mode: one 16-byte slot of a float16 operand tile), so the row, gain and offset are requested with six 16-byte
@@ -84,15 +67,23 @@ void launch_rope_table(float* out, int max_seq, int dh, float theta, hipStream_t
 // residual stream may consist of (1, 4 or 8): the row is then h + bias + share 0 + share 1 + ..., added in that
 // order, written back and normalised.  The partial loads are issued with the others, before the row count
 // is known, with clamped share indices and the surplus selected away - no branch, no second memory round.
-// SH = -1: the first norm of a forward; the row is the token's embedding (+ the position's), it starts the residual stream,
-// and the position's rotary factors are copied from the table (an embedding launch of its own cost 1.9 - 4.8 us).
+// SH = -1: the first norm of a forward; the row is the token's embedding (+ the position's) and starts the residual stream
+// (an embedding launch of its own cost 1.9 - 4.8 us).  The rotary factors of all rows come from workgroups of their own behind the
+// rows' (n_rows_grid of them): their double-precision pow / cos / sin take 2.5 us, next to the rows' norm instead of ahead of it.
 template <typename AT, int ARCH, int NI, int SH>
 __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g,
                                                    const float* __restrict__ b, float eps, int d,
                                                    const int* __restrict__ n_rows, AT* __restrict__ act_out,
-                                                   float* __restrict__ f32_out, NormPending pend, EmbedSource emb) {
+                                                   float* __restrict__ f32_out, NormPending pend, EmbedSource emb, int n_rows_grid) {
   __shared__ float s_sum[4], s_sq[4];
   const int r = blockIdx.x, tid = threadIdx.x;
+  if constexpr (SH < 0) {
+    if (r >= n_rows_grid) {
+      const int i = (r - n_rows_grid) * 256 + tid, half = emb.dh >> 1;
+      if (i / half < *n_rows) rope_factors(emb, i / half, i % half);
+      return;
+    }
+  }
   const float4* __restrict__ x4 = reinterpret_cast<const float4*>(h + (size_t)r * d);
   const float4* __restrict__ g4 = reinterpret_cast<const float4*>(g);
   const float4* __restrict__ b4 = reinterpret_cast<const float4*>(b);
@@ -121,9 +112,6 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
         for (int k = 0; k < 8; ++k) x[i][k] += pv[k];
       }
     }
-    if (emb.rope_table && tid < (emb.dh >> 1))
-      reinterpret_cast<float2*>(emb.rope + (size_t)r * emb.dh)[tid] =
-          reinterpret_cast<const float2*>(emb.rope_table + (size_t)min(pos, emb.max_seq - 1) * emb.dh)[tid];
   }
   if constexpr (SH > 0) {
     const float4* __restrict__ pb4 = reinterpret_cast<const float4*>(pend.bias ? pend.bias : g);
@@ -207,10 +195,12 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
 template <typename AT, int ARCH, int NI>
 static void launch_norm_ni(const float* h, const float* g, const float* b, float eps, int d, const int* n_rows,
                            void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np, const EmbedSource* emb) {
-#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out, np, es)
   EmbedSource es;
   memset(&es, 0, sizeof es);
-  if (emb) { es = *emb; SPRINTER_NORM(-1); }
+  if (emb) es = *emb;
+  const int rope_wgs = es.rope ? (int)(((size_t)max_rows * (es.dh / 2) + 255) / 256) : 0;
+#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows + rope_wgs), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out, np, es, max_rows)
+  if (emb) SPRINTER_NORM(-1);
   else if (np.shares <= 0) SPRINTER_NORM(0);
   else if (np.shares == 1) SPRINTER_NORM(1);
   else if (np.shares <= 4) SPRINTER_NORM(4);

@@ -109,3 +109,25 @@ def test_create_static_rejects_what_does_not_fit(lib):
     assert str(need) in msg and str(limit) in msg
     assert lib.sprinter_create_static(None, None, C.byref(ctx)) == -1
     assert lib.sprinter_create_static(C.byref(c), None, None) == -1
+
+
+@pytest.mark.parametrize("dtype", [W.DT_F32, W.DT_BF16])
+@pytest.mark.parametrize("kind", ["gpt", "llama"])
+def test_workspace_grows_with_max_seq_by_the_caches_alone(lib, kind, dtype):
+    """A longer max_seq costs the KV caches and the token history of its positions and nothing else: 256-byte alignment of the
+    one buffer that is no multiple of it is all the slack there is."""
+    from dataclasses import replace
+    base = W.mini_config(kind, dtype, max_batch=4)
+    base = replace(base, draft=replace(base.draft, max_pos=4096), target=replace(base.target, max_pos=4096))
+    es = 4 if dtype == W.DT_F32 else 2
+    per_pos = 4 * base.max_batch + sum(2 * m.n_layer * base.max_batch * m.n_kv_head * m.d_head * es for m in (base.draft, base.target))
+    short, long = (_ws(lib, replace(base, max_seq=s)) for s in (64, 1024))
+    assert short[0] == 0 and long[0] == 0
+    assert abs((long[1] - short[1]) - (1024 - 64) * per_pos) <= 256
+
+
+def test_long_caches_of_a_small_pair_fit_the_static_workspace(lib):
+    """60000 positions of a one-layer pair with one KV head of 64 columns: 2 x 15 MB of caches."""
+    m = W.ModelCfg(W.ARCH_LLAMA, 1, 256, 4, 1, 512, 1000, 60000, 1e-5, 10000.0)
+    rc, need, _ = _ws(lib, W.SprinterCfg(m, m, 32, W.DT_BF16, 1, 60000, chunk_rows=64))
+    assert rc == 0 and need <= 40 << 20
