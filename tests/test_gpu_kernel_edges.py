@@ -114,3 +114,40 @@ def test_keys_shared_by_several_workgroups(B):
     draft = W.ModelCfg(W.ARCH_LLAMA, 1, 256, 4, 4, 136, 83, 1700, 1e-5, 10000.0)
     target = W.ModelCfg(W.ARCH_LLAMA, 1, 1024, 8, 8 if B == 3 else 4, 136, 83, 1700, 1e-5, 10000.0)
     _check(draft, target, B, W.DT_BF16, prompt_len=1630, prompt_len_min=810, tau=1.5, n_gen=3, max_seq=1664, whole_prompt=True)
+
+
+@pytest.mark.parametrize("group", [1, 4])
+def test_non_finite_token_leaves_earlier_window_entries_alone(group):
+    """A drafted token whose target embedding is not a number spoils the target's view of the positions from its own on, and
+    nothing before: up to that point the round (coins, residual draws) is that of a target with a finite embedding, although
+    earlier entries of the window share one pass over the row's keys and values with the later ones."""
+    from dataclasses import replace
+    from parity_util import Pair
+    X, gamma, B = 3, 4, 40
+    draft = _llama(1, 128, 2, 2, 136, 11)
+    target = _llama(2, 512, 4, 4 // group, 136, 11)
+    cfg = W.SprinterCfg(draft, target, 24, W.DT_BF16, B, 48, temperature=0.15, seed=51, name="nan", batch=B, prompt_len=30,
+                        prompt_len_min=3, prompt_dist="uniform", weight_seed=551, prompt_seed=651, sd_gamma=gamma)
+    rounds = []
+    for value in (0.0, np.nan):
+        dw, tw, vw = W.make_weights(cfg)
+        tw["tok_emb"][X] = value
+        p = Pair(cfg, weights=(dw, tw, vw))
+        p.prompts[p.prompts == X] = X + 1
+        p.gpu.prefill(p.prompts, p.plen)
+        rounds.append({k: v.cpu().numpy() for k, v in p.gpu.sd_generate(gamma, 1).items()})
+        p.close()
+    clean, nan = rounds
+    assert np.array_equal(clean["draft"], nan["draft"])
+    decided_before = 0
+    for b in range(B):
+        at = np.flatnonzero(clean["draft"][b, 0] == X)
+        first = int(at[0]) if len(at) else gamma               # entries 0 .. first of the window have not seen X
+        n = int(clean["n_acc"][b, 0])
+        if n <= first:
+            assert int(nan["n_acc"][b, 0]) == n and np.array_equal(nan["tok"][b], clean["tok"][b]), (b, first, n)
+            decided_before += first < gamma
+        else:
+            assert int(nan["n_acc"][b, 0]) > first
+    print(group, "rows with X in the window that were decided before it:", decided_before, flush=True)
+    assert decided_before >= 2
