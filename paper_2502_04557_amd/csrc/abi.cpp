@@ -780,6 +780,11 @@ int sprinter_prefill(sprinter_ctx* ctx, const int32_t* dev_prompt, const int32_t
     std::vector<int> off((size_t)B + 1, 0);
     for (int b = 0; b < B; ++b) off[b + 1] = off[b] + host_prompt_len[b] - 1;
     const long long E = off[B];
+    // Runs of a few positions go through the attention of short runs: the kernel for long ones takes 16 or 32 entries a wave, so it
+    // walks through that many runs one after the other.  Whole prefill of a pair of two layers each, 12 heads of 64 and 32 of 128,
+    // short-run / long-run attention: 16 rows x 3 positions 310 / 466 us, 128 rows x 1 422 / 863, x 3 635 / 728, x 5 756 / 770,
+    // x 8 968 / 887; 512 rows x 1 867 / 1120, x 2 1232 / 1155, x 5 2203 / 1993.
+    const bool long_runs = E >= 8LL * B || (E > 768 && E >= 2LL * B);
     if (hipMemcpyAsync(ctx->ent_off, off.data(), ((size_t)B + 1) * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)                  // (off is a local: the copy must be over before it goes)
       return fail(ctx, SPRINTER_E_HIP, "copy of the prefill work list failed");
@@ -793,8 +798,8 @@ int sprinter_prefill(sprinter_ctx* ctx, const int32_t* dev_prompt, const int32_t
       const int n = (int)std::min<long long>(ctx->rows_alloc, E - start);
       ca.start = (int)start; ca.n = n;
       launch_catchup_chunk(ca, s);
-      forward(ctx, dq, tp.rd(), n, false, 0u, nullptr, true, true);
-      forward(ctx, tp, tp.rd(), n, false, 1u, nullptr, true, true);
+      forward(ctx, dq, tp.rd(), n, false, 0u, nullptr, true, long_runs);
+      forward(ctx, tp, tp.rd(), n, false, 1u, nullptr, true, long_runs);
       // bound the number of launches in flight (tools that keep per-dispatch state have died on long backlogs)
       if ((chunk & 3) == 3 && hipStreamSynchronize(s) != hipSuccess) return fail(ctx, SPRINTER_E_HIP, "stream synchronisation failed");
     }

@@ -151,3 +151,12 @@ def test_non_finite_token_leaves_earlier_window_entries_alone(group):
             assert int(nan["n_acc"][b, 0]) > first
     print(group, "rows with X in the window that were decided before it:", decided_before, flush=True)
     assert decided_before >= 2
+
+
+@pytest.mark.parametrize("B, lo, hi", [(300, 1, 4), (16, 6, 9), (96, 9, 9), (1, 2, 2)])
+def test_prefill_of_short_prompts(B, lo, hi):
+    """Few cached positions per row, which the attention of short runs takes (up to 7 in the mean, or below 2 in large batches), and
+    8 of them, which is the first mean the kernel for long runs gets; rows without any among them."""
+    draft = W.ModelCfg(W.ARCH_LLAMA, 2, 256, 4, 2, 136, 83, 48, 1e-5, 10000.0)
+    target = _llama(2, 512, 4, 1, 136, 83)
+    _check(draft, target, B, W.DT_BF16, prompt_len=hi, prompt_len_min=lo, tau=1.5, n_gen=2, whole_prompt=True, seed=61)
