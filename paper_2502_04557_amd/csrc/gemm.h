@@ -25,7 +25,9 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int
 }
 
 // The kernel for 17 and more rows (k_gemm_tile.hip): whether a shape takes it, and its launch (returns the K shares of EPI_PART).
-bool gemm_takes_tile(int epi, const GemmArgs& a, int rows);
+// gemm_tile_choice: 16 x tile (0 - 4: 256 x 256, 128 x 128, 64 x 128, 64 x 64, 32 x 64) + K shares; a host function.
+bool gemm_takes_tile(int epi, int N, int rows);
+int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares);
 int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipStream_t s);
 
 }  // namespace sprinter

@@ -442,9 +442,9 @@ static void launch_gemm_f32(const GemmArgs& a, int max_rows, int shares, hipStre
 template <int EPI>
 static void launch_gemm_bf16(const GemmArgs& a, int max_rows, hipStream_t s) {
   // Up to 16 rows: one 16-column tile per workgroup (two per wave for wide outputs), K split over its 8 waves.
-  // (Measured and dropped for that case: folding the layer norm into this kernel - every workgroup
+  // (Measured and dropped for that case: folding the layer norm into this kernel at 16 rows - every workgroup
   // then normalises the whole activation matrix again, 13.6 us against 5.3 + 5.0 us for norm + GEMM at
-  // d = 1600 - and splitting K over workgroups with a last-arriver reduction - its two device-scope fences
+  // d = 1600; up to 4 rows it pays: k_gemm_norm.hip - and splitting K over workgroups with a last-arriver reduction - its two device-scope fences
   // cost more than the 4 us they save; and a variant that requests all of a wave's weight and activation
   // tiles up front (K <= 2048) - no faster.)
   // wide outputs with a short K: two column tiles per wave share the activation fragments (at K = 4096 one tile per
@@ -452,12 +452,14 @@ static void launch_gemm_bf16(const GemmArgs& a, int max_rows, hipStream_t s) {
   if (max_rows <= 16 && a.n_tiles >= 256 && a.Kt < 100)
     hipLaunchKernelGGL((k_gemm16<2, EPI>), dim3((a.n_tiles + 1) / 2), dim3(512), 0, s, a);
   else if (max_rows <= 16) hipLaunchKernelGGL((k_gemm16<1, EPI>), dim3(a.n_tiles), dim3(512), 0, s, a);
-  else if (gemm_takes_tile(EPI, a, max_rows)) launch_gemm_tile(EPI, a, max_rows, 1, s);
+  else if (gemm_takes_tile(EPI, a.N, max_rows)) launch_gemm_tile(EPI, a, max_rows, 1, s);
   else {
-    // 17 .. 64 rows; column tiles per wave that share the activation fragments: as many as leave about 192 workgroups
+    // 17 .. 64 rows.  Two column tiles per wave, which share the activation fragments, where one would need a second round of
+    // workgroups (one per compute unit): 4352 x 4096 (272 tiles) at 20 / 40 / 64 rows 15.8 / 19.1 / 23.3 us with one, 12.6 / 14.9 /
+    // 17.6 with two; 4096 x 4096 (256) 10.0 / 12.1 / 14.5 and 12.6 / 14.9 / 17.5.
     constexpr bool DUAL = EPI == EPI_SWIGLU;
 #define SPRINTER_ROWS(MT_, NTW_) hipLaunchKernelGGL((k_gemm_rows<MT_, NTW_, EPI>), grid, dim3(512), 0, s, a)
-    const int mt = (max_rows + 15) / 16, ntw = !DUAL && a.n_tiles >= 256 ? 2 : 1;
+    const int mt = (max_rows + 15) / 16, ntw = !DUAL && a.n_tiles > 256 ? 2 : 1;
     const dim3 grid((a.n_tiles + ntw - 1) / ntw);
     if constexpr (!DUAL) {
       if (ntw == 2) { if (mt == 2) SPRINTER_ROWS(2, 2); else if (mt == 3) SPRINTER_ROWS(3, 2); else SPRINTER_ROWS(4, 2); }

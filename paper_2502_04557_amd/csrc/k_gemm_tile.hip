@@ -195,19 +195,25 @@ static void launch_tile(const GemmArgs& a, int rows, int sk, hipStream_t s) {
   hipLaunchKernelGGL((k_gemm_tile<T, EPI>), dim3(gm * gn, sk), dim3(T::waves * 64), 0, s, a, x_tiles, gm, gn);
 }
 
-template <int EPI>
-static int launch_tile_epi(const GemmArgs& a, int rows, int max_shares, hipStream_t s) {
+int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares) {
   static const TileCost cost[5] = {{256, 256, 1, 8.0f, 1355.f, 0.f, 1.22f}, {128, 128, 2, 5.4f, 608.f, 465.f, 1.10f},
                                    {64, 128, 2, 4.2f, 478.f, 200.f, 0.83f}, {64, 64, 2, 3.7f, 327.f, 517.f, 0.64f},
                                    {32, 64, 3, 3.4f, 290.f, 293.f, 1.23f}};
+  const int Kt = (K + 31) / 32;
   int best = 0, sk = 1;
   float best_us = 1e30f;
   for (int i = 0; i < 5; ++i)
-    for (int k = 1; k <= max_shares && (k == 1 || a.Kt / k >= 3); ++k) {
-      const float us = tile_us(cost[i], EPI, rows, a.N, a.Kt, k);
+    for (int k = 1; k <= max_shares && (k == 1 || Kt / k >= 3); ++k) {
+      const float us = tile_us(cost[i], epi, rows, N, Kt, k);
       if (us < best_us) { best_us = us; best = i; sk = k; }
     }
-  switch (best) {
+  return best * 16 + sk;
+}
+
+template <int EPI>
+static int launch_tile_epi(const GemmArgs& a, int rows, int max_shares, hipStream_t s) {
+  const int choice = gemm_tile_choice(EPI, rows, a.N, a.K, max_shares), sk = choice % 16;
+  switch (choice / 16) {
     case 0: launch_tile<TileL, EPI>(a, rows, sk, s); break;
     case 1: launch_tile<TileM, EPI>(a, rows, sk, s); break;
     case 2: launch_tile<TileS, EPI>(a, rows, sk, s); break;
@@ -217,15 +223,17 @@ static int launch_tile_epi(const GemmArgs& a, int rows, int max_shares, hipStrea
   return sk;
 }
 
-// 17 - 64 rows of an output that cannot be left in K shares: under 160 workgroups of the narrowest tile the K-split kernel of
-// k_gemm.hip, whose 8 waves share a column tile, is ahead (6144 x 4096 at 20 / 40 / 64 rows, 96 workgroups: 13.9 / 17.9 / 20.4
-// against 18.9 / 21.2 / 21.1 us; 6400 x 1600, 100: 9.7 against 12.0 at 20); with 192 and more this one is (12288 x 4096: 26.2 /
-// 27.1 / 31.3 against 23.2 / 28.4 / 28.8; 2 x 8192 x 2048: 18.6 against 15.2 at 64).  Partial products are ahead at any size:
+// 17 - 64 rows of an output that cannot be left in K shares: the K-split kernel of k_gemm.hip, whose 8 waves share a column tile
+// (a pair of them), runs one workgroup per compute unit, so its time jumps where its 256 are exceeded - at 128 workgroups of this
+// kernel's narrowest tile.  Up to there it is ahead at K from about 1000 on (8192 x 4096 at 20 / 40 / 64 rows 15.5 / 17.4 / 19.5
+// against 19.3 / 19.3 / 19.5 us; 8192 x 1600 8.7 / 10.1 / 10.7 against 10.6; 2 x 4096 x 4096 14.7 / 16.4 / 19.0 against 19.5); from
+// 132 on this one is, at any K (8448 x 4096 22.2 / 25.6 / 31.6 against 19.4 / 22.5 / 22.7; 8448 x 512 7.1 / 8.6 / 8.1 against 4.8 /
+// 5.4 / 5.6; 2 x 4224 x 2048 12.7 / 15.0 / 17.7 against 11.3 / 12.4 / 12.5).  Partial products are ahead at any size:
 // 4096 x 4096 12.2 -> 8.8 at 20 rows, 1600 x 6400 9.7 -> 6.9, 4096 x 14336 33.9 -> 24.7 at 64; and so is everything from 65 rows
 // on, where that kernel takes two passes (4800 x 1600 at 80 rows 12.2 -> 9.0, 2 x 3072 x 768 9.1 -> 6.8; 12288 x 4096 36.9 / 37.4).
-bool gemm_takes_tile(int epi, const GemmArgs& a, int rows) {
+bool gemm_takes_tile(int epi, int N, int rows) {
   const int cols = epi == EPI_SWIGLU ? 32 : 64;
-  return rows > 64 || (rows > 16 && (epi == EPI_PART || (a.N + cols - 1) / cols >= 160));
+  return rows > 64 || (rows > 16 && (epi == EPI_PART || (N + cols - 1) / cols > 128));
 }
 
 int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipStream_t s) {

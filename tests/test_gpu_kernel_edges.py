@@ -61,10 +61,10 @@ def test_norm_inside_the_product(B, dtype):
 
 @pytest.mark.parametrize("B, prompt_len", [(7, 20), (9, 59), (8, 114)])
 def test_tiles_of_many_rows(B, prompt_len):
-    """Prefill passes of 133, 522 and 904 rows (none a multiple of a tile): the 64-row tile with K shares, the 128-row tile and
-    the 256-row tile (FFN-up of the target at 522 and 904 rows), a last k tile that is a quarter and a whole one too many for
-    pairs of k tiles (FFN-down, K = 3080 and 5128), column tiles beyond the last one, GELU and SwiGLU.  The prefilled caches
-    carry every position, so the first steps' logits depend on all of them."""
+    """Prefill passes of 133, 522 and 904 rows (none a multiple of a tile): the 32- and 64-row tiles with K shares, at 904 rows also the
+    256-row tile (FFN-up of the target) and the 128-row tile (its FFN-down); a last k tile that is a quarter full and an odd number of
+    k tiles (FFN-down, K = 3080 and 5128), column tiles beyond the last one, GELU and SwiGLU.  The prefilled caches carry every
+    position, so the first steps' logits depend on all of them.  (Every tile: test_every_tile_with_every_epilogue.)"""
     draft = W.ModelCfg(W.ARCH_GPT, 2, 768, 12, 12, 3080, 331, 128)
     target = W.ModelCfg(W.ARCH_LLAMA, 2, 1024, 16, 16, 5128, 331, 128, 1e-5, 10000.0)
     _check(draft, target, B, W.DT_BF16, prompt_len=prompt_len, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=128, whole_prompt=True)
@@ -160,3 +160,66 @@ def test_prefill_of_short_prompts(B, lo, hi):
     draft = W.ModelCfg(W.ARCH_LLAMA, 2, 256, 4, 2, 136, 83, 48, 1e-5, 10000.0)
     target = _llama(2, 512, 4, 1, 136, 83)
     _check(draft, target, B, W.DT_BF16, prompt_len=hi, prompt_len_min=lo, tau=1.5, n_gen=2, whole_prompt=True, seed=61)
+
+
+EPI_F32, EPI_GELU, EPI_SWIGLU, EPI_PART = 0, 2, 3, 4
+
+
+def _host(name, *args):
+    """An internal host function of the library (a launcher's rule), by its mangled name."""
+    from paper_2502_04557_amd import binding
+    return binding.load_library()[name](*args)
+
+
+def _takes_tile(epi, N, rows):
+    return bool(_host("_ZN8sprinter15gemm_takes_tileEiii", epi, N, rows) & 1)
+
+
+def _tiles(m, rows):
+    """What the launcher picks for the four products of a layer at `rows` rows: the tile (0: 256 x 256, 1: 128 x 128, 2: 64 x 128, 3: 64 x 64,
+    4: 32 x 64) and, of partial products, the K shares.  A few rows of a fused pass are not meant."""
+    up = EPI_GELU if m.arch == W.ARCH_GPT else EPI_SWIGLU
+    pick = lambda *a: divmod(_host("_ZN8sprinter16gemm_tile_choiceEiiiii", *a), 16)
+    return dict(qkv=pick(EPI_F32, rows, m.d_qkv, m.d_model, 1)[0], o=pick(EPI_PART, rows, m.d_model, m.d_model, 8),
+                up=pick(up, rows, m.d_ff, m.d_model, 1)[0], down=pick(EPI_PART, rows, m.d_model, m.d_ff, 8))
+
+
+def _g(d, ff):
+    return W.ModelCfg(W.ARCH_GPT, 2, d, d // 64, d // 64, ff, 83, 320)
+
+
+def _l(dh, H, KVH, ff):
+    return W.ModelCfg(W.ARCH_LLAMA, 2, dh * H, H, KVH, ff, 83, 320, 1e-5, 10000.0)
+
+
+@pytest.mark.parametrize("B, P, draft, target, draft_tiles, target_tiles", [
+    (8, 258, _g(256, 712), _l(128, 16, 8, 72), dict(qkv=2, o=(3, 1), up=2, down=(2, 3)), dict(qkv=0, o=(0, 2), up=4, down=(3, 1))),
+    (8, 258, _g(192, 8200), _l(64, 8, 1, 136), dict(qkv=2, o=(4, 1), up=1, down=(1, 7)), dict(qkv=2, o=(2, 1), up=3, down=(2, 1))),
+    (8, 162, _g(128, 264), _l(128, 16, 2, 72), dict(up=4), dict(qkv=1, o=(1, 1))),
+    (3, 258, _g(768, 3080), _l(64, 12, 12, 5128), dict(), dict(o=(2, 3), up=0, down=(2, 6))),
+    (7, 148, _l(64, 8, 4, 72), _g(768, 8200), dict(), dict(qkv=2, o=(3, 1), up=0, down=(1, 4))),
+    (9, 59, _g(128, 136), _l(64, 8, 4, 72), dict(), dict(qkv=3, o=(3, 3), up=4, down=(4, 1))),
+    (6, 12, _l(64, 2, 1, 8200), _l(128, 12, 12, 8200), dict(up=2, down=(4, 8)), dict(up=1, o=(4, 3), down=(3, 5))),
+    (5, 8, _g(128, 8200), _l(64, 2, 2, 136), dict(up=3, down=(4, 8)), dict()),
+])
+def test_every_tile_with_every_epilogue(B, P, draft, target, draft_tiles, target_tiles):
+    """Prefill passes of 35 - 2056 rows that are picked for each of the five tiles with each epilogue (float32, GELU, gate + up, partial
+    products in one and in several shares), a few rows beyond a tile's multiple, with odd and even numbers of k tiles, a last one that is
+    not full, and column tiles beyond the last one."""
+    rows = B * (P - 1)
+    for m, want in ((draft, draft_tiles), (target, target_tiles)):
+        got = _tiles(m, rows)
+        assert want == {k: got[k] for k in want}, got
+        if rows <= 64 and "up" in want:
+            assert _takes_tile(EPI_GELU if m.arch == W.ARCH_GPT else EPI_SWIGLU, m.d_ff, rows)
+    _check(draft, target, B, W.DT_BF16, prompt_len=P, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=-(-(P + 4) // 32) * 32, whole_prompt=True, seed=71)
+
+
+@pytest.mark.parametrize("B", [17, 33, 64])
+@pytest.mark.parametrize("gelu, gate_up", [(4096, 4096), (4104, 4104), (8192, 72), (8200, 72)])
+def test_either_side_of_the_wide_product_rules(B, gelu, gate_up):
+    """17 - 64 rows, 2 - 4 row tiles: FFN-up on the K-split kernel with one column tile per wave (256 tiles) and with two (257 and 512), and
+    just beyond on the LDS tiles; gate + up likewise (256 and 257 tiles)."""
+    assert [_takes_tile(EPI_GELU, n, B) for n in (4096, 4104, 8192, 8200)] == [False, False, False, True]
+    assert [_takes_tile(EPI_SWIGLU, n, B) for n in (4096, 4104)] == [False, True]
+    _check(_gpt(1, 128, gelu, 83), _llama(1, 192, 3, 3, gate_up, 83), B, W.DT_BF16, tau=1.5, prompt_len=3, n_gen=2, seed=81)
