@@ -219,7 +219,8 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
   sc.hf = (float*)bump.take((size_t)rows * md.d * 4);
   sc.hfn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.rope = (float*)bump.take((size_t)rows * md.dh * 4);
-  sc.part = (float*)bump.take((size_t)PART_SHARES * rows * md.d * 4);
+  // also the scratch of a split attention, which is the smaller one: bf16 buffers hold 64 rows or more, 512 d >= 256 (H / KVH) (dh + 2)
+  sc.part = (float*)bump.take(std::max((size_t)PART_SHARES * rows * md.d, bf ? attn_split_floats(md) : 0) * 4);
   sc.n_lm_wg = lmhead_num_wg(c.dtype, md.V);
   sc.am_part = (unsigned long long*)bump.take((size_t)sc.n_lm_wg * rows * 8);
   int* rd_n = (int*)bump.take(4);

@@ -97,9 +97,15 @@ void launch_attention(int dtype, const ModelDims& md, const float* y, const floa
                       void* kcache, void* vcache, size_t layer_off, int ctx_bound /* upper bound of the rows' cache lengths */,
                       int max_seq /* slots per (row, KV head) of the caches; bf16: a multiple of 32 */,
                       void* ao, int max_rows, float* split, hipStream_t s, int phase = 0);
-// split: scratch, the partial products' buffer (free between a layer's first norm and its O-projection; its PART_SHARES x rows x d
-// floats hold the at most 256 / KVH x H / KVH x (dh + 2) of a split launch); phase 0: append the row's new key / value to the cache and attend (rows of one launch own different caches);
+// split: scratch of attn_split_floats (bf16), the partial products' buffer, which is free between a layer's first norm and its
+// O-projection.  phase 0: append the row's new key / value to the cache and attend (rows of one launch own different caches);
 // phase 1: append only; phase 2: attend only (the pair serves launches where several rows share a cache).
+
+// Workgroups that share a row's keys in the decode attention of bf16 mode (1: one per row and KV head); a host function.
+constexpr int SPLIT_WGS = 256;   // rows x KV heads x workgroups per row and KV head stay within it
+int attn_split(int dh, int kvh, int rows, int ctx_bound);
+// Partial results of a split launch: [row][KV head][workgroup][H / KVH][dh + 2].
+inline size_t attn_split_floats(const ModelDims& md) { return (size_t)SPLIT_WGS * (md.H / md.KVH) * (md.dh + 2); }
 
 // The verifier's hidden layer over the rows of the draft pass; part[chunk][row] receives each chunk's share of the logit.
 struct VerifierArgs {

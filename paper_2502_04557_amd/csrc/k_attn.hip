@@ -901,6 +901,17 @@ static size_t attn_smem_bytes(int DH, int G, int max_seq) {
   return (size_t)(G * DH + 2 * DH + 4 * G * DH + G * max_seq) * sizeof(float);
 }
 
+// A compute unit pulls at most 48 KB/us, so one workgroup needs 21 us for 2000 keys of 128 columns: few rows with long contexts
+// share the keys over as many workgroups as the compute units allow, at the price of a merge launch.  Both launches together, one
+// workgroup / split, 8 KV heads of 128 columns: 4 rows (split 8) at 1024 keys 19.0 / 13.2 us, 2016 29.9 / 14.6; 16 rows (2) at 1024
+// 22.9 / 21.7, 2016 36.7 / 32.5; of 64 columns: 4 rows at 1536 13.7 / 9.7, 2016 16.5 / 10.3; 16 rows at 1536 16.5 / 16.4, 2016 19.7 /
+// 18.9.  The line is where a split in two breaks even (16 rows, 128 columns: 768 keys 19.3 / 20.4; a launch works in steps of 256
+// keys a workgroup, and from 769 on it is four against two); a split in 8 is ahead from about 256 KB on.
+int attn_split(int dh, int kvh, int rows, int ctx_bound) {
+  if ((long long)kvh * rows > SPLIT_WGS / 2 || ctx_bound < 512 || (size_t)ctx_bound * dh * 4 < 400 * 1024) return 1;
+  return std::min(8, SPLIT_WGS / (kvh * rows));
+}
+
 template <int DH>
 static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bound, hipStream_t s) {
   if (a.phase == 1) {          // append only
@@ -921,11 +932,8 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
     else hipLaunchKernelGGL((k_attn_runs_bf16<DH, 4>), grid, dim3(256), 0, s, a);
     return;
   }
-  // A compute unit pulls at most 48 KB/us, so one workgroup needs 21 us for 2000 keys of 128 columns: few rows with long
-  // contexts share the keys over several workgroups, at the price of a merge launch (3 rows x 8 KV heads, 1500 - 2000 keys of
-  // 128 columns: 29.6 -> 10.3 + 4.6 us; 4 rows, 64 columns: 16.6 -> 7.5 + 3.3).  400 KB a workgroup are where the two meet.
-  const int split = std::min(8, 256 / (a.KVH * max_rows));
-  if (wide && split > 1 && (size_t)ctx_bound * DH * 4 >= 400 * 1024) {
+  const int split = attn_split(DH, a.KVH, max_rows, ctx_bound);
+  if (split > 1) {
     grid.z = split;
     hipLaunchKernelGGL((k_attn_dec_bf16<DH, 8>), grid, dim3(512), 0, s, a);
     hipLaunchKernelGGL((k_attn_merge<DH>), dim3(a.H, max_rows), dim3(DH), 0, s, a, split);

@@ -109,8 +109,8 @@ def test_short_runs_share_a_pass(group):
 
 @pytest.mark.parametrize("B", [1, 3])
 def test_keys_shared_by_several_workgroups(B):
-    """Few rows with contexts long enough that several workgroups share a row's keys: 8 and 4 of them, one or two query heads per
-    KV head, head dimension 128 (from 800 positions) and 64 (from 1600), the new key in the last block of another workgroup's."""
+    """Few rows with contexts long enough that 8 workgroups share a row's keys, in one step each: one or two query heads per KV
+    head, head dimension 128 (from 800 positions) and 64 (from 1600), the new key in the last block of another workgroup's."""
     draft = W.ModelCfg(W.ARCH_LLAMA, 1, 256, 4, 4, 136, 83, 1700, 1e-5, 10000.0)
     target = W.ModelCfg(W.ARCH_LLAMA, 1, 1024, 8, 8 if B == 3 else 4, 136, 83, 1700, 1e-5, 10000.0)
     _check(draft, target, B, W.DT_BF16, prompt_len=1630, prompt_len_min=810, tau=1.5, n_gen=3, max_seq=1664, whole_prompt=True)
@@ -223,3 +223,18 @@ def test_either_side_of_the_wide_product_rules(B, gelu, gate_up):
     assert [_takes_tile(EPI_GELU, n, B) for n in (4096, 4104, 8192, 8200)] == [False, False, False, True]
     assert [_takes_tile(EPI_SWIGLU, n, B) for n in (4096, 4104)] == [False, True]
     _check(_gpt(1, 128, gelu, 83), _llama(1, 192, 3, 3, gate_up, 83), B, W.DT_BF16, tau=1.5, prompt_len=3, n_gen=2, seed=81)
+
+
+@pytest.mark.parametrize("H, KVH, B, longest, split", [(8, 8, 16, 1100, 2), (8, 8, 10, 1300, 3), (8, 4, 16, 1150, 4), (8, 8, 6, 1400, 5),
+                                                       (16, 2, 21, 1600, 6), (8, 4, 9, 1850, 7), (8, 1, 3, 2100, 8)])
+def test_keys_shared_in_several_steps(H, KVH, B, longest, split):
+    """Every split of a row's keys over 2 - 8 workgroups, the longest rows in more than one step per workgroup; 1 - 8 query heads per KV
+    head; shorter rows leave some workgroups without keys."""
+    dh = 64 if split == 6 else 128
+    for ctx in (longest, longest + 2):
+        assert _host("_ZN8sprinter10attn_splitEiiii", dh, KVH, B, ctx) == split
+    assert longest > 256 * split                             # (8 waves of 32 keys per workgroup and step)
+    draft = W.ModelCfg(W.ARCH_LLAMA, 1, 128, 2, 2, 72, 83, 2200, 1e-5, 10000.0)
+    target = W.ModelCfg(W.ARCH_LLAMA, 1, dh * H, H, KVH, 72, 83, 2200, 1e-5, 10000.0)
+    _check(draft, target, B, W.DT_BF16, prompt_len=longest, prompt_len_min=40, tau=1.5, n_gen=2, max_seq=-(-(longest + 4) // 32) * 32,
+           whole_prompt=True, seed=90 + split)
