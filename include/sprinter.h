@@ -222,8 +222,8 @@ int sprinter_load_weights(sprinter_ctx* ctx, int which, const char* const* names
  * prompt token at position P_b-1.  All (row, position) pairs go through both
  * models in row-major chunks of cfg.chunk_rows tokens per pass over the weights
  * (bf16: matrix-core GEMMs over the whole chunk and causal matrix-core attention
- * over each row's run of positions; float32: the vector kernels, 16 tokens per
- * pass by default).  The
+ * over each row's run of positions; float32: the float32 matrix-core GEMMs and
+ * one attention workgroup per token and KV head, 16 tokens per pass by default).  The
  * stream is drained every 4 passes.  dev_prompt is [B, max_prompt] int32 (padding
  * is never read), host_prompt_len[B] has 1 <= P_b <= max_prompt.  Errors:
  * B > max_batch, P_b out of range, max_prompt > max_seq (or > max_pos), weights

@@ -365,7 +365,7 @@ size_t carve(const sprinter_cfg& c, void* base, sprinter_ctx* ctx, size_t* scrat
 // One model forward over the rows described by rd (device-side count).
 // shared_caches: several rows of rd may belong to one batch row (consecutive positions): every layer appends all
 // new keys / values first and attends in a second launch.  long_runs: those entries come in long runs of
-// consecutive positions (prefill), so the attending launch lets 8 queries share one pass over the row's cache.
+// consecutive positions (prefill), so the attending launch lets up to 32 of them share one pass over the row's cache.
 // ver: the verifier's work, done by the LM head's launch.
 void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool want_head, unsigned stream_id,
              float* logits_out, bool shared_caches = false, bool long_runs = false, const VerifierArgs* ver = nullptr) {

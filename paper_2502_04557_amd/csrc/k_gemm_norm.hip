@@ -12,9 +12,11 @@ namespace sprinter {
 // them in the order of k_norm, takes the statistics in two passes, and leaves the normalised rows in LDS, from where the
 // matrix instructions take them.  Workgroup 0 also writes the updated residual rows - to the other of two buffers, since its
 // neighbours are still reading this one.  What it costs is R d (1 + shares) floats per workgroup through L2 next to its own
-// weights, so it is taken only while that stays small (gemm_takes_norm): norm + product as two launches against one, at 1 / 2 / 4 rows
-// and 4 shares: d = 1600, N = 4800: 9.0 / 9.1 / 9.1 -> 6.4 / 7.2 / 8.8 us; N = 6400: 9.5 -> 7.2 / 8.0 / 9.5; d = 2048 (RMS),
-// N = 3072: 8.0 -> 5.4 / 6.0 / 7.4; N = 2 x 8192: 17.3 -> 14.6 / 15.1 / 16.4; at 8 rows 2 - 3 us slower than two launches.
+// weights, so it is taken only while that stays small (gemm_takes_norm).  In a chain - partial product, norm, product - as three
+// launches against two, at 1 / 2 / 3 / 4 rows, us: d = 1600, FFN-down in 4 shares, QKV 4800: 14.9 -> 13.1 / 13.4 / 14.2 / 15.1; O-proj
+// in 2, FFN-up 6400: 12.7 -> 10.7 / 11.4 / 12.0 / 12.7; d = 2048 (RMS), 4 shares, QKV 3072: 16.1 -> 13.5 / 14.2 / 14.9 / 15.5; 2 shares,
+// 2 x 8192: 20.7 -> 18.5 / 19.1 / 19.3 / 19.8; d = 768, 4 shares, QKV 2304: 12.0 -> 7.7 / 8.3 / 9.1 / 9.7; d = 512, 3 shares, 1024:
+// 11.6 -> 8.0 / 7.5 / 7.6 / 8.1.  Fewer shares cost the partial product more than they save here (1600, 4 rows: 15.1 with 4, 16.2 with 2).
 // R rows; thread t takes float4 t of every row (d <= 2048), so gain, offset and bias are fetched once.
 template <typename AT, int R, int NTW, int EPI>
 __global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
@@ -182,8 +184,8 @@ __global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
   gemm_epilogue<EPI, AT>(a, a.rows_live, m, n, s1, sg, pbias);
 }
 
-// The line: a row costs about 0.75 us of a 1600-wide launch, and a launch saves 3.3 - 3.5 us less the 1 us the prologue takes
-// at any row count.  Wider rows (4096: 896 workgroups for FFN-up) lose already at one: 45.6 -> 48.4 us.
+// The line: one row saves about 2 us of a 1600-wide chain and each further one gives 0.6 - 0.7 back, so the fourth breaks even there;
+// narrower chains are still ahead with four.  At 8 rows the fused launch was 2 - 3 us slower at 1600 and 2048.  Wider rows (4096: 896 workgroups for FFN-up) lose already at one: 45.6 -> 48.4 us.
 bool gemm_takes_norm(int d, int rows) { return rows <= 4 && d <= 2048; }
 
 template <typename AT, int NTW, int EPI>
