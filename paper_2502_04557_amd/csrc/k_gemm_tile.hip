@@ -16,9 +16,9 @@ namespace sprinter {
 // The weight fragment is the first operand, so that the accumulator holds four consecutive COLUMNS of one row per lane:
 // the epilogue stores 16 bytes of float32 or 8 bytes of an activation operand tile at a time.
 // What bounds it (4096 rows, 256 x 256 tile): 1247 cycles per k tile, of which the matrix instructions are 1024 and the
-// LDS (96 KiB of fragment reads and 32 KiB of arriving loads at 128 B a cycle) as many; the clock falls to 1.75 GHz under
-// that load.  FFN-up 2 x 14336 x 4096: 856 -> 720 us (1.34 PFLOP/s), FFN-down 4096 x 11008: 327 -> 275, QKV 12288 x 4096:
-// 458 -> 350, against one that shared only the activations through LDS and waited for all its loads at every barrier.
+// LDS (96 KiB of fragment reads and 32 KiB of arriving loads at 128 B a cycle) as many; the clock falls to 1.75 GHz in
+// a loop of this launch and to 1.9 - 2.0 in a whole prefill, where it issues 1.3 PFLOP/s.  FFN-up 2 x 14336 x 4096: 856 -> 720 us
+// (1.34 PFLOP/s), FFN-down 4096 x 11008: 327 -> 275, QKV 12288 x 4096: 458 -> 350, against one that shared only the activations through LDS and waited for all its loads at every barrier.
 // Also measured: 32 x 32 x 16 instructions (8 - 20 % slower), a fifth stage (no faster), 4 waves of 128 x 128 (the compiler
 // moves accumulators between register files: 1.5 times slower).
 template <int WM, int WN, int MT, int NT, int S>

@@ -342,10 +342,9 @@ def test_large_vocabulary_many_rows():
 @pytest.mark.parametrize("chunk_rows", [0, 256])
 def test_prefill_matrix_core_kernels_mid_size(chunk_rows):
     """A prompt set large enough (9 ragged prompts, about 600 tokens) and models wide enough that prefill takes the
-    column-split GEMM for 128+ rows (FFN-up with 225 column tiles and a half-filled last k tile, the partial-output
-    GEMMs with K shares; the narrow QKV falls back to the K-split kernel) and the causal matrix-core attention at
-    head dimension 64 (draft, 2 query heads per KV head) and 128 (target, 4 per KV head), with row counts that are not
-    multiples of the 128-row groups or the 16-entry attention blocks; once in a single pass and once in passes of 256
+    LDS-tile GEMMs (FFN-up with 225 column tiles and a half-filled last k tile, the partial-output GEMMs with K shares) and
+    the causal matrix-core attention at head dimension 64 (draft, 2 query heads per KV head) and 128 (target, 4 per KV head),
+    with row counts that are not multiples of the tiles' rows or the 16-entry attention blocks; once in a single pass and once in passes of 256
     entries (runs split over pass borders).  The caches feed every later step: 6 steps replayed by the oracle."""
     from parity_util import compare_replay, close_enough, eps_of
     draft = W.ModelCfg(W.ARCH_LLAMA, 2, 512, 8, 4, 1408, 2003, 128, 1e-5, 10000.0)
@@ -375,9 +374,8 @@ def test_prefill_matrix_core_kernels_mid_size(chunk_rows):
 
 
 def test_hundred_target_rows_column_split_partial_products():
-    """100 rows, all rejected (threshold above 1), through a target wide enough (d 2048, FFN 8192) that the partial-product
-    GEMMs of 97 - 127 rows take the column-split kernel with a single, partly filled 128-row group (FFN-down: 16 column
-    groups x 8 K shares), while QKV and FFN-up stay on the K-split kernels (two passes of 4 and 3 row tiles).  Target
+    """100 rows, all rejected (threshold above 1), through a wide target (d 2048, FFN 8192): every product on LDS tiles whose
+    last row group is partly filled, O-proj and FFN-down in K shares.  Target
     logits and hidden states of every row against the oracle, two steps."""
     from parity_util import compare_replay, close_enough, eps_of
     draft = W.ModelCfg(W.ARCH_LLAMA, 1, 256, 4, 2, 512, 1201, 64, 1e-5, 10000.0)
@@ -405,7 +403,7 @@ def test_hundred_target_rows_column_split_partial_products():
 @pytest.mark.parametrize("ctx", [0, 1])
 def test_long_context_few_rows(ctx):
     """Contexts of 770-900 keys with 3 rows: the attention launch takes its 8-wave variant (few workgroups, long
-    contexts; draft: head dimension 64, 2 query heads per KV head; target: head dimension 128, 4 per KV head).
+    contexts), the target's with several workgroups per row's keys (draft: head dimension 64, 2 query heads per KV head; target: head dimension 128, 4 per KV head).
     Every row replayed by the oracle; also in full-prefix mode (append-only + attend-only launches)."""
     from parity_util import compare_replay
     G = 6
@@ -430,7 +428,7 @@ def test_long_context_few_rows(ctx):
 @pytest.mark.parametrize("ctx,rej", [(0, 0), (1, 1)])
 def test_maximum_batch(ctx, rej):
     """The largest batch the library accepts (1024 rows; the decide / finish kernels then use all 16 waves of
-    their single workgroup, the GEMMs 16 passes of 64 rows) on the smallest models: compaction against the
+    their single workgroup, the GEMMs many row groups) on the smallest models: compaction against the
     brute-force list for every step, whole-batch rules, and the oracle on the first, the last and 6 seeded rows.
     Second case: the same with the full-prefix target context and the p/q correction."""
     from dataclasses import replace

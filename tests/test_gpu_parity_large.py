@@ -213,7 +213,7 @@ def test_c3_full_size_sampled_rows(llama7b, ctx, rej):
 
 def test_c3_speculative_decoding_sampled_rows(llama7b):
     """Standard speculative decoding (Sec. 2, Eq. (1)) at config 3's size, gamma = 4: the target pass of a round carries
-    32 x 5 = 160 entries (the column-split GEMMs, the LM head over 160 rows, the p/q check at vocabulary 32000), the first
+    32 x 5 = 160 entries (LDS-tile GEMMs, the LM head over 160 rows, the p/q check at vocabulary 32000), the first
     draft pass of a round up to 64.  The oracle replays three rows on the GPU's history; the bookkeeping is checked for all."""
     from oracle import sprinter as osp, sd_baseline as osd
     from parity_util import compare_sd_rounds, sd_rounds_to_lists
