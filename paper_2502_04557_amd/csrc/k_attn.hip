@@ -735,7 +735,7 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
 // waves: wave w takes the 32-key blocks w, w + NW, ..., and the waves' partial results are merged through LDS.  A workgroup
 // whose entry is not the first of its group (the run's first entry, or a position that is a multiple of 16 / G) has nothing to
 // do.  A value that is not finite must not reach earlier entries of its group (0 x NaN is NaN): the blocks with the group's own
-// keys are looked through for one, and then each position takes the values of its own keys alone.  (80 entries in 16 windows of 5, 25 heads of 64, 110 keys: 22.0 us with a pass per entry, 9.9 now; 16 entries of one
+// keys are looked through for one; entries that see it get NaN, the products of the others take zeros.  (80 entries in 16 windows of 5, 25 heads of 64, 110 keys: 22.0 us with a pass per entry, 9.9 now; 16 entries of one
 // each: 8.5 and 5.9.)
 template <int DH, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
@@ -847,28 +847,37 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
       for (int ct = 0; ct < CT; ++ct)
         V[ct] = __builtin_bit_cast(u32x4, vt_fix(__builtin_bit_cast(uint4, V[ct]), kb + lq * 8, max_slot + 1, 0u));
     }
-    bool odd = false;                                            // an infinity or NaN among the values of a block with the group's own keys
-    if (n > 1 && kb + 31 > slot0) {                              // (scalar)
+    unsigned odd = 0;                                            // an infinity or NaN among the values of a block with the group's own keys:
+    if (n > 1 && kb + 31 > slot0) {                              // (scalar) an exponent of all ones carries into the sign's place
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) odd |= (V[ct][e] & 0x7f80u) == 0x7f80u || (V[ct][e] & 0x7f800000u) == 0x7f800000u;
+        for (int e = 0; e < 4; ++e) odd |= (V[ct][e] & 0x7f807f80u) + 0x00800080u;
     }
-    if (__any(odd)) {                                            // (uniform) position by position, later keys' values zeroed
-      for (int i = 0; i < n; ++i) {
+    if (__any((odd & 0x80008000u) != 0)) {                       // (uniform) queries from the first such key on get NaN, the others zeros in its place
+      int first = max_slot + 1;
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const uint4 vf = vt_fix(__builtin_bit_cast(uint4, V[ct]), kb + lq * 8, slot0 + i + 1, 0u);
-          const f32x4 o = mfma_bf16(vf, pl, mfma_bf16(vf, ph, O[ct]));
-          if (slot == slot0 + i) O[ct] = o;
-        }
+      for (int e = 0; e < 8; ++e) {
+        bool bad = false;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) bad |= ((V[ct][e >> 1] >> (16 * (e & 1))) & 0x7f80u) == 0x7f80u;
+        const u64 lanes = __ballot(bad);
+        if (lanes) first = min(first, kb + (__builtin_ctzll(lanes) >> 4) * 8 + e);
+        __builtin_amdgcn_sched_barrier(0);                       // (registers)
       }
-    } else {
+      if (slot >= first) l_run = NAN;
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) O[ct] = mfma_bf16(__builtin_bit_cast(uint4, V[ct]), ph, O[ct]);
+      for (int ct = 0; ct < CT; ++ct) {
+        asm volatile("" : "+v"(V[ct]));                          // (else the test's sums are kept in registers for the next lines)
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) O[ct] = mfma_bf16(__builtin_bit_cast(uint4, V[ct]), pl, O[ct]);
+        for (int e = 0; e < 4; ++e) V[ct][e] &= ~(((((V[ct][e] & 0x7f807f80u) + 0x00800080u) & 0x80008000u) >> 15) * 0xffffu);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) O[ct] = mfma_bf16(__builtin_bit_cast(uint4, V[ct]), ph, O[ct]);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) O[ct] = mfma_bf16(__builtin_bit_cast(uint4, V[ct]), pl, O[ct]);
     __builtin_amdgcn_sched_barrier(0);
     fetch_v(kb + 32 * NW);
     __builtin_amdgcn_sched_barrier(0);
