@@ -28,10 +28,12 @@ __global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
   __shared__ float red[8 * NI4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
   const int nt0 = blockIdx.x * NTW, d = a.K;
-  if (nt0 >= a.n_tiles) {                               // one workgroup more with rotary positions: the rows' factors
-    const int half = f.emb.dh >> 1;
-    if (tid < R * half) rope_factors(f.emb, tid / half, tid % half);
-    return;
+  if constexpr (EPI == EPI_F32) {
+    if (__builtin_expect(nt0 >= a.n_tiles, 0)) {        // QKV of a first layer with rotary positions: one workgroup more for the rows' factors
+      const int half = f.emb.dh >> 1;
+      if (tid < R * half) rope_factors(f.emb, tid / half, tid % half);
+      return;
+    }
   }
   // ---- this wave's share of K: k tiles w, w + 8, .. (bf16) or 16-k groups [g0, g1) (float32); first weights requested
   const int n_k = BF ? a.Kt : d >> 4;

@@ -78,8 +78,8 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
                                                    float* __restrict__ f32_out, NormPending pend, EmbedSource emb, int n_rows_grid) {
   __shared__ float s_sum[4], s_sq[4];
   const int r = blockIdx.x, tid = threadIdx.x;
-  if constexpr (SH < 0) {
-    if (r >= n_rows_grid) {
+  if constexpr (SH < 0 && ARCH == 1) {
+    if (__builtin_expect(r >= n_rows_grid, 0)) {
       const int i = (r - n_rows_grid) * 256 + tid, half = emb.dh >> 1;
       if (i / half < *n_rows) rope_factors(emb, i / half, i % half);
       return;
