@@ -96,11 +96,26 @@ __device__ __forceinline__ void rope_factors(const EmbedSource& e, int r, int k)
   const double ang = (double)e.rd.pos[r] * inv;
   reinterpret_cast<float2*>(e.rope + (size_t)r * e.dh)[k] = make_float2((float)cos(ang), (float)sin(ang));
 }
-__device__ __forceinline__ float gelu_tanh(float x) {
-  const float c = 0.7978845608028654f;   // sqrt(2/pi)
-  return 0.5f * x * (1.0f + tanhf(c * (x + 0.044715f * x * x * x)));
+// x / (1 + exp(-t)), the form of both activations: GELU (tanh) is x (1 + tanh u) / 2 = x / (1 + exp(-2 u)), which has no cancellation
+// on the negative side.  A matrix product's epilogue runs 64 - 256 of these per lane, so it is 19 straight-line instructions
+// instead of the library's expf and an IEEE division (tanhf has branches besides): e = exp(-|t|) is the hardware's exp2 with the
+// rounding error of |t| log2(e) put back in first order, the quotient by 1 + e (e x for t < 0) the hardware's reciprocal and one
+// correction, which also takes what the sum's rounding lost.  2032 x 6400 x 1600 with GELU 58 -> 52 us, 80 x 6400 x 1600 10.5 -> 9.6.
+// Error (2-norm) against 64 bits, before -> now, x within 3: GELU 3.6e-8 -> 2.7e-8, SiLU 4.1e-8 -> 2.7e-8.
+__device__ __forceinline__ float times_logistic(float x, float t) {
+  constexpr float L = 1.44269504f, L_LO = 1.92596303e-8f, LN2 = 0.693147181f;   // log2(e) as a float and what it misses
+  const float ta = fminf(fabsf(t), 104.f), z = ta * -L;      // (exp(-104) is 0)
+  const float dz = __builtin_fmaf(ta, -L_LO, __builtin_fmaf(ta, -L, -z)), e0 = __builtin_amdgcn_exp2f(z);
+  const float e = __builtin_fmaf(e0, dz * LN2, e0), d = 1.0f + e, d_lo = e - (d - 1.0f);
+  const float n = t < 0.f ? x * e : x, r = __builtin_amdgcn_rcpf(d), q = n * r;
+  const float rest = __builtin_fmaf(-d_lo, q, __builtin_fmaf(-d, q, n));
+  return fabsf(n) < INFINITY ? __builtin_fmaf(rest, r, q) : q;
 }
-__device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
+__device__ __forceinline__ float gelu_tanh(float x) {
+  const float c2 = 1.5957691216057308f;   // 2 sqrt(2/pi)
+  return times_logistic(x, c2 * (x + 0.044715f * x * x * x));
+}
+__device__ __forceinline__ float silu(float x) { return times_logistic(x, x); }
 
 // The wave's index inside its workgroup as a scalar.  Conditions built from it are then scalar too,
 // so the compiler branches around matrix instructions instead of masking them with EXEC: the MFMA
