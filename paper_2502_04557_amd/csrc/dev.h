@@ -96,12 +96,13 @@ __device__ __forceinline__ void rope_factors(const EmbedSource& e, int r, int k)
   const double ang = (double)e.rd.pos[r] * inv;
   reinterpret_cast<float2*>(e.rope + (size_t)r * e.dh)[k] = make_float2((float)cos(ang), (float)sin(ang));
 }
-// x / (1 + exp(-t)), the form of both activations: GELU (tanh) is x (1 + tanh u) / 2 = x / (1 + exp(-2 u)), which has no cancellation
-// on the negative side.  A matrix product's epilogue runs 64 - 256 of these per lane, so it is 19 straight-line instructions
-// instead of the library's expf and an IEEE division (tanhf has branches besides): e = exp(-|t|) is the hardware's exp2 with the
-// rounding error of |t| log2(e) put back in first order, the quotient by 1 + e (e x for t < 0) the hardware's reciprocal and one
-// correction, which also takes what the sum's rounding lost.  2032 x 6400 x 1600 with GELU 58 -> 52 us, 80 x 6400 x 1600 10.5 -> 9.6.
-// Error (2-norm) against 64 bits, before -> now, x within 3: GELU 3.6e-8 -> 2.7e-8, SiLU 4.1e-8 -> 2.7e-8.
+// Both activations are x / (1 + exp(-t)): SiLU with t = x, GELU (tanh) with t = 2 u, since x (1 + tanh u) / 2 = x / (1 + exp(-2 u)) -
+// without the cancellation on the negative side.  A matrix product's epilogue runs 64 - 256 of them per lane, one wave per SIMD
+// in the large tiles, so they are short straight-line code around the hardware's exp2 and reciprocal (1 ulp each) instead of the
+// library's expf / tanhf and an IEEE division.
+// For a float32 result (times_logistic): e = exp(-|t|) with the rounding error of |t| log2(e) put back in first order, and one
+// correction of the quotient, which also takes what the sum's rounding lost.  Error (2-norm) against 64 bits, library -> this, x
+// within 3: GELU 3.6e-8 -> 2.7e-8, SiLU 4.1e-8 -> 2.7e-8.
 __device__ __forceinline__ float times_logistic(float x, float t) {
   constexpr float L = 1.44269504f, L_LO = 1.92596303e-8f, LN2 = 0.693147181f;   // log2(e) as a float and what it misses
   const float ta = fminf(fabsf(t), 104.f), z = ta * -L;      // (exp(-104) is 0)
@@ -111,11 +112,23 @@ __device__ __forceinline__ float times_logistic(float x, float t) {
   const float rest = __builtin_fmaf(-d_lo, q, __builtin_fmaf(-d, q, n));
   return fabsf(n) < INFINITY ? __builtin_fmaf(rest, r, q) : q;
 }
-__device__ __forceinline__ float gelu_tanh(float x) {
+// For a result that is rounded to float16 next, without the corrections: 5e-8 (2-norm) before that rounding, whose own 2.1e-4 stays the
+// same to seven digits.  On one 256 x 256 tile of GELU the long form took 13 us of epilogue; 2032 x 6400 x 1600 58 -> 51 us.
+__device__ __forceinline__ float times_logistic_exp2(float x, float z) {        // z = -t log2(e); (exp2 is infinite: 0)
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
+}
+template <typename T> __device__ __forceinline__ float gelu_tanh(float x);      // T: the element type of what it is stored to
+template <> __device__ __forceinline__ float gelu_tanh<float>(float x) {
   const float c2 = 1.5957691216057308f;   // 2 sqrt(2/pi)
   return times_logistic(x, c2 * (x + 0.044715f * x * x * x));
 }
-__device__ __forceinline__ float silu(float x) { return times_logistic(x, x); }
+template <> __device__ __forceinline__ float gelu_tanh<bf16_t>(float x) {
+  constexpr float C = -2.3022081985f;     // -2 sqrt(2/pi) log2(e)
+  return times_logistic_exp2(x, x * __builtin_fmaf(x * x, 0.044715f * C, C));
+}
+template <typename T> __device__ __forceinline__ float silu(float x);
+template <> __device__ __forceinline__ float silu<float>(float x) { return times_logistic(x, x); }
+template <> __device__ __forceinline__ float silu<bf16_t>(float x) { return times_logistic_exp2(x, x * -1.44269504f); }
 
 // The wave's index inside its workgroup as a scalar.  Conditions built from it are then scalar too,
 // so the compiler branches around matrix instructions instead of masking them with EXEC: the MFMA

@@ -15,24 +15,28 @@ namespace sprinter {
 // kt + 1 are read into a second register set between the matrix instructions of kt.
 // The weight fragment is the first operand, so that the accumulator holds four consecutive COLUMNS of one row per lane:
 // the epilogue stores 16 bytes of float32 or 8 bytes of an activation operand tile at a time.
-// What bounds it (4096 rows, 256 x 256 tile): 1247 cycles per k tile, of which the matrix instructions are 1024 and the
-// LDS (96 KiB of fragment reads and 32 KiB of arriving loads at 128 B a cycle) as many; the clock falls to 1.75 GHz in
-// a loop of this launch and to 1.9 - 2.0 in a whole prefill, where it issues 1.3 PFLOP/s.  FFN-up 2 x 14336 x 4096: 856 -> 720 us
-// (1.34 PFLOP/s), FFN-down 4096 x 11008: 327 -> 275, QKV 12288 x 4096: 458 -> 350, against one that shared only the activations through LDS and waited for all its loads at every barrier.
-// Also measured: 32 x 32 x 16 instructions (8 - 20 % slower), a fifth stage (no faster), 4 waves of 128 x 128 (the compiler
-// moves accumulators between register files: 1.5 times slower).
+// The 256 x 256 tile is four waves of 128 x 128, one per SIMD, whose accumulators are all 256 accumulation registers: a k tile
+// costs the LDS 64 KiB of fragment reads and 32 KiB of arriving loads, 768 of the 1024 cycles that its matrix instructions take at
+// 128 B a cycle (eight waves of 64 x 128: 96 KiB, as many cycles as the products).  What bounds it (4096 rows): 1150 - 1180 cycles
+// per k tile (eight waves: 1310 - 1410) at a clock that the power holds to 1.7 GHz in a loop of this launch and 1.9 - 2.0 in a whole
+// prefill; then the epilogue, whose stores (float32) or activations no other wave hides.  In a loop of one launch, eight waves -> four, us:
+// FFN-up 2 x 14336 x 4096 846 -> 802, 2 x 11008 x 4096 621 -> 582, 2 x 8192 x 2048 234 -> 218, QKV 12288 x 4096 362 -> 329, 6144 x 4096
+// 206 -> 194, O-proj 4096 x 4096 117 -> 108, FFN-down 4096 x 14336 383 -> 356 (1.36 PFLOP/s).
+// Also measured: 32 x 32 x 16 instructions (8 - 20 % slower), a fifth stage (no faster), two fragment reads per row tile instead of
+// three and a later first one (equal), 256 x 128 tiles of four waves (10 - 20 % slower but where the last round is half empty).
 template <int WM, int WN, int MT, int NT, int S>
 struct GemmTile {                                       // WM x WN waves, MT x NT operand tiles per wave, S stages
   static constexpr int wm = WM, wn = WN, mt = MT, nt = NT, stages = S, waves = WM * WN;
+  static constexpr bool pinned = MT * NT == 64;         // the accumulators fill a wave's 256 accumulation registers
 };
-using TileL = GemmTile<4, 2, 4, 8, 4>;                  // 256 x 256, 128 KiB: one workgroup per compute unit
+using TileL = GemmTile<2, 2, 8, 8, 4>;                  // 256 x 256, 128 KiB: one workgroup per compute unit
 using TileM = GemmTile<2, 2, 4, 4, 5>;                  // 128 x 128, 80 KiB: two
 using TileS = GemmTile<2, 2, 2, 4, 6>;                  // 64 x 128, 72 KiB: two
 using TileX = GemmTile<2, 2, 2, 2, 8>;                  // 64 x 64, 64 KiB: two
 using TileN = GemmTile<1, 2, 2, 2, 8>;                  // 32 x 64, 48 KiB: three
 
 template <typename T, int EPI>
-__global__ __launch_bounds__(T::waves * 64, 2) void k_gemm_tile(GemmArgs a, int x_tiles, int gm, int gn) {
+__global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(GemmArgs a, int x_tiles, int gm, int gn) {
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
   constexpr int WN = T::wn, MT = T::mt, NT = T::nt, S = T::stages;
   constexpr int TMT = T::wm * MT, TNT = WN * NT, LT = TMT + TNT, PER = LT / T::waves;   // operand tiles per stage, per wave
@@ -122,22 +126,148 @@ __global__ __launch_bounds__(T::waves * 64, 2) void k_gemm_tile(GemmArgs a, int 
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((S - 2) * PER) : "memory");
   __builtin_amdgcn_sched_barrier(0);
   read(A, k0);
+  // Pinned accumulators: one wave per SIMD has nobody to hide behind, so the order of a k tile is written out - a fragment read of
+  // the next k tile after every second product, a load to LDS after every NT - and the products are in asm, which keeps the
+  // accumulators where they are (given the builtins in pieces, the compiler moves them between the register files: 600 moves per two
+  // k tiles).  The first s_nop lies between the accumulators' initialisation and their first use.
+  auto product = [&](f32x4& c, const u32x4& wf, const u32x4& xf) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(wf), "v"(xf));
+  };
+  auto step = [&](const Frag& f, Frag& nx, int kt) {
+    constexpr int RPR = 3, GAP = (NT + RPR) / (RPR + 1);   // fragment reads per row tile, products between them
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier\n\ts_nop 3" ::"n"((S - 3) * PER) : "memory");
+    const u32x4* sn = &ring[(kt + 1 - k0) % S][0][lane];
+    const size_t off = (size_t)min(kt + S - 1, k1 - 1) * 1024;
+    const int slot = (kt + S - 1 - k0) % S;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        product(acc[i][j], f.w[j], f.x[i]);
+        const int r = i * RPR + j / GAP;
+        if (j % GAP == GAP - 1 && j / GAP < RPR && r < MT + NT) {
+          if (r < NT) nx.w[r] = sn[(TMT + wn * NT + r) * 64];
+          else nx.x[r - NT] = sn[(wm * MT + r - NT) * 64];
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (j == NT - 1) {
+#pragma unroll
+          for (int q = i * PER / MT; q < (i + 1) * PER / MT; ++q)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + off),
+                                             (__attribute__((address_space(3))) void*)&ring[slot][w * PER + q][0], 16, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+  };
+  // The last products are on their way for some cycles more, which the compiler does not know: before anything that may read an
+  // accumulator (the end of the loop is such a place).
+  auto settle = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
   int kt = k0;
-  for (; kt + 2 <= k1; kt += 2) {
-    top(kt);
-    read(B, kt + 1);
-    mul(A);
-    weave();
-    top(kt + 1);
-    read(A, kt + 2);
-    mul(B);
-    weave();
+  if constexpr (T::pinned) {
+    for (; kt + 2 <= k1; kt += 2) {
+      step(A, B, kt);
+      step(B, A, kt + 1);
+      settle();
+    }
+    if (kt < k1) {
+      asm volatile("s_nop 3");
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) product(acc[i][j], A.w[j], A.x[i]);
+      settle();
+    }
+  } else {
+    for (; kt + 2 <= k1; kt += 2) {
+      top(kt);
+      read(B, kt + 1);
+      mul(A);
+      weave();
+      top(kt + 1);
+      read(A, kt + 2);
+      mul(B);
+      weave();
+    }
+    if (kt < k1) mul(A);
   }
-  if (kt < k1) mul(A);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the clamped loads of the last stages still write to LDS
   // lane (lq, l16): row l16 of a row tile, columns 4 lq .. + 3 of a column tile (N is a multiple of 8)
   const int l16 = lane & 15, lq = lane >> 4;
   float* part = (EPI == EPI_PART) ? a.part + (size_t)sk * a.part_stride : nullptr;
+  if constexpr (T::pinned && (EPI == EPI_F32 || EPI == EPI_PART)) {
+    // float32 rows: 16 rows at a time through a wave's own piece of the ring, so that a store covers 512 bytes of a row (64 bytes of
+    // 16 rows each took 10.5 us per workgroup, now 7.5)
+    __syncthreads();
+    constexpr int LD = NT * 16 + 4, LPR = NT * 4;       // floats per row in LDS, lanes per row
+    float* buf = reinterpret_cast<float*>(&ring[0][0][0]) + w * 16 * LD;
+    const int c4 = (lane % LPR) * 4, n = (bn * WN + wn) * NT * 16 + c4;
+    const bool n_ok = n < a.N;
+    f32x4 bias = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (EPI != EPI_PART && a.bias && n_ok) bias = *reinterpret_cast<const f32x4*>(a.bias + n);
+    float* __restrict__ dst = (EPI == EPI_PART ? part : a.out_f32) + n;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int m0 = (bm * TMT + wm * MT + i) * 16;
+#pragma unroll
+      for (int j = 0; j < NT; ++j) *reinterpret_cast<f32x4*>(buf + l16 * LD + j * 16 + lq * 4) = acc[i][j];
+      __builtin_amdgcn_wave_barrier();                  // (LDS operations of one wave complete in order)
+#pragma unroll
+      for (int r = 0; r < 16; r += 64 / LPR) {
+        const int row = r + lane / LPR, m = m0 + row;
+        f32x4 v = *reinterpret_cast<const f32x4*>(buf + row * LD + c4);
+        if (EPI == EPI_F32) v += bias;
+        if (m < n_rows && n_ok) *reinterpret_cast<f32x4*>(dst + (size_t)m * a.ldo) = v;
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    return;
+  }
+  if constexpr (T::pinned && (EPI == EPI_GELU || EPI == EPI_SWIGLU)) {
+    // Activations: two row tiles at a time into LDS, then one operand tile of the output (16 rows x 32 columns, 8 columns a lane) per
+    // round of a loop that stays a loop: written out over the accumulators it is 8000 instructions, run once per workgroup and
+    // fetched from L2.
+    __syncthreads();
+    constexpr int LD = NT * 16 + 4, RT = 2, OT = COLS / 2;
+    float* buf = reinterpret_cast<float*>(&ring[0][0][0]) + w * RT * 16 * LD;
+#pragma unroll
+    for (int i0 = 0; i0 < MT; i0 += RT) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) *reinterpret_cast<f32x4*>(buf + (i * 16 + l16) * LD + j * 16 + lq * 4) = acc[i0 + i][j];
+      __builtin_amdgcn_wave_barrier();                  // (LDS operations of one wave complete in order)
+#pragma unroll 1
+      for (int q = 0; q < RT * OT; ++q) {
+        const int i = q / OT, ct = q % OT, m = (bm * TMT + wm * MT + i0 + i) * 16 + l16, n = (bn * WN + wn) * COLS * 16 + ct * 32 + lq * 8;
+        const float* p = buf + (i * 16 + l16) * LD + ct * 32 + lq * 8;
+        float c[8], o[8];
+        *reinterpret_cast<f32x4*>(&c[0]) = *reinterpret_cast<const f32x4*>(p);
+        *reinterpret_cast<f32x4*>(&c[4]) = *reinterpret_cast<const f32x4*>(p + 4);
+        const bool ok = m < n_rows && n < a.N;
+        if constexpr (EPI == EPI_GELU) {
+          float b[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          if (a.bias && ok) load_row(a.bias + n, b);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = gelu_tanh<bf16_t>(c[e] + b[e]);
+        } else {
+          float u[8];
+          *reinterpret_cast<f32x4*>(&u[0]) = *reinterpret_cast<const f32x4*>(p + COLS * 16);
+          *reinterpret_cast<f32x4*>(&u[4]) = *reinterpret_cast<const f32x4*>(p + COLS * 16 + 4);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = silu<bf16_t>(c[e]) * u[e];
+        }
+        if (ok)
+          *reinterpret_cast<uint4*>((bf16_t*)a.out_act + act_idx<bf16_t>(m, n, a.out_K)) =
+              make_uint4(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]), pk_f16(o[4], o[5]), pk_f16(o[6], o[7]));
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < COLS; ++j) {
     const int n = ((bn * WN + wn) * COLS + j) * 16 + lq * 4;
@@ -157,12 +287,12 @@ __global__ __launch_bounds__(T::waves * 64, 2) void k_gemm_tile(GemmArgs a, int 
       } else {
         float o[4];
         if constexpr (EPI == EPI_GELU) {
-          o[0] = gelu_tanh(c[0] + bias.x); o[1] = gelu_tanh(c[1] + bias.y);
-          o[2] = gelu_tanh(c[2] + bias.z); o[3] = gelu_tanh(c[3] + bias.w);
+          o[0] = gelu_tanh<bf16_t>(c[0] + bias.x); o[1] = gelu_tanh<bf16_t>(c[1] + bias.y);
+          o[2] = gelu_tanh<bf16_t>(c[2] + bias.z); o[3] = gelu_tanh<bf16_t>(c[3] + bias.w);
         } else {
           const f32x4 u = acc[i][COLS + j];
 #pragma unroll
-          for (int v = 0; v < 4; ++v) o[v] = silu(c[v]) * u[v];
+          for (int v = 0; v < 4; ++v) o[v] = silu<bf16_t>(c[v]) * u[v];
         }
         *reinterpret_cast<uint2*>((bf16_t*)a.out_act + act_idx<bf16_t>(m, n, a.out_K)) = make_uint2(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]));
       }
