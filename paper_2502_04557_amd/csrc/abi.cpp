@@ -378,14 +378,14 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   const size_t pl_d = act_elems(dt, rows, md.d), pl_a = act_elems(dt, rows, md.H * md.dh), pl_f = act_elems(dt, rows, md.ff);
   const EmbedSource emb{m.tok_emb, m.pos_emb, rd, md.arch == SPRINTER_ARCH_LLAMA ? sc.rope : nullptr, md.theta, md.V, md.max_pos, md.dh};
   // O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
-  // them (and the bias) into the residual stream before it normalises the row.
+  // them (and the bias) into the residual stream before it normalises the row.  A product in one piece adds itself.
   const size_t part_stride = (size_t)rows * md.d;
   // a few rows: the norms before QKV and FFN-up are part of those launches
   const bool fused = !shared_caches && gemm_takes_norm(md.d, max_rows);
   float *h = sc.h, *h_other = sc.h2;
   NormPending pend{sc.part, part_stride, 0, nullptr};
   auto resid_gemm = [&](const void* W, const void* X, size_t plane, int K, const float* bias) {
-    pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, fused ? 4 : PART_SHARES, max_rows, s);
+    pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, fused ? 4 : PART_SHARES, bias, h, max_rows, s);
     pend.bias = bias;
   };
   auto norm = [&](const float* g, const float* b, void* out, float* f32_out, const EmbedSource* src = nullptr) {

@@ -24,7 +24,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int
   else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu<AT>(v) * v2);
 }
 
-// The kernel for 17 and more rows (k_gemm_tile.hip): whether a shape takes it, and its launch (returns the K shares of EPI_PART).
+// The kernel for 17 and more rows (k_gemm_tile.hip): whether a shape takes it, and its launch (returns the K shares of EPI_PART; 0: one
+// share, added to a.out_f32).
 // gemm_tile_choice: 16 x tile (0 - 4: 256 x 256, 128 x 128, 64 x 128, 64 x 64, 32 x 64) + K shares; a host function.
 bool gemm_takes_tile(int epi, int N, int rows);
 int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares);

@@ -73,11 +73,12 @@ struct NormPending {
 void launch_norm(int dtype, int arch, const float* h, const float* g, const float* b, float eps, int d,
                  const int* n_rows, void* act_out, float* f32_out, int max_rows, hipStream_t s,
                  const NormPending* pend = nullptr, const EmbedSource* emb = nullptr);
-// part[s] = X[:, K share s] W[:, K share s]^T for s < returned share count (<= max_shares)
+// The product X W^T that is to be added, with bias (or NULL), to the residual rows h.  Returns the K shares (<= max_shares) that it
+// has left as part[s] = X[:, K share s] W[:, K share s]^T, for the norm that follows to add up (NormPending) - or 0: h is updated.
 int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
-                     size_t part_stride, int max_shares, int max_rows, hipStream_t s);
+                     size_t part_stride, int max_shares, const float* bias, float* h, int max_rows, hipStream_t s);
 
-enum { EPI_F32 = 0, EPI_GELU = 2, EPI_SWIGLU = 3, EPI_PART = 4 /* partial product of one K share */ };
+enum { EPI_F32 = 0, EPI_GELU = 2, EPI_SWIGLU = 3, EPI_PART = 4 /* partial product of one K share */, EPI_RESID = 5 /* out += bias + product */ };
 // Y[M,N] = X[M,K] W[N,K]^T (+bias) with epilogue; X in activation layout, W in weight layout.
 // x_elems: elements the activation buffer X holds (its row tiles bound what a kernel may fetch).
 void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* X, size_t x_elems,

@@ -494,7 +494,7 @@ void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* 
 }
 
 int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
-                     size_t part_stride, int max_shares, int max_rows, hipStream_t s) {
+                     size_t part_stride, int max_shares, const float* bias, float* h, int max_rows, hipStream_t s) {
   GemmArgs a;
   memset(&a, 0, sizeof a);
   a.W = W; a.X = X; a.x_elems = x_elems; a.n_rows = n_rows; a.N = N; a.K = K;
@@ -519,6 +519,7 @@ int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, co
     else hipLaunchKernelGGL((k_gemm16_part<1>), dim3(groups * sk), dim3(512), 0, s, a);
     return sk;
   }
+  a.bias = bias; a.out_f32 = h;
   return launch_gemm_tile(EPI_PART, a, max_rows, max_shares, s);
 }
 

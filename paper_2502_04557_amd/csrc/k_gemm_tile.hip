@@ -198,7 +198,7 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
   // lane (lq, l16): row l16 of a row tile, columns 4 lq .. + 3 of a column tile (N is a multiple of 8)
   const int l16 = lane & 15, lq = lane >> 4;
   float* part = (EPI == EPI_PART) ? a.part + (size_t)sk * a.part_stride : nullptr;
-  if constexpr (T::pinned && (EPI == EPI_F32 || EPI == EPI_PART)) {
+  if constexpr (T::pinned && (EPI == EPI_F32 || EPI == EPI_PART || EPI == EPI_RESID)) {
     // float32 rows: 16 rows at a time through a wave's own piece of the ring, so that a store covers 512 bytes of a row (64 bytes of
     // 16 rows each took 10.5 us per workgroup, now 7.5)
     __syncthreads();
@@ -208,18 +208,29 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
     const bool n_ok = n < a.N;
     f32x4 bias = (f32x4){0.f, 0.f, 0.f, 0.f};
     if (EPI != EPI_PART && a.bias && n_ok) bias = *reinterpret_cast<const f32x4*>(a.bias + n);
-    float* __restrict__ dst = (EPI == EPI_PART ? part : a.out_f32) + n;
+    float* __restrict__ dst = (EPI == EPI_PART ? part : a.out_f32) + (n_ok ? n : 0);
+    constexpr int RPI = 64 / LPR, NR = 16 / RPI;        // rows per instruction, instructions per row tile
+    // EPI_RESID: the rows' own values, requested a row tile ahead (rows beyond the count: the last one again, dropped)
+    f32x4 own[2][EPI == EPI_RESID ? NR : 1];
+    auto fetch = [&](int i) {
+      const int m0 = (bm * TMT + wm * MT + i) * 16;
+#pragma unroll
+      for (int q = 0; q < NR; ++q) own[i & 1][q] = *reinterpret_cast<const f32x4*>(dst + (size_t)max(min(m0 + q * RPI + lane / LPR, n_rows - 1), 0) * a.ldo);
+    };
+    if constexpr (EPI == EPI_RESID) fetch(0);
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       const int m0 = (bm * TMT + wm * MT + i) * 16;
+      if constexpr (EPI == EPI_RESID) if (i + 1 < MT) fetch(i + 1);
 #pragma unroll
       for (int j = 0; j < NT; ++j) *reinterpret_cast<f32x4*>(buf + l16 * LD + j * 16 + lq * 4) = acc[i][j];
       __builtin_amdgcn_wave_barrier();                  // (LDS operations of one wave complete in order)
 #pragma unroll
-      for (int r = 0; r < 16; r += 64 / LPR) {
-        const int row = r + lane / LPR, m = m0 + row;
+      for (int q = 0; q < NR; ++q) {
+        const int row = q * RPI + lane / LPR, m = m0 + row;
         f32x4 v = *reinterpret_cast<const f32x4*>(buf + row * LD + c4);
         if (EPI == EPI_F32) v += bias;
+        if constexpr (EPI == EPI_RESID) v = (own[i & 1][q] + bias) + v;   // the norm's order: row, bias, product
         if (m < n_rows && n_ok) *reinterpret_cast<f32x4*>(dst + (size_t)m * a.ldo) = v;
       }
       __builtin_amdgcn_wave_barrier();
@@ -274,6 +285,12 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
     if (n >= a.N) continue;
     float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
     if (EPI != EPI_PART && a.bias) bias = *reinterpret_cast<const float4*>(a.bias + n);
+    float4 own[EPI == EPI_RESID ? MT : 1];              // (requested together; rows beyond the count: the last one again, dropped)
+    if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+        own[i] = *reinterpret_cast<const float4*>(a.out_f32 + (size_t)max(min((bm * TMT + wm * MT + i) * 16 + l16, n_rows - 1), 0) * a.ldo + n);
+    }
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
       const int m = (bm * TMT + wm * MT + i) * 16 + l16;
@@ -281,6 +298,9 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
       const f32x4 c = acc[i][j];
       if constexpr (EPI == EPI_PART) {
         *reinterpret_cast<float4*>(part + (size_t)m * a.ldo + n) = make_float4(c[0], c[1], c[2], c[3]);
+      } else if constexpr (EPI == EPI_RESID) {          // the norm's order: row, bias, product
+        *reinterpret_cast<float4*>(a.out_f32 + (size_t)m * a.ldo + n) = make_float4((own[i].x + bias.x) + c[0], (own[i].y + bias.y) + c[1],
+                                                                                     (own[i].z + bias.z) + c[2], (own[i].w + bias.w) + c[3]);
       } else if constexpr (EPI == EPI_F32) {
         *reinterpret_cast<float4*>(a.out_f32 + (size_t)m * a.ldo + n) =
             make_float4(c[0] + bias.x, c[1] + bias.y, c[2] + bias.z, c[3] + bias.w);
@@ -341,16 +361,14 @@ int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares) {
 }
 
 template <int EPI>
-static int launch_tile_epi(const GemmArgs& a, int rows, int max_shares, hipStream_t s) {
-  const int choice = gemm_tile_choice(EPI, rows, a.N, a.K, max_shares), sk = choice % 16;
-  switch (choice / 16) {
+static void launch_tile_epi(int tile, const GemmArgs& a, int rows, int sk, hipStream_t s) {
+  switch (tile) {
     case 0: launch_tile<TileL, EPI>(a, rows, sk, s); break;
     case 1: launch_tile<TileM, EPI>(a, rows, sk, s); break;
     case 2: launch_tile<TileS, EPI>(a, rows, sk, s); break;
     case 3: launch_tile<TileX, EPI>(a, rows, sk, s); break;
     default: launch_tile<TileN, EPI>(a, rows, sk, s); break;
   }
-  return sk;
 }
 
 // 17 - 64 rows of an output that cannot be left in K shares: the K-split kernel of k_gemm.hip, whose 8 waves share a column tile
@@ -366,13 +384,19 @@ bool gemm_takes_tile(int epi, int N, int rows) {
   return rows > 64 || (rows > 16 && (epi == EPI_PART || (N + cols - 1) / cols > 128));
 }
 
+// A product in one K share is added to the residual rows by its own epilogue, so that the norm that follows reads the rows alone.
+// Product and norm together, us: 4096 x 4096 at 4096 rows 159 -> 148, 4096 x 14336 408 -> 389, 2048 x 2048 65.4 -> 60.4, 768 x 768 24.3 ->
+// 22.8, 1500 rows of 512 x 512 11.4 -> 10.2; nowhere slower than the noise where the rule below picks one share (80 rows and more).
 int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipStream_t s) {
+  const int choice = gemm_tile_choice(epi, rows, a.N, a.K, epi == EPI_PART ? max_shares : 1), tile = choice / 16, sk = choice % 16;
   switch (epi) {
-    case EPI_F32: return launch_tile_epi<EPI_F32>(a, rows, 1, s);
-    case EPI_GELU: return launch_tile_epi<EPI_GELU>(a, rows, 1, s);
-    case EPI_SWIGLU: return launch_tile_epi<EPI_SWIGLU>(a, rows, 1, s);
-    default: return launch_tile_epi<EPI_PART>(a, rows, max_shares, s);
+    case EPI_F32: launch_tile_epi<EPI_F32>(tile, a, rows, 1, s); return 1;
+    case EPI_GELU: launch_tile_epi<EPI_GELU>(tile, a, rows, 1, s); return 1;
+    case EPI_SWIGLU: launch_tile_epi<EPI_SWIGLU>(tile, a, rows, 1, s); return 1;
   }
+  if (sk > 1) { launch_tile_epi<EPI_PART>(tile, a, rows, sk, s); return sk; }
+  launch_tile_epi<EPI_RESID>(tile, a, rows, 1, s);
+  return 0;
 }
 
 }  // namespace sprinter
