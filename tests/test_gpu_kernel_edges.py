@@ -215,6 +215,16 @@ def test_every_tile_with_every_epilogue(B, P, draft, target, draft_tiles, target
     _check(draft, target, B, W.DT_BF16, prompt_len=P, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=-(-(P + 4) // 32) * 32, whole_prompt=True, seed=71)
 
 
+@pytest.mark.parametrize("target", [_l(64, 33, 33, 776), _g(2176, 776)])
+def test_large_tile_adds_itself(target):
+    """4080 rows of O-proj and FFN-down on the 256 x 256 tile in one K share, which adds the product (GPT: and the bias) to the residual rows:
+    255 row tiles (the last tile of 256 rows is not full), column tiles beyond the last one, odd and even numbers of k tiles (25, 66, 68)."""
+    rows = 16 * 255
+    got = _tiles(target, rows)
+    assert got["o"] == got["down"] == (0, 1), got
+    _check(_g(128, 136), target, 16, W.DT_BF16, prompt_len=256, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=288, whole_prompt=True, seed=75)
+
+
 @pytest.mark.parametrize("B", [17, 33, 64])
 @pytest.mark.parametrize("gelu, gate_up", [(4096, 4096), (4104, 4104), (8192, 72), (8200, 72)])
 def test_either_side_of_the_wide_product_rules(B, gelu, gate_up):
