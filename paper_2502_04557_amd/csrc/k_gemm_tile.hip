@@ -27,35 +27,35 @@ namespace sprinter {
 template <int WM, int WN, int MT, int NT, int S>
 struct GemmTile {                                       // WM x WN waves, MT x NT operand tiles per wave, S stages
   static constexpr int wm = WM, wn = WN, mt = MT, nt = NT, stages = S, waves = WM * WN;
-  static constexpr bool pinned = MT * NT == 64;         // the accumulators fill a wave's 256 accumulation registers
+  static constexpr bool pinned = MT == 8;               // accumulators pinned to accumulation registers (256 x 256: all 256 of a wave)
 };
 using TileL = GemmTile<2, 2, 8, 8, 4>;                  // 256 x 256, 128 KiB: one workgroup per compute unit
+using TileH = GemmTile<2, 2, 8, 4, 4>;                  // 256 x 128, for the last round of the one above
 using TileM = GemmTile<2, 2, 4, 4, 5>;                  // 128 x 128, 80 KiB: two
 using TileS = GemmTile<2, 2, 2, 4, 6>;                  // 64 x 128, 72 KiB: two
 using TileX = GemmTile<2, 2, 2, 2, 8>;                  // 64 x 64, 64 KiB: two
 using TileN = GemmTile<1, 2, 2, 2, 8>;                  // 32 x 64, 48 KiB: three
 
+// Workgroups go round-robin over the 8 XCDs: each XCD takes a contiguous run of the n_blk workgroups' work.
+__device__ __forceinline__ int xcd_run(int id, int n_blk) {
+  const int xcd = id & 7, q = n_blk >> 3, rem = n_blk & 7;
+  return xcd * q + min(xcd, rem) + (id >> 3);
+}
+
+// Output tile (bm, bn) of share sk of SK.
 template <typename T, int EPI>
-__global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(GemmArgs a, int x_tiles, int gm, int gn) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm, int bn, int sk, int SK, void* lds) {
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
   constexpr int WN = T::wn, MT = T::mt, NT = T::nt, S = T::stages;
   constexpr int TMT = T::wm * MT, TNT = WN * NT, LT = TMT + TNT, PER = LT / T::waves;   // operand tiles per stage, per wave
   constexpr int COLS = DUAL ? NT / 2 : NT;              // output column tiles of a wave (SwiGLU: gate tiles, then up tiles)
   static_assert(LT % T::waves == 0 && NT % 2 == 0 && S >= 4, "");
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  __shared__ u32x4 ring[S][LT][64];
+  auto& ring = *reinterpret_cast<u32x4(*)[S][LT][64]>(lds);
   const int lane = threadIdx.x & 63, w = wave_index(), wm = w / WN, wn = w % WN;
   const int Kt = a.Kt;
-  // EPI_PART: blockIdx.y = K share, the partial product goes to part[share] (summed by the norm that follows)
-  const int sk = (EPI == EPI_PART) ? blockIdx.y : 0, SK = (EPI == EPI_PART) ? gridDim.y : 1;
+  // EPI_PART: the partial product goes to part[share] (summed by the norm that follows)
   const int k0 = (int)((long long)Kt * sk / SK), k1 = (int)((long long)Kt * (sk + 1) / SK);
-  // Workgroups go round-robin over the 8 XCDs: each XCD takes a contiguous run of tiles, ordered in bands of GM row groups,
-  // so that what it has in flight at a time (32 compute units) shares rows and columns in its own L2.
-  constexpr int GM = TMT >= 16 ? 4 : 8;
-  const int n_blk = gm * gn, id = blockIdx.x, xcd = id & 7, q = n_blk >> 3, rem = n_blk & 7;
-  const int t = xcd * q + min(xcd, rem) + (id >> 3);
-  const int band = t / (GM * gn), in_band = t - band * GM * gn, bh = min(GM, gm - band * GM);
-  const int bm = band * GM + in_band % bh, bn = in_band / bh;
   // this wave's PER operand tiles of a stage; tiles beyond the buffers are clamped, their products dropped by the epilogue
   const char* src[PER];
 #pragma unroll
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(wf), "v"(xf));
   };
   auto step = [&](const Frag& f, Frag& nx, int kt) {
-    constexpr int RPR = 3, GAP = (NT + RPR) / (RPR + 1);   // fragment reads per row tile, products between them
+    constexpr int RPR = NT == 8 ? 3 : 2, GAP = (NT + RPR - 1) / (RPR + 1);   // fragment reads per row tile, products between them
     asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier\n\ts_nop 3" ::"n"((S - 3) * PER) : "memory");
     const u32x4* sn = &ring[(kt + 1 - k0) % S][0][lane];
     const size_t off = (size_t)min(kt + S - 1, k1 - 1) * 1024;
@@ -320,6 +320,32 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
   }
 }
 
+// blockIdx.y = K share (partial products).  Tiles in bands of GM row groups, so that what an XCD has in flight at a time (32 compute
+// units) shares rows and columns in its own L2.
+template <typename T>
+__device__ __forceinline__ void tile_place(int t, int gm, int gn, int& bm, int& bn) {
+  constexpr int GM = T::wm * T::mt >= 16 ? 4 : 8;
+  const int band = t / (GM * gn), in_band = t - band * GM * gn, bh = min(GM, gm - band * GM);
+  bm = band * GM + in_band % bh; bn = in_band / bh;
+}
+// whole: workgroups with a whole tile; those behind them (256 x 256 tile only) take half a tile each.
+template <typename T, int EPI>
+__global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(GemmArgs a, int x_tiles, int gm, int gn, int whole) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[T::stages * (T::wm * T::mt + T::wn * T::nt) * 1024];
+  const int id = blockIdx.x;
+  int bm, bn;
+  if constexpr (T::pinned) {
+    if (id >= whole) {                                  // (scalar)
+      const int t = xcd_run(id - whole, gridDim.x - whole);
+      tile_place<T>(whole + (t >> 1), gm, gn, bm, bn);
+      gemm_tile<TileH, EPI>(a, x_tiles, bm, 2 * bn + (t & 1), 0, 1, lds);
+      return;
+    }
+  }
+  tile_place<T>(xcd_run(id, whole), gm, gn, bm, bn);
+  gemm_tile<T, EPI>(a, x_tiles, bm, bn, EPI == EPI_PART ? blockIdx.y : 0, EPI == EPI_PART ? gridDim.y : 1, lds);
+}
+
 // Which tile, and how many K shares (partial products), for a shape: the one with the smallest estimate of
 //   start + max(rounds of workgroups x cycles, padded products / rate, weights and shares / HBM rate) + the shares' way into the norm.
 // Per tile: workgroups a compute unit holds, microseconds before the first product and after the last, cycles per k tile of a
@@ -338,11 +364,17 @@ static float tile_us(const TileCost& c, int epi, int rows, int N, int Kt, int sk
   return c.start_us + std::max(cycles / 2400.f, std::max(product, memory)) + part / 4.5e6f + (epi == EPI_PART && sk > 4 ? 0.3f : 0.f);
 }
 
+// One workgroup of the 256 x 256 tile runs per compute unit: a last round with work for at most half of them is dealt out in halves of
+// 256 x 128, 0.6 of a round.  us: 384 tiles (6144 x 4096 at 4096 rows) 193 -> 169, 336 (3528 rows) 181 -> 153, 602 (2 x 11008 x 4096 at
+// 1792 rows) 270 -> 250, 1376 (4096 rows) 645 -> 634, 1568 (2 x 14336 x 4096 at 3528 rows) 662 -> 648.
+static int tiles_in_halves(int tiles) { return tiles > 256 && tiles % 256 <= 128 ? tiles % 256 : 0; }
+
 template <typename T, int EPI>
 static void launch_tile(const GemmArgs& a, int rows, int sk, hipStream_t s) {
   constexpr int tm = T::wm * T::mt * 16, cols = T::wn * T::nt * 16 / (EPI == EPI_SWIGLU ? 2 : 1);
   const int x_tiles = (int)(a.x_elems / ((size_t)a.Kt * 512)), gm = (rows + tm - 1) / tm, gn = (a.N + cols - 1) / cols;
-  hipLaunchKernelGGL((k_gemm_tile<T, EPI>), dim3(gm * gn, sk), dim3(T::waves * 64), 0, s, a, x_tiles, gm, gn);
+  const int tiles = gm * gn, rest = T::pinned && sk == 1 ? tiles_in_halves(tiles) : 0, whole = tiles - rest;
+  hipLaunchKernelGGL((k_gemm_tile<T, EPI>), dim3(whole + 2 * rest, sk), dim3(T::waves * 64), 0, s, a, x_tiles, gm, gn, whole);
 }
 
 int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares) {

@@ -225,6 +225,17 @@ def test_large_tile_adds_itself(target):
     _check(_g(128, 136), target, 16, W.DT_BF16, prompt_len=256, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=288, whole_prompt=True, seed=75)
 
 
+@pytest.mark.parametrize("target", [_l(64, 32, 32, 3064), _g(2048, 5896)])
+def test_last_round_in_halves(target):
+    """4080 rows of products whose 16 x 24 tiles of 256 x 256 fill the compute units once and half of them again: the rest goes out in halves.
+    QKV, gate + up and GELU, a last column tile that is not full (3064, 5896)."""
+    rows = 16 * 255
+    got = _tiles(target, rows)
+    for k, cols in (("qkv", target.d_qkv), ("up", target.d_ff * (2 if target.arch == W.ARCH_LLAMA else 1))):
+        assert got[k] == 0 and 0 < 16 * -(-cols // 256) - 256 <= 128, (k, got)
+    _check(_g(128, 136), target, 16, W.DT_BF16, prompt_len=256, prompt_len_min=0, n_gen=2, tau=1.5, max_seq=288, whole_prompt=True, seed=76)
+
+
 @pytest.mark.parametrize("B", [17, 33, 64])
 @pytest.mark.parametrize("gelu, gate_up", [(4096, 4096), (4104, 4104), (8192, 72), (8200, 72)])
 def test_either_side_of_the_wide_product_rules(B, gelu, gate_up):
