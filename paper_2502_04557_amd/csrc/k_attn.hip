@@ -559,6 +559,62 @@ __device__ __forceinline__ float quarter_sum(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// The queries of one wave of the kernel below, rotated and scaled (in base-2 units), to LDS in operand layout [set][32 columns]
+// [hi, lo][lane]: 16 entries from `first` on (beyond the last row: that one again) of heads h0 and h0 + 1 (PAIR), or 32 entries of head
+// h0.  The lanes go along the rows, 4 columns each (16 rows x 16 pieces of 32 bytes at once took the memory pipeline 4 times as
+// long).  All of a set's loads (PAIR: both sets') are requested together: left to the compiler they went out four at a time, 16 trips to
+// memory one after the other, 20 us of a wave's life.
+template <int DH, bool PAIR>
+__device__ __forceinline__ void queries_to_lds(const AttnArgs& a, int first, int n_rows, int h0, uint4 (*q)[DH / 32][2][64]) {
+  constexpr int LPR = DH / 4, RPI = 64 / LPR, NI = 16 / RPI, SETS = PAIR ? 2 : 1;   // lanes per row, rows per instruction, instructions
+  const int lane = threadIdx.x & 63, c4 = (lane % LPR) * 4, sub = lane / LPR;
+  const float scale = a.scale * 1.4426950408889634f, sg = c4 >= DH / 2 ? 1.f : -1.f;
+#pragma unroll
+  for (int s0 = 0; s0 < 2; s0 += SETS) {
+    float4 x[SETS][NI];
+    auto row = [&](int i) { return min(first + (PAIR ? 0 : 16 * s0) + i * RPI + sub, n_rows - 1); };
+    auto load = [&](float4 (&v)[SETS][NI], int col) {
+#pragma unroll
+      for (int s = 0; s < SETS; ++s)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) v[s][i] = *reinterpret_cast<const float4*>(a.y + (size_t)row(i) * a.dqkv + (size_t)(h0 + s) * DH + col);
+    };
+    load(x, c4);
+    if (a.use_rope) {                                            // (uniform)
+      float4 xp[SETS][NI], c[NI], d[NI];                         // cos, sin, cos, sin
+      load(xp, c4 ^ (DH / 2));
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const float4* __restrict__ cs = reinterpret_cast<const float4*>(a.rope + (size_t)row(i) * DH + 2 * (c4 % (DH / 2)));
+        c[i] = cs[0]; d[i] = cs[1];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < SETS; ++s)
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          float4& v = x[s][i];
+          const float4 w = xp[s][i];
+          v.x = v.x * c[i].x + sg * (w.x * c[i].y); v.y = v.y * c[i].z + sg * (w.y * c[i].w);
+          v.z = v.z * d[i].x + sg * (w.z * d[i].y); v.w = v.w * d[i].z + sg * (w.w * d[i].w);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < SETS; ++s)
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        uint2 qh, ql;
+        split2(x[s][i].x * scale, x[s][i].y * scale, qh.x, ql.x);
+        split2(x[s][i].z * scale, x[s][i].w * scale, qh.y, ql.y);
+        const int at = ((c4 & 31) >> 3) * 16 + i * RPI + sub;    // operand lane of the row, columns c4 & ~7 .. + 7
+        *reinterpret_cast<uint2*>((char*)&q[s0 + s][c4 >> 5][0][at] + (c4 & 4) * 2) = qh;
+        *reinterpret_cast<uint2*>((char*)&q[s0 + s][c4 >> 5][1][at] + (c4 & 4) * 2) = ql;
+      }
+    __builtin_amdgcn_sched_barrier(0);                           // one set's loads at a time (registers)
+  }
+  __builtin_amdgcn_wave_barrier();                               // (a wave's LDS operations complete in order)
+}
+
 // Causal attention on the matrix cores for a multi-entry pass whose entries come in runs of consecutive positions of
 // one batch row (prefill); every key and value of the pass is already cached (the append-only launch ran before).
 // One wave takes two sets of 16 queries that read the same keys: two heads of one KV head over 16 entries (PAIR), or one
@@ -570,9 +626,9 @@ __device__ __forceinline__ float quarter_sum(float v) {
 //     straight from the cache, keys beyond the run's last one zeroed (0 x NaN is NaN).  The accumulator holds four
 //     consecutive columns of one query per lane: 8-byte stores.
 // The keys of the next block are requested when this block's have been used, and the values likewise.
-// Per launch at 4096 entries: 32 heads x 128 columns, prompts of 255: 145 -> 81 us; 32 heads over 8 KV heads, 511: 187 -> 92;
-// contexts up to 2000: 362 -> 170.  What bounds it now is the latency of the keys and values (3900 cycles per block of 32 keys
-// for 1024 cycles of matrix instructions, at two waves per SIMD).  What bounded the version before (16 queries of one head per
+// Per launch at 4096 entries: 32 heads x 128 columns, prompts of 64 - 512: 80 us, with the queries' loads requested together 74; 32 heads
+// over 8 KV heads, 512: 91 -> 81.  What bounds it now: the softmax's vector instructions next to the products (about 1000 cycles
+// each per block of 32 keys and wave), and some 18 us of a wave's life outside its blocks, for which two waves per SIMD are few.  What bounded the version before (16 queries of one head per
 // wave, the query along the registers, P through LDS, 366 registers) was not arithmetic either: one descriptor read after the
 // other, and barriers that waited for the prefetched block every time.
 template <int DH, bool PAIR>
@@ -580,7 +636,7 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
   constexpr int T = DH / 32, CT = DH / 16, E = PAIR ? 16 : 32;
   constexpr float NEG = -1e30f;
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  __shared__ u32x4 lds_q[2][T][2][64];                           // [set][32 columns][hi, lo][lane]
+  __shared__ uint4 lds_q[2][T][2][64];                           // (in registers the queries spill at 128 columns)
   const int n_rows = *a.rd.n_rows, r0 = (gridDim.y - 1 - blockIdx.y) * E;   // the longest contexts first
   if (r0 >= n_rows) return;
   const int lane = threadIdx.x, l16 = lane & 15, lq = lane >> 4, S = a.max_seq, G = a.H / a.KVH;
@@ -589,6 +645,7 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
   const int e_b = a.rd.b[mine], e_slot = a.rd.slot[mine];        // lane e: entry e's batch row and position in the cache
   const int b_prev = __shfl_up(e_b, 1);                          // (by all lanes: an inactive one would read as 0)
   u64 starts = __ballot(lane < n_here && (lane == 0 || e_b != b_prev));
+  queries_to_lds<DH, PAIR>(a, r0, n_rows, h0, lds_q);
   while (starts) {
     const int s0 = __builtin_ctzll(starts);
     starts &= starts - 1;
@@ -613,40 +670,12 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
     };
     fetch_k(0);
     fetch_v(0);
-    // Queries, rotated and scaled (in base-2 units), to LDS in operand layout: in registers they spill at 128 columns.  The lanes
-    // go along the rows, 4 columns each (16 rows x 16 pieces of 32 bytes at once took the memory pipeline 4 times as long).
     int slot[2];                                                 // a query's position; -1: not of this run, every key masked
-    const float scale = a.scale * 1.4426950408889634f;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const int e = l16 + (PAIR ? 0 : 16 * s), sl = __shfl(e_slot, e);
       slot[s] = (e >= s0 && e < s1) ? sl : -1;
-      constexpr int LPR = DH / 4, RPI = 64 / LPR;                // lanes per row, rows per instruction
-      const int c4 = (lane % LPR) * 4;
-      const bool upper = c4 >= DH / 2;
-#pragma unroll
-      for (int i = 0; i < 16 / RPI; ++i) {
-        const int row = i * RPI + lane / LPR, re = r0 + min(max(row + (PAIR ? 0 : 16 * s), s0), s1 - 1);
-        const float* __restrict__ y = a.y + (size_t)re * a.dqkv + (size_t)(h0 + (PAIR ? s : 0)) * DH;
-        float4 x = *reinterpret_cast<const float4*>(y + c4);
-        if (a.use_rope) {                                        // (uniform)
-          const float4 xp = *reinterpret_cast<const float4*>(y + (c4 ^ (DH / 2)));
-          const float4* __restrict__ cs = reinterpret_cast<const float4*>(a.rope + (size_t)re * DH + 2 * (c4 % (DH / 2)));
-          const float4 c = cs[0], d = cs[1];                     // cos, sin, cos, sin
-          const float sg = upper ? 1.f : -1.f;
-          x.x = x.x * c.x + sg * (xp.x * c.y); x.y = x.y * c.z + sg * (xp.y * c.w);
-          x.z = x.z * d.x + sg * (xp.z * d.y); x.w = x.w * d.z + sg * (xp.w * d.w);
-        }
-        uint2 qh, ql;
-        split2(x.x * scale, x.y * scale, qh.x, ql.x);
-        split2(x.z * scale, x.w * scale, qh.y, ql.y);
-        const int at = ((c4 & 31) >> 3) * 16 + row;              // operand lane of row `row`, columns c4 & ~7 .. + 7
-        *reinterpret_cast<uint2*>((char*)&lds_q[s][c4 >> 5][0][at] + (c4 & 4) * 2) = qh;
-        *reinterpret_cast<uint2*>((char*)&lds_q[s][c4 >> 5][1][at] + (c4 & 4) * 2) = ql;
-      }
-      __builtin_amdgcn_sched_barrier(0);                         // one set's loads at a time (registers)
     }
-    __builtin_amdgcn_wave_barrier();                             // (one wave: its LDS operations complete in order)
     f32x4 O[2][CT];
     float m_run[2] = {NEG, NEG}, l_run[2] = {0.f, 0.f};          // (l_run: this lane's keys only)
 #pragma unroll
@@ -663,7 +692,7 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
         for (int hl = 0; hl < 2; ++hl)                           // (four independent chains)
 #pragma unroll
           for (int s = 0; s < 2; ++s) {
-            const uint4 q = __builtin_bit_cast(uint4, lds_q[s][t][hl][lane]);
+            const uint4 q = lds_q[s][t][hl][lane];
             sc[s][0] = mfma_bf16(__builtin_bit_cast(uint4, K[0][t]), q, sc[s][0]);
             sc[s][1] = mfma_bf16(__builtin_bit_cast(uint4, K[1][t]), q, sc[s][1]);
           }
