@@ -559,7 +559,7 @@ __device__ __forceinline__ float quarter_sum(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
-// The queries of one wave of the kernel below, rotated and scaled (in base-2 units), to LDS in operand layout [set][32 columns]
+// The queries of one wave of the two kernels below, rotated and scaled (in base-2 units), to LDS in operand layout [set][32 columns]
 // [hi, lo][lane]: 16 entries from `first` on (beyond the last row: that one again) of heads h0 and h0 + 1 (PAIR), or 32 entries of head
 // h0.  The lanes go along the rows, 4 columns each (16 rows x 16 pieces of 32 bytes at once took the memory pipeline 4 times as
 // long).  All of a set's loads (PAIR: both sets') are requested together: left to the compiler they went out four at a time, 16 trips to
@@ -627,9 +627,9 @@ __device__ __forceinline__ void queries_to_lds(const AttnArgs& a, int first, int
 //     consecutive columns of one query per lane: 8-byte stores.
 // The keys of the next block are requested when this block's have been used, and the values likewise.
 // Per launch at 4096 entries: 32 heads x 128 columns, prompts of 64 - 512: 80 us, with the queries' loads requested together 74; 32 heads
-// over 8 KV heads, 512: 91 -> 81.  What bounds it now: the softmax's vector instructions next to the products (about 1000 cycles
-// each per block of 32 keys and wave), and some 18 us of a wave's life outside its blocks, for which two waves per SIMD are few.  What bounded the version before (16 queries of one head per
-// wave, the query along the registers, P through LDS, 366 registers) was not arithmetic either: one descriptor read after the
+// over 8 KV heads, 512: 90 -> 81; contexts up to 2000: 176 -> 164.  What bounds it now, by a fit over those: 1.5 us per block of 32 keys
+// and pair of waves of a SIMD, of which the matrix instructions are 1, and about 15 us of a wave's life outside its blocks.
+// What bounded the version before (16 queries of one head per wave, the query along the registers, P through LDS, 366 registers) was not arithmetic either: one descriptor read after the
 // other, and barriers that waited for the prefetched block every time.
 template <int DH, bool PAIR>
 __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
@@ -750,6 +750,167 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
       if (slot[s] < 0) continue;
       const int m = r0 + l16 + (PAIR ? 0 : 16 * s);
       bf16_t* __restrict__ dst = ao + act_idx<bf16_t>(m, (h0 + (PAIR ? s : 0)) * DH + lq * 4, a.ao_K);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {                          // 16 columns on: half an operand tile (256 elements)
+        const f32x4 o = O[s][ct] * inv;
+        *reinterpret_cast<uint2*>(dst + ct * 256) = make_uint2(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]));
+      }
+    }
+  }
+}
+
+// 16 bytes per lane from memory to LDS at `lds` + 16 x lane.  In asm, because the compiler puts a wait for every such load of its builtin
+// in front of this kernel's next read of LDS; the kernel's own waits count them.
+__device__ __forceinline__ void lds_load16(const bf16_t* src, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(src) : "memory", "m0");
+}
+
+// The same with the keys and values of a KV head shared by the four waves of a workgroup: a wave takes two heads over 16 entries as
+// above, the four of them the head pairs of the KV head, times as many groups of 16 entries as that leaves waves for (2, 4, 8 heads per
+// KV head: 64, 32, 16 entries).  Blocks of 32 keys go to LDS in operand order (a ring of S stages, global_load_lds: no registers, one
+// quarter of a block per wave), so the register room goes to the queries, which are read from LDS once instead of per block, and a
+// key or value crosses from L2 to a compute unit a quarter as often.  The same bits as above.  What bounds it, by the same fit: 1.2 us per
+// block and pair of waves, vector next to matrix instructions; the 15 us outside are the same.
+// us per launch at 4096 entries, 32 heads of 128 columns over 8: prompts of 512 81 -> 73, contexts up to 2000 164 -> 136.
+template <int DH>
+__global__ __launch_bounds__(256, 2) void k_attn_mfma_shared_bf16(AttnArgs a) {
+  constexpr int T = DH / 32, CT = DH / 16, S = 4, F = 2 * T + CT;   // F fragments per block; waves 0, 1: keys, 2, 3: values, T each
+  constexpr float NEG = -1e30f;
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  __shared__ u32x4 ring[S][F][64];
+  static_assert(S * F == 4 * 2 * T * 2, "the four waves' queries pass through the ring");
+  const int n_rows = *a.rd.n_rows, G = a.H / a.KVH, pairs = G >> 1, E = 64 / pairs;
+  const int r0 = (gridDim.y - 1 - blockIdx.y) * E;               // the longest contexts first
+  if (r0 >= n_rows) return;
+  const int lane = threadIdx.x & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4, max_seq = a.max_seq;
+  const int kvh = blockIdx.x, h0 = kvh * G + 2 * (w % pairs), e0 = 16 * (w / pairs);
+  const int n_here = min(E, n_rows - r0), mine = r0 + min(lane, n_here - 1);
+  const int e_b = a.rd.b[mine], e_slot = a.rd.slot[mine];        // lane e: entry e's batch row and position in the cache
+  const int b_prev = __shfl_up(e_b, 1);                          // (by all lanes: an inactive one would read as 0)
+  u64 starts = __ballot(lane < n_here && (lane == 0 || e_b != b_prev));
+  uint4(*q_lds)[T][2][64] = reinterpret_cast<uint4(*)[T][2][64]>(&ring[0][0][0] + w * (2 * T * 2 * 64));
+  queries_to_lds<DH, true>(a, r0 + e0, n_rows, h0, q_lds);       // (through the wave's quarter of the ring)
+  uint4 Q[2][T][2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+      for (int hl = 0; hl < 2; ++hl) Q[s][t][hl] = q_lds[s][t][hl][lane];
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // every wave has its queries: the ring is free
+  while (starts) {                                               // (the same for the four waves, as are s0, s1 and n_blk)
+    const int s0 = __builtin_ctzll(starts);
+    starts &= starts - 1;
+    const int s1 = starts ? __builtin_ctzll(starts) : n_here;    // entries s0 .. s1 - 1 belong to batch row b, positions ascend
+    const int b = __builtin_amdgcn_readlane(e_b, s0), max_slot = __builtin_amdgcn_readlane(e_slot, s1 - 1), n_blk = (max_slot >> 5) + 1;
+    const int q0 = max(s0, e0), q1 = min(s1, e0 + 16);           // this wave's entries of the run (none: it only loads)
+    const int my_min = q0 < q1 ? __builtin_amdgcn_readlane(e_slot, q0) : 0, my_max = q0 < q1 ? __builtin_amdgcn_readlane(e_slot, q1 - 1) : -1;
+    const size_t head = ((size_t)b * a.KVH + kvh) * (size_t)max_seq * DH;
+    const bf16_t* __restrict__ Kc = (const bf16_t*)a.kcache + a.layer_off + head;
+    const bf16_t* __restrict__ Vc = (const bf16_t*)a.vcache + a.layer_off + head;
+    const int e_mine = e0 + l16, sl = __shfl(e_slot, e_mine);
+    const int slot = (e_mine >= q0 && e_mine < q1) ? sl : -1;    // the lane's query's position; -1: not of this run, never stored
+    // Row i of key tile t2 is key 8 (i / 4) + 4 t2 + i % 4; keys beyond the run's last one: that one again, masked.  Blocks beyond
+    // the last one: it again, never read.
+    const int key_lane = (l16 >> 2) * 8 + (l16 & 3) + (w & 1) * 4;
+    auto issue = [&](int i) {
+      const int kb = min(i, n_blk - 1) * 32;
+      const bf16_t* src = w < 2 ? Kc + (size_t)min(kb + key_lane, max_slot) * DH + lq * 8 : Vc + (size_t)kb * DH + (w - 2) * (T * 512) + lane * 8;
+      const int step = w < 2 ? 32 : 512;                         // (scalar)
+      const unsigned dst = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)&ring[i % S][w * T][0];
+#pragma unroll
+      for (int j = 0; j < T; ++j) lds_load16(src + j * step, __builtin_amdgcn_readfirstlane(dst + j * 1024));
+    };
+    f32x4 O[2][CT];
+    float m_run[2] = {NEG, NEG}, l_run[2] = {0.f, 0.f};          // (l_run: this lane's keys only)
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) O[s][ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < S - 1; ++i) issue(i);
+    for (int i = 0; i < n_blk; ++i) {
+      // this wave's part of block i has landed, its reads of block i - 1 are back; then the same of every wave
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((S - 2) * T) : "memory");
+      issue(i + S - 1);
+      const int kb = i * 32;
+      if (kb > my_max) continue;                                 // (scalar) nothing here that an entry of this wave sees
+      const u32x4(*blk)[64] = ring[i % S];
+      f32x4 sc[2][2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) sc[s][0] = sc[s][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const uint4 k0 = __builtin_bit_cast(uint4, blk[t][lane]), k1 = __builtin_bit_cast(uint4, blk[T + t][lane]);
+#pragma unroll
+        for (int hl = 0; hl < 2; ++hl)                           // (four independent chains)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const uint4 q = Q[s][t][hl];
+            sc[s][0] = mfma_bf16(k0, q, sc[s][0]);
+            sc[s][1] = mfma_bf16(k1, q, sc[s][1]);
+          }
+      }
+      u32x4 V[CT];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) V[ct] = blk[2 * T + ct][lane];
+      const bool edge = kb + 31 > my_min;                        // (scalar) some entry of the run does not see the whole block
+      const int left = slot - kb - lq * 8;                       // keys 0 .. left of this lane's 8 are valid
+      uint4 ph[2], pl[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        float x[8], mx = NEG;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = sc[s][e >> 2][e & 3];
+        if (edge) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) x[e] = e <= left ? x[e] : NEG;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, x[e]);
+        const float mn = fmaxf(m_run[s], quarter_max(mx));
+        if (__any(mn > m_run[s])) {                              // (uniform) the running maximum of some query moves
+          const float corr = __builtin_amdgcn_exp2f(m_run[s] - mn);
+          l_run[s] *= corr;
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) O[s][ct] *= corr;
+          m_run[s] = mn;
+        }
+        float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(x[e] - mn);
+        if (edge) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) p[e] = e <= left ? p[e] : 0.f;
+        }
+        l_run[s] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        split2(p[0], p[1], ph[s].x, pl[s].x);
+        split2(p[2], p[3], ph[s].y, pl[s].y);
+        split2(p[4], p[5], ph[s].z, pl[s].z);
+        split2(p[6], p[7], ph[s].w, pl[s].w);
+      }
+      if (kb + 31 > my_max) {                                    // (scalar) zero the values of keys beyond the wave's last one
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          V[ct] = __builtin_bit_cast(u32x4, vt_fix(__builtin_bit_cast(uint4, V[ct]), kb + lq * 8, my_max + 1, 0u));
+      }
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const uint4 vf = __builtin_bit_cast(uint4, V[ct]);
+        O[0][ct] = mfma_bf16(vf, ph[0], O[0][ct]);
+        O[1][ct] = mfma_bf16(vf, ph[1], O[1][ct]);
+        O[0][ct] = mfma_bf16(vf, pl[0], O[0][ct]);
+        O[1][ct] = mfma_bf16(vf, pl[1], O[1][ct]);
+      }
+    }
+    // The clamped loads of the last stages still write to LDS; then the ring is free for the next run.
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    bf16_t* __restrict__ ao = (bf16_t*)a.ao;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const float inv = 1.0f / quarter_sum(l_run[s]);
+      if (slot < 0) continue;
+      bf16_t* __restrict__ dst = ao + act_idx<bf16_t>(r0 + e_mine, (h0 + s) * DH + lq * 4, a.ao_K);
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {                          // 16 columns on: half an operand tile (256 elements)
         const f32x4 o = O[s][ct] * inv;
@@ -957,7 +1118,13 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
     return;
   }
   if (a.phase == 3) {          // attend-only over runs of consecutive positions of one row: the matrix-core kernel
-    if (G > 1) hipLaunchKernelGGL((k_attn_mfma_bf16<DH, true>), dim3(a.H / 2, (max_rows + 15) / 16), dim3(64), 0, s, a);
+    // Shared by four waves from where the longest prompt is 16 times their 128 / G entries: below, the workgroups' start and the waves
+    // without entries of a run cost what the sharing gives.  us at 4096 entries, alone / shared, prompts of half to all of the
+    // length: 32 heads over 8 of 128 columns, 100: 35 / 37, 512: 64 / 59, 1000: 99 / 87, 2000: 162 / 126; of 64, 512: 36 / 36, 2000: 97 / 88;
+    // 16 over 8, 512: 43 / 44, 1000: 62 / 53, 2000: 112 / 100; 16 over 2, 100: 22 / 22, 512: 42 / 38, 2000: 112 / 98.
+    if (G > 1 && (long long)ctx_bound * G >= 2048)
+      hipLaunchKernelGGL((k_attn_mfma_shared_bf16<DH>), dim3(a.KVH, (max_rows + 128 / G - 1) / (128 / G)), dim3(256), 0, s, a);
+    else if (G > 1) hipLaunchKernelGGL((k_attn_mfma_bf16<DH, true>), dim3(a.H / 2, (max_rows + 15) / 16), dim3(64), 0, s, a);
     else hipLaunchKernelGGL((k_attn_mfma_bf16<DH, false>), dim3(a.H, (max_rows + 31) / 32), dim3(64), 0, s, a);
     return;
   }

@@ -81,6 +81,19 @@ def test_prefill_attention_runs(group, chunk_rows):
     _check(draft, target, 13, W.DT_BF16, prompt_len=41, prompt_len_min=1, tau=1.5, whole_prompt=True, chunk_rows=chunk_rows, seed=21 + group)
 
 
+@pytest.mark.parametrize("chunk_rows", [0, 192])
+@pytest.mark.parametrize("group, B, longest", [(2, 4, 1030), (4, 6, 520), (8, 9, 260)])
+def test_prefill_attention_shared_by_waves(group, B, longest, chunk_rows):
+    """Prompts of one token to the first lengths that the rule gives it: the four waves of a workgroup take 64, 32 or 16 entries of one
+    or several runs, some waves none of a run's, from one block of 32 keys to more than the ring holds; whole in one pass or split
+    over passes of 192 entries; head dimensions 64 and 128."""
+    assert longest * group >= 2048
+    draft = W.ModelCfg(W.ARCH_LLAMA, 1, 512, 8, 8 // group, 136, 83, 1088, 1e-5, 10000.0)
+    target = W.ModelCfg(W.ARCH_LLAMA, 1, 1024, 8, 8 // group, 136, 83, 1088, 1e-5, 10000.0)
+    _check(draft, target, B, W.DT_BF16, prompt_len=longest, prompt_len_min=1, tau=1.5, n_gen=2, max_seq=-(-(longest + 4) // 32) * 32, whole_prompt=True,
+           chunk_rows=chunk_rows, seed=41 + group)
+
+
 @pytest.mark.parametrize("B", [17, 40, 65, 80])
 def test_small_tiles(B):
     """17 - 80 rows of one step, all rejected: the 32- and 64-row tiles with K shares down to three k tiles each, a row count
