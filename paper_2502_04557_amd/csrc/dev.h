@@ -96,39 +96,14 @@ __device__ __forceinline__ void rope_factors(const EmbedSource& e, int r, int k)
   const double ang = (double)e.rd.pos[r] * inv;
   reinterpret_cast<float2*>(e.rope + (size_t)r * e.dh)[k] = make_float2((float)cos(ang), (float)sin(ang));
 }
-// Both activations are x / (1 + exp(-t)): SiLU with t = x, GELU (tanh) with t = 2 u, since x (1 + tanh u) / 2 = x / (1 + exp(-2 u)) -
-// without the cancellation on the negative side.  A matrix product's epilogue runs 64 - 256 of them per lane, one wave per SIMD
-// in the large tiles, so they are short straight-line code around the hardware's exp2 and reciprocal (1 ulp each) instead of the
-// library's expf / tanhf and an IEEE division.
-// For a float32 result (times_logistic): e = exp(-|t|) with the rounding error of |t| log2(e) put back in first order, and one
-// correction of the quotient, which also takes what the sum's rounding lost.  Error (2-norm) against 64 bits, library -> this, x
-// within 3: GELU 3.6e-8 -> 2.7e-8, SiLU 4.1e-8 -> 2.7e-8.
-__device__ __forceinline__ float times_logistic(float x, float t) {
-  constexpr float L = 1.44269504f, L_LO = 1.92596303e-8f, LN2 = 0.693147181f;   // log2(e) as a float and what it misses
-  const float ta = fminf(fabsf(t), 104.f), z = ta * -L;      // (exp(-104) is 0)
-  const float dz = __builtin_fmaf(ta, -L_LO, __builtin_fmaf(ta, -L, -z)), e0 = __builtin_amdgcn_exp2f(z);
-  const float e = __builtin_fmaf(e0, dz * LN2, e0), d = 1.0f + e, d_lo = e - (d - 1.0f);
-  const float n = t < 0.f ? x * e : x, r = __builtin_amdgcn_rcpf(d), q = n * r;
-  const float rest = __builtin_fmaf(-d_lo, q, __builtin_fmaf(-d, q, n));
-  return fabsf(n) < INFINITY ? __builtin_fmaf(rest, r, q) : q;
+// The library's tanhf / expf and an IEEE division, also where the result is rounded to float16 next: the hardware's exp2 and reciprocal
+// without corrections (2 x 14336 x 4096 at 4096 rows 722 -> 693 us, GELU 2032 x 6400 x 1600 54 -> 48) put SiLU's error (2-norm against 64
+// bits) at 1.2e-7 for 3.6e-8 on -6 .. -3 and 2.1e-7 for 3.5e-8 on -12 .. -6, and five times as many stored values beside the right one.
+__device__ __forceinline__ float gelu_tanh(float x) {
+  const float c = 0.7978845608028654f;   // sqrt(2/pi)
+  return 0.5f * x * (1.0f + tanhf(c * (x + 0.044715f * x * x * x)));
 }
-// For a result that is rounded to float16 next, without the corrections: 5e-8 (2-norm) before that rounding, whose own 2.1e-4 stays the
-// same to seven digits.  On one 256 x 256 tile of GELU the long form took 13 us of epilogue; 2032 x 6400 x 1600 58 -> 51 us.
-__device__ __forceinline__ float times_logistic_exp2(float x, float z) {        // z = -t log2(e); (exp2 is infinite: 0)
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(z));
-}
-template <typename T> __device__ __forceinline__ float gelu_tanh(float x);      // T: the element type of what it is stored to
-template <> __device__ __forceinline__ float gelu_tanh<float>(float x) {
-  const float c2 = 1.5957691216057308f;   // 2 sqrt(2/pi)
-  return times_logistic(x, c2 * (x + 0.044715f * x * x * x));
-}
-template <> __device__ __forceinline__ float gelu_tanh<bf16_t>(float x) {
-  constexpr float C = -2.3022081985f;     // -2 sqrt(2/pi) log2(e)
-  return times_logistic_exp2(x, x * __builtin_fmaf(x * x, 0.044715f * C, C));
-}
-template <typename T> __device__ __forceinline__ float silu(float x);
-template <> __device__ __forceinline__ float silu<float>(float x) { return times_logistic(x, x); }
-template <> __device__ __forceinline__ float silu<bf16_t>(float x) { return times_logistic_exp2(x, x * -1.44269504f); }
+__device__ __forceinline__ float silu(float x) { return x / (1.0f + expf(-x)); }
 
 // The wave's index inside its workgroup as a scalar.  Conditions built from it are then scalar too,
 // so the compiler branches around matrix instructions instead of masking them with EXEC: the MFMA

@@ -20,8 +20,8 @@ template <int EPI, typename AT>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int m, int n, float v, float v2, float bias) {
   if (m >= n_rows || n >= a.N) return;
   if (EPI == EPI_F32) a.out_f32[(size_t)m * a.ldo + n] = v + bias;
-  else if (EPI == EPI_GELU) act_store<AT>((AT*)a.out_act, m, n, a.out_K, gelu_tanh<AT>(v + bias));
-  else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu<AT>(v) * v2);
+  else if (EPI == EPI_GELU) act_store<AT>((AT*)a.out_act, m, n, a.out_K, gelu_tanh(v + bias));
+  else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu(v) * v2);
 }
 
 // The kernel for 17 and more rows (k_gemm_tile.hip): whether a shape takes it, and its launch (returns the K shares of EPI_PART; 0: one

@@ -2,6 +2,7 @@
 // batches).
 #include "gemm.h"
 #include <algorithm>
+#include <type_traits>
 #include <cstring>
 
 namespace sprinter {
@@ -20,8 +21,10 @@ namespace sprinter {
 // 128 B a cycle (eight waves of 64 x 128: 96 KiB, as many cycles as the products).  What bounds it (4096 rows): 1150 - 1180 cycles
 // per k tile (eight waves: 1310 - 1410) at a clock that the power holds to 1.7 GHz in a loop of this launch and 1.9 - 2.0 in a whole
 // prefill; then the epilogue, whose stores (float32) or activations no other wave hides.  In a loop of one launch, eight waves -> four, us:
-// FFN-up 2 x 14336 x 4096 846 -> 802, 2 x 11008 x 4096 621 -> 582, 2 x 8192 x 2048 234 -> 218, QKV 12288 x 4096 362 -> 329, 6144 x 4096
-// 206 -> 194, O-proj 4096 x 4096 117 -> 108, FFN-down 4096 x 14336 383 -> 356 (1.36 PFLOP/s).
+// FFN-up 2 x 14336 x 4096 746 -> 722, 2 x 11008 x 4096 603 -> 563, 2 x 8192 x 2048 227 -> 229, QKV 12288 x 4096 337 -> 311,
+// O-proj 4096 x 4096 113 -> 111, FFN-down 4096 x 14336 373 -> 347 (1.39 PFLOP/s).
+// GELU stays on eight waves: tanhf takes both of its branches for every element, which one wave per SIMD cannot hide (2032 x 6400 x 1600
+// 54 -> 66 us, 3528 x 3072 x 768 33 -> 44).
 // Also measured: 32 x 32 x 16 instructions (8 - 20 % slower), a fifth stage (no faster), two fragment reads per row tile instead of
 // three and a later first one (equal), 256 x 128 tiles of four waves (10 - 20 % slower but where the last round is half empty).
 template <int WM, int WN, int MT, int NT, int S>
@@ -31,6 +34,7 @@ struct GemmTile {                                       // WM x WN waves, MT x N
 };
 using TileL = GemmTile<2, 2, 8, 8, 4>;                  // 256 x 256, 128 KiB: one workgroup per compute unit
 using TileH = GemmTile<2, 2, 8, 4, 4>;                  // 256 x 128, for the last round of the one above
+using TileG = GemmTile<4, 2, 4, 8, 4>;                  // 256 x 256 of eight waves, for GELU
 using TileM = GemmTile<2, 2, 4, 4, 5>;                  // 128 x 128, 80 KiB: two
 using TileS = GemmTile<2, 2, 2, 4, 6>;                  // 64 x 128, 72 KiB: two
 using TileX = GemmTile<2, 2, 2, 2, 8>;                  // 64 x 64, 64 KiB: two
@@ -237,8 +241,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
     }
     return;
   }
-  if constexpr (T::pinned && (EPI == EPI_GELU || EPI == EPI_SWIGLU)) {
-    // Activations: two row tiles at a time into LDS, then one operand tile of the output (16 rows x 32 columns, 8 columns a lane) per
+  if constexpr (T::pinned && EPI == EPI_SWIGLU) {
+    // Gate + up: two row tiles at a time into LDS, then one operand tile of the output (16 rows x 32 columns, 8 columns a lane) per
     // round of a loop that stays a loop: written out over the accumulators it is 8000 instructions, run once per workgroup and
     // fetched from L2.
     __syncthreads();
@@ -259,18 +263,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
         *reinterpret_cast<f32x4*>(&c[0]) = *reinterpret_cast<const f32x4*>(p);
         *reinterpret_cast<f32x4*>(&c[4]) = *reinterpret_cast<const f32x4*>(p + 4);
         const bool ok = m < n_rows && n < a.N;
-        if constexpr (EPI == EPI_GELU) {
-          float b[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          if (a.bias && ok) load_row(a.bias + n, b);
+        float u[8];
+        *reinterpret_cast<f32x4*>(&u[0]) = *reinterpret_cast<const f32x4*>(p + COLS * 16);
+        *reinterpret_cast<f32x4*>(&u[4]) = *reinterpret_cast<const f32x4*>(p + COLS * 16 + 4);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = gelu_tanh<bf16_t>(c[e] + b[e]);
-        } else {
-          float u[8];
-          *reinterpret_cast<f32x4*>(&u[0]) = *reinterpret_cast<const f32x4*>(p + COLS * 16);
-          *reinterpret_cast<f32x4*>(&u[4]) = *reinterpret_cast<const f32x4*>(p + COLS * 16 + 4);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = silu<bf16_t>(c[e]) * u[e];
-        }
+        for (int e = 0; e < 8; ++e) o[e] = silu(c[e]) * u[e];
         if (ok)
           *reinterpret_cast<uint4*>((bf16_t*)a.out_act + act_idx<bf16_t>(m, n, a.out_K)) =
               make_uint4(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]), pk_f16(o[4], o[5]), pk_f16(o[6], o[7]));
@@ -307,12 +304,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
       } else {
         float o[4];
         if constexpr (EPI == EPI_GELU) {
-          o[0] = gelu_tanh<bf16_t>(c[0] + bias.x); o[1] = gelu_tanh<bf16_t>(c[1] + bias.y);
-          o[2] = gelu_tanh<bf16_t>(c[2] + bias.z); o[3] = gelu_tanh<bf16_t>(c[3] + bias.w);
+          o[0] = gelu_tanh(c[0] + bias.x); o[1] = gelu_tanh(c[1] + bias.y);
+          o[2] = gelu_tanh(c[2] + bias.z); o[3] = gelu_tanh(c[3] + bias.w);
         } else {
           const f32x4 u = acc[i][COLS + j];
 #pragma unroll
-          for (int v = 0; v < 4; ++v) o[v] = silu<bf16_t>(c[v]) * u[v];
+          for (int v = 0; v < 4; ++v) o[v] = silu(c[v]) * u[v];
         }
         *reinterpret_cast<uint2*>((bf16_t*)a.out_act + act_idx<bf16_t>(m, n, a.out_K)) = make_uint2(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]));
       }
@@ -365,8 +362,8 @@ static float tile_us(const TileCost& c, int epi, int rows, int N, int Kt, int sk
 }
 
 // One workgroup of the 256 x 256 tile runs per compute unit: a last round with work for at most half of them is dealt out in halves of
-// 256 x 128, 0.6 of a round.  us: 384 tiles (6144 x 4096 at 4096 rows) 193 -> 169, 336 (3528 rows) 181 -> 153, 602 (2 x 11008 x 4096 at
-// 1792 rows) 270 -> 250, 1376 (4096 rows) 645 -> 634, 1568 (2 x 14336 x 4096 at 3528 rows) 662 -> 648.
+// 256 x 128, 0.6 of a round.  us: 384 tiles (6144 x 4096 at 4096 rows) 196 -> 168, 336 (3528 rows) 182 -> 152, 602 (2 x 11008 x 4096 at
+// 1792 rows) 288 -> 259, 1376 (4096 rows) 596 -> 567, 1568 (2 x 14336 x 4096 at 3528 rows) 698 -> 678.
 static int tiles_in_halves(int tiles) { return tiles > 256 && tiles % 256 <= 128 ? tiles % 256 : 0; }
 
 template <typename T, int EPI>
@@ -395,7 +392,7 @@ int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares) {
 template <int EPI>
 static void launch_tile_epi(int tile, const GemmArgs& a, int rows, int sk, hipStream_t s) {
   switch (tile) {
-    case 0: launch_tile<TileL, EPI>(a, rows, sk, s); break;
+    case 0: launch_tile<std::conditional_t<EPI == EPI_GELU, TileG, TileL>, EPI>(a, rows, sk, s); break;
     case 1: launch_tile<TileM, EPI>(a, rows, sk, s); break;
     case 2: launch_tile<TileS, EPI>(a, rows, sk, s); break;
     case 3: launch_tile<TileX, EPI>(a, rows, sk, s); break;

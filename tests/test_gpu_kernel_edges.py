@@ -240,8 +240,8 @@ def test_large_tile_adds_itself(target):
 
 @pytest.mark.parametrize("target", [_l(64, 32, 32, 3064), _g(2048, 5896)])
 def test_last_round_in_halves(target):
-    """4080 rows of products whose 16 x 24 tiles of 256 x 256 fill the compute units once and half of them again: the rest goes out in halves.
-    QKV, gate + up and GELU, a last column tile that is not full (3064, 5896)."""
+    """4080 rows of products whose 16 x 24 tiles of 256 x 256 fill the compute units once and half of them again: the rest goes out in halves
+    (QKV with and without bias, gate + up) or, of the eight waves of GELU, in a second round; a last column tile that is not full (3064, 5896)."""
     rows = 16 * 255
     got = _tiles(target, rows)
     for k, cols in (("qkv", target.d_qkv), ("up", target.d_ff * (2 if target.arch == W.ARCH_LLAMA else 1))):
