@@ -364,11 +364,11 @@ size_t carve(const sprinter_cfg& c, void* base, sprinter_ctx* ctx, size_t* scrat
 
 // One model forward over the rows described by rd (device-side count).
 // shared_caches: several rows of rd may belong to one batch row (consecutive positions): every layer appends all
-// new keys / values first and attends in a second launch.  long_runs: those entries come in long runs of
-// consecutive positions (prefill), so the attending launch lets up to 32 of them share one pass over the row's cache.
+// new keys / values first and attends in a second launch.  run_len > 0: those entries come in long runs of consecutive
+// positions (prefill), that many in the mean, so the attending launch lets up to 64 of them share one pass over the row's cache.
 // ver: the verifier's work, done by the LM head's launch.
 void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool want_head, unsigned stream_id,
-             float* logits_out, bool shared_caches = false, bool long_runs = false, const VerifierArgs* ver = nullptr) {
+             float* logits_out, bool shared_caches = false, int run_len = 0, const VerifierArgs* ver = nullptr) {
   const int dt = ctx->cfg.dtype;
   const ModelDims& md = m.md;
   hipStream_t s = ctx->stream;
@@ -413,7 +413,7 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
                        kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, 1);
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
-                       kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, long_runs ? 3 : 2);
+                       kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, run_len > 0 ? 3 : 2, run_len);
     } else {
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
                        kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s);
@@ -487,7 +487,7 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
   const bool sd = ctx->cfg.reject_mode == 1;
   const VerifierArgs ver{dq.sc.hf, dq.md.d, ctx->cfg.ver_d_hidden, (const float*)ctx->v_w1, (const float*)ctx->v_b1,
                          (const float*)ctx->v_w2, ctx->ver_part, B, ctx->ver_chunks};
-  forward(ctx, dq, dq.rd(), B, true, 0u, sd ? ctx->dl : (out ? out->draft_logits : nullptr), false, false, &ver);
+  forward(ctx, dq, dq.rd(), B, true, 0u, sd ? ctx->dl : (out ? out->draft_logits : nullptr), false, 0, &ver);
   if (sd && out && out->draft_logits) launch_copy_f32(ctx->dl, out->draft_logits, dq.rd_n, dq.md.V, B, s);
   if (out && out->draft_hidden) launch_copy_f32(dq.sc.hf, out->draft_hidden, dq.rd_n, dq.md.d, B, s);
   DecideArgs da;
@@ -785,7 +785,7 @@ int sprinter_prefill(sprinter_ctx* ctx, const int32_t* dev_prompt, const int32_t
     // walks through that many runs one after the other.  Whole prefill of a pair of two layers each, 12 heads of 64 and 32 of 128,
     // short-run / long-run attention: 16 rows x 3 positions 310 / 466 us, 128 rows x 1 422 / 863, x 3 635 / 728, x 5 756 / 770,
     // x 8 968 / 887; 512 rows x 1 867 / 1120, x 2 1232 / 1155, x 5 2203 / 1993.
-    const bool long_runs = E >= 8LL * B || (E > 768 && E >= 2LL * B);
+    const int run_len = E >= 8LL * B || (E > 768 && E >= 2LL * B) ? (int)(E / B) : 0;
     if (hipMemcpyAsync(ctx->ent_off, off.data(), ((size_t)B + 1) * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)                  // (off is a local: the copy must be over before it goes)
       return fail(ctx, SPRINTER_E_HIP, "copy of the prefill work list failed");
@@ -799,8 +799,8 @@ int sprinter_prefill(sprinter_ctx* ctx, const int32_t* dev_prompt, const int32_t
       const int n = (int)std::min<long long>(ctx->rows_alloc, E - start);
       ca.start = (int)start; ca.n = n;
       launch_catchup_chunk(ca, s);
-      forward(ctx, dq, tp.rd(), n, false, 0u, nullptr, true, long_runs);
-      forward(ctx, tp, tp.rd(), n, false, 1u, nullptr, true, long_runs);
+      forward(ctx, dq, tp.rd(), n, false, 0u, nullptr, true, run_len);
+      forward(ctx, tp, tp.rd(), n, false, 1u, nullptr, true, run_len);
       // bound the number of launches in flight (tools that keep per-dispatch state have died on long backlogs)
       if ((chunk & 3) == 3 && hipStreamSynchronize(s) != hipSuccess) return fail(ctx, SPRINTER_E_HIP, "stream synchronisation failed");
     }

@@ -97,10 +97,12 @@ void launch_gemm_norm(int dtype, int epi, const NormFusion& f, const void* W, co
 void launch_attention(int dtype, const ModelDims& md, const float* y, const float* rope, const RowDesc& rd,
                       void* kcache, void* vcache, size_t layer_off, int ctx_bound /* upper bound of the rows' cache lengths */,
                       int max_seq /* slots per (row, KV head) of the caches; bf16: a multiple of 32 */,
-                      void* ao, int max_rows, float* split, hipStream_t s, int phase = 0);
+                      void* ao, int max_rows, float* split, hipStream_t s, int phase = 0, int run_len = 0);
 // split: scratch of attn_split_floats (bf16), the partial products' buffer, which is free between a layer's first norm and its
 // O-projection.  phase 0: append the row's new key / value to the cache and attend (rows of one launch own different caches);
-// phase 1: append only; phase 2: attend only (the pair serves launches where several rows share a cache).
+// phase 1: append only; phase 2: attend only (the pair serves launches where several rows share a cache); phase 3: attend only, the rows
+// in long runs of consecutive positions of one batch row (prefill), run_len of them in the mean.
+bool attn_shared(int dh, int H, int KVH, int entries, int ctx_bound, int run_len);   // which kernel phase 3 takes; a host function
 
 // Workgroups that share a row's keys in the decode attention of bf16 mode (1: one per row and KV head); a host function.
 constexpr int SPLIT_WGS = 256;   // rows x KV heads x workgroups per row and KV head stay within it

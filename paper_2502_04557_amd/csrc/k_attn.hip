@@ -1111,18 +1111,28 @@ int attn_split(int dh, int kvh, int rows, int ctx_bound) {
   return std::min(8, SPLIT_WGS / (kvh * rows));
 }
 
+// Prefill of grouped queries: whether four waves share the keys and values of a KV head.  Below one wave per SIMD in the whole launch (1024 pairs
+// of heads x 16 entries) each has the memory to itself, and the workgroup's start and the waves without entries of a run cost what
+// nothing gives back; likewise where the longest prompt is short, 3.5 times as far at 64 columns (half the bytes of a key, and half the work to
+// hide the start behind), and where the prompts cover less than half of a workgroup's 128 / G entries in the mean: it goes through its
+// runs one after the other.
+// us, one wave / shared: one prompt of 600, 16 heads over 2 of 128 columns 28.2 / 28.5, 32 over 8 of 64 20.1 / 21.0; four of 512, 32 over 8 of
+// 128 48 / 43, of 1000, 16 over 8 73 / 65; 4096 entries in 512s, 32 over 8 of 128 73 / 66; six of 768, 32 over 8 of 64 57 / 62, three of 1500, 32 over 4 of
+// 64 90 / 76; one of 1030 and 100 of 10, 12 over 6 of 64 32 / 41, 16 over 8 of 128 51 / 58.  Of 948 such points (1 - 300 prompts of 9 - 2000
+// entries, 12 shapes) the rule shares 253, 13 % faster in the mean; two of them are slower for it, by 2 and 4 %.
+bool attn_shared(int dh, int H, int KVH, int entries, int ctx_bound, int run_len) {
+  const int G = H / KVH;
+  return G > 1 && (long long)(H / 2) * ((entries + 15) / 16) >= 1024 && (long long)ctx_bound * G >= (dh == 64 ? 7168 : 2048) && (long long)run_len * G >= 64;
+}
+
 template <int DH>
-static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bound, hipStream_t s) {
+static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bound, int run_len, hipStream_t s) {
   if (a.phase == 1) {          // append only
     hipLaunchKernelGGL((k_kv_append_bf16<DH>), dim3(a.KVH, (max_rows + 7) / 8), dim3(64), 0, s, a);
     return;
   }
   if (a.phase == 3) {          // attend-only over runs of consecutive positions of one row: the matrix-core kernel
-    // Shared by four waves from where the longest prompt is 16 times their 128 / G entries: below, the workgroups' start and the waves
-    // without entries of a run cost what the sharing gives.  us at 4096 entries, alone / shared, prompts of half to all of the
-    // length: 32 heads over 8 of 128 columns, 100: 35 / 37, 512: 64 / 59, 1000: 99 / 87, 2000: 162 / 126; of 64, 512: 36 / 36, 2000: 97 / 88;
-    // 16 over 8, 512: 43 / 44, 1000: 62 / 53, 2000: 112 / 100; 16 over 2, 100: 22 / 22, 512: 42 / 38, 2000: 112 / 98.
-    if (G > 1 && (long long)ctx_bound * G >= 2048)
+    if (attn_shared(DH, a.H, a.KVH, max_rows, ctx_bound, run_len))
       hipLaunchKernelGGL((k_attn_mfma_shared_bf16<DH>), dim3(a.KVH, (max_rows + 128 / G - 1) / (128 / G)), dim3(256), 0, s, a);
     else if (G > 1) hipLaunchKernelGGL((k_attn_mfma_bf16<DH, true>), dim3(a.H / 2, (max_rows + 15) / 16), dim3(64), 0, s, a);
     else hipLaunchKernelGGL((k_attn_mfma_bf16<DH, false>), dim3(a.H, (max_rows + 31) / 32), dim3(64), 0, s, a);
@@ -1162,7 +1172,7 @@ static void launch_attn_g(const AttnArgs& a, int G, int max_rows, hipStream_t s)
 
 void launch_attention(int dtype, const ModelDims& md, const float* y, const float* rope, const RowDesc& rd,
                       void* kcache, void* vcache, size_t layer_off, int ctx_bound, int max_seq, void* ao,
-                      int max_rows, float* split, hipStream_t s, int phase) {
+                      int max_rows, float* split, hipStream_t s, int phase, int run_len) {
   AttnArgs a;
   a.phase = (phase == 3 && dtype == 0) ? 2 : phase;      // the run-sharing kernel exists for bf16 only
   a.y = y; a.rope = rope; a.rd = rd; a.kcache = kcache; a.vcache = vcache; a.layer_off = layer_off;
@@ -1173,7 +1183,7 @@ void launch_attention(int dtype, const ModelDims& md, const float* y, const floa
   if (dtype == 0) {
     if (md.dh == 64) launch_attn_g<float, 64>(a, G, max_rows, s); else launch_attn_g<float, 128>(a, G, max_rows, s);
   } else {
-    if (md.dh == 64) launch_attn_bf16<64>(a, G, max_rows, ctx_bound, s); else launch_attn_bf16<128>(a, G, max_rows, ctx_bound, s);
+    if (md.dh == 64) launch_attn_bf16<64>(a, G, max_rows, ctx_bound, run_len, s); else launch_attn_bf16<128>(a, G, max_rows, ctx_bound, run_len, s);
   }
 }
 

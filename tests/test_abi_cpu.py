@@ -28,6 +28,29 @@ def test_exports_every_declared_symbol(lib):
         assert hasattr(lib, name), name
 
 
+@pytest.mark.parametrize("dh, H, KVH, lens, shared", [
+    # measured: one wave / four waves sharing, us
+    (128, 32, 8, [511] * 8, True),                 # 73.4 / 65.7
+    (128, 32, 8, [999] * 4, True),                 # 110 / 89
+    (128, 16, 8, [1499] * 3, True),                # 101 / 80
+    (64, 32, 8, [1999] * 2, True),                 # (four of 1500 - 2000: 97 / 88)
+    (128, 16, 2, [299], False),                    # 16.8 / 18.3: too few waves
+    (128, 16, 2, [255] * 2, False),                # 14.4 / 16.1
+    (64, 8, 1, [999] * 2, False),                  # 30.8 / 33.1
+    (64, 8, 1, [511] * 4, False),                  # 17.7 / 18.8
+    (64, 32, 8, [767] * 6, False),                 # 57 / 62: short keys
+    (64, 12, 6, [1030] + [10] * 100, False),       # 32 / 41: one long prompt among short ones
+    (128, 16, 8, [1030] + [10] * 100, False),      # 51 / 58
+    (128, 16, 8, [1030] + [9] * 300, False),       # 60 / 70
+    (128, 16, 8, [199] * 20, False),               # 28 / 30
+    (128, 32, 32, [999] * 4, False),               # no grouped queries
+])
+def test_shared_prefill_attention_only_where_it_is_ahead(lib, dh, H, KVH, lens, shared):
+    """Which attention kernel a prefill pass takes, at measured points on either side (lens: cached positions per row, one pass)."""
+    rule = lib["_ZN8sprinter11attn_sharedEiiiiii"]
+    assert bool(rule(dh, H, KVH, sum(lens), max(lens) + 1, sum(lens) // len(lens)) & 1) == shared
+
+
 def test_struct_layout_matches_header():
     from paper_2502_04557_amd import binding
     assert C.sizeof(binding.ModelCfgC) == 40
