@@ -8,12 +8,16 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_min=2, n_gen=3, tau=0.5, max_seq=48, seed=7, whole_prompt=False, chunk_rows=0):
-    """Decode steps of one configuration; returns the rejected rows per step."""
+def _check(draft, target, B, dtype, *, ver_hidden=24, prompt_len=5, prompt_len_min=2, n_gen=3, tau=0.5, max_seq=48, seed=7, whole_prompt=False, chunk_rows=0, full_row=False):
+    """Decode steps of one configuration; returns the rejected rows per step.  full_row: the last prompt has the full length."""
     from parity_util import Pair, compare_replay, close_enough, eps_of
     cfg = W.SprinterCfg(draft, target, ver_hidden, dtype, B, max_seq, tau=tau, seed=seed, name="edges", batch=B, prompt_len=prompt_len,
                         prompt_len_min=prompt_len_min, n_gen=n_gen, prompt_dist="uniform", weight_seed=500 + seed, prompt_seed=600 + seed, chunk_rows=chunk_rows)
     p = Pair(cfg, ver_scale=8.0)
+    if full_row:
+        p.prompts, p.plen = np.pad(p.prompts, ((0, 0), (0, prompt_len - p.prompts.shape[1]))), p.plen.copy()
+        p.plen[-1] = prompt_len
+        p.prompts[-1] = np.random.default_rng(seed).integers(0, draft.vocab, prompt_len)
     eps = eps_of(cfg)
     outs, _ = p.gpu_steps(n_gen)
     g = {k: np.stack([o[k2] for o in outs], axis=1) for k, k2 in
@@ -75,23 +79,29 @@ def test_tiles_of_many_rows(B, prompt_len):
 def test_prefill_attention_runs(group, chunk_rows):
     """Prompts of 1 - 40 tokens: runs that begin and end anywhere in a block of 8 cached slots, of 16 or 32 entries and of 32
     keys, one or many in a block, whole in one pass or split over passes of 64 entries; 1, 2 and 8 query heads per KV head, head
-    dimensions 64 and 128, with and without rotary positions."""
-    draft = W.ModelCfg(W.ARCH_LLAMA, 1, 512, 8, 8 // group, 136, 83, 48, 1e-5, 10000.0)
-    target = _llama(1, 1024, 8, 8 // group, 136, 83) if group > 1 else _gpt(1, 128, 136, 83)
+    dimensions 64 and 128, with and without rotary positions.  (Two layers: the first one's attention is what the second one caches.)"""
+    draft = W.ModelCfg(W.ARCH_LLAMA, 2, 512, 8, 8 // group, 136, 83, 48, 1e-5, 10000.0)
+    target = _llama(2, 1024, 8, 8 // group, 136, 83) if group > 1 else _gpt(2, 128, 136, 83)
     _check(draft, target, 13, W.DT_BF16, prompt_len=41, prompt_len_min=1, tau=1.5, whole_prompt=True, chunk_rows=chunk_rows, seed=21 + group)
 
 
-@pytest.mark.parametrize("chunk_rows", [0, 192])
-@pytest.mark.parametrize("group, B, longest", [(2, 4, 1030), (4, 6, 520), (8, 9, 260)])
+@pytest.mark.parametrize("chunk_rows", [0, 2112])
+@pytest.mark.parametrize("group, B, longest", [(2, 5, 1030), (4, 10, 520), (8, 20, 260)])
 def test_prefill_attention_shared_by_waves(group, B, longest, chunk_rows):
-    """Prompts of one token to the first lengths that the rule gives it: the four waves of a workgroup take 64, 32 or 16 entries of one
-    or several runs, some waves none of a run's, from one block of 32 keys to more than the ring holds; whole in one pass or split
-    over passes of 192 entries; head dimensions 64 and 128."""
-    assert longest * group >= 2048
-    draft = W.ModelCfg(W.ARCH_LLAMA, 1, 512, 8, 8 // group, 136, 83, 1088, 1e-5, 10000.0)
-    target = W.ModelCfg(W.ARCH_LLAMA, 1, 1024, 8, 8 // group, 136, 83, 1088, 1e-5, 10000.0)
-    _check(draft, target, B, W.DT_BF16, prompt_len=longest, prompt_len_min=1, tau=1.5, n_gen=2, max_seq=-(-(longest + 4) // 32) * 32, whole_prompt=True,
-           chunk_rows=chunk_rows, seed=41 + group)
+    """Ragged prompts whose longest one has the first length that the rule shares, 16 heads of 128: whole in one pass, or in two of which the
+    second goes back to one wave (the kernels give the same bits).  Two layers: the first one's attention is what the second one caches."""
+    draft = W.ModelCfg(W.ARCH_GPT, 1, 128, 2, 2, 136, 83, 1088)
+    target = W.ModelCfg(W.ARCH_LLAMA, 2, 2048, 16, 16 // group, 136, 83, 1088, 1e-5, 10000.0)
+    seed = 41 + group
+    cfg = W.SprinterCfg(draft, target, 24, W.DT_BF16, B, 1088, seed=seed, name="rule", batch=B, prompt_len=longest, prompt_len_min=longest // 4,
+                        prompt_dist="uniform", prompt_seed=600 + seed)
+    plen = W.make_prompts(cfg)[1]
+    plen[-1] = longest                                       # (full_row)
+    E = int(plen.sum()) - B
+    shared = lambda entries: bool(_host("_ZN8sprinter11attn_sharedEiiiiii", 128, 16, 16 // group, entries, int(plen.max()), E // B) & 1)
+    assert shared(min(E, chunk_rows or E)) and (not chunk_rows or not shared(E - chunk_rows)), (E, plen)
+    _check(draft, target, B, W.DT_BF16, prompt_len=longest, prompt_len_min=longest // 4, tau=1.5, n_gen=2, max_seq=-(-(longest + 4) // 32) * 32,
+           whole_prompt=True, chunk_rows=chunk_rows, seed=seed, full_row=True)
 
 
 @pytest.mark.parametrize("B", [17, 40, 65, 80])
