@@ -149,3 +149,34 @@ def test_float32_activations_to_their_ends(rows):
     W[:2, :2] *= 2.0
     got = _activation(F32, EPI_SWIGLU, x, W, W2, None, N, K)
     assert got[0, 0] == np.inf and np.isnan(got[0, 1]) and (got[1:, :2] == 0).all()
+
+
+@pytest.mark.parametrize("K", [520, 1024])
+@pytest.mark.parametrize("with_bias", [True, False])
+def test_last_round_in_halves_adds_itself(K, with_bias):
+    """3561 rows of 5768 columns, which the 256 x 256 tile adds to the residual rows: 14 x 23 tiles, 66 of them beyond the first round of 256
+    workgroups, in halves of 256 x 128; odd and even numbers of k tiles, a last one that is not full, neither rows nor columns a multiple of the
+    tile.  Products of float16 values are exact in float32, their sum and the two additions off by at most 2^-24 of the absolute sums each."""
+    import torch
+    rows, live, N = 3568, 3561, 5768
+    assert _tile(EPI_PART, rows, N, K, 8) == (0, 1) and 0 < -(-rows // 256) * -(-N // 256) - 256 <= 128
+    g = torch.Generator(device="cuda").manual_seed(K)
+    rnd = lambda *s: torch.empty(s, device="cuda").normal_(generator=g)
+    x, w, h = rnd(rows, K).half().float(), (rnd(N, K) * 0.05).half().float(), rnd(rows, N)
+    bias = rnd(N) if with_bias else None
+    X, W, out = _operand(x), _operand(w), h.clone()
+    n = torch.tensor([live], dtype=torch.int32, device="cuda")
+    shares = _lib()["_ZN8sprinter16launch_gemm_partEiPKvS1_mPKiiiPfmiPKfS4_iP12ihipStream_t"](
+        BF16, _ptr(W), _ptr(X), C.c_size_t(X.numel()), _ptr(n), N, K, _ptr(None), C.c_size_t(rows * N), 8, _ptr(bias), _ptr(out), rows,
+        C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert shares == 0
+    b = torch.zeros(N, device="cuda") if bias is None else bias
+    want = h.double() + b.double() + x.double() @ w.double().T
+    bound = 2.0 ** -24 * ((K + 2) * (x.abs().double() @ w.abs().double().T) + 2 * (h.abs() + b.abs()).double())
+    worst = float(((out.double() - want).abs() / bound)[:live].max())
+    print(K, with_bias, "worst share of the bound", round(worst, 4), flush=True)
+    assert worst <= 1
+    assert torch.equal(out[live:], h[live:])                 # rows beyond the count stay as they are
+    # the bound tells a missing k tile in any element
+    assert bool(((x[:, 32:64].double() @ w[:, 32:64].double().T).abs() > bound)[:live].float().mean() > 0.5)
