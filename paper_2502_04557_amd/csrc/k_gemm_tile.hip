@@ -331,7 +331,7 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
   __shared__ __attribute__((aligned(1024))) unsigned char lds[T::stages * (T::wm * T::mt + T::wn * T::nt) * 1024];
   const int id = blockIdx.x;
   int bm, bn;
-  if constexpr (T::pinned) {
+  if constexpr (T::pinned && EPI != EPI_PART) {         // (partial products: several shares, never in halves)
     if (id >= whole) {                                  // (scalar)
       const int t = xcd_run(id - whole, gridDim.x - whole);
       tile_place<T>(whole + (t >> 1), gm, gn, bm, bn);
