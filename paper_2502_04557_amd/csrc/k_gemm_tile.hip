@@ -243,8 +243,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
   }
   if constexpr (T::pinned && EPI == EPI_SWIGLU) {
     // Gate + up: two row tiles at a time into LDS, then one operand tile of the output (16 rows x 32 columns, 8 columns a lane) per
-    // round of a loop that stays a loop: written out over the accumulators it is 8000 instructions, run once per workgroup and
-    // fetched from L2.
+    // round of a loop that stays a loop: written out over the accumulators it is thousands of instructions, run once per workgroup and
+    // fetched from L2 (the loop unrolled by 2 or 8: equal).
     __syncthreads();
     constexpr int LD = NT * 16 + 4, RT = 2, OT = COLS / 2;
     float* buf = reinterpret_cast<float*>(&ring[0][0][0]) + w * RT * 16 * LD;
@@ -346,9 +346,13 @@ __global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(
 // Which tile, and how many K shares (partial products), for a shape: the one with the smallest estimate of
 //   start + max(rounds of workgroups x cycles, padded products / rate, weights and shares / HBM rate) + the shares' way into the norm.
 // Per tile: workgroups a compute unit holds, microseconds before the first product and after the last, cycles per k tile of a
-// workgroup that has its compute unit for itself and what each further one adds, PFLOP/s on a full chip.  The constants are a
-// fit to 1050 timings of 113 shapes (20 - 4096 rows, K 768 - 14336, N 768 - 14336, 1 - 8 shares; the fits are 7 - 11 % off in
-// the mean); the pick is 1 % slower than the best tile and share count in the mean, at worst 13 %.
+// workgroup that has its compute unit for itself and what each further one adds, PFLOP/s on a full chip.  The constants are a fit to
+// 1050 timings of 113 shapes (20 - 4096 rows, K 768 - 14336, N 768 - 14336, 1 - 8 shares) of the kernels before the 256 x 256 tile had four
+// waves (1355 cycles and 1.22 PFLOP/s are those of eight, which GELU still takes), before a last round went out in halves and before one
+// share added itself: here it counts as a partial product that the norm reads.  Against every tile and share count of the present kernels
+// over 235 shapes (the products of five model pairs at 20 - 4096 rows, partial products with the norm behind them) the pick is 2.3 %
+// slower than the best in the mean and 10 - 29 % at 21 of them: QKV and GELU of 4800 - 6400 columns at 140 - 300 rows (6400 x 1600 at 140
+// rows 15.2 for 11.8 us), O-proj of 768 columns in two shares for one (2032 rows 19.3 for 15.7).
 struct TileCost { int tm, tn, per_cu; float start_us, cycles, shared, rate; };
 static float tile_us(const TileCost& c, int epi, int rows, int N, int Kt, int sk) {
   const int mats = epi == EPI_SWIGLU ? 2 : 1, cols = c.tn / mats, slots = 256 * c.per_cu;
@@ -415,7 +419,8 @@ bool gemm_takes_tile(int epi, int N, int rows) {
 
 // A product in one K share is added to the residual rows by its own epilogue, so that the norm that follows reads the rows alone.
 // Product and norm together, us: 4096 x 4096 at 4096 rows 159 -> 148, 4096 x 14336 408 -> 389, 2048 x 2048 65.4 -> 60.4, 768 x 768 24.3 ->
-// 22.8, 1500 rows of 512 x 512 11.4 -> 10.2; nowhere slower than the noise where the rule below picks one share (80 rows and more).
+// 22.8, 1500 rows of 512 x 512 11.4 -> 10.2; nowhere slower than the noise where the rule above picks one share: from 17 rows where K leaves no
+// two shares of three k tiles (up to 160), from 18 - 90 at K 256 - 1600 and the widest outputs, else from a few hundred.
 int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipStream_t s) {
   const int choice = gemm_tile_choice(epi, rows, a.N, a.K, epi == EPI_PART ? max_shares : 1), tile = choice / 16, sk = choice % 16;
   switch (epi) {
