@@ -1113,16 +1113,17 @@ int attn_split(int dh, int kvh, int rows, int ctx_bound) {
 
 // Prefill of grouped queries: whether four waves share the keys and values of a KV head.  Below one wave per SIMD in the whole launch (1024 pairs
 // of heads x 16 entries) each has the memory to itself, and the workgroup's start and the waves without entries of a run cost what
-// nothing gives back; likewise where the longest prompt is short, 3.5 times as far at 64 columns (half the bytes of a key, and half the work to
+// nothing gives back; likewise where the longest prompt is short, five times as far at 64 columns (half the bytes of a key, and half the work to
 // hide the start behind), and where the prompts cover less than half of a workgroup's 128 / G entries in the mean: it goes through its
-// runs one after the other.
-// us, one wave / shared: one prompt of 600, 16 heads over 2 of 128 columns 28.2 / 28.5, 32 over 8 of 64 20.1 / 21.0; four of 512, 32 over 8 of
-// 128 48 / 43, of 1000, 16 over 8 73 / 65; 4096 entries in 512s, 32 over 8 of 128 73 / 66; six of 768, 32 over 8 of 64 57 / 62, three of 1500, 32 over 4 of
-// 64 90 / 76; one of 1030 and 100 of 10, 12 over 6 of 64 32 / 41, 16 over 8 of 128 51 / 58.  Of 948 such points (1 - 300 prompts of 9 - 2000
-// entries, 12 shapes) the rule shares 253, 13 % faster in the mean; two of them are slower for it, by 2 and 4 %.
+// runs one after the other.  us, one wave / shared, heads and KV heads, columns:
+//   shared: four of 512, 32 over 8, 128: 48 / 43; four of 1000, 16 over 8, 128: 73 / 65; eight of 512, 32 over 8, 128: 73 / 66; three of 1500, 32 over 4, 64: 90 / 76
+//   not: one of 300, 16 over 2, 128: 16.8 / 18.3; one of 600, 28.2 / 28.5; six of 768, 32 over 8, 64: 57 / 62; 20 of 200, 16 over 8, 128: 28 / 30;
+//        one of 1030 and 100 of 10, 12 over 6, 64: 32 / 41, 16 over 8, 128: 51 / 58
+// Of 948 such points (1 - 300 prompts of 9 - 2000 entries, 12 shapes) the rule shares 299, 12 % faster in the mean; two of them are slower for
+// it, by 2 and 4 %.
 bool attn_shared(int dh, int H, int KVH, int entries, int ctx_bound, int run_len) {
   const int G = H / KVH;
-  return G > 1 && (long long)(H / 2) * ((entries + 15) / 16) >= 1024 && (long long)ctx_bound * G >= (dh == 64 ? 7168 : 2048) && (long long)run_len * G >= 64;
+  return G > 1 && (long long)(H / 2) * ((entries + 15) / 16) >= 1024 && (long long)ctx_bound * G >= (dh == 64 ? 7168 : 1536) && (long long)run_len * G >= 64;
 }
 
 template <int DH>

@@ -33,6 +33,7 @@ def test_exports_every_declared_symbol(lib):
     (128, 32, 8, [511] * 8, True),                 # 73.4 / 65.7
     (128, 32, 8, [999] * 4, True),                 # 110 / 89
     (128, 16, 8, [1499] * 3, True),                # 101 / 80
+    (128, 16, 8, [999] * 4, True),                 # 73 / 65
     (64, 32, 8, [1999] * 2, True),                 # (four of 1500 - 2000: 97 / 88)
     (128, 16, 2, [299], False),                    # 16.8 / 18.3: too few waves
     (128, 16, 2, [255] * 2, False),                # 14.4 / 16.1

@@ -86,7 +86,7 @@ def test_prefill_attention_runs(group, chunk_rows):
 
 
 @pytest.mark.parametrize("chunk_rows", [0, 2112])
-@pytest.mark.parametrize("group, B, longest", [(2, 5, 1030), (4, 10, 520), (8, 20, 260)])
+@pytest.mark.parametrize("group, B, longest", [(2, 6, 770), (4, 11, 390), (8, 20, 200)])
 def test_prefill_attention_shared_by_waves(group, B, longest, chunk_rows):
     """Ragged prompts whose longest one has the first length that the rule shares, 16 heads of 128: whole in one pass, or in two of which the
     second goes back to one wave (the kernels give the same bits).  Two layers: the first one's attention is what the second one caches."""
