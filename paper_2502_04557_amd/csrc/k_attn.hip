@@ -12,7 +12,7 @@ namespace sprinter {
 struct AttnArgs {
   const float* y; const float* rope; RowDesc rd;
   void* kcache; void* vcache; size_t layer_off;
-  int H, KVH, dqkv, max_seq, use_rope; float scale;
+  int H, KVH, G, lg, dqkv, max_seq, use_rope; float scale;   // G = H / KVH = 1 << lg
   void* ao; int ao_K;
   float* split;   // k_attn_dec_bf16 with gridDim.z > 1: partial results [row][KV head][z][query head][DH + 2]
   int phase;   // 0 append + attend, 1 append only, 2 attend only, 3 attend only over long runs of one row (launcher only)
@@ -171,18 +171,11 @@ __global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
 __device__ __forceinline__ size_t vt_index(int slot, int d, int DH) {
   return (size_t)(slot >> 5) * (size_t)(32 * DH) + (size_t)(d >> 4) * 512 + (size_t)(((((slot & 31) >> 3) << 4) + (d & 15)) * 8 + (slot & 7));
 }
-// One operand piece of a value tile (8 consecutive keys from `key0` of one column): keys after `slot` become 0 (the
-// cache may hold anything there, and 0 x NaN is NaN on the matrix cores), key == slot becomes `own` (bf16 bits).
-__device__ __forceinline__ uint4 vt_fix(uint4 v, int key0, int slot, unsigned own) {
-  unsigned w[4] = {v.x, v.y, v.z, v.w};
+// A value tile's operand piece is 8 consecutive keys of one column, two a register: masks of its first n keys.  The keys beyond a
+// row's last one are cleared with them (the cache may hold anything there, and 0 x NaN is NaN on the matrix cores).
+__device__ __forceinline__ void vt_first(int n, unsigned (&keep)[4]) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const int key = key0 + e;
-    unsigned h = (e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu);
-    h = key > slot ? 0u : (key == slot ? own : h);
-    w[e >> 1] = (e & 1) ? ((w[e >> 1] & 0xffffu) | (h << 16)) : ((w[e >> 1] & 0xffff0000u) | h);
-  }
-  return make_uint4(w[0], w[1], w[2], w[3]);
+  for (int e = 0; e < 4; ++e) keep[e] = n > 2 * e + 1 ? 0xffffffffu : n > 2 * e ? 0xffffu : 0u;
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding global access
@@ -202,52 +195,53 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // operands of the block that holds slot `slot`, which is the row's last block; keys beyond it are masked.
 // The waves' partial results are merged through LDS at the end.  gridDim.z > 1: that many workgroups share the keys (their waves
 // count on), each leaves its unnormalised result, maximum and sum in a.split, and k_attn_merge puts them together.
-template <int DH, int NW>
+template <int DH, int NW, int NV, bool ROPE>
 __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
-  constexpr int T = DH / 32, CT = DH / 16, PS = 36, HALF = DH / 2, GMAX = 8;
+  constexpr int T = DH / 32, CT = DH / 16, PS = 36, HALF = DH / 2, GMAX = 4 * NV;
   constexpr float NEG = -1e30f;
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) float lds_p[NW][GMAX * PS];
-  __shared__ __attribute__((aligned(16))) bf16_t lds_kn[DH];
+  __shared__ __attribute__((aligned(16))) bf16_t lds_kn[DH], lds_vn[DH];
   __shared__ uint4 lds_q[2][T][64];
   __shared__ float s_ml[NW][GMAX][2];
   __shared__ float s_o[NW][GMAX][DH];
   const int r = blockIdx.y;
   const int kvh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = wave_index();
-  const int l16 = lane & 15, lq = lane >> 4, G = a.H / a.KVH;
-  // What depends on the row index alone is requested first, before the row count and the row's descriptor are
-  // known (the projection buffer holds every row the grid covers): the new value per column (every wave), and for
-  // wave t < T the 32-column piece t of the query heads and of the new key with their rotary partners and angles.
-  // The G query heads form one operand (row l16 = head min(l16, G - 1): rows beyond G repeat the last head and are
-  // ignored).  Spread over T waves the preparation is a quarter of the arithmetic per wave and its loads overlap
-  // the descriptor's round trips (one wave doing all of it after the descriptor took 3.4 of c2's 7.4 us).
+  const int l16 = lane & 15, lq = lane >> 4, G = a.G;
+  const int n_rows = *a.rd.n_rows, b = a.rd.b[r], slot = a.rd.slot[r], S = a.max_seq;   // (the lists hold every row the grid covers)
+  const int op_head = min((l16 >> 2) * NV + min(l16 & 3, NV - 1), G - 1);               // the head that operand row l16 holds
+  // What depends on the row index alone is requested first, before the row's descriptor is known (the projection buffer holds
+  // every row the grid covers): wave t < T takes the 32-column piece t of the query heads and of the new key, with their rotary
+  // partners and angles, wave VW the new value; the others request nothing here (a load costs the compute unit's address unit 16
+  // cycles whether its data are dropped or not).
+  constexpr int VW = T < NW ? T : NW - 1;
   const float* __restrict__ y = a.y + (size_t)r * a.dqkv;
   const float* __restrict__ rp = a.rope + (size_t)r * DH;
-  const float* __restrict__ yq = y + (size_t)(kvh * G + min(l16, G - 1)) * DH;
+  const float* __restrict__ yq = y + (size_t)(kvh * G + op_head) * DH;
   const float* __restrict__ yk = y + (size_t)(a.H + kvh) * DH;
   const float* __restrict__ yv = y + (size_t)(a.H + a.KVH + kvh) * DH;
-  float vraw[CT];
+  const int d0 = w * 32 + lq * 8, p0 = d0 ^ HALF;
+  float x[8], xp[8], kx[8], kp[8], cs[16], vraw[DH / 64];
+  if (w < T) {                                                   // (scalar)
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) vraw[ct] = yv[ct * 16 + l16];
-  const int tq = min(w, T - 1);                                  // this wave's piece (waves beyond T repeat the last one and drop it)
-  const int d0 = tq * 32 + lq * 8, p0 = d0 ^ HALF;
-  float x[8], xp[8], kx[8], kp[8], cs[16];
+    for (int i = 0; i < 2; ++i) {
+      *reinterpret_cast<float4*>(&x[4 * i]) = reinterpret_cast<const float4*>(yq + d0)[i];
+      *reinterpret_cast<float4*>(&kx[4 * i]) = reinterpret_cast<const float4*>(yk + d0)[i];
+      if (ROPE) {
+        *reinterpret_cast<float4*>(&xp[4 * i]) = reinterpret_cast<const float4*>(yq + p0)[i];
+        *reinterpret_cast<float4*>(&kp[4 * i]) = reinterpret_cast<const float4*>(yk + p0)[i];
+      }
+    }
+    if (ROPE) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const float4 u = reinterpret_cast<const float4*>(yq + d0)[i], v = reinterpret_cast<const float4*>(yq + p0)[i];
-    const float4 ku = reinterpret_cast<const float4*>(yk + d0)[i], kv = reinterpret_cast<const float4*>(yk + p0)[i];
-    x[4 * i] = u.x; x[4 * i + 1] = u.y; x[4 * i + 2] = u.z; x[4 * i + 3] = u.w;
-    xp[4 * i] = v.x; xp[4 * i + 1] = v.y; xp[4 * i + 2] = v.z; xp[4 * i + 3] = v.w;
-    kx[4 * i] = ku.x; kx[4 * i + 1] = ku.y; kx[4 * i + 2] = ku.z; kx[4 * i + 3] = ku.w;
-    kp[4 * i] = kv.x; kp[4 * i + 1] = kv.y; kp[4 * i + 2] = kv.z; kp[4 * i + 3] = kv.w;
+      for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(&cs[4 * i]) = reinterpret_cast<const float4*>(rp + 2 * (d0 % HALF))[i];
+    }
   }
+  if (w == VW) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float4 u = reinterpret_cast<const float4*>(rp + 2 * (d0 % HALF))[i];
-    cs[4 * i] = u.x; cs[4 * i + 1] = u.y; cs[4 * i + 2] = u.z; cs[4 * i + 3] = u.w;
+    for (int i = 0; i < DH / 64; ++i) vraw[i] = yv[i * 64 + lane];
   }
-  if (r >= *a.rd.n_rows) return;
-  const int b = a.rd.b[r], slot = a.rd.slot[r], S = a.max_seq;
+  if (r >= n_rows) return;
   bf16_t* __restrict__ Kc = (bf16_t*)a.kcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
   bf16_t* __restrict__ Vc = (bf16_t*)a.vcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
   const int wz = blockIdx.z * NW + w, NZ = gridDim.z * NW;      // this wave among all that share the keys
@@ -272,46 +266,48 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
   };
   Blk A, B;
   fetch(A, wz * 32);
-  {
+  if (w < T) {
     const bool upper = d0 >= HALF;
     float qv[8], kn[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float c = a.use_rope ? cs[2 * i] : 1.f, sn = a.use_rope ? cs[2 * i + 1] : 0.f;
-      qv[i] = (upper ? x[i] * c + xp[i] * sn : x[i] * c - xp[i] * sn) * a.scale;
-      kn[i] = upper ? kx[i] * c + kp[i] * sn : kx[i] * c - kp[i] * sn;
+      if (ROPE) {
+        const float c = cs[2 * i], sn = cs[2 * i + 1];
+        qv[i] = (upper ? x[i] * c + xp[i] * sn : x[i] * c - xp[i] * sn) * a.scale;
+        kn[i] = upper ? kx[i] * c + kp[i] * sn : kx[i] * c - kp[i] * sn;
+      } else {
+        qv[i] = x[i] * a.scale;
+        kn[i] = kx[i];
+      }
     }
     uint4 qh, ql;
-    u32x4 knew;
     split2(qv[0], qv[1], qh.x, ql.x);
     split2(qv[2], qv[3], qh.y, ql.y);
     split2(qv[4], qv[5], qh.z, ql.z);
     split2(qv[6], qv[7], qh.w, ql.w);
-    knew.x = (unsigned)f2bf(kn[0]) | ((unsigned)f2bf(kn[1]) << 16);
-    knew.y = (unsigned)f2bf(kn[2]) | ((unsigned)f2bf(kn[3]) << 16);
-    knew.z = (unsigned)f2bf(kn[4]) | ((unsigned)f2bf(kn[5]) << 16);
-    knew.w = (unsigned)f2bf(kn[6]) | ((unsigned)f2bf(kn[7]) << 16);
-    if (w < T) {                                                 // (scalar)
-      lds_q[0][tq][lane] = qh;                                   // hi, lo planes of the query operand, for every wave
-      lds_q[1][tq][lane] = ql;
-      if (l16 == 0) {                                            // the new key: into LDS for the row's last block, and into the cache
-        *reinterpret_cast<u32x4*>(lds_kn + d0) = knew;
-        if (blockIdx.z == 0) *reinterpret_cast<u32x4*>(Kc + (size_t)slot * DH + d0) = knew;
-      }
+    lds_q[0][w][lane] = qh;                                      // hi, lo planes of the query operand, for every wave
+    lds_q[1][w][lane] = ql;
+    if (l16 == 0) {                                              // the new key: into LDS for the row's last block, and into the cache
+      const u32x4 knew = {pk_bf16(kn[0], kn[1]), pk_bf16(kn[2], kn[3]), pk_bf16(kn[4], kn[5]), pk_bf16(kn[6], kn[7])};
+      *reinterpret_cast<u32x4*>(lds_kn + d0) = knew;
+      if (blockIdx.z == 0) *reinterpret_cast<u32x4*>(Kc + (size_t)slot * DH + d0) = knew;
     }
   }
-  unsigned vnew[CT / 2];                                         // the new value of columns ct * 16 + l16 as bf16 bits, two per register
+  if (w == VW) {                                                 // the new value likewise
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const unsigned h = f2bf(vraw[ct]);
-    if (wz == 0 && lq == 0) Vc[vt_index(slot, ct * 16 + l16, DH)] = (bf16_t)h;
-    if (ct & 1) vnew[ct >> 1] |= h << 16; else vnew[ct >> 1] = h;
+    for (int i = 0; i < DH / 64; ++i) {
+      const bf16_t h = (bf16_t)pk_bf16(vraw[i], 0.f);
+      lds_vn[i * 64 + lane] = h;
+      if (blockIdx.z == 0) Vc[vt_index(slot, i * 64 + lane, DH)] = h;
+    }
   }
   lds_barrier();                                                 // the query operand and the new key are in LDS for every wave
   f32x4 O[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) O[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float m_run[4] = {NEG, NEG, NEG, NEG}, l_run[4] = {0.f, 0.f, 0.f, 0.f};
+  float m_run[NV], l_run[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) { m_run[v] = NEG; l_run[v] = 0.f; }
   float* myp = lds_p[w];
   auto step = [&](Blk& Bk, int kb) {
     if (kb + 31 >= slot) {                                       // (scalar) the row's last block or beyond: patch the new key in
@@ -334,11 +330,10 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
         sc[tile] = mfma_bf16(lds_q[1][t][lane], kf, sc[tile]);
       }
     }
-    // accumulator register v of lane (lq, l16) is head lq * 4 + v, key kb + tile * 16 + l16
+    // accumulator register v of lane (lq, l16) is head lq * NV + v (beyond G: the last head again), key kb + tile * 16 + l16
+    const bool ok0 = kb + l16 <= slot, ok1 = kb + 16 + l16 <= slot;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int last = (lq * 4 + v < G) ? slot : -1;             // last valid key of accumulator row v (head lq * 4 + v)
-      const bool ok0 = kb + l16 <= last, ok1 = kb + 16 + l16 <= last;
+    for (int v = 0; v < NV; ++v) {
       const float mx = group_max16(fmaxf(ok0 ? sc[0][v] : NEG, ok1 ? sc[1][v] : NEG));
       const float mn = fmaxf(m_run[v], mx);
       const float corr = __expf(m_run[v] - mn);
@@ -347,16 +342,14 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
       m_run[v] = mn;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) O[ct][v] *= corr;
-      if (lq < 2) {                                              // heads 0 .. 7 (rows beyond G hold zeros)
-        myp[(lq * 4 + v) * PS + l16] = p0;
-        myp[(lq * 4 + v) * PS + 16 + l16] = p1;
-      }
+      myp[(lq * NV + v) * PS + l16] = p0;
+      myp[(lq * NV + v) * PS + 16 + l16] = p1;
     }
     __builtin_amdgcn_wave_barrier();                             // LDS operations of one wave complete in order
-    uint4 ph, pl;                                                // P in operand layout: head l16, keys lq * 8 .. + 8
+    uint4 ph, pl;                                                // P in operand layout: row l16's head, keys lq * 8 .. + 8
     {
-      const float4 u = *reinterpret_cast<const float4*>(myp + (l16 & 7) * PS + lq * 8);
-      const float4 x = *reinterpret_cast<const float4*>(myp + (l16 & 7) * PS + lq * 8 + 4);
+      const float* pr = myp + ((l16 >> 2) * NV + min(l16 & 3, NV - 1)) * PS + lq * 8;
+      const float4 u = *reinterpret_cast<const float4*>(pr), x = *reinterpret_cast<const float4*>(pr + 4);
       split2(u.x, u.y, ph.x, pl.x);
       split2(u.z, u.w, ph.y, pl.y);
       split2(x.x, x.y, ph.z, pl.z);
@@ -364,12 +357,17 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
     }
     __builtin_amdgcn_wave_barrier();
     if (kb + 31 >= slot) {                                       // (scalar) new value in, keys beyond the row's last one out
+      const int at = slot - kb - lq * 8;                         // where slot lies among this lane's 8 keys
+      unsigned keep[4], own[4], vnew[CT];
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const unsigned own = (ct & 1) ? (vnew[ct >> 1] >> 16) : (vnew[ct >> 1] & 0xffffu);
-        const uint4 f = vt_fix(make_uint4(Bk.v[ct].x, Bk.v[ct].y, Bk.v[ct].z, Bk.v[ct].w), kb + lq * 8, slot, own);
-        Bk.v[ct].x = f.x; Bk.v[ct].y = f.y; Bk.v[ct].z = f.z; Bk.v[ct].w = f.w;
-      }
+      for (int ct = 0; ct < CT; ++ct) vnew[ct] = lds_vn[ct * 16 + l16] * 0x10001u;
+      vt_first(at, keep);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) own[e] = at == 2 * e ? 0xffffu : at == 2 * e + 1 ? 0xffff0000u : 0u;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Bk.v[ct][e] = (Bk.v[ct][e] & keep[e]) | (vnew[ct] & own[e]);
     }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
@@ -378,7 +376,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
       O[ct] = mfma_bf16(pl, vf, O[ct]);
     }
   };
-  for (int i = 0; i < n_steps; i += 2) {
+  if (DH == 64 && n_steps == 1) step(A, wz * 32);                // (scalar) no second block to request (a third copy spills at 128)
+  else for (int i = 0; i < n_steps; i += 2) {
     const int kb = (i * NZ + wz) * 32;
     fetch(B, kb + 32 * NZ);
     __builtin_amdgcn_sched_barrier(0);
@@ -391,10 +390,10 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  // merge the waves: heads lq * 4 + v < G live in the lanes of the first G / 4 (rounded up) DPP rows
+  // merge the waves: head lq * NV + v lives in the lanes of DPP row lq
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int g = lq * 4 + v;
+  for (int v = 0; v < NV; ++v) {
+    const int g = lq * NV + v;
     if (g < G) {
       if (l16 == 0) { s_ml[w][g][0] = m_run[v]; s_ml[w][g][1] = l_run[v]; }
 #pragma unroll
@@ -428,7 +427,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
 // One workgroup per (query head, row): the n <= 8 partial results of k_attn_dec_bf16, in their order.
 template <int DH>
 __global__ __launch_bounds__(DH) void k_attn_merge(AttnArgs a, int n) {
-  const int h = blockIdx.x, r = blockIdx.y, G = a.H / a.KVH, kvh = h / G, g = h % G, i = threadIdx.x;
+  const int h = blockIdx.x, r = blockIdx.y, G = a.G, kvh = h / G, g = h % G, i = threadIdx.x;
   const float* __restrict__ p = a.split + (((size_t)r * a.KVH + kvh) * n * G + g) * (DH + 2);
   float m[8], l[8], o[8];
 #pragma unroll
@@ -639,7 +638,7 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
   __shared__ uint4 lds_q[2][T][2][64];                           // (in registers the queries spill at 128 columns)
   const int n_rows = *a.rd.n_rows, r0 = (gridDim.y - 1 - blockIdx.y) * E;   // the longest contexts first
   if (r0 >= n_rows) return;
-  const int lane = threadIdx.x, l16 = lane & 15, lq = lane >> 4, S = a.max_seq, G = a.H / a.KVH;
+  const int lane = threadIdx.x, l16 = lane & 15, lq = lane >> 4, S = a.max_seq, G = a.G;
   const int h0 = PAIR ? 2 * blockIdx.x : blockIdx.x, kvh = h0 / G;
   const int n_here = min(E, n_rows - r0), mine = r0 + min(lane, n_here - 1);
   const int e_b = a.rd.b[mine], e_slot = a.rd.slot[mine];        // lane e: entry e's batch row and position in the cache
@@ -727,9 +726,12 @@ __global__ __launch_bounds__(64, 2) void k_attn_mfma_bf16(AttnArgs a) {
         split2(p[6], p[7], ph[s].w, pl[s].w);
       }
       if (kb + 31 > max_slot) {                                  // (scalar) zero the values of keys beyond the run's last one
+        unsigned keep[4];
+        vt_first(max_slot + 1 - kb - lq * 8, keep);
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
-          V[ct] = __builtin_bit_cast(u32x4, vt_fix(__builtin_bit_cast(uint4, V[ct]), kb + lq * 8, max_slot + 1, 0u));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) V[ct][e] &= keep[e];
       }
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
@@ -779,7 +781,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma_shared_bf16(AttnArgs a) {
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   __shared__ u32x4 ring[S][F][64];
   static_assert(S * F == 4 * 2 * T * 2, "the four waves' queries pass through the ring");
-  const int n_rows = *a.rd.n_rows, G = a.H / a.KVH, pairs = G >> 1, E = 64 / pairs;
+  const int n_rows = *a.rd.n_rows, G = a.G, pairs = G >> 1, E = 64 / pairs;
   const int r0 = (gridDim.y - 1 - blockIdx.y) * E;               // the longest contexts first
   if (r0 >= n_rows) return;
   const int lane = threadIdx.x & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4, max_seq = a.max_seq;
@@ -890,9 +892,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma_shared_bf16(AttnArgs a) {
         split2(p[6], p[7], ph[s].w, pl[s].w);
       }
       if (kb + 31 > my_max) {                                    // (scalar) zero the values of keys beyond the wave's last one
+        unsigned keep[4];
+        vt_first(my_max + 1 - kb - lq * 8, keep);
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
-          V[ct] = __builtin_bit_cast(u32x4, vt_fix(__builtin_bit_cast(uint4, V[ct]), kb + lq * 8, my_max + 1, 0u));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) V[ct][e] &= keep[e];
       }
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
@@ -927,7 +932,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma_shared_bf16(AttnArgs a) {
 // do.  A value that is not finite must not reach earlier entries of its group (0 x NaN is NaN): the blocks with the group's own
 // keys are looked through for one; entries that see it get NaN, the products of the others take zeros.  (80 entries in 16 windows of 5, 25 heads of 64, 110 keys: 22.0 us with a pass per entry, 9.9 now; 16 entries of one
 // each: 8.5 and 5.9.)
-template <int DH, int NW>
+template <int DH, int NW, bool ROPE>
 __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
   constexpr int T = DH / 32, CT = DH / 16;
   constexpr float NEG = -1e30f;
@@ -936,18 +941,34 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
   __shared__ float s_ml[NW][16][2];
   __shared__ __attribute__((aligned(16))) float s_o[NW][16][DH + 4];
   const int n_rows = *a.rd.n_rows, r = blockIdx.y, kvh = blockIdx.x;
-  if (r >= n_rows) return;
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4, S = a.max_seq;
-  const int G = a.H / a.KVH, M = 16 / G;
-  // lane i: entry r - 1 + i; the group is entry r and those that continue it up to the next multiple of M
-  const int ri = r - 1 + lane;
+  const int lg = a.lg, G = 1 << lg, M = 16 >> lg;
+  // lane i: entry r - 1 + i; the group is entry r and those that continue it up to the next multiple of M.  The descriptors and the
+  // queries of all M entries that may be in it are requested together, before the row count is known (the buffers hold every row
+  // the grid covers); what belongs to no entry of the group is masked below.
+  const int ri = r - 1 + lane, r_last = (int)gridDim.y - 1;
+  const int at = min(max(ri, 0), r_last), e_b = a.rd.b[at], e_slot = a.rd.slot[at];
+  constexpr int LPR = DH / 4, RPI = 64 / LPR, QI = (16 / RPI + NW - 1) / NW;   // lanes per query, queries per instruction, instructions per wave
+  const int c4 = (lane % LPR) * 4;
+  float4 qx[QI], qp[QI], qc[QI][2];
+#pragma unroll
+  for (int i = 0; i < QI; ++i) {
+    const int col = min((i * NW + w) * RPI + lane / LPR, 15), re = min(r + (col >> lg), r_last);
+    const float* __restrict__ y = a.y + (size_t)re * a.dqkv + (size_t)(kvh * G + (col & (G - 1))) * DH;
+    qx[i] = *reinterpret_cast<const float4*>(y + c4);
+    if (ROPE) {
+      const float4* __restrict__ cs = reinterpret_cast<const float4*>(a.rope + (size_t)re * DH + 2 * (c4 % (DH / 2)));
+      qp[i] = *reinterpret_cast<const float4*>(y + (c4 ^ (DH / 2)));
+      qc[i][0] = cs[0]; qc[i][1] = cs[1];                        // cos, sin, cos, sin
+    }
+  }
+  if (r >= n_rows) return;
   const bool listed = ri >= 0 && ri < n_rows;
-  const int at = min(max(ri, 0), n_rows - 1), e_b = a.rd.b[at], e_slot = a.rd.slot[at];
   const int b = __builtin_amdgcn_readlane(e_b, 1), slot0 = __builtin_amdgcn_readlane(e_slot, 1);
   const u64 follows = __ballot(listed && e_b == b && e_slot == slot0 + lane - 1);
-  if ((follows & 1) && slot0 % M != 0) return;                   // (uniform) entry r - 1's group holds this entry
-  const u64 group = __ballot(lane >= 2 && lane <= M && e_slot % M != 0) & follows;
-  const int n = 1 + __builtin_ctzll(~(group >> 2)), n_col = n * G, max_slot = slot0 + n - 1;
+  if ((follows & 1) && (slot0 & (M - 1)) != 0) return;           // (uniform) entry r - 1's group holds this entry
+  const u64 group = __ballot(lane >= 2 && lane <= M && (e_slot & (M - 1)) != 0) & follows;
+  const int n = 1 + __builtin_ctzll(~(group >> 2)), n_col = n << lg, max_slot = slot0 + n - 1;
   const bf16_t* __restrict__ Kc = (const bf16_t*)a.kcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
   const bf16_t* __restrict__ Vc = (const bf16_t*)a.vcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
   u32x4 K[2][T], V[CT];
@@ -968,18 +989,13 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
   fetch_k(w * 32);
   fetch_v(w * 32);
   {
-    constexpr int LPR = DH / 4, RPI = 64 / LPR;                  // lanes per query, queries per instruction
-    const int c4 = (lane % LPR) * 4;
     const float scale = a.scale * 1.4426950408889634f, sg = c4 >= DH / 2 ? 1.f : -1.f;
 #pragma unroll
-    for (int i = 0; i < (16 / RPI + NW - 1) / NW; ++i) {
-      const int col = (i * NW + w) * RPI + lane / LPR, cc = min(col, n_col - 1), re = r + cc / G;
-      const float* __restrict__ y = a.y + (size_t)re * a.dqkv + (size_t)(kvh * G + cc % G) * DH;
-      float4 x = *reinterpret_cast<const float4*>(y + c4);
-      if (a.use_rope) {                                          // (uniform)
-        const float4 xp = *reinterpret_cast<const float4*>(y + (c4 ^ (DH / 2)));
-        const float4* __restrict__ cs = reinterpret_cast<const float4*>(a.rope + (size_t)re * DH + 2 * (c4 % (DH / 2)));
-        const float4 c = cs[0], d = cs[1];                       // cos, sin, cos, sin
+    for (int i = 0; i < QI; ++i) {
+      const int col = (i * NW + w) * RPI + lane / LPR;
+      float4 x = qx[i];
+      if (ROPE) {
+        const float4 xp = qp[i], c = qc[i][0], d = qc[i][1];
         x.x = x.x * c.x + sg * (xp.x * c.y); x.y = x.y * c.z + sg * (xp.y * c.w);
         x.z = x.z * d.x + sg * (xp.z * d.y); x.w = x.w * d.z + sg * (xp.w * d.w);
       }
@@ -994,7 +1010,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
     }
   }
   lds_barrier();
-  const int slot = l16 < n_col ? slot0 + l16 / G : -1;           // this lane's query; -1: none, every key masked
+  const int slot = l16 < n_col ? slot0 + (l16 >> lg) : -1;           // this lane's query; -1: none, every key masked
   f32x4 O[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) O[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -1033,9 +1049,12 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
     split2(p[4], p[5], ph.z, pl.z);
     split2(p[6], p[7], ph.w, pl.w);
     if (kb + 31 > max_slot) {                                    // (scalar) zero the values of keys beyond the group's last one
+      unsigned keep[4];
+      vt_first(max_slot + 1 - kb - lq * 8, keep);
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
-        V[ct] = __builtin_bit_cast(u32x4, vt_fix(__builtin_bit_cast(uint4, V[ct]), kb + lq * 8, max_slot + 1, 0u));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) V[ct][e] &= keep[e];
     }
     unsigned odd = 0;                                            // an infinity or NaN among the values of a block with the group's own keys:
     if (n > 1 && kb + 31 > slot0) {                              // (scalar) an exponent of all ones carries into the sign's place
@@ -1144,19 +1163,21 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
   dim3 grid(a.KVH, max_rows);
   const bool wide = (long long)a.KVH * max_rows <= 256 && ctx_bound >= 512;
   if (a.phase == 2) {          // attend-only, short runs
-    if (wide) hipLaunchKernelGGL((k_attn_runs_bf16<DH, 8>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_attn_runs_bf16<DH, 4>), grid, dim3(256), 0, s, a);
+#define SPRINTER_RUNS(NW, ROPE) hipLaunchKernelGGL((k_attn_runs_bf16<DH, NW, ROPE>), grid, dim3(NW * 64), 0, s, a)
+    if (a.use_rope) { if (wide) SPRINTER_RUNS(8, true); else SPRINTER_RUNS(4, true); }
+    else { if (wide) SPRINTER_RUNS(8, false); else SPRINTER_RUNS(4, false); }
+#undef SPRINTER_RUNS
     return;
   }
   const int split = attn_split(DH, a.KVH, max_rows, ctx_bound);
-  if (split > 1) {
-    grid.z = split;
-    hipLaunchKernelGGL((k_attn_dec_bf16<DH, 8>), grid, dim3(512), 0, s, a);
-    hipLaunchKernelGGL((k_attn_merge<DH>), dim3(a.H, max_rows), dim3(DH), 0, s, a, split);
-    return;
-  }
-  if (wide) hipLaunchKernelGGL((k_attn_dec_bf16<DH, 8>), grid, dim3(512), 0, s, a);
-  else hipLaunchKernelGGL((k_attn_dec_bf16<DH, 4>), grid, dim3(256), 0, s, a);
+  grid.z = split;
+#define SPRINTER_DEC(NW, NV, ROPE) hipLaunchKernelGGL((k_attn_dec_bf16<DH, NW, NV, ROPE>), grid, dim3(NW * 64), 0, s, a)
+#define SPRINTER_DEC_NW(NV, ROPE) do { if (wide || split > 1) SPRINTER_DEC(8, NV, ROPE); else SPRINTER_DEC(4, NV, ROPE); } while (0)
+  if (G <= 4) { if (a.use_rope) SPRINTER_DEC_NW(1, true); else SPRINTER_DEC_NW(1, false); }
+  else { if (a.use_rope) SPRINTER_DEC_NW(2, true); else SPRINTER_DEC_NW(2, false); }
+#undef SPRINTER_DEC_NW
+#undef SPRINTER_DEC
+  if (split > 1) hipLaunchKernelGGL((k_attn_merge<DH>), dim3(a.H, max_rows), dim3(DH), 0, s, a, split);
 }
 
 template <typename T, int DH>
@@ -1177,7 +1198,7 @@ void launch_attention(int dtype, const ModelDims& md, const float* y, const floa
   AttnArgs a;
   a.phase = (phase == 3 && dtype == 0) ? 2 : phase;      // the run-sharing kernel exists for bf16 only
   a.y = y; a.rope = rope; a.rd = rd; a.kcache = kcache; a.vcache = vcache; a.layer_off = layer_off;
-  a.H = md.H; a.KVH = md.KVH; a.dqkv = md.dqkv; a.max_seq = max_seq; a.use_rope = md.arch == 1;
+  a.H = md.H; a.KVH = md.KVH; a.G = md.H / md.KVH; a.lg = __builtin_ctz(a.G); a.dqkv = md.dqkv; a.max_seq = max_seq; a.use_rope = md.arch == 1;
   a.scale = 1.0f / sqrtf((float)md.dh);
   a.ao = ao; a.ao_K = md.H * md.dh; a.split = split;
   int G = md.H / md.KVH;
