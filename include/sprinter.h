@@ -120,8 +120,9 @@ typedef struct {
  *   0 <= sd_gamma <= 16.
  *   chunk_rows: rows of the activation buffers = entries one pass over the
  *   weights takes in a multi-entry forward (prefill, full-prefix work lists,
- *   speculative-decoding windows).  0 = default (bf16: 4096; float32: 16); else a
- *   multiple of 64 in [64, 4096].  Never below max_batch rounded up. */
+ *   speculative-decoding windows).  0 = default (bf16: 4096; float32: 256, on the
+ *   static workspace 16); else a multiple of 64 in [64, 4096].  Never below max_batch
+ *   rounded up. */
 typedef struct {
   sprinter_model_cfg draft, target;
   int32_t ver_d_in, ver_d_hidden;
@@ -195,8 +196,8 @@ int sprinter_create(const sprinter_cfg* cfg, void* dev_workspace, size_t workspa
  * context made here therefore learns the number of rejected rows through a small device-to-host copy
  * and a stream synchronisation per step instead of a polled pinned word (about 10 us more per step).
  * Weights, prompts and outputs are passed to the later calls as for any other context.
- * Errors: cfg whose sprinter_workspace_bytes exceeds the limit (SPRINTER_E_WORKSPACE, both sizes in
- * the message); a second context of this kind on a device while the first is alive
+ * Errors: cfg whose workspace exceeds the limit (sprinter_workspace_bytes, in float32 mode less what
+ * chunk_rows = 0 stands for beyond 16 rows; SPRINTER_E_WORKSPACE, both sizes in the message); a second context of this kind on a device while the first is alive
  * (SPRINTER_E_STATE): all such contexts of a device share that one array, so they must not overlap
  * - destroy one before creating the next.  The array keeps the previous context's contents; create
  * clears everything that has to start at zero. */
@@ -229,7 +230,7 @@ int sprinter_load_weights(sprinter_ctx* ctx, int which, const char* const* names
  * models in row-major chunks of cfg.chunk_rows tokens per pass over the weights
  * (bf16: matrix-core GEMMs over the whole chunk and causal matrix-core attention
  * over each row's run of positions; float32: the float32 matrix-core GEMMs and
- * one attention workgroup per token and KV head, 16 tokens per pass by default).  The
+ * one attention workgroup per token and KV head, 256 tokens per pass by default).  The
  * stream is drained every 4 passes.  dev_prompt is [B, max_prompt] int32 (padding
  * is never read), host_prompt_len[B] has 1 <= P_b <= max_prompt.  Errors:
  * B > max_batch, P_b out of range, max_prompt > max_seq (or > max_pos), weights

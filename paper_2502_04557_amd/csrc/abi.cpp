@@ -152,7 +152,7 @@ size_t esize(int dtype) { return dtype == SPRINTER_F32 ? 4 : 2; }
 size_t act_elems(int dtype, int rows, int K) { return (size_t)rows * (dtype == SPRINTER_F32 ? K : round_up(K, 32)); }
 size_t packed_elems(int N, int K) { return (size_t)round_up(N, 16) * round_up(K, 32); }
 
-constexpr int DEFAULT_CHUNK_ROWS = 4096;
+constexpr int DEFAULT_CHUNK_ROWS = 4096, DEFAULT_CHUNK_ROWS_F32 = 256, STATIC_CHUNK_ROWS_F32 = 16;
 
 const char* check_model(const sprinter_model_cfg& m, const char* who, char* buf, size_t n) {
 #define BAD(...) do { snprintf(buf, n, __VA_ARGS__); return buf; } while (0)
@@ -296,19 +296,17 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
 
 // Rows the activation buffers hold = entries one pass of a multi-entry forward takes (prefill chunks, full-prefix
 // work lists, speculative-decoding windows).
-int chunk_rows_of(const sprinter_cfg& c) {
+int chunk_rows_of(const sprinter_cfg& c, int want) {
   const int batch_rows = rows_alloc_for(c.target_ctx_mode == 1 ? std::min(2 * c.max_batch, 1024) : c.max_batch);
-  const int want = c.chunk_rows > 0 ? c.chunk_rows : (c.dtype == SPRINTER_BF16 ? DEFAULT_CHUNK_ROWS : 16);
   return std::max(want, batch_rows);
 }
 
-// Lays the whole workspace out; ctx == nullptr only measures.  Returns total bytes.
-size_t carve(const sprinter_cfg& c, void* base, sprinter_ctx* ctx, size_t* scratch_begin, size_t* scratch_end) {
+// Lays the whole workspace out for passes of `want` rows; ctx == nullptr only measures.  Returns total bytes.
+size_t carve_rows(const sprinter_cfg& c, int want, void* base, sprinter_ctx* ctx) {
   Bump bump(base);
   // full-prefix mode: every committed token reaches the target once, so a step's work list averages one entry
   // per batch row with wide swings; buffers for twice the batch keep most steps to a single pass.
-  // bf16: a prefill pass takes DEFAULT_CHUNK_ROWS prompt tokens per pass over the weights unless cfg.chunk_rows says otherwise
-  const int rows = chunk_rows_of(c);
+  const int rows = chunk_rows_of(c, want);
   carve_model(bump, c, c.draft, ctx ? &ctx->draft : nullptr, rows);
   carve_model(bump, c, c.target, ctx ? &ctx->target : nullptr, rows);
   int chunks = verifier_num_chunks(c.ver_d_hidden);
@@ -373,8 +371,15 @@ size_t carve(const sprinter_cfg& c, void* base, sprinter_ctx* ctx, size_t* scrat
     sd.inv_temperature = c.temperature > 0.f ? 1.0f / c.temperature : 0.f;
     ctx->sd = sd; ctx->sd_rd2 = rd2;
   }
-  (void)scratch_begin; (void)scratch_end;
   return total;
+}
+
+// cfg.chunk_rows, or by default DEFAULT_CHUNK_ROWS prompt tokens per pass over the weights in bf16 mode.  In float32 mode a pass is a
+// chain of short launches whatever its rows, so the default is 256 of them (24 prompts of 5 - 60 tokens through 2 + 4 layers: 22
+// passes of 32 rows 4.4 ms, 3 of 256 0.7) - 16 on the static workspace, which is short.
+size_t carve(const sprinter_cfg& c, bool on_static, void* base, sprinter_ctx* ctx) {
+  const int standard = c.dtype == SPRINTER_BF16 ? DEFAULT_CHUNK_ROWS : on_static ? STATIC_CHUNK_ROWS_F32 : DEFAULT_CHUNK_ROWS_F32;
+  return carve_rows(c, c.chunk_rows > 0 ? c.chunk_rows : standard, base, ctx);
 }
 
 // One model forward over the rows described by rd (device-side count).
@@ -656,7 +661,7 @@ int create_common(const sprinter_cfg* cfg, void* dev_workspace, void* hip_stream
   ctx->cfg = *cfg;
   ctx->stream = (hipStream_t)hip_stream;
   ctx->err[0] = 0;
-  carve(*cfg, dev_workspace, ctx, nullptr, nullptr);
+  carve(*cfg, static_dev >= 0, dev_workspace, ctx);
   // verifier tensors
   auto vwant = [&](const char* name, int64_t r, int64_t c, const void** slot) {
     ctx->v_expected.push_back(Expected{name, r, c, false, slot, nullptr, nullptr, nullptr, false});
@@ -713,7 +718,7 @@ int sprinter_workspace_bytes(const sprinter_cfg* cfg, size_t* out_bytes) {
   char buf[256];
   int rc = validate_cfg(cfg, buf, sizeof buf);
   if (rc) return fail(nullptr, rc, "%s", buf);
-  *out_bytes = carve(*cfg, nullptr, nullptr, nullptr, nullptr);
+  *out_bytes = carve(*cfg, false, nullptr, nullptr);
   return SPRINTER_OK;
 }
 
@@ -725,7 +730,7 @@ int sprinter_create(const sprinter_cfg* cfg, void* dev_workspace, size_t workspa
   int rc = validate_cfg(cfg, buf, sizeof buf);
   if (rc) return fail(nullptr, rc, "%s", buf);
   if (((uintptr_t)dev_workspace) & 255) return fail(nullptr, SPRINTER_E_WORKSPACE, "workspace is not 256-byte aligned");
-  size_t need = carve(*cfg, nullptr, nullptr, nullptr, nullptr);
+  size_t need = carve(*cfg, false, nullptr, nullptr);
   if (workspace_bytes < need)
     return fail(nullptr, SPRINTER_E_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
   return create_common(cfg, dev_workspace, hip_stream, -1, out_ctx);
@@ -737,7 +742,7 @@ int sprinter_create_static(const sprinter_cfg* cfg, void* hip_stream, sprinter_c
   char buf[256];
   int rc = validate_cfg(cfg, buf, sizeof buf);
   if (rc) return fail(nullptr, rc, "%s", buf);
-  const size_t need = carve(*cfg, nullptr, nullptr, nullptr, nullptr);
+  const size_t need = carve(*cfg, true, nullptr, nullptr);
   if (need > STATIC_WORKSPACE_BYTES)
     return fail(nullptr, SPRINTER_E_WORKSPACE, "this configuration needs %zu bytes of workspace, the static workspace holds %zu",
                 need, STATIC_WORKSPACE_BYTES);
@@ -856,7 +861,7 @@ int sprinter_prefill(sprinter_ctx* ctx, const int32_t* dev_prompt, const int32_t
     // Chunked prefill: all (row, position) pairs, row-major, go through both models rows_alloc at a time with the
     // kernels of the multi-entry target pass (every layer appends the chunk's keys / values, then attends), so the
     // weights are streamed once per rows_alloc prompt tokens instead of once per position of the batch
-    // (bf16: 4096 tokens per pass through the matrix-core kernels; float32: 16 unless cfg.chunk_rows says otherwise).
+    // (bf16: 4096 tokens per pass through the matrix-core kernels; float32: 256, or cfg.chunk_rows).
     std::vector<int> off((size_t)B + 1, 0);
     for (int b = 0; b < B; ++b) off[b + 1] = off[b] + host_prompt_len[b] - 1;
     const long long E = off[B];
