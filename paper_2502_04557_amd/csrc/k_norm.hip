@@ -71,13 +71,20 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
 // SH = -1: the first norm of a forward; the row is the token's embedding (+ the position's) and starts the residual stream
 // (an embedding launch of its own cost 1.9 - 4.8 us).  The rotary factors of all rows come from workgroups of their own behind the
 // rows' (n_rows_grid of them): their double-precision pow / cos / sin take 2.5 us, next to the rows' norm instead of ahead of it.
+// The row of workgroup id.  An operand tile holds 16 bytes of each of 16 rows side by side, and workgroups go round-robin over the 8
+// XCDs: in order, every 128-byte line was written in pieces by 8 L2s.  Of 128 workgroups, the 16 of an XCD take the 16 rows of a tile.
+// us at 4096 / 1785 / 512 rows, in order -> so: 4096 columns 39.7 / 20.3 / 6.3 -> 28.6 / 12.5 / 4.7, 1600 with 4 shares 34.1 / 15.4 / 5.7 ->
+// 28.1 / 13.7 / 4.7; 199 rows of 4096 4.0 -> 3.2.
+__device__ __forceinline__ int norm_row(int id, int rows) {
+  return id < (rows & ~127) ? (id & ~127) + (id & 7) * 16 + ((id >> 3) & 15) : id;
+}
 template <typename AT, int ARCH, int NI, int SH>
 __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g,
                                                    const float* __restrict__ b, float eps, int d,
                                                    const int* __restrict__ n_rows, AT* __restrict__ act_out,
                                                    float* __restrict__ f32_out, NormPending pend, EmbedSource emb, int n_rows_grid) {
   __shared__ float s_sum[4], s_sq[4];
-  const int r = blockIdx.x, tid = threadIdx.x;
+  const int r = norm_row(blockIdx.x, n_rows_grid), tid = threadIdx.x;
   if constexpr (SH < 0 && ARCH == 1) {
     if (__builtin_expect(r >= n_rows_grid, 0)) {
       const int i = (r - n_rows_grid) * 256 + tid, half = emb.dh >> 1;
