@@ -427,6 +427,17 @@ void forward(sprinter_ctx* ctx, hipStream_t s, Model& m, const RowDesc& rd, int 
   };
   for (int i = 0; i < md.n_layer; ++i) {
     const LayerW& L = m.layers[i];
+    if (!want_head && i + 1 == md.n_layer) {
+      // A prefill position only has to fill the caches: the last layer projects to its key and value columns (their rows of the matrix
+      // begin at a multiple of 64, so at an operand tile of the packed one) and appends them; its queries and attention have no reader.
+      const int nq = md.H * md.dh;
+      norm(L.n1g, L.n1b, sc.xn, nullptr, i == 0 ? &emb : nullptr);
+      launch_gemm(dt, EPI_F32, (const char*)L.wqkv + (size_t)nq * act_elems(dt, 1, md.d) * esize(dt), nullptr, sc.xn, pl_d, rd.n_rows, md.dqkv - nq, md.d,
+                  L.bqkv ? L.bqkv + nq : nullptr, sc.y + nq, md.dqkv, nullptr, md.dqkv, max_rows, s);
+      launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
+                       kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, 1);
+      return;
+    }
     norm_gemm(L.n1g, L.n1b, EPI_F32, L.wqkv, nullptr, md.dqkv, L.bqkv, sc.y, nullptr, i == 0 ? &emb : nullptr);
     if (shared_caches) {
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
@@ -437,13 +448,11 @@ void forward(sprinter_ctx* ctx, hipStream_t s, Model& m, const RowDesc& rd, int 
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
                        kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s);
     }
-    if (!want_head && i + 1 == md.n_layer) break;   // a prefill position only has to fill the caches
     resid_gemm(L.wo, sc.ao, pl_a, md.H * md.dh, L.bo);
     if (md.arch == SPRINTER_ARCH_GPT) norm_gemm(L.n2g, L.n2b, EPI_GELU, L.w1, nullptr, md.ff, L.b1, nullptr, sc.mid);
     else norm_gemm(L.n2g, L.n2b, EPI_SWIGLU, L.wg, L.wu, md.ff, nullptr, nullptr, sc.mid);
     resid_gemm(L.w2, sc.mid, pl_f, md.ff, L.b2);
   }
-  if (!want_head) return;
   norm((const float*)m.normf_g, (const float*)m.normf_b, sc.hfn, sc.hf);
   SamplerArgs sa;
   sa.seed_lo = (unsigned)(ctx->cfg.seed & 0xFFFFFFFFull);
