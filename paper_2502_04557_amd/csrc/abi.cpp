@@ -195,7 +195,7 @@ int validate_cfg(const sprinter_cfg* c, char* buf, size_t n) {
   if (c->sd_gamma < 0 || c->sd_gamma > 16) BAD("sd_gamma %d outside [0, 16]", c->sd_gamma);
   if (c->chunk_rows != 0 && (c->chunk_rows < 64 || c->chunk_rows > 4096 || c->chunk_rows % 64 != 0))
     BAD("chunk_rows %d is not 0 or a multiple of 64 in [64, 4096]", c->chunk_rows);
-  // the float32 attention kernel keeps one score per cached key in LDS; the bf16 kernels keep none
+  // float32 mode is for short contexts: one score per cached key and query head of a KV head, with the operands, in 64 KB
   if (c->dtype == SPRINTER_F32) for (const sprinter_model_cfg* m : {&c->draft, &c->target}) {
     int dh = m->d_model / m->n_head, G = m->n_head / m->n_kv_head;
     size_t lds = (size_t)(G * dh + 2 * dh + 4 * G * dh + G * c->max_seq) * 4;

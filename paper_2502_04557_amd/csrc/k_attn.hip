@@ -18,147 +18,143 @@ struct AttnArgs {
   int phase;   // 0 append + attend, 1 append only, 2 attend only, 3 attend only over long runs of one row (launcher only)
 };
 
-template <typename T, int DH, int G>
-__global__ __launch_bounds__(256) void k_attn(AttnArgs a) {
-  extern __shared__ float smem[];
-  __shared__ float s4[4];
-  __shared__ float s_inv[G];
-  float* qs = smem;                    // [G][DH]
-  float* knew = qs + G * DH;           // [DH]
-  float* vnew = knew + DH;             // [DH]
-  float* red = vnew + DH;              // [4][G][DH]
-  float* sc = red + 4 * G * DH;        // [G][max_seq]
-  const int r = blockIdx.y;
-  if (r >= *a.rd.n_rows) return;
-  const int kvh = blockIdx.x, tid = threadIdx.x;
-  const int b = a.rd.b[r], slot = a.rd.slot[r], nk = slot + 1, S = a.max_seq;
+// float32 mode.  One workgroup of four waves per (row, KV head), which attends for the G query heads that share the KV head in one pass
+// over the cached keys.  A key is a DPP row of 16 lanes, each with DH / 16 consecutive columns; a wave takes blocks of 32 keys - 8 per
+// DPP row - whose keys and values are requested together.  Every DPP row is a stream of its own with its maximum, sum and
+// output columns, so nothing crosses rows or waves before the end, where LDS merges the 16 streams.  Queries, new key and new
+// value are computed from the projection by every wave in the layout it uses them in, without LDS.
+// What bounds it is latency: arguments, then descriptors and projection, then keys and values, then about 200 vector instructions per
+// block.  us per launch, of a kernel with one pass over the keys for the scores, one for the values and barriers and shuffles through
+// LDS in between -> of this one: heads of 64, 1 row of 40 keys 4.5 -> 3.4, 6 rows x 8 heads x 60 keys 6.6 -> 4.1, 24 x 8 x 90 10.9 -> 5.3; of 128,
+// 3 x 8 x 300 43.6 -> 11.2, 8 heads per KV head, 2 x 2 x 500 138 -> 39.  Against 64 bits (2-norm, mean of 20 shapes) 1.22e-7 and 1.24e-7.
+template <int DH, int G, bool ROPE>
+__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
+  constexpr int E = DH / 16, Q4 = E / 4, NK = 8, KB = 4 * NK, HALF = DH / 2;   // columns per lane, float4s of them, keys per stream and block
+  __shared__ float s_m[16][G], s_l[16][G];
+  __shared__ __attribute__((aligned(16))) float s_o[16][G][DH];
+  const int r = blockIdx.y, kvh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
+  const int n_rows = *a.rd.n_rows, b = a.rd.b[r], slot = a.rd.slot[r], S = a.max_seq;   // (the lists hold every row the grid covers)
   const float* __restrict__ y = a.y + (size_t)r * a.dqkv;
-  const float* __restrict__ cs = a.rope + (size_t)r * DH;
-  constexpr int HALF = DH / 2;
-  for (int idx = tid; idx < G * DH; idx += 256) {
-    int g = idx / DH, i = idx % DH;
-    const float* qh = y + (size_t)(kvh * G + g) * DH;
-    float val = qh[i];
-    if (a.use_rope) {
-      int j = i < HALF ? i : i - HALF;
-      float c = cs[2 * j], sn = cs[2 * j + 1];
-      val = i < HALF ? qh[i] * c - qh[i + HALF] * sn : qh[i] * c + qh[i - HALF] * sn;
+  const int d0 = l16 * E, p0 = d0 ^ HALF;
+  const float* __restrict__ yk = y + (size_t)(a.H + kvh) * DH;
+  const float* __restrict__ yv = y + (size_t)(a.H + a.KVH + kvh) * DH;
+  float q[G][E], kn[E], vn[E];
+  {
+    float qp[G][E], kp[E], cs[2 * E];
+    auto load = [&](float (&x)[E], const float* p) {
+#pragma unroll
+      for (int i = 0; i < Q4; ++i) *reinterpret_cast<float4*>(&x[4 * i]) = reinterpret_cast<const float4*>(p)[i];
+    };
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      load(q[g], y + (size_t)(kvh * G + g) * DH + d0);
+      if (ROPE) load(qp[g], y + (size_t)(kvh * G + g) * DH + p0);
     }
-    qs[idx] = val * a.scale;
+    load(kn, yk + d0);
+    load(vn, yv + d0);
+    if (ROPE) {
+      load(kp, yk + p0);
+      const float4* c4 = reinterpret_cast<const float4*>(a.rope + (size_t)r * DH + 2 * (d0 % HALF));
+#pragma unroll
+      for (int i = 0; i < 2 * Q4; ++i) *reinterpret_cast<float4*>(&cs[4 * i]) = c4[i];
+    }
+    if (r >= n_rows) return;
+    const bool upper = d0 >= HALF;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      if (ROPE) {
+        const float c = cs[2 * e], sn = cs[2 * e + 1];
+#pragma unroll
+        for (int g = 0; g < G; ++g) q[g][e] = (upper ? q[g][e] * c + qp[g][e] * sn : q[g][e] * c - qp[g][e] * sn) * a.scale;
+        kn[e] = upper ? kn[e] * c + kp[e] * sn : kn[e] * c - kp[e] * sn;
+      } else {
+#pragma unroll
+        for (int g = 0; g < G; ++g) q[g][e] *= a.scale;
+      }
+    }
   }
-  T* __restrict__ Kc = (T*)a.kcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
-  T* __restrict__ Vc = (T*)a.vcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
-  for (int i = tid; i < DH; i += 256) {
-    const float* kh = y + (size_t)(a.H + kvh) * DH;
-    const float* vh = y + (size_t)(a.H + a.KVH + kvh) * DH;
-    float kv = kh[i];
-    if (a.use_rope) {
-      int j = i < HALF ? i : i - HALF;
-      float c = cs[2 * j], sn = cs[2 * j + 1];
-      kv = i < HALF ? kh[i] * c - kh[i + HALF] * sn : kh[i] * c + kh[i - HALF] * sn;
+  float* __restrict__ Kc = (float*)a.kcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH + d0;
+  float* __restrict__ Vc = (float*)a.vcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH + d0;
+  if (a.phase != 2 && tid < 16) {
+#pragma unroll
+    for (int i = 0; i < Q4; ++i) {
+      reinterpret_cast<float4*>(Kc + (size_t)slot * DH)[i] = *reinterpret_cast<const float4*>(&kn[4 * i]);
+      reinterpret_cast<float4*>(Vc + (size_t)slot * DH)[i] = *reinterpret_cast<const float4*>(&vn[4 * i]);
     }
-    T kt = from_f<T>(kv), vt = from_f<T>(vh[i]);
-    if (a.phase != 2) {
-      Kc[(size_t)slot * DH + i] = kt;
-      Vc[(size_t)slot * DH + i] = vt;
-    }
-    knew[i] = to_f<T>(kt);             // the entry as later steps will read it back
-    vnew[i] = to_f<T>(vt);
   }
   if (a.phase == 1) return;
-  __syncthreads();
-
-  constexpr int EPL = 16 / sizeof(T);  // elements per 16-byte lane load
-  constexpr int LPK = DH / EPL;        // lanes per key
-  constexpr int KPW = 64 / LPK;        // keys per wave per iteration
-  const int lane = tid & 63, w = tid >> 6;
-  const int chunk = lane % LPK, kin = lane / LPK;
-  float qreg[G][EPL];
+  float m[G], l[G], o[G][E];
 #pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) qreg[g][e] = qs[g * DH + chunk * EPL + e];
-
-  // pass 1: scores
-  for (int key0 = w * KPW; key0 < nk; key0 += 4 * KPW) {
-    int key = key0 + kin;
-    float kv[EPL];
-    if (key < slot) {
-      uint4 raw = *reinterpret_cast<const uint4*>(Kc + (size_t)key * DH + chunk * EPL);
-      const T* t = reinterpret_cast<const T*>(&raw);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) kv[e] = to_f<T>(t[e]);
-    } else {
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) kv[e] = (key == slot) ? knew[chunk * EPL + e] : 0.f;
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float p = 0.f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) p += qreg[g][e] * kv[e];
-#pragma unroll
-      for (int o = 1; o < LPK; o <<= 1) p += __shfl_xor(p, o);
-      if (chunk == 0 && key < nk) sc[g * S + key] = p;
-    }
-  }
-  __syncthreads();
-  // softmax over the nk keys of every head
   for (int g = 0; g < G; ++g) {
-    float mx = -INFINITY;
-    for (int k = tid; k < nk; k += 256) mx = fmaxf(mx, sc[g * S + k]);
-    mx = block_max256(mx, s4);
-    float sum = 0.f;
-    for (int k = tid; k < nk; k += 256) {
-      float e = expf(sc[g * S + k] - mx);
-      sc[g * S + k] = e;
-      sum += e;
-    }
-    sum = block_sum256(sum, s4);
-    if (tid == 0) s_inv[g] = 1.0f / sum;
+    m[g] = -INFINITY; l[g] = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) o[g][e] = 0.f;
   }
-  __syncthreads();
-  // pass 2: weighted values
-  float acc[G][EPL];
+  for (int kb = w * KB; kb <= slot; kb += 4 * KB) {              // (scalar) key of stream lq: kb + 4 j + lq
+    float k[NK][E], v[NK][E];
 #pragma unroll
-  for (int g = 0; g < G; ++g)
+    for (int j = 0; j < NK; ++j)
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
-  for (int key0 = w * KPW; key0 < nk; key0 += 4 * KPW) {
-    int key = key0 + kin;
-    float vv[EPL];
-    if (key < slot) {
-      uint4 raw = *reinterpret_cast<const uint4*>(Vc + (size_t)key * DH + chunk * EPL);
-      const T* t = reinterpret_cast<const T*>(&raw);
+      for (int i = 0; i < Q4; ++i) {
+        const size_t off = (size_t)min(kb + 4 * j + lq, slot) * DH;
+        *reinterpret_cast<float4*>(&k[j][4 * i]) = reinterpret_cast<const float4*>(Kc + off)[i];
+        *reinterpret_cast<float4*>(&v[j][4 * i]) = reinterpret_cast<const float4*>(Vc + off)[i];
+      }
+    if (kb + KB > slot) {                                        // (scalar) the row's last block: its own key and value, which the cache may not hold yet
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) vv[e] = to_f<T>(t[e]);
-    } else {
+      for (int j = 0; j < NK; ++j) {
+        const bool own = kb + 4 * j + lq >= slot;                // (and in place of what lies behind: masked below)
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) vv[e] = (key == slot) ? vnew[chunk * EPL + e] : 0.f;
+        for (int e = 0; e < E; ++e) { k[j][e] = own ? kn[e] : k[j][e]; v[j][e] = own ? vn[e] : v[j][e]; }
+      }
     }
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      float p = key < nk ? sc[g * S + key] : 0.f;
+      float s[NK], mx = m[g];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) acc[g][e] += p * vv[e];
+      for (int j = 0; j < NK; ++j) {
+        float d = q[g][0] * k[j][0];
+#pragma unroll
+        for (int e = 1; e < E; ++e) d += q[g][e] * k[j][e];
+        s[j] = kb + 4 * j + lq <= slot ? group_sum<16>(d) : -INFINITY;
+        mx = fmaxf(mx, s[j]);
+      }
+      if (kb + lq <= slot) {                                     // (the same in a stream's 16 lanes) it has a key in this block
+        const float corr = expf(m[g] - mx);
+        m[g] = mx;
+        l[g] *= corr;
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[g][e] *= corr;
+#pragma unroll
+        for (int j = 0; j < NK; ++j) {
+          const float p = expf(s[j] - mx);
+          l[g] += p;
+#pragma unroll
+          for (int e = 0; e < E; ++e) o[g][e] += p * v[j][e];
+        }
+      }
     }
   }
+  const int st = w * 4 + lq;
 #pragma unroll
-  for (int g = 0; g < G; ++g)
+  for (int g = 0; g < G; ++g) {
+    if (l16 == 0) { s_m[st][g] = m[g]; s_l[st][g] = l[g]; }
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      float v = acc[g][e];
-#pragma unroll
-      for (int o = LPK; o < 64; o <<= 1) v += __shfl_xor(v, o);
-      if (kin == 0) red[(w * G + g) * DH + chunk * EPL + e] = v;
-    }
+    for (int i = 0; i < Q4; ++i) *reinterpret_cast<float4*>(&s_o[st][g][d0 + 4 * i]) = *reinterpret_cast<const float4*>(&o[g][4 * i]);
+  }
   __syncthreads();
-  T* __restrict__ ao = (T*)a.ao;
   for (int idx = tid; idx < G * DH; idx += 256) {
-    int g = idx / DH;
-    float o = ((red[idx] + red[G * DH + idx]) + red[2 * G * DH + idx]) + red[3 * G * DH + idx];
-    o *= s_inv[g];
-    act_store<T>(ao, r, kvh * G * DH + idx, a.ao_K, o);
+    const int g = idx / DH, i = idx % DH;
+    float mx = s_m[0][g], den = 0.f, num = 0.f;                  // (stream 0 has key 0)
+#pragma unroll
+    for (int t = 1; t < 16; ++t) mx = fmaxf(mx, s_m[t][g]);
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const float c = expf(s_m[t][g] - mx);
+      den += c * s_l[t][g];
+      num += c * s_o[t][g][i];
+    }
+    act_store<float>((float*)a.ao, r, kvh * G * DH + idx, a.ao_K, num / den);
   }
 }
 
@@ -1115,10 +1111,6 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
   }
 }
 
-static size_t attn_smem_bytes(int DH, int G, int max_seq) {
-  return (size_t)(G * DH + 2 * DH + 4 * G * DH + G * max_seq) * sizeof(float);
-}
-
 // A compute unit pulls at most 48 KB/us, so one workgroup needs 21 us for 2000 keys of 128 columns: few rows with long contexts
 // share the keys over as many workgroups as the compute units allow, at the price of a merge launch.  Both launches together, one
 // workgroup / split, 8 KV heads of 128 columns: 4 rows (split 8) at 1024 keys 19.0 / 13.2 us, 2016 29.9 / 14.6; 16 rows (2) at 1024
@@ -1186,16 +1178,18 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
   if (split > 1) hipLaunchKernelGGL((k_attn_merge<DH>), dim3(a.H, max_rows), dim3(DH), 0, s, a, split);
 }
 
-template <typename T, int DH>
-static void launch_attn_g(const AttnArgs& a, int G, int max_rows, hipStream_t s) {
-  dim3 grid(a.KVH, max_rows), block(256);
-  size_t sm = attn_smem_bytes(DH, G, a.max_seq);
-  switch (G) {
-    case 1: hipLaunchKernelGGL((k_attn<T, DH, 1>), grid, block, sm, s, a); break;
-    case 2: hipLaunchKernelGGL((k_attn<T, DH, 2>), grid, block, sm, s, a); break;
-    case 4: hipLaunchKernelGGL((k_attn<T, DH, 4>), grid, block, sm, s, a); break;
-    default: hipLaunchKernelGGL((k_attn<T, DH, 8>), grid, block, sm, s, a); break;
+template <int DH>
+static void launch_attn_f32(const AttnArgs& a, int max_rows, hipStream_t s) {
+  const dim3 grid(a.KVH, max_rows);
+#define SPRINTER_AF32(G) do { if (a.use_rope) hipLaunchKernelGGL((k_attn_f32<DH, G, true>), grid, dim3(256), 0, s, a); \
+                              else hipLaunchKernelGGL((k_attn_f32<DH, G, false>), grid, dim3(256), 0, s, a); } while (0)
+  switch (a.G) {
+    case 1: SPRINTER_AF32(1); break;
+    case 2: SPRINTER_AF32(2); break;
+    case 4: SPRINTER_AF32(4); break;
+    default: SPRINTER_AF32(8); break;
   }
+#undef SPRINTER_AF32
 }
 
 void launch_attention(int dtype, const ModelDims& md, const float* y, const float* rope, const RowDesc& rd,
@@ -1209,7 +1203,7 @@ void launch_attention(int dtype, const ModelDims& md, const float* y, const floa
   a.ao = ao; a.ao_K = md.H * md.dh; a.split = split;
   int G = md.H / md.KVH;
   if (dtype == 0) {
-    if (md.dh == 64) launch_attn_g<float, 64>(a, G, max_rows, s); else launch_attn_g<float, 128>(a, G, max_rows, s);
+    if (md.dh == 64) launch_attn_f32<64>(a, max_rows, s); else launch_attn_f32<128>(a, max_rows, s);
   } else {
     if (md.dh == 64) launch_attn_bf16<64>(a, G, max_rows, ctx_bound, run_len, s); else launch_attn_bf16<128>(a, G, max_rows, ctx_bound, run_len, s);
   }
