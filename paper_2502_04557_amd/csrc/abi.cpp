@@ -401,6 +401,11 @@ void forward(sprinter_ctx* ctx, hipStream_t s, Model& m, const RowDesc& rd, int 
   const size_t part_stride = (size_t)rows * md.d;
   // a few rows: the norms before QKV and FFN-up are part of those launches
   const bool fused = !shared_caches && gemm_takes_norm(md.d, max_rows);
+  // Short passes (work lists, speculative windows) of a model without rotary positions: the projection's epilogue puts keys and values
+  // where the append launch would.  (A key's rotary partner is another workgroup's; and a prefill pass gathers 8 slots of a value column
+  // into one store in that launch, where an epilogue would write 2 bytes at a time.)
+  // The append launch was 4.1 us per layer of 25 heads of 64 at 24 - 80 entries, next to 45 - 60 us of the others.
+  const bool append_in_qkv = shared_caches && run_len == 0 && dt == SPRINTER_BF16 && md.arch == SPRINTER_ARCH_GPT;
   float *h = sc.h, *h_other = sc.h2;
   NormPending pend{sc.part, part_stride, 0, nullptr};
   auto resid_gemm = [&](const void* W, const void* X, size_t plane, int K, const float* bias) {
@@ -438,10 +443,18 @@ void forward(sprinter_ctx* ctx, hipStream_t s, Model& m, const RowDesc& rd, int 
                        kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, 1);
       return;
     }
-    norm_gemm(L.n1g, L.n1b, EPI_F32, L.wqkv, nullptr, md.dqkv, L.bqkv, sc.y, nullptr, i == 0 ? &emb : nullptr);
+    if (append_in_qkv) {
+      const size_t at = m.layer_stride * i * esize(dt);
+      const KvDest kv{(char*)m.kcache + at, (char*)m.vcache + at, rd.b, rd.slot, md.H * md.dh, md.KVH * md.dh, md.dh, md.KVH, kv_slots(ctx->cfg)};
+      norm(L.n1g, L.n1b, sc.xn, nullptr, i == 0 ? &emb : nullptr);
+      launch_gemm_qkv(L.wqkv, sc.xn, pl_d, rd.n_rows, md.dqkv, md.d, L.bqkv, sc.y, kv, max_rows, s);
+    } else {
+      norm_gemm(L.n1g, L.n1b, EPI_F32, L.wqkv, nullptr, md.dqkv, L.bqkv, sc.y, nullptr, i == 0 ? &emb : nullptr);
+    }
     if (shared_caches) {
-      launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
-                       kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, 1);
+      if (!append_in_qkv)
+        launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
+                         kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, 1);
       launch_attention(dt, md, sc.y, sc.rope, rd, m.kcache, m.vcache, m.layer_stride * i, ctx->max_prompt_len + (int)ctx->steps_done,
                        kv_slots(ctx->cfg), sc.ao, max_rows, sc.part, s, run_len > 0 ? 3 : 2, run_len);
     } else {

@@ -96,6 +96,15 @@ __device__ __forceinline__ void rope_factors(const EmbedSource& e, int r, int k)
   const double ang = (double)e.rd.pos[r] * inv;
   reinterpret_cast<float2*>(e.rope + (size_t)r * e.dh)[k] = make_float2((float)cos(ang), (float)sin(ang));
 }
+// Layout of the bf16 value cache.  The key cache is row-major [slot][DH]: a row is already what the matrix
+// instruction wants for S = Q K^T (contraction over DH).  O = P V contracts over the keys, so the values are kept
+// as operand tiles of V^T: per (row, KV head) blocks of 32 slots, a block holds DH / 16 tiles of 16 columns x 32
+// keys (1 KiB, lane = (key % 32) / 8 * 16 + column % 16, 8 consecutive keys per lane).  A wave then fetches a
+// value tile with one coalesced 16-byte-per-lane load and feeds it to the MFMA unchanged; appending one key is
+// DH scattered 2-byte stores.  Slots per (row, KV head) are a multiple of 32 (AttnArgs::max_seq in bf16 mode).
+__device__ __forceinline__ size_t vt_index(int slot, int d, int DH) {
+  return (size_t)(slot >> 5) * (size_t)(32 * DH) + (size_t)(d >> 4) * 512 + (size_t)(((((slot & 31) >> 3) << 4) + (d & 15)) * 8 + (slot & 7));
+}
 // The library's tanhf / expf and an IEEE division, also where the result is rounded to float16 next: the hardware's exp2 and reciprocal
 // without corrections (2 x 14336 x 4096 at 4096 rows 722 -> 693 us, GELU 2032 x 6400 x 1600 54 -> 48) put SiLU's error (2-norm against 64
 // bits) at 1.2e-7 for 3.6e-8 on -6 .. -3 and 2.1e-7 for 3.5e-8 on -12 .. -6, and five times as many stored values beside the right one.

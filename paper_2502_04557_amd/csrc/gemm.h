@@ -12,14 +12,24 @@ struct GemmArgs {
   const float* bias; float* out_f32; int ldo; void* out_act; int out_K;
   size_t x_elems;     // elements the activation buffer X holds (bf16 mode)
   int SK; float* part; size_t part_stride;   // k_gemm16_part: K shares, partial outputs [SK][rows][N], floats per share
+  KvDest kv;          // EPI_QKV
   int rows_live;      // the host's bound on the row count: rows from here on exist in no launch, their activations are not fetched
 };
 
-// bias: the column's bias (0 if none)
+// EPI_QKV: column n >= q_cols of an entry whose cache slot is (b, slot): its key or value element.  The values are bf16 bits.
+__device__ __forceinline__ bf16_t* kv_element(const KvDest& d, int b, int slot, int n) {
+  const bool v = n >= d.q_cols + d.kv_cols;
+  const int c = n - d.q_cols - (v ? d.kv_cols : 0), head = c >> (d.dh == 128 ? 7 : 6), i = c & (d.dh - 1);   // (heads of 64 or 128)
+  const size_t row = ((size_t)b * d.KVH + head) * (size_t)d.S * d.dh;
+  return v ? (bf16_t*)d.vcache + row + vt_index(slot, i, d.dh) : (bf16_t*)d.kcache + row + (size_t)slot * d.dh + i;
+}
+
+// bias: the column's bias (0 if none); b, slot: EPI_QKV
 template <int EPI, typename AT>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int m, int n, float v, float v2, float bias) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int n_rows, int m, int n, float v, float v2, float bias, int b = 0, int slot = 0) {
   if (m >= n_rows || n >= a.N) return;
-  if (EPI == EPI_F32) a.out_f32[(size_t)m * a.ldo + n] = v + bias;
+  if (EPI == EPI_F32 || (EPI == EPI_QKV && n < a.kv.q_cols)) a.out_f32[(size_t)m * a.ldo + n] = v + bias;
+  else if (EPI == EPI_QKV) *kv_element(a.kv, b, slot, n) = f2bf(v + bias);
   else if (EPI == EPI_GELU) act_store<AT>((AT*)a.out_act, m, n, a.out_K, gelu_tanh(v + bias));
   else act_store<AT>((AT*)a.out_act, m, n, a.out_K, silu(v) * v2);
 }

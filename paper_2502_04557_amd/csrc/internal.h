@@ -78,12 +78,19 @@ void launch_norm(int dtype, int arch, const float* h, const float* g, const floa
 int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,
                      size_t part_stride, int max_shares, const float* bias, float* h, int max_rows, hipStream_t s);
 
-enum { EPI_F32 = 0, EPI_GELU = 2, EPI_SWIGLU = 3, EPI_PART = 4 /* partial product of one K share */, EPI_RESID = 5 /* out += bias + product */ };
+enum { EPI_F32 = 0, EPI_GELU = 2, EPI_SWIGLU = 3, EPI_PART = 4 /* partial product of one K share */, EPI_RESID = 5 /* out += bias + product */,
+       EPI_QKV = 6 /* queries to out, keys and values to the caches */ };
+// Where EPI_QKV puts columns [q_cols, q_cols + kv_cols) (keys) and the kv_cols behind them (values) of row m: slot[m] of batch row b[m]
+// of the bf16 caches of one layer, as launch_attention's phase 1 does where the model has no rotary positions.
+struct KvDest { void *kcache, *vcache; const int *b, *slot; int q_cols, kv_cols, dh, KVH, S; };
 // Y[M,N] = X[M,K] W[N,K]^T (+bias) with epilogue; X in activation layout, W in weight layout.
 // x_elems: elements the activation buffer X holds (its row tiles bound what a kernel may fetch).
 void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* X, size_t x_elems,
                  const int* n_rows, int N, int K, const float* bias, float* out_f32, int ldo, void* out_act,
                  int out_K, int max_rows, hipStream_t s);
+// The QKV projection with EPI_QKV (bf16 mode): y[M, N] holds the queries, the rest of its columns is not written.
+void launch_gemm_qkv(const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, const float* bias, float* y,
+                     const KvDest& kv, int max_rows, hipStream_t s);
 
 // QKV / FFN-up of a few rows with the norm before it in the same launch (k_gemm_norm.hip): X = norm(h_in + pending) or
 // norm(embedding); the updated residual rows go to h_out (a buffer other than h_in).  At most 4 pending shares.

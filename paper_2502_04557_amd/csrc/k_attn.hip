@@ -158,15 +158,6 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
   }
 }
 
-// Layout of the bf16 value cache.  The key cache is row-major [slot][DH]: a row is already what the matrix
-// instruction wants for S = Q K^T (contraction over DH).  O = P V contracts over the keys, so the values are kept
-// as operand tiles of V^T: per (row, KV head) blocks of 32 slots, a block holds DH / 16 tiles of 16 columns x 32
-// keys (1 KiB, lane = (key % 32) / 8 * 16 + column % 16, 8 consecutive keys per lane).  A wave then fetches a
-// value tile with one coalesced 16-byte-per-lane load and feeds it to the MFMA unchanged; appending one key is
-// DH scattered 2-byte stores.  Slots per (row, KV head) are a multiple of 32 (AttnArgs::max_seq in bf16 mode).
-__device__ __forceinline__ size_t vt_index(int slot, int d, int DH) {
-  return (size_t)(slot >> 5) * (size_t)(32 * DH) + (size_t)(d >> 4) * 512 + (size_t)(((((slot & 31) >> 3) << 4) + (d & 15)) * 8 + (slot & 7));
-}
 // A value tile's operand piece is 8 consecutive keys of one column, two a register: masks of its first n keys.  The keys beyond a
 // row's last one are cleared with them (the cache may hold anything there, and 0 x NaN is NaN on the matrix cores).
 __device__ __forceinline__ void vt_first(int n, unsigned (&keep)[4]) {

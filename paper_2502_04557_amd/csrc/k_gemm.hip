@@ -67,6 +67,8 @@ __global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
   const int n = nt0 * 16 + c;
   const bool n_ok = tid < NOUT && n < a.N;
   const float pbias = (n_ok && a.bias) ? a.bias[n] : 0.f;
+  int kv_b = 0, kv_slot = 0;
+  if (EPI == EPI_QKV) { const int mc = min(m, a.rows_live - 1); kv_b = a.kv.b[mc]; kv_slot = a.kv.slot[mc]; }
   // (The row count is only needed by the epilogue: launches are sized by the host for rows that exist, so the loop
   // does not wait for it.)
   const int n_rows = *a.n_rows;
@@ -113,7 +115,7 @@ __global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
     s1 += red[((size_t)q * NI2 + it) * 64 + sl];
     if (DUAL) s2 += red[((size_t)q * NI2 + NI + it) * 64 + sl];
   }
-  gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, pbias);
+  gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, pbias, kv_b, kv_slot);
 }
 
 // bf16-mode GEMM for 17 .. 64 rows (MT row tiles of 16) of outputs too narrow for k_gemm_tile, NTW column tiles per workgroup,
@@ -190,6 +192,15 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) A.xh[u][mt] = B.xh[u][mt] = make_uint4(0u, 0u, 0u, 0u);
   load(A, min(kw, Kt - 1));
+  constexpr int NO = (MT * NTW + 1) / 2;                      // output elements per thread
+  int kv_b[EPI == EPI_QKV ? NO : 1] = {0}, kv_slot[EPI == EPI_QKV ? NO : 1] = {0};
+  if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+      const int mc = min((i * 512 + (int)threadIdx.x) / (16 * NTW), a.rows_live - 1);
+      kv_b[i] = a.kv.b[mc]; kv_slot[i] = a.kv.slot[mc];
+    }
+  }
   const int n_rows = *a.n_rows;                               // only the epilogue needs it (passes are sized by the host)
   // (the scheduling barriers keep the compiler from sinking a buffer's loads down to their first use)
   for (int kt = kw; kt < Kt; kt += 2 * STEP) {
@@ -240,7 +251,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
   __syncthreads();
   constexpr bool ACT_OUT = (EPI == EPI_GELU || EPI == EPI_SWIGLU);
 #pragma unroll
-  for (int i = 0; i < (MT * NTW + 1) / 2; ++i) {
+  for (int i = 0; i < NO; ++i) {
     const int o = i * 512 + (int)threadIdx.x;        // element index among the MT*16 x NTW*16 outputs
     if (o >= 256 * MT * NTW) break;
     int mt, m16, c;
@@ -257,7 +268,7 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
     const float s2 = DUAL ? red[(((NTW + j) * MT + mt) * 4 + v) * 64 + sl] : 0.f;
     if (m >= n_rows || n >= a.N) continue;
     const float bias = a.bias ? a.bias[n] : 0.f;
-    gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias);
+    gemm_epilogue<EPI, bf16_t>(a, n_rows, m, n, s1, s2, bias, kv_b[EPI == EPI_QKV ? i : 0], kv_slot[EPI == EPI_QKV ? i : 0]);
   }
 }
 
@@ -491,6 +502,15 @@ void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* 
       default: launch_gemm_bf16<EPI_SWIGLU>(a, max_rows, s); break;
     }
   }
+}
+
+void launch_gemm_qkv(const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, const float* bias, float* y,
+                     const KvDest& kv, int max_rows, hipStream_t s) {
+  GemmArgs a;
+  memset(&a, 0, sizeof a);
+  a.W = W; a.X = X; a.x_elems = x_elems; a.n_rows = n_rows; a.N = N; a.K = K; a.Kt = (K + 31) / 32; a.n_tiles = (N + 15) / 16;
+  a.bias = bias; a.out_f32 = y; a.ldo = N; a.kv = kv; a.rows_live = max_rows;
+  launch_gemm_bf16<EPI_QKV>(a, max_rows, s);
 }
 
 int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, float* part,

@@ -123,6 +123,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
     __builtin_amdgcn_sched_group_barrier(0x008, MT * NT, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
+  int kv_b[EPI == EPI_QKV ? MT : 1], kv_slot[EPI == EPI_QKV ? MT : 1];   // the cache slots of this lane's rows
+  if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      const int mc = min((bm * TMT + wm * MT + i) * 16 + (lane & 15), a.rows_live - 1);
+      kv_b[i] = a.kv.b[mc]; kv_slot[i] = a.kv.slot[mc];
+    }
+  }
 #pragma unroll
   for (int i = 0; i < S - 1; ++i) issue(k0 + i);
   const int n_rows = *a.n_rows;                         // only the epilogue needs it
@@ -298,6 +306,18 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
       } else if constexpr (EPI == EPI_RESID) {          // the norm's order: row, bias, product
         *reinterpret_cast<float4*>(a.out_f32 + (size_t)m * a.ldo + n) = make_float4((own[i].x + bias.x) + c[0], (own[i].y + bias.y) + c[1],
                                                                                      (own[i].z + bias.z) + c[2], (own[i].w + bias.w) + c[3]);
+      } else if constexpr (EPI == EPI_QKV) {
+        const float o[4] = {c[0] + bias.x, c[1] + bias.y, c[2] + bias.z, c[3] + bias.w};
+        if (n < a.kv.q_cols) {                          // (the three parts and a head are multiples of 4 columns)
+          *reinterpret_cast<float4*>(a.out_f32 + (size_t)m * a.ldo + n) = make_float4(o[0], o[1], o[2], o[3]);
+        } else {
+          bf16_t* p = kv_element(a.kv, kv_b[i], kv_slot[i], n);
+          if (n < a.kv.q_cols + a.kv.kv_cols) *reinterpret_cast<uint2*>(p) = make_uint2(pk_bf16(o[0], o[1]), pk_bf16(o[2], o[3]));
+          else {                                        // (columns of a value tile are 8 elements apart)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[8 * e] = f2bf(o[e]);
+          }
+        }
       } else if constexpr (EPI == EPI_F32) {
         *reinterpret_cast<float4*>(a.out_f32 + (size_t)m * a.ldo + n) =
             make_float4(c[0] + bias.x, c[1] + bias.y, c[2] + bias.z, c[3] + bias.w);
@@ -396,7 +416,7 @@ int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares) {
 template <int EPI>
 static void launch_tile_epi(int tile, const GemmArgs& a, int rows, int sk, hipStream_t s) {
   switch (tile) {
-    case 0: launch_tile<std::conditional_t<EPI == EPI_GELU, TileG, TileL>, EPI>(a, rows, sk, s); break;
+    case 0: launch_tile<std::conditional_t<EPI == EPI_GELU || EPI == EPI_QKV, TileG, TileL>, EPI>(a, rows, sk, s); break;
     case 1: launch_tile<TileM, EPI>(a, rows, sk, s); break;
     case 2: launch_tile<TileS, EPI>(a, rows, sk, s); break;
     case 3: launch_tile<TileX, EPI>(a, rows, sk, s); break;
@@ -426,6 +446,7 @@ int launch_gemm_tile(int epi, const GemmArgs& a, int rows, int max_shares, hipSt
   switch (epi) {
     case EPI_F32: launch_tile_epi<EPI_F32>(tile, a, rows, 1, s); return 1;
     case EPI_GELU: launch_tile_epi<EPI_GELU>(tile, a, rows, 1, s); return 1;
+    case EPI_QKV: launch_tile_epi<EPI_QKV>(tile, a, rows, 1, s); return 1;
     case EPI_SWIGLU: launch_tile_epi<EPI_SWIGLU>(tile, a, rows, 1, s); return 1;
   }
   if (sk > 1) { launch_tile_epi<EPI_PART>(tile, a, rows, sk, s); return sk; }
