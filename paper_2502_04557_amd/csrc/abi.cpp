@@ -226,12 +226,12 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
   void* vc = bump.take(layer_stride * md.n_layer * es);
   ModelScratch sc;
   sc.h = (float*)bump.take((size_t)rows * md.d * 4);
-  sc.h2 = sc.h + (size_t)4 * md.d;       // (rows >= 16; only passes of at most 4 rows use it)
   sc.xn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.y = (float*)bump.take((size_t)rows * md.dqkv * 4);
   sc.ao = bump.take(act_elems(c.dtype, rows, md.H * md.dh) * es);
   sc.mid = bump.take(act_elems(c.dtype, rows, md.ff) * es);
   sc.hf = (float*)bump.take((size_t)rows * md.d * 4);
+  sc.h2 = sc.hf;                         // (a pass writes hf at its very end, when the rows are back in h: two exchanges per layer)
   sc.hfn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.rope = (float*)bump.take((size_t)rows * md.dh * 4);
   // also the scratch of a split attention, which is the smaller one: bf16 buffers hold 64 rows or more, 512 d >= 256 (H / KVH) (dh + 2)

@@ -37,7 +37,7 @@ struct ModelDims {
 constexpr int PART_SHARES = 8;   // most K shares launch_gemm_part may use
 struct ModelScratch {  // per-model activation buffers, sized for max_batch rows
   float* h;            // [M, d] residual stream, float32
-  float* h2;           // [4, d] a few rows' residual stream: launch_gemm_norm alternates between rows 0 .. 3 of h and this, its rows 4 .. 7
+  float* h2;           // a few rows' residual stream: launch_gemm_norm alternates between h and this, which is hf
   void* xn;            // [M, d] normalised GEMM input (activation layout)
   float* y;            // [M, dqkv] QKV projection output, float32
   void* ao;            // [M, H*dh] attention output (activation layout)

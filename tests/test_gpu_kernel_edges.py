@@ -63,6 +63,16 @@ def test_norm_inside_the_product(B, dtype):
     _check(_llama(3, 640, 10, 5, 136, 83), _gpt(2, 2048 if B == 2 else 1024, 4232, 83), B, dtype, tau=1.5)
 
 
+@pytest.mark.parametrize("dtype", [W.DT_F32, W.DT_BF16])
+@pytest.mark.parametrize("B", [5, 8, 9, 12, 13, 16, 17])
+def test_norm_inside_the_product_of_narrow_models(B, dtype):
+    """Up to 512 columns the norm is folded in up to 16 rows, four groups of threads with 2, 3 or 4 rows each: the first and last row
+    counts of each, one row beyond, rows of 128 to 512 columns (a group's threads from a quarter to all in use), heads of 128
+    with rotary factors for 16 rows, column tiles in pairs."""
+    _check(_gpt(2, 128, 200, 83), _llama(3, 512, 4, 2, 4104, 83), B, dtype, tau=1.5)
+    _check(_llama(2, 320, 5, 5, 136, 83), _gpt(2, 448, 4232, 83), B, dtype, tau=1.5)
+
+
 @pytest.mark.parametrize("B, prompt_len", [(7, 20), (9, 59), (8, 114)])
 def test_tiles_of_many_rows(B, prompt_len):
     """Prefill passes of 133, 522 and 904 rows (none a multiple of a tile): the 32- and 64-row tiles with K shares, at 904 rows also the
