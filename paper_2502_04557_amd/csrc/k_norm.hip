@@ -200,12 +200,95 @@ __global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const
   }
 }
 
+// The same for the many rows of a prefill pass (bf16 mode, activations only, nothing pending), a row per wave and four rows per workgroup: no barrier
+// stands between a row's loads and its statistics, and the float16 rows leave through LDS, four rows of a tile side by side - 64
+// bytes to an address, where a row alone has 16.  The columns, and with them the order of every sum, are those of k_norm: chunk
+// 256 i + 64 v + lane is thread 64 v + lane's i-th there.  LDS slot of (chunk c, row r): 4 c + (r ^ (c / 4 % 4)), which spreads a wave's
+// stores over the banks.  What bounds it: 100 MB at 4096 x 4096 take 17 us at the rate of a copy, it 24.
+template <int ARCH, int NI>
+__global__ __launch_bounds__(256) void k_norm_rows(const float* __restrict__ h, const float* __restrict__ g, const float* __restrict__ b,
+                                                   float eps, int d, const int* __restrict__ n_rows, bf16_t* __restrict__ act_out, int groups) {
+  extern __shared__ __align__(16) uint4 tile[];
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), id = blockIdx.x;
+  // the 4 workgroups of a row tile on one XCD
+  const int grp = id < (groups & ~31) ? (id & ~31) + (id & 7) * 4 + ((id >> 3) & 3) : id, r0 = grp * 4, r = r0 + w;
+  const int n = *n_rows, n_chunks = d >> 3;
+  if (r0 >= n) return;
+  if (r < n) {                                       // (scalar)
+    const float* __restrict__ hrow = h + (size_t)r * d;
+    float x[NI][4][8];
+    auto chunk = [&](int i, int v) { return min(i * 256 + v * 64 + lane, n_chunks - 1); };
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) load_row(hrow + chunk(i, v) * 8, x[i][v]);
+    auto total = [&](const float (&s)[4]) {
+      float t[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) t[v] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(wave_total(s[v])), 63));
+      return ((t[0] + t[1]) + t[2]) + t[3];
+    };
+    float s[4] = {0.f, 0.f, 0.f, 0.f}, mean = 0.f;
+    if (ARCH == 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s[v] += i * 256 + v * 64 + lane < n_chunks ? x[i][v][e] : 0.f;
+      mean = total(s) / (float)d;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      s[v] = 0.f;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { const float c = i * 256 + v * 64 + lane < n_chunks ? x[i][v][e] - mean : 0.f; s[v] += c * c; }
+    }
+    const float rstd = 1.0f / sqrtf(total(s) / (float)d + eps);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int c = i * 256 + v * 64 + lane;
+        float gg[8], bb[8], o[8];
+        load_row(g + chunk(i, v) * 8, gg);
+        if (ARCH == 0) load_row(b + chunk(i, v) * 8, bb);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          o[e] = (x[i][v][e] - mean) * rstd * gg[e];
+          if (ARCH == 0) o[e] += bb[e];
+        }
+        if (c < n_chunks) tile[c * 4 + (w ^ ((c >> 2) & 3))] = make_uint4(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]), pk_f16(o[4], o[5]), pk_f16(o[6], o[7]));
+      }
+  }
+  __syncthreads();
+  const int Kt = (d + 31) >> 5, row = tid & 3;
+  if (r0 + row >= n) return;
+  for (int c = tid >> 2; c < n_chunks; c += 64) {
+    const size_t slot = ((size_t)(r0 >> 4) * Kt + (c >> 2)) * 512 + (((c & 3) << 4) + (r0 & 15) + row) * 8;
+    *reinterpret_cast<uint4*>(act_out + slot) = tile[c * 4 + (row ^ ((c >> 2) & 3))];
+  }
+}
+
+// k_norm_rows / k_norm, us: 4096 rows of 4096 columns 24.2 / 28.7, 2048 12.1 / 15.3, 768 5.8 / 6.2; 1785 rows of 4096 10.4 / 12.5, 2048 6.1 / 6.5, but 1600
+// 6.1 / 5.8; 1000 rows of 4096 7.6 / 7.2: too few waves for their loads.  (With shares to add it is 5 - 20 % slower at any size: k_norm
+// requests them all together.)
+static bool norm_takes_rows(int d, int rows) { return rows >= 3072 || (rows >= 1536 && d >= 2048); }
 template <typename AT, int ARCH, int NI>
 static void launch_norm_ni(const float* h, const float* g, const float* b, float eps, int d, const int* n_rows,
                            void* act_out, float* f32_out, int max_rows, hipStream_t s, const NormPending& np, const EmbedSource* emb) {
   EmbedSource es;
   memset(&es, 0, sizeof es);
   if (emb) es = *emb;
+  if constexpr (sizeof(AT) == 2) {
+    if (!emb && !f32_out && np.shares <= 0 && norm_takes_rows(d, max_rows)) {
+      const int groups = (max_rows + 3) / 4;
+      hipLaunchKernelGGL((k_norm_rows<ARCH, NI>), dim3(groups), dim3(256), (size_t)d * 8, s, h, g, b, eps, d, n_rows, (bf16_t*)act_out, groups);
+      return;
+    }
+  }
   const int rope_wgs = es.rope ? (int)(((size_t)max_rows * (es.dh / 2) + 255) / 256) : 0;
 #define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows + rope_wgs), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out, np, es, max_rows)
   if (emb) SPRINTER_NORM(-1);
