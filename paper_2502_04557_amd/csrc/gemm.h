@@ -16,7 +16,8 @@ struct GemmArgs {
   int rows_live;      // the host's bound on the row count: rows from here on exist in no launch, their activations are not fetched
 };
 
-// EPI_QKV: column n >= q_cols of an entry whose cache slot is (b, slot): its key or value element.  The values are bf16 bits.
+// EPI_QKV takes the place of the append launch of short passes (4.1 us per layer at 24 - 80 entries of 25 heads of 64; the product itself is
+// not measurably slower for it): column n >= q_cols of an entry whose cache slot is (b, slot): its key or value element.  The values are bf16 bits.
 __device__ __forceinline__ bf16_t* kv_element(const KvDest& d, int b, int slot, int n) {
   const bool v = n >= d.q_cols + d.kv_cols;
   const int c = n - d.q_cols - (v ? d.kv_cols : 0), head = c >> (d.dh == 128 ? 7 : 6), i = c & (d.dh - 1);   // (heads of 64 or 128)

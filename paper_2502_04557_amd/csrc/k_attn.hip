@@ -178,8 +178,15 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // of a tile sit in one DPP row), P through a wave-private piece of LDS into operand layout (hi + lo), V^T tiles
 // straight from the cache, O += P V.  A block's keys and value tiles are requested a whole step ahead (two register
 // buffers; the query operand is kept in LDS to make room); nothing in the loop synchronises waves.  The row's own key and value
-// (the token being processed) are computed in the prologue, appended to the cache by wave 0 and patched into the
-// operands of the block that holds slot `slot`, which is the row's last block; keys beyond it are masked.
+// (the token being processed) are computed in the prologue, appended to the cache by the waves that prepared them and patched from
+// LDS into the operands of the block that holds slot `slot`, which is the row's last block; keys beyond it are masked.
+// What bounds a short context is the wave's own instructions: alone on its SIMD it issues one every 4 - 5 cycles.  Operand row 4 j + v
+// therefore holds head j NV + v (NV = 1 up to four heads, 2 for eight; the rows between repeat a head), so that the softmax of an
+// accumulator is done for NV registers instead of four: 2450 -> 790 cycles per step at 64 columns and one head.  us per launch in a chain,
+// with that, with the masks of the last block in two instructions a register and with loads only in the waves that use them: heads of 64,
+// 150 keys, 25 of them: 6 rows 6.15 -> 5.08, 16 rows 8.4 -> 7.5; 60 keys, 1 row 4.7 -> 3.1; of 128, 300 keys, 32: 3 rows 10.5 -> 8.7, 33 rows (162
+// MB) 41.9 -> 38.1; 8 KV heads, 540 keys, 17 rows 16.9 -> 14.5.  Long contexts and many rows: the cache, at 4.3 - 4.8 TB/s.  (8 waves from 140
+// keys on: 6 rows of 25 heads 5.08 -> 4.69, but 16 rows of 12 x 300 keys 6.6 -> 7.2 and 3 rows of 32 x 128 columns 8.7 -> 10.8.)
 // The waves' partial results are merged through LDS at the end.  gridDim.z > 1: that many workgroups share the keys (their waves
 // count on), each leaves its unnormalised result, maximum and sum in a.split, and k_attn_merge puts them together.
 template <int DH, int NW, int NV, bool ROPE>
@@ -917,8 +924,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma_shared_bf16(AttnArgs a) {
 // waves: wave w takes the 32-key blocks w, w + NW, ..., and the waves' partial results are merged through LDS.  A workgroup
 // whose entry is not the first of its group (the run's first entry, or a position that is a multiple of 16 / G) has nothing to
 // do.  A value that is not finite must not reach earlier entries of its group (0 x NaN is NaN): the blocks with the group's own
-// keys are looked through for one; entries that see it get NaN, the products of the others take zeros.  (80 entries in 16 windows of 5, 25 heads of 64, 110 keys: 22.0 us with a pass per entry, 9.9 now; 16 entries of one
-// each: 8.5 and 5.9.)
+// keys are looked through for one; entries that see it get NaN, the products of the others take zeros.  (80 entries in 16 windows of 5,
+// 25 heads of 64, 110 keys: 22.0 us with a pass per entry, 9.9 so; 16 entries of one each: 8.5 and 5.9.  With the queries requested ahead of
+// the descriptors, 150 keys: 26 entries of 12 heads 6.2 -> 5.9, 12 of 25 7.15 -> 6.85, 80 of 25 9.9 -> 9.7, 160 of 32 x 128 37.1 -> 35.6.)
 template <int DH, int NW, bool ROPE>
 __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
   constexpr int T = DH / 32, CT = DH / 16;
