@@ -578,6 +578,9 @@ int wait_ticket(sprinter_ctx* ctx, volatile unsigned long long* word, unsigned t
   }
 }
 
+// The target's QKV rows, free once its pass has ended, hold the partial results of the coins.
+size_t coin_bytes(const sprinter_ctx* ctx, const Model& tp) { return (size_t)ctx->rows_alloc * tp.md.dqkv * 4; }
+
 int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, int32_t* g_tok, uint8_t* g_accept,
                   float* g_score, int32_t* g_draft_tok) {
   hipStream_t s = ctx->stream;
@@ -637,7 +640,7 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
     rc = run_pass(ctx, tp, tp.rd(), R, 1u, sd ? ctx->tl : (out ? out->target_logits : nullptr), !sd && out && out->target_logits);
     if (rc) return rc;
     if (sd) {
-      launch_sd_correct(sa, R, s);
+      launch_sd_correct(sa, R, tp.sc.y, coin_bytes(ctx, tp), s);
       if (out && out->target_logits) launch_copy_f32(ctx->tl, out->target_logits, tp.rd_n, tp.md.V, R, s);
     }
     if (out && out->target_hidden) launch_copy_f32(tp.sc.hf, out->target_hidden, tp.rd_n, tp.md.d, R, s);
@@ -658,7 +661,7 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
       if (rc) return rc;
       if (sd) {
         sa.t_last = ctx->t_last;
-        launch_sd_correct(sa, n, s);
+        launch_sd_correct(sa, n, tp.sc.y, coin_bytes(ctx, tp), s);
       } else {
         launch_catchup_collect(tp.sc.am_part, tp.sc.n_lm_wg, lm_row_pad(n), tp.rd_n, tp.rd_b, ctx->t_last,
                                ctx->committed, n, s);
@@ -1016,7 +1019,7 @@ int sprinter_sd_generate(sprinter_ctx* ctx, int gamma, int n_rounds, int32_t* de
       const int n = std::min(rows, E - start);
       launch_sd_target_list(sd, start, n, T, s);
       if ((rc = run_pass(ctx, tp, tp.rd(), n, 1u, sd.tlw + (size_t)start * Vt, false, true))) return rc;
-      launch_sd_window_check(sd, start, n, tp.sc.am_part, tp.sc.n_lm_wg, lm_row_pad(n), s);
+      launch_sd_window_check(sd, start, n, tp.sc.am_part, tp.sc.n_lm_wg, lm_row_pad(n), tp.sc.y, coin_bytes(ctx, tp), s);
     }
     // 4. commit
     SdFinishArgs fa;

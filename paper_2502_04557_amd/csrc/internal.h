@@ -193,7 +193,7 @@ void launch_catchup_chunk(const CatchupArgs& a, hipStream_t s);
 void launch_catchup_collect(const unsigned long long* am_part, int n_lm_wg, int Mpad, const int* n_rows, const int* t_b,
                             const int* t_last, int* committed, int max_rows, hipStream_t s);
 
-// Rejection by the p/q coin and the residual of Eq. (1): one workgroup per row of the target pass.
+// Rejection by the p/q coin and the residual of Eq. (1).  work: scratch that is free after the pass (coin.h).
 struct SdArgs {
   const float* dl;            // [batch rows][V] draft logits of the step
   const float* tl;            // [pass rows][V] target logits of the pass
@@ -201,7 +201,7 @@ struct SdArgs {
   const int* draft_tok; int V; float inv_temperature; unsigned seed_lo, seed_hi;
   int* committed; int* coin_kept;
 };
-void launch_sd_correct(const SdArgs& a, int max_rows, hipStream_t s);
+void launch_sd_correct(const SdArgs& a, int max_rows, void* work, size_t work_bytes, hipStream_t s);
 void launch_set_i32(int* p, int v, hipStream_t s);
 
 // ---- standard speculative decoding (Sec. 2, Eq. (1)) on the same models: k_sd.hip -------------------
@@ -233,10 +233,10 @@ void launch_sd_draft_next(const SdBase& a, int j, const unsigned long long* am_p
                           const int* is_last, int logits_row_base, RowDescW out, int max_rows, hipStream_t s);
 // Entries [start, start + n) of the target pass: entry e = b * (gamma + 1) + j reads position len_q[b] + j.
 void launch_sd_target_list(const SdBase& a, int start, int n, RowDescW out, hipStream_t s);
-// One workgroup per entry of the chunk: the p/q coin and, where it fails, the residual draw; entry gamma of a
+// The p/q coin of every entry of the chunk and, where it fails, the residual draw; entry gamma of a
 // row takes the target's own sample (the extra token).
 void launch_sd_window_check(const SdBase& a, int start, int n, const unsigned long long* am_part, int n_lm_wg, int Mpad,
-                            hipStream_t s);
+                            void* work, size_t work_bytes, hipStream_t s);
 struct SdFinishArgs {
   int round, n_rounds, tok_stride;
   int* o_tok; int* o_n_tok; int* o_n_acc; int* o_draft;

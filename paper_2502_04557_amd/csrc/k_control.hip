@@ -286,23 +286,34 @@ void launch_catchup_collect(const unsigned long long* am_part, int n_lm_wg, int 
 }
 
 // ===================================== rejection by p/q coin + residual (Sec. 2, Eq. (1))
-// One workgroup per row of the target pass.  q = softmax(draft logits / T), p = softmax(target logits / T):
-// three sweeps over the vocabulary (maxima, sums of exponentials, and - only if the coin rejects - the
-// Gumbel-max draw from max(0, p - q), on ln(p - q) + noise of the target stream).  float32 throughout.
-__global__ __launch_bounds__(COIN_THREADS) void k_sd_correct(SdArgs a) {
+// w.S workgroups per row of the target pass (coin.h).
+__device__ __forceinline__ bool corrected(const SdArgs& a, int i) { return i < *a.n_rows && !(a.t_last && !a.t_last[i]); }
+
+__global__ __launch_bounds__(COIN_THREADS) void k_sd_correct_sums(SdArgs a, CoinWork w) {
   const int i = blockIdx.x;
-  if (i >= *a.n_rows) return;
-  if (a.t_last && !a.t_last[i]) return;
+  if (corrected(a, i)) coin_slice(a.dl + (size_t)a.t_b[i] * a.V, a.tl + (size_t)i * a.V, a.V, a.inv_temperature, w, i);
+}
+template <bool ONE>
+__global__ __launch_bounds__(COIN_THREADS) void k_sd_correct(SdArgs a, CoinWork w) {
+  const int i = blockIdx.x;
+  if (!corrected(a, i)) return;
   const int b = a.t_b[i], t = a.t_pos[i] + 1, x = a.draft_tok[b], V = a.V;
   int drawn = 0;
-  const bool kept = coin_or_residual(a.dl + (size_t)b * V, a.tl + (size_t)i * V, V, a.inv_temperature, a.seed_lo, a.seed_hi, b, t, x, &drawn);
-  if (threadIdx.x == 0) {
-    a.committed[b] = kept ? x : drawn;
-    if (kept) atomicAdd(a.coin_kept, 1);
+  const CoinSays say = coin_draw<ONE>(a.dl + (size_t)b * V, a.tl + (size_t)i * V, V, a.inv_temperature, a.seed_lo, a.seed_hi, b, t, x,
+                                 w, i, &drawn);
+  if (threadIdx.x == 0 && say != COIN_NOTHING) {
+    a.committed[b] = say == COIN_KEPT ? x : drawn;
+    if (say == COIN_KEPT) atomicAdd(a.coin_kept, 1);
   }
 }
-void launch_sd_correct(const SdArgs& a, int max_rows, hipStream_t s) {
-  hipLaunchKernelGGL(k_sd_correct, dim3(max_rows), dim3(COIN_THREADS), 0, s, a);
+void launch_sd_correct(const SdArgs& a, int max_rows, void* work, size_t work_bytes, hipStream_t s) {
+  const CoinWork w = coin_work(work, work_bytes, max_rows, a.V);
+  if (w.S == 1) {
+    hipLaunchKernelGGL(k_sd_correct<true>, dim3(max_rows), dim3(COIN_THREADS), 0, s, a, w);
+    return;
+  }
+  hipLaunchKernelGGL(k_sd_correct_sums, dim3(max_rows, w.S), dim3(COIN_THREADS), 0, s, a, w);
+  hipLaunchKernelGGL(k_sd_correct<false>, dim3(max_rows, w.S), dim3(COIN_THREADS), 0, s, a, w);
 }
 
 __global__ void k_set_i32(int* p, int v) { *p = v; }

@@ -71,14 +71,20 @@ void launch_sd_target_list(const SdBase& a, int start, int n, RowDescW out, hipS
   hipLaunchKernelGGL(k_sd_target_list, dim3(1), dim3(1024), 0, s, a, start, n, out);
 }
 
-// One workgroup per entry of the target pass: the coin of a window token and, where it fails, its replacement; the last entry
+// w.S workgroups per entry of the target pass: the coin of a window token and, where it fails, its replacement; the last entry
 // of a window gives the extra token.
+__global__ __launch_bounds__(COIN_THREADS) void k_sd_window_sums(SdBase a, int start, CoinWork w) {
+  const int i = blockIdx.x, per = a.gamma + 1, e = start + i, b = e / per, j = e - b * per, V = a.V;
+  if (j < a.gamma)
+    coin_slice(a.dlw + (size_t)a.qrow[b * a.gamma + j] * V, a.tlw + (size_t)e * V, V, a.inv_temperature, w, i);
+}
+template <bool ONE>
 __global__ __launch_bounds__(COIN_THREADS) void k_sd_window_check(SdBase a, int start, const u64* __restrict__ am_part, int n_lm_wg,
-                                                                  int Mpad) {
+                                                                  int Mpad, CoinWork w) {
   const int i = blockIdx.x, tid = threadIdx.x;
   const int per = a.gamma + 1, e = start + i, b = e / per, j = e - b * per, V = a.V;
   if (j == a.gamma) {                                    // the extra token: the target's own sample of this entry
-    if (wave_index() == 0) {
+    if (blockIdx.y == 0 && wave_index() == 0) {
       const u64 k = merge_partials(am_part, n_lm_wg, Mpad, i, tid & 63);
       if (tid == 0) a.alt[b * per + j] = key_index(k);
     }
@@ -86,16 +92,22 @@ __global__ __launch_bounds__(COIN_THREADS) void k_sd_window_check(SdBase a, int 
   }
   const int t = a.st.len_q[b] + j + 1;                   // sequence position of the checked token
   int drawn = 0;
-  const bool kept = coin_or_residual(a.dlw + (size_t)a.qrow[b * a.gamma + j] * V, a.tlw + (size_t)e * V, V, a.inv_temperature,
-                                     a.seed_lo, a.seed_hi, b, t, a.win[b * a.gamma + j], &drawn);
-  if (tid == 0) {
-    a.kept[b * a.gamma + j] = kept ? 1 : 0;
-    if (!kept) a.alt[b * per + j] = drawn;
+  const CoinSays say = coin_draw<ONE>(a.dlw + (size_t)a.qrow[b * a.gamma + j] * V, a.tlw + (size_t)e * V, V, a.inv_temperature,
+                                 a.seed_lo, a.seed_hi, b, t, a.win[b * a.gamma + j], w, i, &drawn);
+  if (tid == 0 && say != COIN_NOTHING) {
+    a.kept[b * a.gamma + j] = say == COIN_KEPT ? 1 : 0;
+    if (say == COIN_DRAWN) a.alt[b * per + j] = drawn;
   }
 }
 void launch_sd_window_check(const SdBase& a, int start, int n, const unsigned long long* am_part, int n_lm_wg, int Mpad,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_sd_window_check, dim3(n), dim3(COIN_THREADS), 0, s, a, start, am_part, n_lm_wg, Mpad);
+                            void* work, size_t work_bytes, hipStream_t s) {
+  const CoinWork w = coin_work(work, work_bytes, n, a.V);
+  if (w.S == 1) {
+    hipLaunchKernelGGL(k_sd_window_check<true>, dim3(n), dim3(COIN_THREADS), 0, s, a, start, am_part, n_lm_wg, Mpad, w);
+    return;
+  }
+  hipLaunchKernelGGL(k_sd_window_sums, dim3(n, w.S), dim3(COIN_THREADS), 0, s, a, start, w);
+  hipLaunchKernelGGL(k_sd_window_check<false>, dim3(n, w.S), dim3(COIN_THREADS), 0, s, a, start, am_part, n_lm_wg, Mpad, w);
 }
 
 // Single workgroup, one thread per row: the first failed coin ends the window; commit, advance the state, and
