@@ -185,7 +185,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // accumulator is done for NV registers instead of four: 2450 -> 790 cycles per step at 64 columns and one head.  us per launch in a chain,
 // with that, with the masks of the last block in two instructions a register and with loads only in the waves that use them: heads of 64,
 // 150 keys, 25 of them: 6 rows 6.15 -> 5.08, 16 rows 8.4 -> 7.5; 60 keys, 1 row 4.7 -> 3.1; of 128, 300 keys, 32: 3 rows 10.5 -> 8.7, 33 rows (162
-// MB) 41.9 -> 38.1; 8 KV heads, 540 keys, 17 rows 16.9 -> 14.5.  Long contexts and many rows: the cache, at 4.3 - 4.8 TB/s.  (8 waves from 140
+// MB) 41.9 -> 36.4; 8 KV heads, 540 keys, 17 rows 16.9 -> 13.1.  Long contexts and many rows: the cache, at 4.3 - 4.8 TB/s.  (8 waves from 140
 // keys on: 6 rows of 25 heads 5.08 -> 4.69, but 16 rows of 12 x 300 keys 6.6 -> 7.2 and 3 rows of 32 x 128 columns 8.7 -> 10.8.)
 // The waves' partial results are merged through LDS at the end.  gridDim.z > 1: that many workgroups share the keys (their waves
 // count on), each leaves its unnormalised result, maximum and sum in a.split, and k_attn_merge puts them together.
@@ -242,21 +242,40 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
   const int n_steps = (slot + 32 * NZ) / (32 * NZ);             // blocks 0 .. slot / 32, NZ per step
   // Two register buffers: a block's key fragments and value tiles are requested a whole step ahead (the query
   // operand lives in LDS to make room for them).
-  // A block beyond the row's last one is read at the last one's address (scalar clamp) and fully masked; inside a
-  // block nothing is clamped: the caches hold a multiple of 32 slots per (row, KV head), so every key of a block
-  // that exists lies inside the cache.  Per-lane base addresses once, block offsets are scalars.
+  // A block beyond the row's last one (a last step has up to NZ - 1, and the loop requests a step more than it uses) is fully masked.
+  // At 128 columns it is requested from buffers of no length (a scalar choice): zeros, and the compute unit pulls nothing, where
+  // reading the last block again took its share of 48 KB/us (heads of 128, 300 keys, 32 of them: 33 rows 39.0 -> 36.4 us, 59 rows 62.2 -> 59.2;
+  // 8 KV heads, 540 keys, 17 rows 14.3 -> 13.1).  At 64 columns the descriptors cost few workgroups as much as the loads (25 heads, 150
+  // keys, 6 rows 4.9 / 5.2; 8 KV heads, 1800 keys, 4 rows 8.3 / 8.8; but 25 heads, 16 rows 7.5 / 7.0): the last one again, a scalar clamp.
+  // Inside a block nothing is clamped: the caches hold a multiple of 32 slots per (row, KV head), so every key of a block that
+  // exists lies inside the cache.  Per-lane addresses or offsets once, block offsets are scalars.
   struct Blk { u32x4 k[2][T]; u32x4 v[CT]; };
-  const bf16_t* const k_lane = Kc + (size_t)l16 * DH + lq * 8;
-  const bf16_t* const v_lane = Vc + lane * 8;
+  const int k_lane = l16 * DH + lq * 8, v_lane = lane * 8;       // elements
+  const bf16_t *const k_ptr = Kc + k_lane, *const v_ptr = Vc + v_lane;
   const int kb_last = slot & ~31;
   auto fetch = [&](Blk& B, int kb) {
-    const size_t off = (size_t)min(kb, kb_last) * DH;            // elements; the same for keys and value tiles
+    if constexpr (DH == 128) {
+      const bool in = kb <= kb_last;
+      const int bytes = in ? 32 * DH * 2 : 0;                    // of a block's keys, and of its value tiles
+      const size_t off = (size_t)(in ? kb : 0) * DH;
+      const auto kr = __builtin_amdgcn_make_buffer_rsrc(Kc + off, 0, bytes, 0x00020000);
+      const auto vr = __builtin_amdgcn_make_buffer_rsrc(Vc + off, 0, bytes, 0x00020000);
 #pragma unroll
-    for (int tile = 0; tile < 2; ++tile)
+      for (int tile = 0; tile < 2; ++tile)
 #pragma unroll
-      for (int t = 0; t < T; ++t) B.k[tile][t] = *reinterpret_cast<const u32x4*>(k_lane + off + tile * 16 * DH + t * 32);
+        for (int t = 0; t < T; ++t)
+          B.k[tile][t] = __builtin_amdgcn_raw_buffer_load_b128(kr, 2 * (k_lane + tile * 16 * DH + t * 32), 0, 0);
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct) B.v[ct] = *reinterpret_cast<const u32x4*>(v_lane + off + ct * 512);
+      for (int ct = 0; ct < CT; ++ct) B.v[ct] = __builtin_amdgcn_raw_buffer_load_b128(vr, 2 * (v_lane + ct * 512), 0, 0);
+    } else {
+      const size_t off = (size_t)min(kb, kb_last) * DH;          // elements; the same for keys and value tiles
+#pragma unroll
+      for (int tile = 0; tile < 2; ++tile)
+#pragma unroll
+        for (int t = 0; t < T; ++t) B.k[tile][t] = *reinterpret_cast<const u32x4*>(k_ptr + off + tile * 16 * DH + t * 32);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) B.v[ct] = *reinterpret_cast<const u32x4*>(v_ptr + off + ct * 512);
+    }
   };
   Blk A, B;
   fetch(A, wz * 32);
