@@ -120,14 +120,15 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
         mx = fmaxf(mx, s[j]);
       }
       if (kb + lq <= slot) {                                     // (the same in a stream's 16 lanes) it has a key in this block
-        const float corr = expf(m[g] - mx);
+        const float off = mx == -INFINITY ? 0.f : mx;            // (all its scores so far are -inf: weights of 0, as in a row with one maximum)
+        const float corr = expf(m[g] - off);
         m[g] = mx;
         l[g] *= corr;
 #pragma unroll
         for (int e = 0; e < E; ++e) o[g][e] *= corr;
 #pragma unroll
         for (int j = 0; j < NK; ++j) {
-          const float p = expf(s[j] - mx);
+          const float p = expf(s[j] - off);
           l[g] += p;
 #pragma unroll
           for (int e = 0; e < E; ++e) o[g][e] += p * v[j][e];

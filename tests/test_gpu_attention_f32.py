@@ -1,0 +1,90 @@
+"""Float32 attention by itself against float64, at the values where one maximum per stream of keys is not one per row."""
+import ctypes as C
+import pytest
+from test_gpu_prefill_attention import _Dims, _Rows, _lib
+
+pytestmark = pytest.mark.gpu
+
+
+class _Step:
+    """One entry per batch row, entry i at slots[i].  The caches are NaN from each row's own slot on."""
+
+    def __init__(self, dh, H, KVH, slots, rope, seed):
+        import torch
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        rnd = lambda *s: torch.empty(s, device="cuda").normal_(generator=g)
+        ints = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+        self.dh, self.H, self.KVH, self.rope, self.slots, n = dh, H, KVH, rope, slots, len(slots)
+        self.n, self.slot, self.dqkv, self.seq = ints([n]), ints(slots), (H + 2 * KVH) * dh, max(slots) + 3
+        self.b = ints([(5 * i + 2) % n if n % 5 else i for i in range(n)])           # (a row's place in the list is not its place in the caches)
+        self.y = rnd(n, self.dqkv)
+        angle = rnd(n, dh // 2) * 10
+        self.cs = torch.stack([angle.cos(), angle.sin()], -1).contiguous()
+        self.k, self.v = rnd(n, KVH, self.seq, dh), rnd(n, KVH, self.seq, dh)
+        for b, s in zip(self.b.tolist(), slots):
+            self.k[b, :, s:], self.v[b, :, s:] = float("nan"), float("nan")
+
+    def new(self):
+        """(queries, keys, values) of the entries in float64, rotated, and the absolute sums behind queries and keys."""
+        import torch
+        dh, H, KVH = self.dh, self.H, self.KVH
+        q, k, v = (t.double().view(len(self.slots), -1, dh) for t in self.y.split([H * dh, KVH * dh, KVH * dh], 1))
+        if not self.rope:
+            return q, k, v, q.abs(), k.abs()
+        c, s = (self.cs[:, None, :, i].double() for i in (0, 1))
+        halves = lambda t: (t[..., :dh // 2], t[..., dh // 2:])
+        turn = lambda lo, hi: torch.cat([lo * c - hi * s, hi * c + lo * s], -1)
+        size = lambda lo, hi: torch.cat([lo * c.abs() + hi * s.abs(), hi * c.abs() + lo * s.abs()], -1)
+        return turn(*halves(q)), turn(*halves(k)), v, size(*halves(q.abs())), size(*halves(k.abs()))
+
+    def run(self, phase=0):
+        """Outputs [rows, H, dh]; phase 0 appends and attends, 1 only appends, 2 only attends."""
+        import torch
+        n, dh, H = len(self.slots), self.dh, self.H
+        out = torch.full((n, H, dh), float("nan"), device="cuda")
+        d = _Dims(int(self.rope), 1, H * dh, H, self.KVH, dh, 64, 64, self.seq, self.dqkv, 1e-5, 1e4)
+        r = _Rows(*(t.data_ptr() for t in (self.n, self.b, self.b, self.slot, self.slot)))
+        p = lambda t: C.c_void_p(t.data_ptr())
+        _lib()["_ZN8sprinter16launch_attentionEiRKNS_9ModelDimsEPKfS4_RKNS_7RowDescEPvS8_miiS8_iPfP12ihipStream_tii"](
+            0, C.byref(d), p(self.y), p(self.cs), C.byref(r), p(self.k), p(self.v), C.c_size_t(0), max(self.slots) + 1, self.seq, p(out), n, C.c_void_p(0),
+            C.c_void_p(torch.cuda.current_stream().cuda_stream), phase, 0)
+        torch.cuda.synchronize()
+        return out
+
+    def reference(self):
+        """(attention, bound of the kernel's error) in float64."""
+        import torch
+        G, outs, bounds = self.H // self.KVH, [], []
+        q, kn, vn, qa, ka = self.new()
+        for i, (b, s) in enumerate(zip(self.b.tolist(), self.slots)):
+            per_head = lambda t: t.repeat_interleave(G, 0)
+            k, v = (per_head(torch.cat([c[b, :, :s].double(), own[i, :, None]], 1)) for c, own in ((self.k, kn), (self.v, vn)))
+            size = per_head(torch.cat([self.k[b, :, :s].double().abs(), ka[i, :, None]], 1))
+            score = (q[i, :, None] * k).sum(-1) / self.dh ** 0.5
+            w = torch.softmax(score, -1)
+            seen = torch.isfinite(score)
+            # A score is 8 products per lane at most and 4 levels of a tree over rotated (3 roundings each), scaled operands: 24 roundings of
+            # the absolute sum; its distance from a maximum, two exponentials (each of an argument of up to twice the sum) 8 more.  Weights and
+            # values are added key by key in 16 streams, then over the streams, and divided: s / 16 + 40 roundings of the weighted absolute values.
+            e = torch.where(seen, (qa[i, :, None] * size).sum(-1) / self.dh ** 0.5, 0.).amax(-1, keepdim=True) * 32 * 2.0 ** -24
+            o = torch.where(w[..., None] > 0, w[..., None] * v, 0.).sum(1)
+            outs.append(o)
+            bounds.append((2 * e + (s / 16 + 40) * 2.0 ** -24) * torch.where(w[..., None] > 0, w[..., None] * v.abs(), 0.).sum(1))
+        return torch.stack(outs), torch.stack(bounds)
+
+
+# the keys that score -inf: all of one stream, all of a wave's first blocks, the row's first 128 (the first step of every wave), its own
+@pytest.mark.parametrize("dh,H,KVH", [(64, 4, 4), (128, 8, 2), (64, 8, 1)])
+@pytest.mark.parametrize("gone", [lambda j, s: j % 4 == 1, lambda j, s: j // 32 % 4 == 1, lambda j, s: j < 128, lambda j, s: j == s], ids=["stream", "wave", "step", "own"])
+def test_keys_that_score_minus_infinity_have_no_weight(dh, H, KVH, gone):
+    import torch
+    p = _Step(dh, H, KVH, (130, 200, 300), False, dh + H)
+    p.y[:, :H * dh].view(-1, H, dh)[..., 0].abs_().add_(0.1)              # every query's first column is positive
+    for i, (b, s) in enumerate(zip(p.b.tolist(), p.slots)):
+        at = torch.tensor([gone(j, s) for j in range(s)], device="cuda")
+        p.k[b, :, :s, 0] = torch.where(at, float("-inf"), p.k[b, :, :s, 0])
+        if gone(s, s):
+            p.y[i, H * dh:(H + KVH) * dh].view(KVH, dh)[:, 0] = float("-inf")
+    want, bound = p.reference()
+    assert want.isfinite().all()
+    assert ((p.run().double() - want).abs() <= bound).all()
