@@ -103,9 +103,9 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
     if (kb + KB > slot) {                                        // (scalar) the row's last block: its own key and value, which the cache may not hold yet
 #pragma unroll
       for (int j = 0; j < NK; ++j) {
-        const bool own = kb + 4 * j + lq >= slot;                // (and in place of what lies behind: masked below)
+        const int behind = kb + 4 * j + lq - slot;               // > 0: no key (its score is masked below; 0 x its value has to be 0)
 #pragma unroll
-        for (int e = 0; e < E; ++e) { k[j][e] = own ? kn[e] : k[j][e]; v[j][e] = own ? vn[e] : v[j][e]; }
+        for (int e = 0; e < E; ++e) { k[j][e] = behind >= 0 ? kn[e] : k[j][e]; v[j][e] = behind > 0 ? 0.f : behind == 0 ? vn[e] : v[j][e]; }
       }
     }
 #pragma unroll

@@ -88,3 +88,19 @@ def test_keys_that_score_minus_infinity_have_no_weight(dh, H, KVH, gone):
     want, bound = p.reference()
     assert want.isfinite().all()
     assert ((p.run().double() - want).abs() <= bound).all()
+
+
+# the row's own key in the place of 0 - 31 others of its block, in each wave's
+@pytest.mark.parametrize("dh,H,KVH", [(64, 4, 4), (128, 8, 2), (64, 8, 1)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_value_that_is_not_finite_reaches_its_column_alone(dh, H, KVH, value):
+    import torch
+    p = _Step(dh, H, KVH, (0, 1, 5, 31, 32, 70, 127, 128, 200), False, dh + H)
+    own = p.y[:, (H + KVH) * dh:].view(-1, KVH, dh)
+    own[..., 3], own[..., dh - 1] = 0.5, 0.5
+    want, bound = p.reference()
+    own[..., 3], own[..., dh - 1] = value, -value
+    got = p.run().double()
+    assert ((got - want).abs() <= bound)[..., [c for c in range(dh) if c not in (3, dh - 1)]].all()
+    for c, x in ((3, value), (dh - 1, -value)):
+        assert (got[..., c] == x).all() if x == x else got[..., c].isnan().all()
