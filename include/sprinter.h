@@ -24,13 +24,7 @@
  * sprinter_prefill drains the stream every 4 passes; sprinter_get_stats and
  * sprinter_destroy wait for it.  The library never allocates device memory: the
  * caller hands over one workspace.  sprinter_create allocates 256 bytes of
- * pinned host memory (that polled word), freed by sprinter_destroy.  Passes of
- * up to 32 rows through a model of 12 and more layers are recorded when they
- * come for the second time and replayed from the third on (at most 64 per
- * context, on a stream of the context's own that runs nothing): HIP keeps the
- * arguments of their launches, some 100 KB per pass, until new weights are
- * loaded or the context is destroyed.  Where HIP cannot, they are launched one
- * by one as ever; contexts of sprinter_create_static never record.
+ * pinned host memory (that polled word), freed by sprinter_destroy.
  *
  * Conventions
  *   - "dev" pointers are device memory, "host" pointers host memory.

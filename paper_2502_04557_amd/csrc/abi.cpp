@@ -69,17 +69,6 @@ struct Model {
   RowDesc rd() const { return RowDesc{rd_n, rd_b, rd_tok, rd_pos, rd_slot}; }
 };
 
-// A forward pass whose launches have been recorded.  The key is everything that the launches' arguments depend on besides what a
-// context keeps for its life; none of it comes from the caller's buffers.
-struct PassKey {
-  const Model* model; const int* rows_desc; const float* logits; int rows, shared, verifier, attn;
-  bool operator==(const PassKey& o) const {
-    return model == o.model && rows_desc == o.rows_desc && logits == o.logits && rows == o.rows && shared == o.shared && verifier == o.verifier && attn == o.attn;
-  }
-};
-struct PassGraph { PassKey key; int uses; hipGraphExec_t exec; };
-constexpr size_t MAX_PASS_GRAPHS = 64;
-
 }  // namespace
 
 struct sprinter_ctx {
@@ -116,10 +105,6 @@ struct sprinter_ctx {
   int sd_next_entries = 0;       // entries of the next round's first draft pass, once known
   unsigned sd_wait_ticket = 0;   // != 0: the last round's finish kernel will report them under this ticket
   int run_kind = 0;              // since the last prefill: 0 nothing, 1 decode steps, 2 speculative-decoding rounds
-  // recorded passes (run_pass)
-  std::vector<PassGraph> graphs;
-  hipStream_t record_stream = nullptr;   // passes are recorded here; nothing ever runs on it
-  bool graphs_off = false;
   // host bookkeeping
   int B = 0, max_prompt_len = 0;
   long long steps_done = 0;
@@ -387,10 +372,11 @@ size_t carve(const sprinter_cfg& c, bool on_static, void* base, sprinter_ctx* ct
 // new keys / values first and attends in a second launch.  run_len > 0: those entries come in long runs of consecutive
 // positions (prefill), that many in the mean, so the attending launch lets up to 64 of them share one pass over the row's cache.
 // ver: the verifier's work, done by the LM head's launch.
-void forward(sprinter_ctx* ctx, hipStream_t s, Model& m, const RowDesc& rd, int max_rows, bool want_head, unsigned stream_id,
+void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool want_head, unsigned stream_id,
              float* logits_out, bool shared_caches = false, int run_len = 0, const VerifierArgs* ver = nullptr) {
   const int dt = ctx->cfg.dtype;
   const ModelDims& md = m.md;
+  hipStream_t s = ctx->stream;
   ModelScratch& sc = m.sc;
   const int rows = ctx->rows_alloc;
   // elements the activation buffers hold (their row tiles bound what a kernel may fetch)
@@ -476,64 +462,6 @@ void forward(sprinter_ctx* ctx, hipStream_t s, Model& m, const RowDesc& rd, int 
                 logits_out, max_rows, s, ver);
 }
 
-// Whether the passes of a model over so many rows are worth recording.  The host needs 2.5 - 4.5 us per launch (it varies from process
-// to process), and a launch that streams up to about 12 MB of weights takes the GPU no longer: at 12 layers of 17 MB a replay saves
-// 40 us in 390, at 16 of 122 MB nothing.  Starting a graph costs 18 - 22 us, during which the GPU has nothing else: 16 - 30 launches of
-// 3 - 4 us each (2 - 4 layers of 256 - 512 columns) ran 4 % slower as two graphs per step where the host was quick, 12 % faster where not.
-bool records(const sprinter_ctx* ctx, const Model& m, int rows) {
-  const ModelDims& md = m.md;
-  const size_t mats = (size_t)md.d * md.dqkv + (size_t)md.d * md.H * md.dh + (size_t)md.d * md.ff * (md.arch == SPRINTER_ARCH_GPT ? 2 : 3);
-  return ctx->static_dev < 0 && !ctx->graphs_off && md.n_layer >= 12 && rows <= 32 && mats * esize(ctx->cfg.dtype) <= (size_t)84 << 20;
-}
-
-// The pass's launches as an executable graph, or NULL (then recording is given up for the context).
-hipGraphExec_t record_pass(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int rows, unsigned stream_id, float* logits, bool shared,
-                           const VerifierArgs* ver) {
-  if (hipPeekAtLastError() != hipSuccess) return nullptr;   // (a failed launch is reported at the end of the call)
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  bool ok = ctx->record_stream || hipStreamCreateWithFlags(&ctx->record_stream, hipStreamNonBlocking) == hipSuccess;
-  ok = ok && hipStreamBeginCapture(ctx->record_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
-  if (ok) {
-    forward(ctx, ctx->record_stream, m, rd, rows, true, stream_id, logits, shared, 0, ver);
-    ok = hipStreamEndCapture(ctx->record_stream, &graph) == hipSuccess && graph;
-  }
-  ok = ok && hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) == hipSuccess;
-  if (graph) (void)hipGraphDestroy(graph);
-  if (!ok) { (void)hipGetLastError(); ctx->graphs_off = true; return nullptr; }
-  return exec;
-}
-
-// A pass with its LM head over the rows of rd.  Short passes are a chain of launches that the host issues no faster than the GPU runs
-// them; from the third time on they are replayed as a graph, which costs the host 0.3 us per launch.  The second time the pass is
-// launched as it is and recorded behind that (2 - 4 us per launch, while the GPU works).  user_logits: logits goes to the caller's
-// memory, so the pass is not kept.
-// us per layer, launches / graph, where the host needs 3.8 us per launch: 48 layers of 1600, 6 rows 39.1 / 34.7; 12 of 768, 16 rows 32.3 /
-// 26.9, 1 row 24.2 / 19.4; where it needs 2.5, they are equal.
-int run_pass(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int rows, unsigned stream_id, float* logits, bool user_logits, bool shared = false,
-             const VerifierArgs* ver = nullptr) {
-  PassGraph* g = nullptr;
-  if (!user_logits && records(ctx, m, rows)) {
-    const PassKey key{&m, rd.b, logits, rows, shared, ver != nullptr, attention_plan(ctx->cfg.dtype, m.md, rows, ctx->max_prompt_len + (int)ctx->steps_done)};
-    for (PassGraph& q : ctx->graphs) if (q.key == key) { g = &q; break; }
-    if (!g && ctx->graphs.size() < MAX_PASS_GRAPHS) { ctx->graphs.push_back(PassGraph{key, 0, nullptr}); g = &ctx->graphs.back(); }
-  }
-  if (g && g->exec) {
-    if (hipGraphLaunch(g->exec, ctx->stream) != hipSuccess)
-      return fail(ctx, SPRINTER_E_HIP, "launch of a recorded pass failed: %s", hipGetErrorString(hipGetLastError()));
-    return SPRINTER_OK;
-  }
-  forward(ctx, ctx->stream, m, rd, rows, true, stream_id, logits, shared, 0, ver);
-  if (g && ++g->uses == 2) g->exec = record_pass(ctx, m, rd, rows, stream_id, logits, shared, ver);
-  return SPRINTER_OK;
-}
-
-// The stream has nothing in flight that uses them.
-void drop_graphs(sprinter_ctx* ctx) {
-  for (PassGraph& g : ctx->graphs) if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  ctx->graphs.clear();
-}
-
 int check_ready(sprinter_ctx* ctx) {
   if (!ctx->draft.loaded || !ctx->target.loaded || !ctx->v_loaded)
     return fail(ctx, SPRINTER_E_WEIGHTS, "weights not loaded (draft %d, target %d, verifier %d)", (int)ctx->draft.loaded,
@@ -589,8 +517,7 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
   const bool sd = ctx->cfg.reject_mode == 1;
   const VerifierArgs ver{dq.sc.hf, dq.md.d, ctx->cfg.ver_d_hidden, (const float*)ctx->v_w1, (const float*)ctx->v_b1,
                          (const float*)ctx->v_w2, ctx->ver_part, B, ctx->ver_chunks};
-  int rc = run_pass(ctx, dq, dq.rd(), B, 0u, sd ? ctx->dl : (out ? out->draft_logits : nullptr), !sd && out && out->draft_logits, false, &ver);
-  if (rc) return rc;
+  forward(ctx, dq, dq.rd(), B, true, 0u, sd ? ctx->dl : (out ? out->draft_logits : nullptr), false, 0, &ver);
   if (sd && out && out->draft_logits) launch_copy_f32(ctx->dl, out->draft_logits, dq.rd_n, dq.md.V, B, s);
   if (out && out->draft_hidden) launch_copy_f32(dq.sc.hf, out->draft_hidden, dq.rd_n, dq.md.d, B, s);
   DecideArgs da;
@@ -622,7 +549,7 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
   // microseconds; after 2 s without the ticket it falls back to a stream synchronisation.
   int R = -1;
   {
-    rc = wait_ticket(ctx, ctx->host_counts, da.ticket, &R, "the draft pass did not report its rejected rows");
+    int rc = wait_ticket(ctx, ctx->host_counts, da.ticket, &R, "the draft pass did not report its rejected rows");
     if (rc) return rc;
   }
   if (R < 0 || R > B) return fail(ctx, SPRINTER_E_HIP, "device reported %d rejected rows of %d", R, B);
@@ -637,8 +564,7 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
     sa.committed = ctx->committed; sa.coin_kept = ctx->coin_kept;
   }
   if (mode == 0) {
-    rc = run_pass(ctx, tp, tp.rd(), R, 1u, sd ? ctx->tl : (out ? out->target_logits : nullptr), !sd && out && out->target_logits);
-    if (rc) return rc;
+    forward(ctx, tp, tp.rd(), R, true, 1u, sd ? ctx->tl : (out ? out->target_logits : nullptr));
     if (sd) {
       launch_sd_correct(sa, R, tp.sc.y, coin_bytes(ctx, tp), s);
       if (out && out->target_logits) launch_copy_f32(ctx->tl, out->target_logits, tp.rd_n, tp.md.V, R, s);
@@ -657,8 +583,7 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
       const int n = (int)std::min<long long>(ctx->rows_alloc, E - start);
       ca.start = (int)start; ca.n = n;
       launch_catchup_chunk(ca, s);
-      rc = run_pass(ctx, tp, tp.rd(), n, 1u, sd ? ctx->tl : nullptr, false, true);
-      if (rc) return rc;
+      forward(ctx, tp, tp.rd(), n, true, 1u, sd ? ctx->tl : nullptr, true);
       if (sd) {
         sa.t_last = ctx->t_last;
         launch_sd_correct(sa, n, tp.sc.y, coin_bytes(ctx, tp), s);
@@ -831,10 +756,6 @@ int sprinter_load_weights(sprinter_ctx* ctx, int which, const char* const* names
   }
   for (size_t j = 0; j < exp->size(); ++j)
     if (!seen[j]) return fail(ctx, SPRINTER_E_WEIGHTS, "%s: tensor '%s' is missing", who, (*exp)[j].name.c_str());
-  if (!ctx->graphs.empty()) {      // recorded passes hold the old tensors' addresses
-    if (hipStreamSynchronize(ctx->stream) != hipSuccess) return fail(ctx, SPRINTER_E_HIP, "stream synchronisation failed");
-    drop_graphs(ctx);
-  }
   for (int i = 0; i < n; ++i) {
     Expected& e = (*exp)[hit[i]];
     if (e.pack) {
@@ -908,8 +829,8 @@ int sprinter_prefill(sprinter_ctx* ctx, const int32_t* dev_prompt, const int32_t
       const int n = (int)std::min<long long>(ctx->rows_alloc, E - start);
       ca.start = (int)start; ca.n = n;
       launch_catchup_chunk(ca, s);
-      forward(ctx, s, dq, tp.rd(), n, false, 0u, nullptr, true, run_len);
-      forward(ctx, s, tp, tp.rd(), n, false, 1u, nullptr, true, run_len);
+      forward(ctx, dq, tp.rd(), n, false, 0u, nullptr, true, run_len);
+      forward(ctx, tp, tp.rd(), n, false, 1u, nullptr, true, run_len);
       // bound the number of launches in flight (tools that keep per-dispatch state have died on long backlogs)
       if ((chunk & 3) == 3 && hipStreamSynchronize(s) != hipSuccess) return fail(ctx, SPRINTER_E_HIP, "stream synchronisation failed");
     }
@@ -1004,13 +925,13 @@ int sprinter_sd_generate(sprinter_ctx* ctx, int gamma, int n_rounds, int32_t* de
     for (int start = 0; start < E0; start += rows) {
       const int n = std::min(rows, E0 - start);
       launch_sd_take_chunk(sd, start, n, D[0], ctx->t_last, s);
-      if ((rc = run_pass(ctx, dq, ro(D[0]), n, 0u, sd.dlw + (size_t)start * Vd, false, E0 > B))) return rc;
+      forward(ctx, dq, ro(D[0]), n, true, 0u, sd.dlw + (size_t)start * Vd, E0 > B);
       launch_sd_draft_next(sd, 0, dq.sc.am_part, dq.sc.n_lm_wg, lm_row_pad(n), ro(D[0]), ctx->t_last, start, D[1], n, s);
     }
     for (int j = 1; j < gamma; ++j) {
       const RowDescW &in = D[j & 1], &out = D[(j + 1) & 1];
       const int base = 2 * B + (j - 1) * B;
-      if ((rc = run_pass(ctx, dq, ro(in), B, 0u, sd.dlw + (size_t)base * Vd, false))) return rc;
+      forward(ctx, dq, ro(in), B, true, 0u, sd.dlw + (size_t)base * Vd, false);
       launch_sd_draft_next(sd, j, dq.sc.am_part, dq.sc.n_lm_wg, lm_row_pad(B), ro(in), nullptr, base, out, B, s);
     }
     // 2. the target over gamma + 1 positions of every row, 3. coin / residual / extra token per entry
@@ -1018,7 +939,7 @@ int sprinter_sd_generate(sprinter_ctx* ctx, int gamma, int n_rounds, int32_t* de
     for (int start = 0; start < E; start += rows) {
       const int n = std::min(rows, E - start);
       launch_sd_target_list(sd, start, n, T, s);
-      if ((rc = run_pass(ctx, tp, tp.rd(), n, 1u, sd.tlw + (size_t)start * Vt, false, true))) return rc;
+      forward(ctx, tp, tp.rd(), n, true, 1u, sd.tlw + (size_t)start * Vt, true);
       launch_sd_window_check(sd, start, n, tp.sc.am_part, tp.sc.n_lm_wg, lm_row_pad(n), tp.sc.y, coin_bytes(ctx, tp), s);
     }
     // 4. commit
@@ -1067,8 +988,6 @@ int sprinter_get_stats(sprinter_ctx* ctx, sprinter_stats* host_out, int64_t* hos
 void sprinter_destroy(sprinter_ctx* ctx) {
   if (!ctx) return;
   (void)hipStreamSynchronize(ctx->stream);     // a decide kernel still in flight writes into the pinned word
-  drop_graphs(ctx);
-  if (ctx->record_stream) (void)hipStreamDestroy(ctx->record_stream);
   if (ctx->static_dev >= 0) {
     std::lock_guard<std::mutex> lock(g_static_mu);
     g_static[ctx->static_dev].in_use = false;

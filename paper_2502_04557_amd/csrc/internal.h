@@ -114,8 +114,6 @@ bool attn_shared(int dh, int H, int KVH, int entries, int ctx_bound, int run_len
 // Workgroups that share a row's keys in the decode attention of bf16 mode (1: one per row and KV head); a host function.
 constexpr int SPLIT_WGS = 256;   // rows x KV heads x workgroups per row and KV head stay within it
 int attn_split(int dh, int kvh, int rows, int ctx_bound);
-// What the decode attention's launches (phases 0 - 2) depend on ctx_bound for: equal plans, equal launches.
-int attention_plan(int dtype, const ModelDims& md, int rows, int ctx_bound);
 // Partial results of a split launch: [row][KV head][workgroup][H / KVH][dh + 2].
 inline size_t attn_split_floats(const ModelDims& md) { return (size_t)SPLIT_WGS * (md.H / md.KVH) * (md.dh + 2); }
 

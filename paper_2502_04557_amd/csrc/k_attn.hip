@@ -1156,14 +1156,6 @@ bool attn_shared(int dh, int H, int KVH, int entries, int ctx_bound, int run_len
   return G > 1 && (long long)(H / 2) * ((entries + 15) / 16) >= 1024 && (long long)ctx_bound * G >= (dh == 64 ? 7168 : 1536) && (long long)run_len * G >= 64;
 }
 
-// NW = waves per workgroup that share one (row, KV head)'s keys: 8 when the launch has no more workgroups than
-// the chip has compute units and the contexts are long, else 4
-static bool attn_wide(int kvh, int rows, int ctx_bound) { return (long long)kvh * rows <= 256 && ctx_bound >= 512; }
-
-int attention_plan(int dtype, const ModelDims& md, int rows, int ctx_bound) {
-  return dtype == 0 ? 0 : attn_split(md.dh, md.KVH, rows, ctx_bound) * 2 + attn_wide(md.KVH, rows, ctx_bound);
-}
-
 template <int DH>
 static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bound, int run_len, hipStream_t s) {
   if (a.phase == 1) {          // append only
@@ -1177,8 +1169,10 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
     else hipLaunchKernelGGL((k_attn_mfma_bf16<DH, false>), dim3(a.H, (max_rows + 31) / 32), dim3(64), 0, s, a);
     return;
   }
+  // NW = waves per workgroup that share one (row, KV head)'s keys: 8 when the launch has no more workgroups than
+  // the chip has compute units and the contexts are long, else 4
   dim3 grid(a.KVH, max_rows);
-  const bool wide = attn_wide(a.KVH, max_rows, ctx_bound);
+  const bool wide = (long long)a.KVH * max_rows <= 256 && ctx_bound >= 512;
   if (a.phase == 2) {          // attend-only, short runs
 #define SPRINTER_RUNS(NW, ROPE) hipLaunchKernelGGL((k_attn_runs_bf16<DH, NW, ROPE>), grid, dim3(NW * 64), 0, s, a)
     if (a.use_rope) { if (wide) SPRINTER_RUNS(8, true); else SPRINTER_RUNS(4, true); }

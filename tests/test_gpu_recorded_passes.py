@@ -1,7 +1,7 @@
-"""Passes of 12 and more layers are recorded the second time and replayed as a graph from the third on.  A context on the library's
-static workspace launches every pass as it is: both must give the same tokens, flags and scores, bit for bit, over repeated calls with
-eager work in between (a step that exports logits, a new prefill with another batch, new weights, contexts that grow past the length at
-which the attention's launches change)."""
+"""Passes that come again and again, through 12 layers: a context on the caller's workspace and one on the library's static workspace must
+give the same tokens, flags and scores, bit for bit, over repeated calls with eager work in between (a step that exports logits, a new
+prefill with another batch, new weights, contexts that grow past the length at which the attention's launches change); and none of it
+takes device memory, as recording such passes in graphs did (2 MB each)."""
 from dataclasses import replace
 import numpy as np
 import pytest
@@ -60,3 +60,26 @@ def test_recorded_passes_match_launches(dtype, over):
     if not cfg.sd_gamma:
         acc = np.concatenate([o["accept"].ravel() for o in got])
         assert 0 < acc.mean() < 1
+
+
+def test_generate_takes_no_device_memory():
+    """The workspace is all the device memory a context uses, however often the same pass comes."""
+    import torch
+    from paper_2502_04557_amd import binding
+    cfg = _cfg(W.DT_BF16)
+    _run(cfg, static=True)                                # (kernels are loaded at their first launch)
+    dw, tw, vw = W.make_weights(cfg)
+    prompts, plen = W.make_prompts(cfg)
+    s = binding.Sprinter(cfg, "cuda:0")
+    try:
+        for which, w in zip((binding.DRAFT, binding.TARGET, binding.VERIFIER), (dw, tw, _widen(vw))):
+            s.load_weights(which, w)
+        s.prefill(prompts, plen)
+        s.generate(1)
+        held = lambda: (torch.cuda.synchronize(), torch.cuda.mem_get_info()[0] + torch.cuda.memory_reserved())[1]
+        before = held()
+        for _ in range(36):
+            s.generate(1)
+        assert held() == before
+    finally:
+        s.close()
