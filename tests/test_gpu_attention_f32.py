@@ -1,4 +1,5 @@
-"""Float32 attention by itself against float64, at the values where one maximum per stream of keys is not one per row."""
+"""Float32 attention by itself against float64: contexts that end anywhere in the steps of the four waves and of their 16 streams of keys,
+and values at which a maximum per stream is not one per row."""
 import ctypes as C
 import pytest
 from test_gpu_prefill_attention import _Dims, _Rows, _lib
@@ -51,8 +52,8 @@ class _Step:
         torch.cuda.synchronize()
         return out
 
-    def reference(self):
-        """(attention, bound of the kernel's error) in float64."""
+    def reference(self, drop=None):
+        """(attention, bound of the kernel's error) in float64; drop: a key that is left out."""
         import torch
         G, outs, bounds = self.H // self.KVH, [], []
         q, kn, vn, qa, ka = self.new()
@@ -61,6 +62,8 @@ class _Step:
             k, v = (per_head(torch.cat([c[b, :, :s].double(), own[i, :, None]], 1)) for c, own in ((self.k, kn), (self.v, vn)))
             size = per_head(torch.cat([self.k[b, :, :s].double().abs(), ka[i, :, None]], 1))
             score = (q[i, :, None] * k).sum(-1) / self.dh ** 0.5
+            if drop is not None and 0 <= drop < s:
+                score[:, drop] = float("-inf")
             w = torch.softmax(score, -1)
             seen = torch.isfinite(score)
             # A score is 8 products per lane at most and 4 levels of a tree over rotated (3 roundings each), scaled operands: 24 roundings of
@@ -71,6 +74,43 @@ class _Step:
             outs.append(o)
             bounds.append((2 * e + (s / 16 + 40) * 2.0 ** -24) * torch.where(w[..., None] > 0, w[..., None] * v.abs(), 0.).sum(1))
         return torch.stack(outs), torch.stack(bounds)
+
+
+# a step of the four waves is 128 keys: one step, its last key, the next one's first, several; scores that rise (every step has a new
+# maximum), fall, or neither
+SLOTS = (0, 1, 3, 31, 32, 33, 96, 127, 128, 129, 160, 255, 256, 257, 511, 512, 777)
+
+
+@pytest.mark.parametrize("rope", [True, False])
+@pytest.mark.parametrize("dh,H,KVH", [(64, 3, 3), (64, 4, 2), (64, 8, 2), (64, 16, 2), (128, 2, 2), (128, 4, 2), (128, 4, 1), (128, 8, 1)])
+@pytest.mark.parametrize("rise", [0., 0.2, -0.2])
+def test_rows_of_every_length(dh, H, KVH, rise, rope):
+    import torch
+    p = _Step(dh, H, KVH, SLOTS, rope, dh + H)
+    q, kn, vn, _, ka = p.new()
+    for i, (b, s) in enumerate(zip(p.b.tolist(), p.slots)):
+        along = q[i, ::H // KVH].float()
+        p.k[b, :, :s] += (along / along.norm(dim=-1, keepdim=True))[:, None] * (torch.arange(s, device="cuda") * rise)[None, :, None]
+    (want, bound), before, at = p.reference(), (p.k.clone(), p.v.clone()), (p.b.long(), slice(None), p.slot.long())
+    got = p.run()
+    worst = float(((got.double() - want).abs() / bound).max())
+    print(dh, H, KVH, rise, rope, "worst share of the bound", round(worst, 3), flush=True)
+    assert worst <= 1
+    if rise == 0:
+        off = ((p.reference(drop=20)[0] - want).abs() / bound).amax((1, 2))
+        assert (off[torch.tensor(SLOTS, device="cuda") > 20] > 4).all()      # (the bound tells a missing key in every row)
+    # appended: the new key and value of every row, and nothing else
+    assert ((p.k[at].double() - kn).abs() <= ka * 3 * 2.0 ** -24).all() and torch.equal(p.v[at], vn.float())
+    for c, old in zip((p.k, p.v), before):
+        old[at] = c[at]
+        assert torch.equal(c.view(torch.int32), old.view(torch.int32))
+    # the same in two launches, as passes take it whose entries share a row's caches
+    after = p.k.clone(), p.v.clone()
+    p.k[at], p.v[at] = float("nan"), float("nan")
+    assert p.run(1).isnan().all()
+    for c, whole in zip((p.k, p.v), after):
+        assert torch.equal(c.view(torch.int32), whole.view(torch.int32))
+    assert torch.equal(p.run(2), got)
 
 
 # the keys that score -inf: all of one stream, all of a wave's first blocks, the row's first 128 (the first step of every wave), its own
