@@ -26,7 +26,11 @@ struct AttnArgs {
 // What bounds it is latency: arguments, then descriptors and projection, then keys and values, then about 200 vector instructions per
 // block.  us per launch, of a kernel with one pass over the keys for the scores, one for the values and barriers and shuffles through
 // LDS in between -> of this one: heads of 64, 1 row of 40 keys 4.5 -> 3.4, 6 rows x 8 heads x 60 keys 6.6 -> 4.1, 24 x 8 x 90 10.9 -> 5.3; of 128,
-// 3 x 8 x 300 43.6 -> 11.2, 8 heads per KV head, 2 x 2 x 500 138 -> 39.  Against 64 bits (2-norm, mean of 20 shapes) 1.22e-7 and 1.24e-7.
+// 3 x 8 x 300 43.6 -> 11.2, 8 heads per KV head, 2 x 2 x 500 138 -> 39.
+// Sums are taken in pairs - a block's weights and values before they join the stream's, the 16 streams at the end - since a stream has a
+// maximum, and a factor, of its own.  Error against 64 bits (2-norm over the result's, mean of 24 sets of 16 rows), one maximum per row
+// -> in order -> in pairs: 64 columns, 16 - 60 keys 1.24e-7 -> 1.27e-7 -> 1.21e-7, 60 - 130 1.37e-7 -> 1.51e-7 -> 1.32e-7, 130 - 300 1.51e-7 ->
+// 1.66e-7 -> 1.42e-7; 128 columns, 60 - 130 1.46e-7 -> 1.59e-7 -> 1.44e-7; it costs 0.05 - 0.09 us of 3.6 - 13.4 us per launch.
 template <int DH, int G, bool ROPE>
 __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
   constexpr int E = DH / 16, Q4 = E / 4, NK = 8, KB = 4 * NK, HALF = DH / 2;   // columns per lane, float4s of them, keys per stream and block
@@ -123,15 +127,17 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
         const float off = mx == -INFINITY ? 0.f : mx;            // (all its scores so far are -inf: weights of 0, as in a row with one maximum)
         const float corr = expf(m[g] - off);
         m[g] = mx;
-        l[g] *= corr;
+        static_assert(NK == 8, "the sum below");
+        float p[NK];
 #pragma unroll
-        for (int e = 0; e < E; ++e) o[g][e] *= corr;
+        for (int j = 0; j < NK; ++j) p[j] = expf(s[j] - off);
+        l[g] = l[g] * corr + (((p[0] + p[4]) + (p[2] + p[6])) + ((p[1] + p[5]) + (p[3] + p[7])));
 #pragma unroll
-        for (int j = 0; j < NK; ++j) {
-          const float p = expf(s[j] - off);
-          l[g] += p;
+        for (int e = 0; e < E; ++e) {
+          float even = p[0] * v[0][e], odd = p[1] * v[1][e];
 #pragma unroll
-          for (int e = 0; e < E; ++e) o[g][e] += p * v[j][e];
+          for (int j = 2; j < NK; j += 2) { even += p[j] * v[j][e]; odd += p[j + 1] * v[j + 1][e]; }
+          o[g][e] = o[g][e] * corr + (even + odd);
         }
       }
     }
@@ -146,16 +152,20 @@ __global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
   __syncthreads();
   for (int idx = tid; idx < G * DH; idx += 256) {
     const int g = idx / DH, i = idx % DH;
-    float mx = s_m[0][g], den = 0.f, num = 0.f;                  // (stream 0 has key 0)
+    float mx = s_m[0][g], den[16], num[16];                      // (stream 0 has key 0)
 #pragma unroll
     for (int t = 1; t < 16; ++t) mx = fmaxf(mx, s_m[t][g]);
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
       const float c = expf(s_m[t][g] - mx);
-      den += c * s_l[t][g];
-      num += c * s_o[t][g][i];
+      den[t] = c * s_l[t][g];
+      num[t] = c * s_o[t][g][i];
     }
-    act_store<float>((float*)a.ao, r, kvh * G * DH + idx, a.ao_K, num / den);
+#pragma unroll
+    for (int h = 8; h; h >>= 1)
+#pragma unroll
+      for (int t = 0; t < h; ++t) { den[t] += den[t + h]; num[t] += num[t + h]; }
+    act_store<float>((float*)a.ao, r, kvh * G * DH + idx, a.ao_K, num[0] / den[0]);
   }
 }
 

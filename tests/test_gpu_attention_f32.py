@@ -1,6 +1,7 @@
 """Float32 attention by itself against float64: contexts that end anywhere in the steps of the four waves and of their 16 streams of keys,
 and values at which a maximum per stream is not one per row."""
 import ctypes as C
+import numpy as np
 import pytest
 from test_gpu_prefill_attention import _Dims, _Rows, _lib
 
@@ -111,6 +112,18 @@ def test_rows_of_every_length(dh, H, KVH, rise, rope):
     for c, whole in zip((p.k, p.v), after):
         assert torch.equal(c.view(torch.int32), whole.view(torch.int32))
     assert torch.equal(p.run(2), got)
+
+
+# the limits are the errors of an attention with one maximum per row and a tree over the weights, measured on these inputs and rounded up
+@pytest.mark.parametrize("dh,lo,hi,limit", [(64, 16, 60, 1.25e-7), (64, 60, 130, 1.37e-7), (64, 130, 300, 1.52e-7), (128, 60, 130, 1.46e-7), (128, 130, 300, 1.68e-7)])
+def test_error_is_no_larger_than_with_one_maximum_per_row(dh, lo, hi, limit):
+    errors = []
+    for seed in range(24):
+        p = _Step(dh, 8, 8, tuple(np.random.default_rng(seed).integers(lo, hi, 16).tolist()), True, seed)
+        want, got = p.reference()[0], p.run().double()
+        errors.append(float((got - want).norm() / want.norm()))
+    print(dh, lo, hi, "error", np.mean(errors), flush=True)
+    assert np.mean(errors) <= limit
 
 
 # the keys that score -inf: all of one stream, all of a wave's first blocks, the row's first 128 (the first step of every wave), its own
