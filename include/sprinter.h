@@ -116,7 +116,10 @@ typedef struct {
  *   weights takes in a multi-entry forward (prefill, full-prefix work lists,
  *   speculative-decoding windows).  0 = default (bf16: 4096; float32: 256, on the
  *   static workspace 16); else a multiple of 64 in [64, 4096].  Never below max_batch
- *   rounded up. */
+ *   rounded up.
+ *   max_seq: float32 mode takes up to (16384 - 2 dh) / G - 5 dh positions, with G
+ *   query heads of dh columns per KV head (64 columns: 15936, 7808, 3744, 1712 for
+ *   G = 1, 2, 4, 8; 128 columns: 15488, 7424, 3392, 1376). */
 typedef struct {
   sprinter_model_cfg draft, target;
   int32_t ver_d_in, ver_d_hidden;

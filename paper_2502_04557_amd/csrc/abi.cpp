@@ -180,11 +180,12 @@ int validate_cfg(const sprinter_cfg* c, char* buf, size_t n) {
   if (c->sd_gamma < 0 || c->sd_gamma > 16) BAD("sd_gamma %d outside [0, 16]", c->sd_gamma);
   if (c->chunk_rows != 0 && (c->chunk_rows < 64 || c->chunk_rows > 4096 || c->chunk_rows % 64 != 0))
     BAD("chunk_rows %d is not 0 or a multiple of 64 in [64, 4096]", c->chunk_rows);
-  // float32 mode is for short contexts: one score per cached key and query head of a KV head, with the operands, in 64 KB
+  // float32 mode is for short contexts.  Its longest is a limit of this interface (a length that is refused stays refused), not of the
+  // attention kernel, which walks any number of keys.
   if (c->dtype == SPRINTER_F32) for (const sprinter_model_cfg* m : {&c->draft, &c->target}) {
-    int dh = m->d_model / m->n_head, G = m->n_head / m->n_kv_head;
-    size_t lds = (size_t)(G * dh + 2 * dh + 4 * G * dh + G * c->max_seq) * 4;
-    if (lds > 64 * 1024) BAD("attention needs %zu bytes of LDS for max_seq %d (limit 65536)", lds, c->max_seq);
+    const int dh = m->d_model / m->n_head, G = m->n_head / m->n_kv_head, longest = (16384 - 2 * dh) / G - 5 * dh;
+    if (c->max_seq > longest)
+      BAD("float32 mode takes max_seq up to %d with %d query heads of %d columns per KV head, not %d", longest, G, dh, c->max_seq);
   }
   return SPRINTER_OK;
 #undef BAD

@@ -155,3 +155,12 @@ def test_long_caches_of_a_small_pair_fit_the_static_workspace(lib):
     m = W.ModelCfg(W.ARCH_LLAMA, 1, 256, 4, 1, 512, 1000, 60000, 1e-5, 10000.0)
     rc, need, _ = _ws(lib, W.SprinterCfg(m, m, 32, W.DT_BF16, 1, 60000, chunk_rows=64))
     assert rc == 0 and need <= 40 << 20
+
+
+@pytest.mark.parametrize("dh,G,longest", [(64, 1, 15936), (64, 2, 7808), (64, 4, 3744), (64, 8, 1712), (128, 1, 15488), (128, 2, 7424), (128, 4, 3392), (128, 8, 1376)])
+def test_longest_context_of_float32_mode(lib, dh, G, longest):
+    """The lengths that float32 mode takes, as the header gives them; bf16 mode has no such limit."""
+    m = W.ModelCfg(W.ARCH_LLAMA, 1, 8 * dh, 8, 8 // G, 512, 1000, 16384, 1e-5, 10000.0)
+    for dtype, seq, rc in ((W.DT_F32, longest, 0), (W.DT_F32, longest + 1, -2), (W.DT_BF16, longest + 1, 0)):
+        got, _, msg = _ws(lib, W.SprinterCfg(m, m, 32, dtype, 1, seq, chunk_rows=64))
+        assert got == rc and (rc == 0 or f"up to {longest} " in msg), (dtype, seq, msg)
