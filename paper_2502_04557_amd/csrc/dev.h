@@ -14,19 +14,12 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef unsigned long long u64;
 
 // ------------------------------------------------------------------ scalars
-__device__ __forceinline__ float bf2f(bf16_t v) { return __uint_as_float(((unsigned)v) << 16); }
 __device__ __forceinline__ bf16_t f2bf(float f) {   // round to nearest even
   unsigned u = __float_as_uint(f);
   if ((u & 0x7fffffffu) > 0x7f800000u) return (bf16_t)((u >> 16) | 0x40);   // NaN stays NaN
   u += 0x7fffu + ((u >> 16) & 1u);
   return (bf16_t)(u >> 16);
 }
-template <typename T> __device__ __forceinline__ float to_f(T v);
-template <> __device__ __forceinline__ float to_f<float>(float v) { return v; }
-template <> __device__ __forceinline__ float to_f<bf16_t>(bf16_t v) { return bf2f(v); }
-template <typename T> __device__ __forceinline__ T from_f(float v);
-template <> __device__ __forceinline__ float from_f<float>(float v) { return v; }
-template <> __device__ __forceinline__ bf16_t from_f<bf16_t>(float v) { return f2bf(v); }
 
 // Activation layout: float32 mode = row-major [m][K]; bf16 mode = MFMA operand tiles.
 template <typename T> __device__ __forceinline__ size_t act_idx(int m, int k, int K);
@@ -135,22 +128,6 @@ __device__ __forceinline__ u64 shfl_xor_u64(u64 v, int o) {
   return ((u64)hi << 32) | lo;
 }
 __device__ __forceinline__ u64 umax64(u64 a, u64 b) { return a > b ? a : b; }
-
-// block-wide reductions for 256-thread blocks; result broadcast to all threads
-__device__ __forceinline__ float block_sum256(float v, float* s4) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return ((s4[0] + s4[1]) + s4[2]) + s4[3];
-}
-__device__ __forceinline__ float block_max256(float v, float* s4) {
-  v = wave_max(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) s4[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return fmaxf(fmaxf(s4[0], s4[1]), fmaxf(s4[2], s4[3]));
-}
 
 // ------------------------------------------------- Philox4x32-10 + Gumbel
 // Counter-based generator of Salmon et al. (SC'11).  key = seed, counter =
