@@ -493,7 +493,8 @@ void launch_lmhead(int dtype, const void* W, const void* X, size_t x_elems, cons
   } while (0)
     // Row tiles of a pass: as few as the rows need (their random blocks and logarithms are most of its time), 8 at most; more rows in
     // equal passes.  us at 80 / 96 / 160 rows with passes of 8 -> 5 / 6 / 2 x 5: 50257 words x 1600 76 / 77 / 145 -> 52 / 57 / 99, 128256 x 2048 169 / 171 /
-    // 302 -> 123 / 130 / 224, 32000 x 4096 85 / 86 / 156 -> 64 / 67 / 127.
+    // 302 -> 123 / 130 / 224, 32000 x 4096 85 / 86 / 156 -> 64 / 67 / 127; with the logits written too, 80 rows of
+    // 50257 words 95 -> 70.
     const int tiles = (max_rows + 15) / 16, passes = (tiles + 7) / 8, mt = (tiles + passes - 1) / passes;
     if (mt <= 2) SPRINTER_LM(2, 2, 2);
     else if (mt <= 4) SPRINTER_LM(4, 2, 2);

@@ -321,9 +321,10 @@ def test_random_shapes(seed):
 
 def test_large_vocabulary_many_rows():
     """A vocabulary of more than 65536 entries (over 8 column tiles per LM-head workgroup, a pair per wave, last
-    tile ragged) with 80 rows: the LM head variant with 8 row tiles and two column tiles per wave, which the five
+    tile ragged) with 80 rows: the LM head variant with 5 row tiles and two column tiles per wave, which the five
     benchmark shapes never reach (c5 has the vocabulary but 64 rows, c4 the rows but 32000 entries); the target
-    pass takes the 2- and 4-row-tile variants on the same vocabulary.  Every row replayed."""
+    pass takes the 2- and 4-row-tile variants on the same vocabulary.  (The variant with 8: test_gpu_lmhead_rows.py,
+    97 and more rows.)  Every row replayed."""
     from parity_util import compare_replay
     V, B, G = 66003, 80, 4
     cfg = W.SprinterCfg(W.ModelCfg(W.ARCH_LLAMA, 1, 128, 2, 1, 192, V, 32, 1e-5, 10000.0),
