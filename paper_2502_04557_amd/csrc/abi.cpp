@@ -217,7 +217,6 @@ void carve_model(Bump& bump, const sprinter_cfg& c, const sprinter_model_cfg& mc
   sc.ao = bump.take(act_elems(c.dtype, rows, md.H * md.dh) * es);
   sc.mid = bump.take(act_elems(c.dtype, rows, md.ff) * es);
   sc.hf = (float*)bump.take((size_t)rows * md.d * 4);
-  sc.h2 = sc.hf;                         // (a pass writes hf at its very end, when the rows are back in h: two exchanges per layer)
   sc.hfn = bump.take(act_elems(c.dtype, rows, md.d) * es);
   sc.rope = (float*)bump.take((size_t)rows * md.dh * 4);
   // also the scratch of a split attention, which is the smaller one: bf16 buffers hold 64 rows or more, 512 d >= 256 (H / KVH) (dh + 2)
@@ -386,21 +385,22 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   // O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
   // them (and the bias) into the residual stream before it normalises the row.  A product in one piece adds itself.
   const size_t part_stride = (size_t)rows * md.d;
-  // a few rows: the norms before QKV and FFN-up are part of those launches
-  const bool fused = !shared_caches && gemm_takes_norm(md.d, max_rows);
+  // a few rows: they always add themselves, and the norms before QKV and FFN-up are part of those launches (the rows' statistics lie in part,
+  // which the attention only takes between a layer's QKV and its O-proj)
+  const bool adds = !shared_caches && gemm_adds_rows(dt, md.d, max_rows), fused = adds && gemm_takes_norm(dt, md.d, max_rows);
   // Short passes (work lists, speculative windows) of a model without rotary positions: the projection's epilogue puts keys and values
   // where the append launch would.  (A key's rotary partner is another workgroup's; and a prefill pass gathers 8 slots of a value column
   // into one store in that launch, where an epilogue would write 2 bytes at a time.)
   // The append launch was 4.1 us per layer of 25 heads of 64 at 24 - 80 entries, next to 45 - 60 us of the others.
   const bool append_in_qkv = shared_caches && run_len == 0 && dt == SPRINTER_BF16 && md.arch == SPRINTER_ARCH_GPT;
-  float *h = sc.h, *h_other = sc.h2;
   NormPending pend{sc.part, part_stride, 0, nullptr};
   auto resid_gemm = [&](const void* W, const void* X, size_t plane, int K, const float* bias) {
-    pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, fused ? 4 : PART_SHARES, bias, h, max_rows, s);
+    if (adds) { launch_gemm_resid(dt, md.arch, W, X, md.d, K, bias, sc.h, sc.part, max_rows, s); return; }
+    pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, PART_SHARES, bias, sc.h, max_rows, s);
     pend.bias = bias;
   };
   auto norm = [&](const float* g, const float* b, void* out, float* f32_out, const EmbedSource* src = nullptr) {
-    launch_norm(dt, md.arch, h, g, b, md.eps, md.d, rd.n_rows, out, f32_out, max_rows, s,
+    launch_norm(dt, md.arch, sc.h, g, b, md.eps, md.d, rd.n_rows, out, f32_out, max_rows, s,
                 pend.shares > 0 ? &pend : nullptr, src);
     pend.shares = 0;
   };
@@ -408,10 +408,7 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   auto norm_gemm = [&](const float* g, const float* b, int epi, const void* W, const void* W2, int N, const float* bias, float* out_f32,
                        void* out_act, const EmbedSource* src = nullptr) {
     if (fused) {
-      NormFusion nf{h, h_other, g, b, md.eps, md.arch, pend, src ? *src : EmbedSource{}};
-      launch_gemm_norm(dt, epi, nf, W, W2, N, md.d, bias, out_f32, N, out_act, N, max_rows, s);
-      std::swap(h, h_other);
-      pend.shares = 0;
+      launch_norm_gemm(dt, md.arch, epi, sc.h, sc.part, g, b, md.eps, src, sc.h, W, W2, N, md.d, bias, out_f32 ? (void*)out_f32 : out_act, max_rows, s);
     } else {
       norm(g, b, sc.xn, nullptr, src);
       launch_gemm(dt, epi, W, W2, sc.xn, pl_d, rd.n_rows, N, md.d, bias, out_f32, N, out_act, N, max_rows, s);

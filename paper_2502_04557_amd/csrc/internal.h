@@ -37,7 +37,6 @@ struct ModelDims {
 constexpr int PART_SHARES = 8;   // most K shares launch_gemm_part may use
 struct ModelScratch {  // per-model activation buffers, sized for max_batch rows
   float* h;            // [M, d] residual stream, float32
-  float* h2;           // a few rows' residual stream: launch_gemm_norm alternates between h and this, which is hf
   void* xn;            // [M, d] normalised GEMM input (activation layout)
   float* y;            // [M, dqkv] QKV projection output, float32
   void* ao;            // [M, H*dh] attention output (activation layout)
@@ -92,14 +91,14 @@ void launch_gemm(int dtype, int epi, const void* W, const void* W2, const void* 
 void launch_gemm_qkv(const void* W, const void* X, size_t x_elems, const int* n_rows, int N, int K, const float* bias, float* y,
                      const KvDest& kv, int max_rows, hipStream_t s);
 
-// QKV / FFN-up of a few rows with the norm before it in the same launch (k_gemm_norm.hip): X = norm(h_in + pending) or
-// norm(embedding); the updated residual rows go to h_out (a buffer other than h_in).  At most 4 pending shares.
-struct NormFusion {
-  const float* h_in; float* h_out; const float *g, *b; float eps; int arch; NormPending pend; EmbedSource emb;   // emb.tok_emb NULL: h_in
-};
-bool gemm_takes_norm(int d, int rows);
-void launch_gemm_norm(int dtype, int epi, const NormFusion& f, const void* W, const void* W2, int N, int K, const float* bias,
-                      float* out_f32, int ldo, void* out_act, int out_K, int rows, hipStream_t s);
+// A pass of few rows (k_gemm_norm.hip).  gemm_adds_rows: O-projection and FFN-down go through launch_gemm_resid, which adds bias + X W^T to the residual rows h[rows, N] and
+// leaves the statistics of the new ones in stat (16 N bytes are enough).  gemm_takes_norm: QKV and FFN-up go through launch_norm_gemm, out = epilogue(norm(h) W^T), which
+// reads them - or, with emb, the rows' embeddings, which it also writes to h_out.  d, N of launch_gemm_resid: multiples of 64.
+bool gemm_takes_norm(int dtype, int d, int rows);
+bool gemm_adds_rows(int dtype, int d, int rows);
+void launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float* stat, const float* g, const float* b, float eps, const EmbedSource* emb,
+                      float* h_out, const void* W, const void* W2, int N, int d, const float* bias, void* out, int rows, hipStream_t s);
+void launch_gemm_resid(int dtype, int arch, const void* W, const void* X, int N, int K, const float* bias, float* h, float* stat, int rows, hipStream_t s);
 
 void launch_attention(int dtype, const ModelDims& md, const float* y, const float* rope, const RowDesc& rd,
                       void* kcache, void* vcache, size_t layer_off, int ctx_bound /* upper bound of the rows' cache lengths */,

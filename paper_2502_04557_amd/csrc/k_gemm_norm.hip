@@ -1,185 +1,233 @@
-// HIP kernel of the batched SPRINTER decode step for gfx950: QKV projection and FFN-up for a few rows, with the layer norm
-// (and the residual update or embedding before it) folded into the same launch.
+// HIP kernels of the batched SPRINTER decode step for gfx950: the layer of a pass of few rows in five launches.  O-projection and FFN-down add
+// themselves to the residual rows and leave the statistics of what they wrote (k_gemm_resid); QKV projection and FFN-up normalise
+// those rows for themselves (k_norm_gemm).
 #include "gemm.h"
 #include <algorithm>
 #include <cstring>
 
 namespace sprinter {
 
-// At a handful of rows a step is a chain of short dependent launches, and the norm is two of a layer's seven: 3 - 4 us each
-// for a few KiB of work.  Here every workgroup of the product that follows normalises the rows for itself: it requests the
-// weight tiles of its first k tiles, then reads the residual rows and the pending partial products (or the embeddings), adds
-// them in the order of k_norm, takes the statistics in two passes, and leaves the normalised rows in LDS, from where the
-// matrix instructions take them.  Workgroup 0 also writes the updated residual rows - to the other of two buffers, since its
-// neighbours are still reading this one.  What it costs is R d (1 + shares) floats per workgroup through L2 next to its own
-// weights, so it is taken only while that stays small (gemm_takes_norm).  In a chain - partial product, norm, product - as three
-// launches against two, at 1 / 2 / 3 / 4 rows, us: d = 1600, FFN-down in 4 shares, QKV 4800: 14.9 -> 13.1 / 13.4 / 14.2 / 15.1; O-proj
-// in 2, FFN-up 6400: 12.7 -> 10.7 / 11.4 / 12.0 / 12.7; d = 2048 (RMS), 4 shares, QKV 3072: 16.1 -> 13.5 / 14.2 / 14.9 / 15.5; 2 shares,
-// 2 x 8192: 20.7 -> 18.5 / 19.1 / 19.3 / 19.8; d = 768, 4 shares, QKV 2304: 12.0 -> 7.7 / 8.3 / 9.1 / 9.7; d = 512, 3 shares, 1024:
-// 11.6 -> 8.0 / 7.5 / 7.6 / 8.1.  Fewer shares cost the partial product more than they save here (1600, 4 rows: 15.1 with 4, 16.2 with 2).
-// Up to R rows.  Four and less: thread t takes float4 t of every row (d <= 2048), so gain, offset and bias are fetched once.  More (d <= 512): four
-// groups of 128 threads take R / 4 rows each, float4 t % 128 of them.
-template <typename AT, int R, int NTW, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
-  constexpr bool BF = sizeof(AT) == 2;                  // bf16 mode: float16 operand tiles; else float32 rows
-  constexpr bool DUAL = (EPI == EPI_SWIGLU), ACT_OUT = BF && (EPI == EPI_GELU || EPI == EPI_SWIGLU);
-  constexpr int NW = NTW * (DUAL ? 2 : 1), NI4 = NW * 4, U = 8;   // weight tiles per k tile; k tiles (16-k groups) in flight
-  constexpr int RG = R > 4 ? 4 : 1, RT = (R + RG - 1) / RG, WR = 8 / RG;   // groups of threads, rows per thread, waves per row
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// Workgroup barrier that orders LDS traffic only: __syncthreads() also waits for the weights in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// A buffer of n bytes: loads beyond it give zeros and fetch nothing.
+__device__ __forceinline__ auto bytes_at(const void* p, int n) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, n, 0x00020000); }
+constexpr int NOWHERE = 0x7ffffff0;      // an offset beyond any buffer (and what is added to it stays below 2^32)
+__device__ __forceinline__ float last_lane(float v) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63)); }
+
+// Statistics of the residual rows: for every row and every `cols` consecutive columns {sum, sum of squared distances from their mean}
+// (RMS norm: {-, sum of squares}), as the workgroup that wrote the columns took them.  A row's mean and variance are put together from them
+// with no pass over the row: variance d = sum over the groups of theirs + cols (group mean - mean)^2, the update of Chan, Golub and LeVeque,
+// which loses nothing against two passes.
+
+// A chain of short dependent launches is what a pass of few rows is, and the norm as a launch of its own two of a layer's seven: 3 - 4 us for a few KiB of
+// work.  Every workgroup of the product that follows can normalise the rows for itself, if that is cheap: here it reads them once, in one piece, with
+// at most 256 groups of statistics, and the weights it needs are requested behind them and arrive meanwhile.  (Before, it read residual rows and
+// up to four partial products, took the statistics in two passes through LDS and four barriers that waited for all weights in flight: 0.5 us a row
+// of 1600 columns, paid after the weights had arrived.)  The code is straight: buffers whose bounds make loads beyond them zeros instead of
+// branches, so that every wait counts the loads behind the one it is for; a barrier waits for LDS only.
+// A layer in a chain (graph over all layers, cold weights), us, before -> now: 1600 columns (25 heads, 6400), 1 row 28.0 -> 26.1, 4 rows 34.3 -> 28.5,
+// 8 rows (seven launches before) 34.2 -> 30.6; 768 (3072), 1 row 18.4 -> 16.3, 8 rows (seven) 24.5 -> 19.4, 16 rows (seven) 25.6 -> 23.4; 2048 (gate + up
+// 8192), 1 row 39.0 -> 35.4, 4 rows 42.3 -> 36.5, 8 rows (seven) 43.6 -> 38.6; 4096 (11008; seven), 2 rows 91.4 -> 83.2, 4 rows 96.5 -> 85.3; 512 (1344),
+// 4 rows 20.0 -> 17.4, 16 rows 21.6 -> 20.0; float32, 512 (2048), 1 row 22.1 -> 19.5, 8 rows 24.7 -> 22.4.
+// What bounds it: the weights at 4 - 5 TB/s and, of about 5.5 us at 15 MB, the start of a dependent launch, 1.6 us.
+// R = RT RG rows: RG groups of 512 / RG threads, a thread takes 8 columns of RT rows.  U: units of K in flight per wave.
+struct NormGemmArgs {
+  const float *h, *stat, *g, *b; const void *W, *W2; const float* bias; void* out;
+  int d, N, n_tiles, rows, groups; float eps, cols, inv_cols;   // groups of `cols` columns (a power of two) of the statistics
+  float* h_out; EmbedSource emb;                      // EMB: the rows are embeddings; workgroup 0 starts the residual stream with them
+};
+
+template <typename AT, int ARCH, int RT, int RG, int NTW, int EPI, bool EMB>
+__global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
+  constexpr bool BF = sizeof(AT) == 2;
+  constexpr bool DUAL = EPI == EPI_SWIGLU, ACT_OUT = BF && EPI != EPI_F32;
+  constexpr int R = RT * RG, CG = 512 / RG, WR = 8 / RG, NW = NTW * (DUAL ? 2 : 1), NI4 = NW * 4, SR = (R + 7) / 8;
+  constexpr int U = (BF ? 1 : 2) * 16 / RG > 8 ? 8 : (BF ? 1 : 2) * 16 / RG, NG = BF ? (RG >= 2 ? 8 / RG : 4) : RG == 8 ? 2 : 4;   // units in flight; loads of a row's statistics
   extern __shared__ __align__(16) unsigned char smem[];
-  __shared__ __attribute__((aligned(16))) float s_stat[2][R][WR];
+  __shared__ float2 s_stat[R];
+  __shared__ float s_part[2][R][WR];
   __shared__ float red[8 * NI4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
-  const int nt0 = blockIdx.x * NTW, d = a.K;
-  if constexpr (EPI == EPI_F32) {
-    if (__builtin_expect(nt0 >= a.n_tiles, 0)) {        // QKV of a first layer with rotary positions: one workgroup more for the rows' factors
-      const int half = f.emb.dh >> 1;
-      for (int i = tid; i < a.rows_live * half; i += 512) rope_factors(f.emb, i / half, i % half);
+  const int nt0 = blockIdx.x * NTW, d = a.d, units = BF ? d >> 5 : d >> 4;
+  if constexpr (EMB && ARCH == 1) {
+    if (__builtin_expect(nt0 >= a.n_tiles, 0)) {        // one workgroup more for the rows' rotary factors
+      const int half = a.emb.dh >> 1;
+      for (int i = tid; i < a.rows * half; i += 512) rope_factors(a.emb, i / half, i % half);
       return;
     }
   }
-  // ---- this wave's share of K: k tiles w, w + 8, .. (bf16) or 16-k groups [g0, g1) (float32); first weights requested
-  const int n_k = BF ? a.Kt : d >> 4;
-  const int g0 = BF ? w : n_k * w / 8, g1 = BF ? n_k : n_k * (w + 1) / 8, gs = BF ? 8 : 1;
-  const uint4* wp[NW];
+  // ---- statistics, residual rows, gain and offset; then the weights
+  float2 st[SR][NG];
+  if constexpr (!EMB) {
 #pragma unroll
-  for (int j = 0; j < NW; ++j) {
-    const void* W = DUAL && j >= NTW ? a.W2 : a.W;
-    const int nt = min(nt0 + (j % NTW), a.n_tiles - 1);
-    wp[j] = BF ? (const uint4*)W + (size_t)nt * a.Kt * 64 + lane
-               : (const uint4*)((const float*)W + (size_t)min(nt * 16 + l16, a.N - 1) * d + lq * 4);
+    for (int j = 0; j < SR; ++j) if (w + 8 * j < a.rows) {   // (scalar; the first loads, so no later wait depends on it)
+      const float2* sp = (const float2*)a.stat + (size_t)min(w + 8 * j, a.rows - 1) * a.groups;
+#pragma unroll
+      for (int i = 0; i < NG; ++i) st[j][i] = sp[min(lane + 64 * i, a.groups - 1)];
+    }
   }
-  uint4 wv[U][NW];
-  auto load_weights = [&](int g) {
+  const int col = tid % CG, rg = w / WR, n_ch = d >> 3, c8 = min(col, n_ch - 1) * 8;
+  const bool mine = col < n_ch;
+  float x[RT][8], gg[8], bb[8];
+  if constexpr (EMB) {
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (g + u * gs < g1) {                            // (scalar; the tiles beyond the share are skipped below too)
+    for (int i = 0; i < RT; ++i) {
+      const int r = min(rg * RT + i, a.rows - 1);
+      const int tok = min(max(a.emb.rd.tok[r], 0), a.emb.V - 1), pos = max(a.emb.rd.pos[r], 0);
+      load_row((const AT*)a.emb.tok_emb + (size_t)tok * d + c8, x[i]);
+      if (a.emb.pos_emb) {
+        float p[8];
+        load_row((const AT*)a.emb.pos_emb + (size_t)min(pos, a.emb.max_pos - 1) * d + c8, p);
 #pragma unroll
-        for (int j = 0; j < NW; ++j) wv[u][j] = wp[j][(size_t)(g + u * gs) * (BF ? 64 : 4)];
+        for (int e = 0; e < 8; ++e) x[i][e] += p[e];
       }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) load_row(a.h + (size_t)min(rg * RT + i, a.rows - 1) * d + c8, x[i]);
+  }
+  load_row(a.g + c8, gg);
+  if (ARCH == 0) load_row(a.b + c8, bb);
+  __builtin_amdgcn_sched_barrier(0);
+  const int w_lane = BF ? lane * 16 : (l16 * d + lq * 4) * 4;
+  auto tile = [&](int j) {
+    const int nt = nt0 + j % NTW;
+    const char* W = (const char*)(DUAL && j >= NTW ? a.W2 : a.W);
+    return bytes_at(W + (size_t)nt * 16 * d * sizeof(AT), nt < a.n_tiles ? (BF ? 16 : min(16, a.N - nt * 16)) * d * (int)sizeof(AT) : 0);
   };
-  load_weights(g0);
-  // this thread's output element: (row m, column c of the workgroup's 16 NTW columns), as in k_gemm16 / k_gemm_f32
-  int m, c;
+  u32x4 wv[U][NW];
+  auto load_unit = [&](int u, int unit) {
+#pragma unroll
+    for (int j = 0; j < NW; ++j) wv[u][j] = __builtin_amdgcn_raw_buffer_load_b128(tile(j), (BF || unit < units ? w_lane : NOWHERE) + unit * (BF ? 1024 : 64), 0, 0);
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) load_unit(u, w + 8 * u);
+  int m, c;                                             // this thread's output element, as in k_gemm16
   if (ACT_OUT) { m = (tid >> 3) & 15; c = (tid >> 7) * 8 + (tid & 7); }
   else { m = tid / (16 * NTW); c = tid % (16 * NTW); }
   const int n = nt0 * 16 + c;
-  const bool out_ok = tid < NTW * 256 && m < a.rows_live && n < a.N;
+  const bool out_ok = tid < NTW * 256 && m < a.rows && n < a.N;
   const float pbias = (out_ok && a.bias) ? a.bias[n] : 0.f;
-  // ---- residual rows
-  const int n4 = d >> 2, col = tid % (512 / RG), q4 = min(col, n4 - 1), r0 = w / WR * RT;   // this thread's rows: r0 .. (scalar)
-  const bool mine = col < n4;
-  const float4 gg = reinterpret_cast<const float4*>(f.g)[q4];
-  float4 bb = make_float4(0.f, 0.f, 0.f, 0.f), pb = bb, x[RT];
-  if (f.b) bb = reinterpret_cast<const float4*>(f.b)[q4];
-  if (f.emb.tok_emb) {                                  // first norm of a forward: the token's (and the position's) embedding
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (EMB) {
+    if (blockIdx.x == 0 && mine) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+        if (rg * RT + i < a.rows) {
+          float4* o = reinterpret_cast<float4*>(a.h_out + (size_t)(rg * RT + i) * d + c8);
+          o[0] = make_float4(x[i][0], x[i][1], x[i][2], x[i][3]);
+          o[1] = make_float4(x[i][4], x[i][5], x[i][6], x[i][7]);
+        }
+    }
+    float part[RT], mean[RT];
+    auto totals = [&](int slot) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) part[i] = wave_total(mine ? part[i] : 0.f);
+      if (lane == 63) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) s_part[slot][rg * RT + i][w % WR] = part[i];
+      }
+      lds_barrier();
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        part[i] = 0.f;
+#pragma unroll
+        for (int q = 0; q < WR; ++q) part[i] += s_part[slot][rg * RT + i][q];
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < RT; ++i) mean[i] = 0.f;
+    if (ARCH == 0) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) part[i] = ((x[i][0] + x[i][1]) + (x[i][2] + x[i][3])) + ((x[i][4] + x[i][5]) + (x[i][6] + x[i][7]));
+      totals(0);
+#pragma unroll
+      for (int i = 0; i < RT; ++i) mean[i] = part[i] / (float)d;
+    }
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
-      const int r = min(r0 + i, a.rows_live - 1);
-      const int tok = min(max(f.emb.rd.tok[r], 0), f.emb.V - 1), pos = max(f.emb.rd.pos[r], 0);
-      const AT* __restrict__ e = (const AT*)f.emb.tok_emb + (size_t)tok * d;
-      const AT* __restrict__ p = f.emb.pos_emb ? (const AT*)f.emb.pos_emb + (size_t)min(pos, f.emb.max_pos - 1) * d : nullptr;
-      float ev[4], pv[4] = {0.f, 0.f, 0.f, 0.f};
-      load_row(e + q4 * 4, ev);
-      if (p) load_row(p + q4 * 4, pv);
-      x[i] = make_float4(ev[0] + pv[0], ev[1] + pv[1], ev[2] + pv[2], ev[3] + pv[3]);
+      part[i] = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { const float t = x[i][e] - mean[i]; part[i] += t * t; }
+    }
+    totals(1);
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) s_stat[rg * RT + i] = make_float2(mean[i], 1.0f / sqrtf(part[i] / (float)d + a.eps));
     }
   } else {
-    if (f.pend.bias) pb = reinterpret_cast<const float4*>(f.pend.bias)[q4];
-    float4 p[RT][4];
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const size_t q = (size_t)min(r0 + i, a.rows_live - 1) * n4 + q4;
-      x[i] = reinterpret_cast<const float4*>(f.h_in)[q];
+    for (int j = 0; j < SR; ++j) {
+      float mean = 0.f, s = 0.f;
+      if (ARCH == 0) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (s < f.pend.shares) p[i][s] = reinterpret_cast<const float4*>(f.pend.part + (size_t)s * f.pend.stride)[q];   // (scalar test)
-    }
+        for (int i = 0; i < NG; ++i) s += lane + 64 * i < a.groups ? st[j][i].x : 0.f;
+        mean = last_lane(wave_total(s)) / (float)d;
+        s = 0.f;
+      }
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {                       // fixed order: bias, share 0, share 1, ...
-      x[i].x += pb.x; x[i].y += pb.y; x[i].z += pb.z; x[i].w += pb.w;
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (s < f.pend.shares) { x[i].x += p[i][s].x; x[i].y += p[i][s].y; x[i].z += p[i][s].z; x[i].w += p[i][s].w; }
+      for (int i = 0; i < NG; ++i) {
+        float q = st[j][i].y;
+        if (ARCH == 0) { const float t = st[j][i].x * a.inv_cols - mean; q += a.cols * (t * t); }
+        s += lane + 64 * i < a.groups ? q : 0.f;
+      }
+      const float rstd = 1.0f / sqrtf(last_lane(wave_total(s)) / (float)d + a.eps);
+      if (lane == 0 && w + 8 * j < R) s_stat[w + 8 * j] = make_float2(mean, rstd);
     }
   }
-  if (blockIdx.x == 0 && mine) {
+  lds_barrier();
+  // ---- normalised rows to LDS: float16 operand slots [k / 8][row] of 16 bytes, or float32 rows (4 floats of padding)
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
-      if (r0 + i < a.rows_live) reinterpret_cast<float4*>(f.h_out)[(size_t)(r0 + i) * n4 + col] = x[i];
-  }
-  // ---- statistics: the wave (DPP only), then every thread adds the 8 waves' sums.  No shuffles through LDS and one store
-  // block for all rows: a wave-wide butterfly per row, each waited for on its own, was 0.3 us a row.
-  float part[RT];
-  auto row_sums = [&](int slot) {
+  for (int i = 0; i < RT; ++i) {
+    const int r = rg * RT + i;
+    const float2 ms = s_stat[r];
+    float o[8];
 #pragma unroll
-    for (int i = 0; i < RT; ++i) part[i] = wave_total(part[i]);
-    if (lane == 63) {
-#pragma unroll
-      for (int i = 0; i < RT; ++i) if (r0 + i < a.rows_live) s_stat[slot][r0 + i][w % WR] = part[i];
+    for (int e = 0; e < 8; ++e) {
+      o[e] = (x[i][e] - ms.x) * ms.y * gg[e];
+      if (ARCH == 0) o[e] += bb[e];
     }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const float* st = s_stat[slot][min(r0 + i, a.rows_live - 1)];
-      if constexpr (RG == 1) {
-        const float4 u = *reinterpret_cast<const float4*>(st), v = *reinterpret_cast<const float4*>(st + 4);
-        part[i] = (((u.x + u.y) + (u.z + u.w)) + ((v.x + v.y) + (v.z + v.w)));
-      } else {
-        part[i] = st[0] + st[1];                        // (the same sum: the other waves' are zero where d <= 512)
+    if (mine) {
+      if constexpr (BF) *reinterpret_cast<uint4*>(smem + ((size_t)col * R + r) * 16) = make_uint4(pk_f16(o[0], o[1]), pk_f16(o[2], o[3]), pk_f16(o[4], o[5]), pk_f16(o[6], o[7]));
+      else {
+        float4* p = reinterpret_cast<float4*>(smem + ((size_t)r * (d + 4) + c8) * 4);
+        p[0] = make_float4(o[0], o[1], o[2], o[3]);
+        p[1] = make_float4(o[4], o[5], o[6], o[7]);
       }
     }
-  };
-  if (f.arch == 0) {
-#pragma unroll
-    for (int i = 0; i < RT; ++i) part[i] = mine ? (x[i].x + x[i].y) + (x[i].z + x[i].w) : 0.f;
-    row_sums(0);
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const float mean = part[i] / (float)d;
-      x[i].x -= mean; x[i].y -= mean; x[i].z -= mean; x[i].w -= mean;
-    }
   }
-#pragma unroll
-  for (int i = 0; i < RT; ++i) part[i] = mine ? (x[i].x * x[i].x + x[i].y * x[i].y) + (x[i].z * x[i].z + x[i].w * x[i].w) : 0.f;
-  row_sums(1);
-  // ---- normalised rows to LDS: float16 operand slots [k / 8][row] of 16 bytes, or float32 rows (4 floats of padding)
-  if (mine) {
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const float rstd = 1.0f / sqrtf(part[i] / (float)d + f.eps);
-      const float o0 = x[i].x * rstd * gg.x + bb.x, o1 = x[i].y * rstd * gg.y + bb.y;
-      const float o2 = x[i].z * rstd * gg.z + bb.z, o3 = x[i].w * rstd * gg.w + bb.w;
-      const int r = r0 + i;
-      if (r >= a.rows_live) continue;                   // (scalar)
-      if (BF) *reinterpret_cast<uint2*>(smem + ((size_t)(col >> 1) * R + r) * 16 + (col & 1) * 8) = make_uint2(pk_f16(o0, o1), pk_f16(o2, o3));
-      else *reinterpret_cast<float4*>(smem + ((size_t)r * (d + 4) + col * 4) * 4) = make_float4(o0, o1, o2, o3);
-    }
-  }
-  __syncthreads();
-  // ---- product
-  const int xrow = min(l16, a.rows_live - 1);        // (lanes of absent rows repeat the last one; their outputs are dropped)
+  lds_barrier();
+  // ---- product: wave w takes units (32 k, or 16 in float32) w, w + 8, ..
+  const int xrow = min(l16, R - 1);                     // (outputs of rows that do not exist are dropped)
   f32x4 acc[NW];
 #pragma unroll
   for (int j = 0; j < NW; ++j) acc[j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  for (int g = g0; g < g1; g += U * gs) {
-    if (g != g0) load_weights(g);
+  auto use = [&](int u, int unit) {
+    const int k = min(unit, units - 1);                 // (beyond: zero weights)
+    if constexpr (BF) {
+      const uint4 xv = *reinterpret_cast<const uint4*>(smem + ((size_t)(k * 4 + lq) * R + xrow) * 16);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (g + u * gs < g1) {                            // (scalar)
-        if constexpr (BF) {
-          const uint4 xv = *reinterpret_cast<const uint4*>(smem + ((size_t)((g + u * 8) * 4 + lq) * R + xrow) * 16);
+      for (int j = 0; j < NW; ++j) acc[j] = mfma_f16(xv, make_uint4(wv[u][j].x, wv[u][j].y, wv[u][j].z, wv[u][j].w), acc[j]);
+    } else {
+      const float4 xv = *reinterpret_cast<const float4*>(smem + ((size_t)xrow * (d + 4) + k * 16 + lq * 4) * 4);
 #pragma unroll
-          for (int j = 0; j < NW; ++j) acc[j] = mfma_f16(xv, wv[u][j], acc[j]);
-        } else {
-          const float4 xv = *reinterpret_cast<const float4*>(smem + ((size_t)xrow * (d + 4) + (g + u) * 16 + lq * 4) * 4);
-#pragma unroll
-          for (int j = 0; j < NW; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32((&xv.x)[e], __uint_as_float((&wv[u][j].x)[e]), acc[j], 0, 0, 0);
-        }
+      for (int j = 0; j < NW; ++j) {
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.x, __uint_as_float(wv[u][j].x), acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.y, __uint_as_float(wv[u][j].y), acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.z, __uint_as_float(wv[u][j].z), acc[j], 0, 0, 0);
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv.w, __uint_as_float(wv[u][j].w), acc[j], 0, 0, 0);
       }
+    }
+  };
+  int unit = w;
+  for (; unit + 8 * U < units; unit += 8 * U) {         // (scalar)
+#pragma unroll
+    for (int u = 0; u < U; ++u) { use(u, unit + 8 * u); load_unit(u, unit + 8 * (U + u)); }
   }
+#pragma unroll
+  for (int u = 0; u < U; ++u) use(u, unit + 8 * u);
 #pragma unroll
   for (int j = 0; j < NW; ++j)
 #pragma unroll
@@ -187,50 +235,222 @@ __global__ __launch_bounds__(512) void k_gemm_norm(GemmArgs a, NormFusion f) {
   __syncthreads();
   if (!out_ok) return;
   const int it = (c >> 4) * 4 + (m & 3), sl = (m >> 2) * 16 + (c & 15);
-  float s1 = 0.f, sg = 0.f;
+  float s1 = 0.f, s2 = 0.f;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {                         // fixed order: wave 0, 1, ..
     s1 += red[((size_t)q * NI4 + it) * 64 + sl];
-    if (DUAL) sg += red[((size_t)q * NI4 + NTW * 4 + it) * 64 + sl];
+    if (DUAL) s2 += red[((size_t)q * NI4 + NTW * 4 + it) * 64 + sl];
   }
-  gemm_epilogue<EPI, AT>(a, a.rows_live, m, n, s1, sg, pbias);
+  if constexpr (EPI == EPI_F32) ((float*)a.out)[(size_t)m * a.N + n] = s1 + pbias;
+  else if constexpr (EPI == EPI_GELU) act_store<AT>((AT*)a.out, m, n, a.N, gelu_tanh(s1 + pbias));
+  else act_store<AT>((AT*)a.out, m, n, a.N, silu(s1) * s2);
 }
 
-// The line: one row saves about 2 us of a 1600-wide chain and each further one gives 0.6 - 0.7 back, so the fourth breaks even there;
-// narrower chains are still ahead with four.  At 8 rows the fused launch was 2 - 3 us slower at 1600 and 2048.  Wider rows (4096: 896 workgroups for FFN-up) lose already at one: 45.6 -> 48.4 us.
-// Up to 512 columns, where four groups of threads share the rows, it is ahead or equal up to 16, and the chain has two launches less per
-// layer for the host.  us per layer of such a chain, 7 launches / 5, as a graph and where the host needs 3.7 us per launch: 512 columns
-// (RMS), 5 rows 19.7 / 17.1 and 28.4 / 23.9, 8 rows 19.9 / 17.6 and 29.1 / 24.2, 12 rows 20.1 / 18.9, 16 rows 20.2 / 20.4 and 27.7 / 25.8; float32,
-// 512 columns, 8 rows 26.5 / 23.2, 16 rows 28.1 / 27.0; 256 columns, 16 rows 22.3 / 21.5.  (All rows in every thread: 8 rows 21.5 for 17.6.)
-bool gemm_takes_norm(int d, int rows) { return rows <= 4 ? d <= 2048 : rows <= 16 && d <= 512; }
+template <int C>
+__device__ __forceinline__ float columns_sum(float v) {   // over C = 4, 8 or 16 consecutive lanes
+  if constexpr (C > 4) return group_sum<C>(v);
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));           // quad_perm [1,0,3,2]
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));     // quad_perm [2,3,0,1]
+}
+// O-projection and FFN-down of at most 16 rows: h += bias + X W^T in place, and the statistics of what was written.  A workgroup has all of K for its columns, so
+// that it can finish them, and 16 / S columns instead of 16 where that takes to fill the chip (N <= 2048): a weight load then carries S k
+// tiles of the columns - 128 bytes of each for S = 2, a line -, as many bytes per workgroup as K in S shares.  What that costs is the activations of
+// all of K in every workgroup, and the address unit takes 16 cycles per load whatever it brings: so where an operand's 16 rows are not all there, a load
+// carries 16 / RP tiles of RP rows side by side.  Products of unequal k tiles land in accumulator elements of their own and are dropped at the end.
+// Four accumulators at least, and the 8 waves' sums in pairs: what K in shares over workgroups won in precision stays (error of the residual rows against 64 bits,
+// 2-norm, K in shares -> in order -> so: 1600 x 6400, 4 rows 8.7e-8 -> 9.5e-8 -> 6.9e-8; 4096 x 14336, 16 rows 1.58e-7 -> 2.13e-7 -> 1.19e-7).
+// us, K in shares over workgroups and the sum left to the norm -> this: 1600 x 6400, 4 rows 6.3 -> 6.7, 16 rows 7.1 -> 9.0; 1600 x 1600 3.8 -> 3.8;
+// 4096 x 14336 and 4096 x 4096 at 5 - 16 rows 24.7 -> 22.5 and 12.1 -> 8.1; the norms behind it 3.4 -> 2.9, or gone (above).
+struct ResidArgs {
+  const void *W, *X; float *h, *stat; const float* bias; int N, K, rows, groups;
+};
 
-template <typename AT, int NTW, int EPI>
-static void launch_gemm_norm_epi(const GemmArgs& a, const NormFusion& f, int rows, hipStream_t s) {
-  const dim3 grid((a.n_tiles + NTW - 1) / NTW + (f.emb.rope ? 1 : 0));   // (one workgroup has them all)
-  const int R = rows <= 4 ? rows : (rows + 3) / 4 * 4;    // (the kernel's, which strides LDS by it)
-  const size_t lds = sizeof(AT) == 2 ? (size_t)R * a.K * 2 : (size_t)R * (a.K + 4) * 4;
-#define SPRINTER_FUSED(R_) hipLaunchKernelGGL((k_gemm_norm<AT, R_, NTW, EPI>), grid, dim3(512), lds, s, a, f)
-  if (rows == 1) SPRINTER_FUSED(1); else if (rows == 2) SPRINTER_FUSED(2); else if (rows == 3) SPRINTER_FUSED(3); else if (rows == 4) SPRINTER_FUSED(4);
-  else if (rows <= 8) SPRINTER_FUSED(8); else if (rows <= 12) SPRINTER_FUSED(12); else SPRINTER_FUSED(16);
-#undef SPRINTER_FUSED
+// RP: rows an activation load carries (4, 8 or 16).  UG: groups of T = max(16 / RP, S) k tiles in flight per wave.
+template <typename AT, int ARCH, int S, int RP, int UG>
+__global__ __launch_bounds__(512) void k_gemm_resid(ResidArgs a) {
+  constexpr bool BF = sizeof(AT) == 2;
+  constexpr int C = 16 / S, P = 16 / RP, T = P > S ? P : S, NX = T / P, NWL = T / S, NM = NX > NWL ? NX : NWL, KU = BF ? 32 : 16;
+  constexpr int NA = P >= S ? P / S : S;                // accumulators: which of their elements are sums of matching k is below
+  constexpr int D = NA < 4 ? 4 / NA : 1;                // each D times, for groups in turn
+  __shared__ float red[8 * 4 * 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
+  const int K = a.K, kt = (K + KU - 1) / KU, groups = (kt + T - 1) / T, n0 = blockIdx.x * C;
+  const int ws = l16 / C, wc = l16 % C, xp = l16 / RP, xr = l16 % RP;
+  const auto rw = BF ? bytes_at((const char*)a.W + (size_t)(n0 >> 4) * kt * 1024, kt * 1024) : bytes_at((const char*)a.W + (size_t)n0 * K * 4, C * K * 4);
+  const auto rx = BF ? bytes_at(a.X, kt * 1024) : bytes_at(a.X, a.rows * K * 4);
+  const int w_lane = BF ? ws * 1024 + (lq * 16 + (n0 & 15) + wc) * 16 : wc * K * 4 + (ws * 16 + lq * 4) * 4;
+  const int x_lane = xr < a.rows ? (BF ? xp * 1024 + (lq * 16 + xr) * 16 : xr * K * 4 + (xp * 16 + lq * 4) * 4) : NOWHERE;
+  constexpr int TB = BF ? 1024 : 64;                    // bytes from one k tile to the next
+  u32x4 wv[UG][NWL], xv[UG][NX];
+  auto load_group = [&](int u, int g) {
+#pragma unroll
+    for (int i = 0; i < NX; ++i) {
+      const int t = g * T + i * P;
+      xv[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (BF || (t + xp) * KU + lq * 4 < K ? x_lane : NOWHERE) + t * TB, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < NWL; ++i) {
+      const int t = g * T + i * S;
+      wv[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (BF || (t + ws) * KU + lq * 4 < K ? w_lane : NOWHERE) + t * TB, 0, 0);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < UG; ++u) load_group(u, w + 8 * u);
+  // this thread's output element: the row's columns in consecutive lanes
+  const int m = tid / C, c = tid % C, n = n0 + c;
+  const bool out_ok = m < a.rows;
+  float res = 0.f;
+  if (out_ok) { res = a.h[(size_t)m * a.N + n]; if (a.bias) res += a.bias[n]; }
+  f32x4 acc[NA][D];
+#pragma unroll
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int v = 0; v < D; ++v) acc[i][v] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  auto use = [&](int u) {
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      const u32x4 x = xv[u][i % NX], wt = wv[u][i % NWL];
+      f32x4& sum = acc[i % NA][u % D];
+      if constexpr (BF) sum = mfma_f16(make_uint4(x.x, x.y, x.z, x.w), make_uint4(wt.x, wt.y, wt.z, wt.w), sum);
+      else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[e]), __uint_as_float(wt[e]), sum, 0, 0, 0);
+      }
+    }
+  };
+  int g = w;
+  for (; g + 8 * UG < groups; g += 8 * UG) {            // (scalar)
+#pragma unroll
+    for (int u = 0; u < UG; ++u) { use(u); load_group(u, g + 8 * (UG + u)); }
+  }
+#pragma unroll
+  for (int u = 0; u < UG; ++u) use(u);
+  // Operand row RP p + r is row r at k tile p of a load, operand column C s + c column c at tile s: accumulator i sums matching tiles
+  // where p = S i + s (P >= S), or s = i (P = 1).
+  const int mine = P >= S ? (lq * 4 / RP) / S : ws;
+#pragma unroll
+  for (int i = 0; i < NA; ++i) {
+    if constexpr (D == 2) acc[i][0] += acc[i][1];
+    if constexpr (D == 4) acc[i][0] = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    float x = acc[0][0][v];
+#pragma unroll
+    for (int i = 1; i < NA; ++i) x = mine == i ? acc[i][0][v] : x;
+    red[(w * 4 + v) * 64 + lane] = x;
+  }
+  __syncthreads();
+  if (tid >= RP * C) return;
+  float sum[8 * T];
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int row = (P == 1 ? 0 : t * RP) + m, s = t % S;
+      sum[q * T + t] = red[(q * 4 + (row & 3)) * 64 + (row >> 2) * 16 + s * C + c];
+    }
+#pragma unroll
+  for (int half = 4 * T; half; half >>= 1)              // in pairs, always the same ones
+#pragma unroll
+    for (int i = 0; i < half; ++i) sum[i] += sum[i + half];
+  const float v = res + sum[0];
+  float mean = 0.f, dv = v, s1 = 0.f;
+  if (ARCH == 0) { s1 = columns_sum<C>(v); mean = s1 * (1.0f / C); dv = v - mean; }
+  const float s2 = columns_sum<C>(dv * dv);
+  if (!out_ok) return;
+  a.h[(size_t)m * a.N + n] = v;
+  if (c == 0) reinterpret_cast<float2*>(a.stat)[(size_t)m * a.groups + blockIdx.x] = make_float2(s1, s2);
 }
 
-void launch_gemm_norm(int dtype, int epi, const NormFusion& f, const void* W, const void* W2, int N, int K, const float* bias,
-                      float* out_f32, int ldo, void* out_act, int out_K, int rows, hipStream_t s) {
-  GemmArgs a;
-  memset(&a, 0, sizeof a);
-  a.W = W; a.W2 = W2; a.N = N; a.K = K; a.Kt = (K + 31) / 32; a.n_tiles = (N + 15) / 16;
-  a.bias = bias; a.out_f32 = out_f32; a.ldo = ldo; a.out_act = out_act; a.out_K = out_K; a.rows_live = rows;
-#define SPRINTER_EPI(AT, NTW)                                                                 \
-  do {                                                                                        \
-    if (epi == EPI_F32) launch_gemm_norm_epi<AT, NTW, EPI_F32>(a, f, rows, s);                \
-    else if (epi == EPI_GELU) launch_gemm_norm_epi<AT, NTW, EPI_GELU>(a, f, rows, s);         \
-    else launch_gemm_norm_epi<AT, NTW, EPI_SWIGLU>(a, f, rows, s);                            \
+// Column groups of the statistics: 16 / split columns each, at most 256 groups where a product reads them.  float32 rows hold their k side by side, so four columns
+// fill lines too: 512 x 2048, 1 row 5.0 -> 4.0 us, 8 rows 6.0 -> 5.4 but the norms behind it lose that again.
+static int resid_split(int dtype, int N, int rows) { return N > 2048 ? 1 : dtype == 0 && N <= 1024 && rows <= 4 ? 4 : 2; }
+
+// The line: us per layer, seven launches / five.  1600 columns: 8 rows 34.2 / 30.6, 10 rows 35.9 / 35.7, 16 rows 38.4 / 38.9; 2048 (gate + up): 8 rows 43.6 / 38.6, 10 rows 44.1 / 44.6;
+// 4096: 4 rows 96.5 / 85.3, 5 rows 92.9 / 96.8; 768: 16 rows 25.6 / 23.4; 1024: 16 rows 28.8 / 27.2.  (Activations of more than 8 rows fill an operand; 5 rows of 4096 in
+// every thread leave one workgroup per compute unit.)  float32 rows take twice the LDS.
+bool gemm_takes_norm(int dtype, int d, int rows) {
+  if (dtype == 0) return rows <= (d <= 512 ? 16 : d <= 1024 ? 8 : d <= 2048 ? 4 : 0);
+  return rows <= (d <= 1024 ? 16 : d <= 2048 ? 8 : d <= 4096 ? 4 : 0);
+}
+// Whether O-projection and FFN-down add themselves to the residual rows: wherever the norms are in the products and, at most 16 rows, from 2049 columns on, where the
+// columns alone fill the chip.  us per layer with the norms as launches, partial products / this: 4096 (11008), 8 rows 98.6 / 92.9, 16 rows 110.6 / 104.6; 4096 (14336, 8 KV heads),
+// 5 rows 104.2 / 100.0, 16 rows 109.6 / 103.3; but 1600, 16 rows 38.3 / 38.8, 2048 44.6 / 46.4.
+bool gemm_adds_rows(int dtype, int d, int rows) { return gemm_takes_norm(dtype, d, rows) || (dtype != 0 && d > 2048 && rows <= 16); }
+
+template <typename AT, int ARCH, int NTW, int EPI, bool EMB>
+static void launch_norm_gemm_rows(const NormGemmArgs& a, hipStream_t s) {
+  const dim3 grid((a.n_tiles + NTW - 1) / NTW + (EMB && ARCH == 1 ? 1 : 0));
+#define SPRINTER_NG(RT, RG)                                                                                  \
+  do {                                                                                                       \
+    const size_t lds = sizeof(AT) == 2 ? (size_t)RT * RG * a.d * 2 : (size_t)RT * RG * (a.d + 4) * 4;          \
+    hipLaunchKernelGGL((k_norm_gemm<AT, ARCH, RT, RG, NTW, EPI, EMB>), grid, dim3(512), lds, s, a);           \
   } while (0)
-  if (dtype == 0) SPRINTER_EPI(float, 1);
-  else if (a.n_tiles >= 256 && a.Kt < 100) SPRINTER_EPI(bf16_t, 2);   // two column tiles per wave, as k_gemm16
-  else SPRINTER_EPI(bf16_t, 1);
-#undef SPRINTER_EPI
+  constexpr bool BF = sizeof(AT) == 2;
+  if constexpr (NTW == 1) {
+    if (a.d <= 512) { if (a.rows <= 8) SPRINTER_NG(1, 8); else SPRINTER_NG(2, 8); return; }
+    if (a.d <= 1024) {
+      if (a.rows <= 4) { SPRINTER_NG(1, 4); return; }
+      if (a.rows <= 8) { SPRINTER_NG(2, 4); return; }
+      if constexpr (BF) { SPRINTER_NG(4, 4); return; }
+    }
+    if constexpr (BF)
+      if (a.d > 2048) { if (a.rows <= 1) SPRINTER_NG(1, 1); else if (a.rows <= 2) SPRINTER_NG(2, 1); else SPRINTER_NG(4, 1); return; }
+  }
+  if (a.rows <= 2) { SPRINTER_NG(1, 2); return; }
+  if (a.rows <= 4) { SPRINTER_NG(2, 2); return; }
+  if constexpr (BF) SPRINTER_NG(4, 2);
+#undef SPRINTER_NG
+}
+
+template <typename AT, int ARCH>
+static void launch_norm_gemm_arch(int epi, bool emb, const NormGemmArgs& a, hipStream_t s) {
+  constexpr int ACT = ARCH == 0 ? EPI_GELU : EPI_SWIGLU;
+  if constexpr (sizeof(AT) == 2) {
+    if (a.n_tiles >= 256 && a.d > 1024 && a.d <= 2048) {   // two column tiles per wave, as k_gemm16
+      if (epi != EPI_F32) launch_norm_gemm_rows<AT, ARCH, 2, ACT, false>(a, s);
+      else if (emb) launch_norm_gemm_rows<AT, ARCH, 2, EPI_F32, true>(a, s);
+      else launch_norm_gemm_rows<AT, ARCH, 2, EPI_F32, false>(a, s);
+      return;
+    }
+  }
+  if (epi != EPI_F32) launch_norm_gemm_rows<AT, ARCH, 1, ACT, false>(a, s);
+  else if (emb) launch_norm_gemm_rows<AT, ARCH, 1, EPI_F32, true>(a, s);
+  else launch_norm_gemm_rows<AT, ARCH, 1, EPI_F32, false>(a, s);
+}
+
+void launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float* stat, const float* g, const float* b, float eps, const EmbedSource* emb,
+                      float* h_out, const void* W, const void* W2, int N, int d, const float* bias, void* out, int rows, hipStream_t s) {
+  NormGemmArgs a;
+  memset(&a, 0, sizeof a);
+  const int S = resid_split(dtype, d, rows);
+  a.h = h; a.stat = stat; a.g = g; a.b = b; a.W = W; a.W2 = W2; a.bias = bias; a.out = out;
+  a.d = d; a.N = N; a.n_tiles = (N + 15) / 16; a.rows = rows; a.groups = d * S / 16; a.eps = eps; a.cols = 16 / S; a.inv_cols = S / 16.f;
+  a.h_out = h_out;
+  if (emb) a.emb = *emb;
+  if (dtype == 0) { if (arch == 0) launch_norm_gemm_arch<float, 0>(epi, emb, a, s); else launch_norm_gemm_arch<float, 1>(epi, emb, a, s); }
+  else { if (arch == 0) launch_norm_gemm_arch<bf16_t, 0>(epi, emb, a, s); else launch_norm_gemm_arch<bf16_t, 1>(epi, emb, a, s); }
+}
+
+template <typename AT, int ARCH, int S>
+static void launch_gemm_resid_split(const ResidArgs& a, hipStream_t s) {
+  const int ku = sizeof(AT) == 2 ? 32 : 16, kt = (a.K + ku - 1) / ku, rp = a.rows <= 4 ? 4 : a.rows <= 8 ? 8 : 16;
+  const int T = std::max(16 / rp, S), per_wave = ((kt + T - 1) / T + 7) / 8, nwl = T / S;
+#define SPRINTER_RES(RP, UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG>), dim3(a.groups), dim3(512), 0, s, a)
+// (up to 8 weight loads of 16 bytes per lane in flight; 16 where two of them make a group)
+#define SPRINTER_RES_U(RP) do { if (per_wave <= 2 || nwl == 4) SPRINTER_RES(RP, 2); else if (per_wave <= 4) SPRINTER_RES(RP, 4); else SPRINTER_RES(RP, 8); } while (0)
+  if (rp == 4) SPRINTER_RES_U(4); else if (rp == 8) SPRINTER_RES_U(8); else SPRINTER_RES_U(16);
+#undef SPRINTER_RES_U
+#undef SPRINTER_RES
+}
+void launch_gemm_resid(int dtype, int arch, const void* W, const void* X, int N, int K, const float* bias, float* h, float* stat, int rows, hipStream_t s) {
+  const int S = resid_split(dtype, N, rows);
+  const ResidArgs a{W, X, h, stat, bias, N, K, rows, N * S / 16};
+#define SPRINTER_RES(AT, ARCH) do { if (sizeof(AT) == 4 && S == 4) launch_gemm_resid_split<AT, ARCH, sizeof(AT) == 4 ? 4 : 2>(a, s); else if (S == 2) launch_gemm_resid_split<AT, ARCH, 2>(a, s); else launch_gemm_resid_split<AT, ARCH, 1>(a, s); } while (0)
+  if (dtype == 0) { if (arch == 0) SPRINTER_RES(float, 0); else SPRINTER_RES(float, 1); }
+  else { if (arch == 0) SPRINTER_RES(bf16_t, 0); else SPRINTER_RES(bf16_t, 1); }
+#undef SPRINTER_RES
 }
 
 }  // namespace sprinter

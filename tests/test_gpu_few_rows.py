@@ -1,0 +1,87 @@
+"""The launches of a pass of few rows by themselves, every element against float64: the product that adds itself to the residual rows, and the product
+that normalises those rows with the statistics the first one left."""
+import ctypes as C
+import numpy as np
+import pytest
+from test_gpu_products import BF16, F32, _lib, _operand, _ptr
+
+pytestmark = pytest.mark.gpu
+EPS = 1e-5
+
+
+def _takes_norm(dtype, d, rows):
+    return bool(_lib()["_ZN8sprinter15gemm_takes_normEiii"](dtype, d, rows) & 0xFF)
+
+
+def _cases():
+    # both sides of the lines in d (512, 1024, 2048) and of the rows a thread, a load or an operand takes; K: odd numbers of k tiles, a last one partly
+    # filled, less than one round of the waves, several rounds of the loads in flight; columns beyond d: a part of a tile, two tiles per wave
+    for d, K, rows in [(64, 64, (1, 9)), (512, 1344, (3, 8, 16)), (576, 72, (4, 5)), (768, 3072, (1, 4, 8, 9, 16)), (1024, 200, (12,)), (1088, 264, (1, 3, 8)),
+                       (1600, 6400, (1, 2, 4, 5, 8)), (2048, 8192, (7,)), (2112, 2112, (1, 2, 3)), (4096, 14336, (1, 4, 5, 16)), (8192, 96, (13,))]:
+        for r in rows:
+            yield BF16, d, K, r, 40
+    yield BF16, 1600, 1600, 4, 2520
+    for d, K, rows in [(64, 72, (1, 16)), (256, 1024, (4, 5, 16)), (512, 2048, (1, 8)), (1024, 104, (3, 8)), (2048, 64, (4,))]:
+        for r in rows:
+            yield F32, d, K, r, 24
+
+
+@pytest.mark.parametrize("arch", [0, 1])
+@pytest.mark.parametrize("dtype,d,K,rows,more", list(_cases()))
+def test_residual_rows_and_their_norm(dtype, d, K, rows, more, arch):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d * 17 + rows + arch)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    store = (lambda t: t.contiguous()) if dtype == F32 else _operand
+    x, W, bias = rnd(rows, K), rnd(d, K) * 0.1, rnd(d) if arch == 0 else None
+    if dtype == BF16:
+        x, W = x.half().float(), W.half().float()
+    # residual rows as deep models have them: a mean, a few columns far out, rows of different sizes
+    h = (rnd(rows, d) * 3 + 2) * (1 + torch.arange(rows, device="cuda")[:, None])
+    h[:, 5::61] += 150
+    X = store(x)                                              # (operand tiles: the rows of a tile that do not exist must have no effect)
+    if dtype == BF16:
+        X.view(-1, X.shape[1], 4, 16, 8)[:, :, :, rows:] = float("nan")
+    hg, stat = h.clone(), torch.full((16 * d // 4,), float("nan"), device="cuda")
+    _lib()["_ZN8sprinter17launch_gemm_residEiiPKvS1_iiPKfPfS4_iP12ihipStream_t"](
+        dtype, arch, _ptr(store(W)), _ptr(X), d, K, _ptr(bias), _ptr(hg), _ptr(stat), rows, stream)
+    torch.cuda.synchronize()
+    want = h.double() + x.double() @ W.double().T + (0 if bias is None else bias.double())
+    # sums in float32: 32 products of an instruction, a wave's k tiles, 8 waves of at most 4 parts, residual and bias
+    steps = 32 + K / 32 / 8 + 32 + 3
+    bound = steps * 2.0 ** -24 * (h.double().abs() + x.double().abs() @ W.double().abs().T + (0 if bias is None else bias.double().abs()))
+    assert ((hg.double() - want).abs() <= bound).all()
+    if not _takes_norm(dtype, d, rows):
+        assert dtype == BF16 and d > 2048 and rows > 4
+        return
+    # a unit matrix shows the normalised rows themselves; the columns behind it are products
+    gain, off = 1 + 0.1 * rnd(d), 0.1 * rnd(d) if arch == 0 else None
+    V = torch.cat([torch.eye(d, device="cuda"), rnd(more, d)])
+    if dtype == BF16:
+        V = V.half().float()
+    N = d + more
+    y = torch.full((rows, N), float("nan"), device="cuda")
+    _lib()["_ZN8sprinter16launch_norm_gemmEiiiPKfS1_S1_S1_fPKNS_11EmbedSourceEPfPKvS7_iiS1_PviP12ihipStream_t"](
+        dtype, arch, 0, _ptr(hg), _ptr(stat), _ptr(gain), _ptr(off), C.c_float(EPS), _ptr(None), _ptr(None), _ptr(store(V)), _ptr(None), N, d, _ptr(None),
+        _ptr(y), rows, stream)
+    torch.cuda.synchronize()
+    h64 = hg.double()
+    mean = h64.mean(1, keepdim=True) if arch == 0 else torch.zeros(rows, 1, device="cuda", dtype=torch.float64)
+    rstd = 1 / torch.sqrt(((h64 - mean) ** 2).mean(1, keepdim=True) + EPS)
+    scaled = (h64 - mean) * rstd * gain.double()
+    xn = scaled + (0 if off is None else off.double())
+    # float32 arithmetic per element (the difference, three factors, the sum) and in the statistics (4 + 16 steps of their sums); float16 storage
+    fine = 2.0 ** -24 * (24 * scaled.abs() + 24 * (mean * rstd * gain.double()).abs() + 4 * xn.abs())
+    unit = fine + (2.0 ** -11 * 1.001 * xn.abs() + 2.0 ** -25 if dtype == BF16 else 0)
+    assert ((y[:, :d].double() - xn).abs() <= unit).all()
+    V64 = V[d:].double()
+    steps = 32 + d / 32 / 8 + 8
+    bound = unit @ V64.abs().T + steps * 2.0 ** -24 * (xn.abs() @ V64.abs().T)
+    assert ((y[:, d:].double() - xn @ V64.T).abs() <= bound).all()
+    # the bound on the normalised rows sees one group of columns missing from a row's statistics
+    drop = (h64[:, 8:] - mean) ** 2
+    off_by = (scaled * (rstd * torch.sqrt(drop.sum(1, keepdim=True) / d + EPS)).reciprocal() - scaled).abs()
+    if d <= 1024 or dtype == F32:
+        assert (off_by > unit).any()
