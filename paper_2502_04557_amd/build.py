@@ -12,6 +12,8 @@ SOURCES = ["k_norm.hip", "k_gemm.hip", "k_gemm_norm.hip", "k_gemm_tile.hip", "k_
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed-fp32 VALU forms are kept off on the test machines
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first argument words of a kernel are loaded into registers with its dispatch
+         "-mllvm", "-amdgpu-kernarg-preload-count=14",
          "-Wno-unused-command-line-argument"]
 
 

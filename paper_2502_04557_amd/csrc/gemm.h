@@ -2,6 +2,7 @@
 // element.
 #pragma once
 #include "dev.h"
+#include <type_traits>
 
 namespace sprinter {
 
@@ -15,6 +16,23 @@ struct GemmArgs {
   KvDest kv;          // EPI_QKV
   int rows_live;      // the host's bound on the row count: rows from here on exist in no launch, their activations are not fetched
 };
+
+// As arguments of k_gemm16 and k_gemm_rows.  second: bias, or W2 (gate + up has no bias).
+template <int EPI> struct GemmMoreOf { using type = Nothing; };      // (named by the number: a kernel's signature must not name an enumerator of an unnamed type)
+template <> struct GemmMoreOf<EPI_QKV> { using type = KvDest; };
+template <int EPI> using GemmMore = typename GemmMoreOf<EPI>::type;
+#define GEMM_ARGS const void *W_, const void *X_, const void *second_, int Kt_, int N_, int rows_live_, int ldo_, const int *n_rows_, void *out_, GemmMore<EPI> more_
+#define GEMM_VALUES(a, EPI) (a).W, (a).X, EPI == EPI_SWIGLU ? (a).W2 : (const void*)(a).bias, (a).Kt, (a).N, (a).rows_live, \
+    EPI == EPI_F32 || EPI == EPI_QKV ? (a).ldo : (a).out_K, (a).n_rows, EPI == EPI_F32 || EPI == EPI_QKV ? (void*)(a).out_f32 : (a).out_act, gemm_more<EPI>(a)
+template <int EPI> inline GemmMore<EPI> gemm_more(const GemmArgs& a) { if constexpr (EPI == EPI_QKV) return a.kv; else return Nothing{}; }
+template <int EPI>
+__device__ __forceinline__ GemmArgs gemm_args(GEMM_ARGS) {
+  GemmArgs a;
+  a.W = W_; a.X = X_; a.W2 = second_; a.bias = EPI == EPI_SWIGLU ? nullptr : (const float*)second_; a.Kt = Kt_; a.N = N_; a.n_tiles = (N_ + 15) >> 4;
+  a.rows_live = rows_live_; a.ldo = a.out_K = ldo_; a.n_rows = n_rows_; a.out_f32 = (float*)out_; a.out_act = out_;
+  if constexpr (EPI == EPI_QKV) a.kv = more_;
+  return a;
+}
 
 // EPI_QKV takes the place of the append launch of short passes (4.1 us per layer at 24 - 80 entries of 25 heads of 64; the product itself is
 // not measurably slower for it): column n >= q_cols of an entry whose cache slot is (b, slot): its key or value element.  The values are bf16 bits.

@@ -14,9 +14,21 @@ struct AttnArgs {
   void* kcache; void* vcache; size_t layer_off;
   int H, KVH, G, lg, dqkv, max_seq, use_rope; float scale;   // G = H / KVH = 1 << lg
   void* ao; int ao_K;
-  float* split;   // k_attn_dec_bf16 with gridDim.z > 1: partial results [row][KV head][z][query head][DH + 2]
+  float* split;   // k_attn_dec_bf16 with several workgroups per row and KV head: partial results [row][KV head][z][query head][DH + 2]
   int phase;   // 0 append + attend, 1 append only, 2 attend only, 3 attend only over long runs of one row (launcher only)
 };
+
+// The kernels of decode steps take what they use of it as single arguments, what they need first in front (internal.h); their caches are those of the layer.
+#define ATTN_ARGS const float *y_, const int *b_, const int *slot_, void *kcache_, void *vcache_, int H_, int KVH_, int S_, int extra_, const int *n_rows_, void *ao_, const float *rope_
+#define ATTN_VALUES(a, extra, S) (a).y, (a).rd.b, (a).rd.slot, (void*)((char*)(a).kcache + (a).layer_off * (S)), (void*)((char*)(a).vcache + (a).layer_off * (S)), (a).H, (a).KVH, (a).max_seq, extra, (a).rd.n_rows, (a).ao, (a).rope
+template <int DH>
+__device__ __forceinline__ AttnArgs attn_args(ATTN_ARGS, float* split) {
+  AttnArgs a;
+  a.y = y_; a.rd.b = b_; a.rd.slot = slot_; a.rd.n_rows = n_rows_; a.kcache = kcache_; a.vcache = vcache_; a.layer_off = 0; a.rope = rope_;
+  a.H = H_; a.KVH = KVH_; a.dqkv = (H_ + 2 * KVH_) * DH; a.max_seq = S_; a.ao = ao_; a.ao_K = H_ * DH; a.split = split; a.phase = extra_;
+  a.scale = DH == 64 ? 0.125f : 0x1.6a09e6p-4f;                  // 1.0f / sqrtf(DH)
+  return a;
+}
 
 // float32 mode.  One workgroup of four waves per (row, KV head), which attends for the G query heads that share the KV head in one pass
 // over the cached keys.  A key is a DPP row of 16 lanes, each with DH / 16 consecutive columns; a wave takes blocks of 32 keys - 8 per
@@ -32,7 +44,8 @@ struct AttnArgs {
 // -> in order -> in pairs: 64 columns, 16 - 60 keys 1.24e-7 -> 1.27e-7 -> 1.21e-7, 60 - 130 1.37e-7 -> 1.51e-7 -> 1.32e-7, 130 - 300 1.51e-7 ->
 // 1.66e-7 -> 1.42e-7; 128 columns, 60 - 130 1.46e-7 -> 1.59e-7 -> 1.44e-7; it costs 0.05 - 0.09 us of 3.6 - 13.4 us per launch.
 template <int DH, int G, bool ROPE>
-__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
+__global__ __launch_bounds__(256) void k_attn_f32(ATTN_ARGS) {   // extra: phase
+  const AttnArgs a = attn_args<DH>(y_, b_, slot_, kcache_, vcache_, H_, KVH_, S_, extra_, n_rows_, ao_, rope_, nullptr);
   constexpr int E = DH / 16, Q4 = E / 4, NK = 8, KB = 4 * NK, HALF = DH / 2;   // columns per lane, float4s of them, keys per stream and block
   __shared__ float s_m[16][G], s_l[16][G];
   __shared__ __attribute__((aligned(16))) float s_o[16][G][DH];
@@ -198,10 +211,11 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // 150 keys, 25 of them: 6 rows 6.15 -> 5.08, 16 rows 8.4 -> 7.5; 60 keys, 1 row 4.7 -> 3.1; of 128, 300 keys, 32: 3 rows 10.5 -> 8.7, 33 rows (162
 // MB) 41.9 -> 36.4; 8 KV heads, 540 keys, 17 rows 16.9 -> 13.1.  Long contexts and many rows: the cache, at 4.3 - 4.8 TB/s.  (8 waves from 140
 // keys on: 6 rows of 25 heads 5.08 -> 4.69, but 16 rows of 12 x 300 keys 6.6 -> 7.2 and 3 rows of 32 x 128 columns 8.7 -> 10.8.)
-// The waves' partial results are merged through LDS at the end.  gridDim.z > 1: that many workgroups share the keys (their waves
+// The waves' partial results are merged through LDS at the end.  gridDim.z = extra > 1: that many workgroups share the keys (their waves
 // count on), each leaves its unnormalised result, maximum and sum in a.split, and k_attn_merge puts them together.
 template <int DH, int NW, int NV, bool ROPE>
-__global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
+__global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(ATTN_ARGS, float* split_) {   // extra: workgroups per row and KV head
+  const AttnArgs a = attn_args<DH>(y_, b_, slot_, kcache_, vcache_, H_, KVH_, S_, extra_, n_rows_, ao_, rope_, split_);
   constexpr int T = DH / 32, CT = DH / 16, PS = 36, HALF = DH / 2, GMAX = 4 * NV;
   constexpr float NEG = -1e30f;
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -212,7 +226,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
   __shared__ float s_o[NW][GMAX][DH];
   const int r = blockIdx.y;
   const int kvh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = wave_index();
-  const int l16 = lane & 15, lq = lane >> 4, G = a.G;
+  const int l16 = lane & 15, lq = lane >> 4, G = H_ / KVH_;
   const int n_rows = *a.rd.n_rows, b = a.rd.b[r], slot = a.rd.slot[r], S = a.max_seq;   // (the lists hold every row the grid covers)
   const int op_head = min((l16 >> 2) * NV + min(l16 & 3, NV - 1), G - 1);               // the head that operand row l16 holds
   // What depends on the row index alone is requested first, before the row's descriptor is known (the projection buffer holds
@@ -249,7 +263,7 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
   if (r >= n_rows) return;
   bf16_t* __restrict__ Kc = (bf16_t*)a.kcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
   bf16_t* __restrict__ Vc = (bf16_t*)a.vcache + a.layer_off + ((size_t)b * a.KVH + kvh) * (size_t)S * DH;
-  const int wz = blockIdx.z * NW + w, NZ = gridDim.z * NW;      // this wave among all that share the keys
+  const int wz = blockIdx.z * NW + w, NZ = extra_ * NW;          // this wave among all that share the keys
   const int n_steps = (slot + 32 * NZ) / (32 * NZ);             // blocks 0 .. slot / 32, NZ per step
   // Two register buffers: a block's key fragments and value tiles are requested a whole step ahead (the query
   // operand lives in LDS to make room for them).
@@ -438,8 +452,8 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_dec_bf16(AttnArgs a) {
       den += c * s_ml[q][g][1];
       num += c * s_o[q][g][i];
     }
-    if (gridDim.z > 1) {                                         // (uniform)
-      float* __restrict__ o = a.split + ((((size_t)r * a.KVH + kvh) * gridDim.z + blockIdx.z) * G + g) * (DH + 2);
+    if (extra_ > 1) {                                            // (uniform)
+      float* __restrict__ o = a.split + ((((size_t)r * a.KVH + kvh) * extra_ + blockIdx.z) * G + g) * (DH + 2);
       o[i] = num;
       if (i == 0) { o[DH] = mn; o[DH + 1] = den; }
     } else {
@@ -958,7 +972,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_mfma_shared_bf16(AttnArgs a) {
 // 25 heads of 64, 110 keys: 22.0 us with a pass per entry, 9.9 so; 16 entries of one each: 8.5 and 5.9.  With the queries requested ahead of
 // the descriptors, 150 keys: 26 entries of 12 heads 6.2 -> 5.9, 12 of 25 7.15 -> 6.85, 80 of 25 9.9 -> 9.7, 160 of 32 x 128 37.1 -> 35.6.)
 template <int DH, int NW, bool ROPE>
-__global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
+__global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(ATTN_ARGS) {   // extra: entries
+  const AttnArgs a = attn_args<DH>(y_, b_, slot_, kcache_, vcache_, H_, KVH_, S_, extra_, n_rows_, ao_, rope_, nullptr);
   constexpr int T = DH / 32, CT = DH / 16;
   constexpr float NEG = -1e30f;
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -967,11 +982,11 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_runs_bf16(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) float s_o[NW][16][DH + 4];
   const int n_rows = *a.rd.n_rows, r = blockIdx.y, kvh = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4, S = a.max_seq;
-  const int lg = a.lg, G = 1 << lg, M = 16 >> lg;
+  const int G = H_ / KVH_, lg = __builtin_ctz(G), M = 16 >> lg;
   // lane i: entry r - 1 + i; the group is entry r and those that continue it up to the next multiple of M.  The descriptors and the
   // queries of all M entries that may be in it are requested together, before the row count is known (the buffers hold every row
   // the grid covers); what belongs to no entry of the group is masked below.
-  const int ri = r - 1 + lane, r_last = (int)gridDim.y - 1;
+  const int ri = r - 1 + lane, r_last = extra_ - 1;
   const int at = min(max(ri, 0), r_last), e_b = a.rd.b[at], e_slot = a.rd.slot[at];
   constexpr int LPR = DH / 4, RPI = 64 / LPR, QI = (16 / RPI + NW - 1) / NW;   // lanes per query, queries per instruction, instructions per wave
   const int c4 = (lane % LPR) * 4;
@@ -1184,7 +1199,7 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
   dim3 grid(a.KVH, max_rows);
   const bool wide = (long long)a.KVH * max_rows <= 256 && ctx_bound >= 512;
   if (a.phase == 2) {          // attend-only, short runs
-#define SPRINTER_RUNS(NW, ROPE) hipLaunchKernelGGL((k_attn_runs_bf16<DH, NW, ROPE>), grid, dim3(NW * 64), 0, s, a)
+#define SPRINTER_RUNS(NW, ROPE) hipLaunchKernelGGL((k_attn_runs_bf16<DH, NW, ROPE>), grid, dim3(NW * 64), 0, s, ATTN_VALUES(a, max_rows, 2))
     if (a.use_rope) { if (wide) SPRINTER_RUNS(8, true); else SPRINTER_RUNS(4, true); }
     else { if (wide) SPRINTER_RUNS(8, false); else SPRINTER_RUNS(4, false); }
 #undef SPRINTER_RUNS
@@ -1192,7 +1207,7 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
   }
   const int split = attn_split(DH, a.KVH, max_rows, ctx_bound);
   grid.z = split;
-#define SPRINTER_DEC(NW, NV, ROPE) hipLaunchKernelGGL((k_attn_dec_bf16<DH, NW, NV, ROPE>), grid, dim3(NW * 64), 0, s, a)
+#define SPRINTER_DEC(NW, NV, ROPE) hipLaunchKernelGGL((k_attn_dec_bf16<DH, NW, NV, ROPE>), grid, dim3(NW * 64), 0, s, ATTN_VALUES(a, split, 2), a.split)
 #define SPRINTER_DEC_NW(NV, ROPE) do { if (wide || split > 1) SPRINTER_DEC(8, NV, ROPE); else SPRINTER_DEC(4, NV, ROPE); } while (0)
   if (G <= 4) { if (a.use_rope) SPRINTER_DEC_NW(1, true); else SPRINTER_DEC_NW(1, false); }
   else { if (a.use_rope) SPRINTER_DEC_NW(2, true); else SPRINTER_DEC_NW(2, false); }
@@ -1204,8 +1219,8 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
 template <int DH>
 static void launch_attn_f32(const AttnArgs& a, int max_rows, hipStream_t s) {
   const dim3 grid(a.KVH, max_rows);
-#define SPRINTER_AF32(G) do { if (a.use_rope) hipLaunchKernelGGL((k_attn_f32<DH, G, true>), grid, dim3(256), 0, s, a); \
-                              else hipLaunchKernelGGL((k_attn_f32<DH, G, false>), grid, dim3(256), 0, s, a); } while (0)
+#define SPRINTER_AF32(G) do { if (a.use_rope) hipLaunchKernelGGL((k_attn_f32<DH, G, true>), grid, dim3(256), 0, s, ATTN_VALUES(a, a.phase, 4)); \
+                              else hipLaunchKernelGGL((k_attn_f32<DH, G, false>), grid, dim3(256), 0, s, ATTN_VALUES(a, a.phase, 4)); } while (0)
   switch (a.G) {
     case 1: SPRINTER_AF32(1); break;
     case 2: SPRINTER_AF32(2); break;

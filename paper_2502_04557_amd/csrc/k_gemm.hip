@@ -15,7 +15,8 @@ namespace sprinter {
 // scattered 2-byte stores per lane for FFN-up - it took 2.2 of the kernel's 7.1 us.)
 // Accumulator layout of v_mfma_f32_16x16x32: lane l, register v hold n = l % 16, m = (l / 16) * 4 + v.
 template <int NTW, int EPI>
-__global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
+__global__ __launch_bounds__(512) void k_gemm16(GEMM_ARGS) {
+  const GemmArgs a = gemm_args<EPI>(W_, X_, second_, Kt_, N_, rows_live_, ldo_, n_rows_, out_, more_);
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
   constexpr bool ACT_OUT = (EPI == EPI_GELU || EPI == EPI_SWIGLU);
   constexpr int U = 4;      // k tiles per chunk and wave (8 and 16 measured slower)
@@ -126,7 +127,8 @@ __global__ __launch_bounds__(512) void k_gemm16(GemmArgs a) {
 // computed on whatever the buffers hold and dropped by the epilogue; k tiles beyond K are clamped on load
 // and their weight operand zeroed.
 template <int MT, int NTW, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
+__global__ __launch_bounds__(512) void k_gemm_rows(GEMM_ARGS) {
+  const GemmArgs a = gemm_args<EPI>(W_, X_, second_, Kt_, N_, rows_live_, ldo_, n_rows_, out_, more_);
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
   constexpr int NWT = NTW * (DUAL ? 2 : 1);          // weight tiles per k tile and wave
   constexpr int U = (MT * NWT >= 8) ? 1 : 2, STEP = 8 * U;   // k tiles per buffer
@@ -279,7 +281,9 @@ __global__ __launch_bounds__(512) void k_gemm_rows(GemmArgs a) {
 // fences, and every workgroup reads only its share of the activations - which at 16 rows cost as much as
 // the weights: a workgroup needs 64 B of activations (L2) per k for 32 B of weights per k and tile.
 template <int NTW>
-__global__ __launch_bounds__(512) void k_gemm16_part(GemmArgs a) {
+__global__ __launch_bounds__(512) void k_gemm16_part(const void* W_, const void* X_, int Kt_, int N_, int rows_live_, int shares_, float* part_, const int* n_rows_, size_t part_stride_) {
+  GemmArgs a;
+  a.W = W_; a.X = X_; a.Kt = Kt_; a.N = a.ldo = N_; a.n_tiles = (N_ + 15) >> 4; a.rows_live = rows_live_; a.SK = shares_; a.part = part_; a.n_rows = n_rows_; a.part_stride = part_stride_;
   constexpr int U = 4;
   __shared__ float red[8 * NTW * 4 * 64];
   const int lane = threadIdx.x & 63, kw = wave_index();
@@ -358,7 +362,10 @@ __global__ __launch_bounds__(512) void k_gemm16_part(GemmArgs a) {
 // of a 512-wide model (K = 512 and 2048) at 6 - 32 rows 28 -> 4 - 6 us with K shares, at one row 7.2 -> 3.8 us.
 // blockIdx.y = pass over 16 MT rows.
 template <int MT, int U, int EPI>
-__global__ __launch_bounds__(512) void k_gemm_f32(GemmArgs a) {
+__global__ __launch_bounds__(512) void k_gemm_f32(const void* W_, const void* X_, const void* second_, int K_, int N_, int rows_live_, int shares_, const int* n_rows_, void* out_, int ldo_, size_t part_stride_) {
+  GemmArgs a;                                           // second: bias, or W2; out: EPI_PART: the shares' buffer
+  a.W = W_; a.X = X_; a.W2 = second_; a.bias = EPI == EPI_SWIGLU ? nullptr : (const float*)second_; a.K = K_; a.N = N_; a.rows_live = rows_live_; a.n_rows = n_rows_;
+  a.out_f32 = a.part = (float*)out_; a.out_act = out_; a.ldo = a.out_K = ldo_; a.part_stride = part_stride_;
   constexpr bool DUAL = (EPI == EPI_SWIGLU);
   constexpr int NA = DUAL ? 2 : 1;
   __shared__ float red[8][NA * MT * 4][64];
@@ -366,8 +373,8 @@ __global__ __launch_bounds__(512) void k_gemm_f32(GemmArgs a) {
   const int l16 = lane & 15, lq = lane >> 4, K = a.K;
   const int n0 = blockIdx.x * 16, m0 = blockIdx.y * MT * 16;
   // EPI_PART: blockIdx.z = K share, the partial product goes to part[share] (summed by the norm that follows)
-  const int all_groups = (K + 15) >> 4, s0 = all_groups * (int)blockIdx.z / (int)gridDim.z;
-  const int n_groups = all_groups * (int)(blockIdx.z + 1) / (int)gridDim.z - s0;
+  const int all_groups = (K + 15) >> 4, s0 = all_groups * (int)blockIdx.z / shares_;
+  const int n_groups = all_groups * (int)(blockIdx.z + 1) / shares_ - s0;
   const int g0 = s0 + n_groups * kw / 8, g1 = s0 + n_groups * (kw + 1) / 8;
   const int n_col = min(n0 + l16, a.N - 1);             // columns beyond N are computed on the last one and dropped
   const float* __restrict__ wr = (const float*)a.W + (size_t)n_col * K;
@@ -444,7 +451,8 @@ static void launch_gemm_f32(const GemmArgs& a, int max_rows, int shares, hipStre
   // two row tiles per pass from 17 rows on; as many groups of 16 k per request as a wave's share of K has, at most 8
   const int per_wave = ((a.K + 15) / 16 + 8 * shares - 1) / (8 * shares), mt = max_rows <= 16 ? 1 : 2;
   const dim3 grid(a.n_tiles, (max_rows + 16 * mt - 1) / (16 * mt), shares);
-#define SPRINTER_F32(MT_, U_) hipLaunchKernelGGL((k_gemm_f32<MT_, U_, EPI>), grid, dim3(512), 0, s, a)
+#define SPRINTER_F32(MT_, U_) hipLaunchKernelGGL((k_gemm_f32<MT_, U_, EPI>), grid, dim3(512), 0, s, a.W, a.X, EPI == EPI_SWIGLU ? a.W2 : (const void*)a.bias, a.K, a.N, a.rows_live, shares, a.n_rows, \
+    EPI == EPI_PART ? (void*)a.part : EPI == EPI_F32 ? (void*)a.out_f32 : a.out_act, EPI == EPI_PART || EPI == EPI_F32 ? a.ldo : a.out_K, a.part_stride)
   if (mt == 1) { if (per_wave <= 2) SPRINTER_F32(1, 2); else if (per_wave <= 4) SPRINTER_F32(1, 4); else SPRINTER_F32(1, 8); }
   else { if (per_wave <= 2) SPRINTER_F32(2, 2); else if (per_wave <= 4) SPRINTER_F32(2, 4); else SPRINTER_F32(2, 8); }
 #undef SPRINTER_F32
@@ -461,15 +469,15 @@ static void launch_gemm_bf16(const GemmArgs& a, int max_rows, hipStream_t s) {
   // wide outputs with a short K: two column tiles per wave share the activation fragments (at K = 4096 one tile per
   // workgroup is faster: QKV 12288x4096 26 against 32 us, FFN-up 2x11008x4096 40 against 48 us)
   if (max_rows <= 16 && a.n_tiles >= 256 && a.Kt < 100)
-    hipLaunchKernelGGL((k_gemm16<2, EPI>), dim3((a.n_tiles + 1) / 2), dim3(512), 0, s, a);
-  else if (max_rows <= 16) hipLaunchKernelGGL((k_gemm16<1, EPI>), dim3(a.n_tiles), dim3(512), 0, s, a);
+    hipLaunchKernelGGL((k_gemm16<2, EPI>), dim3((a.n_tiles + 1) / 2), dim3(512), 0, s, GEMM_VALUES(a, EPI));
+  else if (max_rows <= 16) hipLaunchKernelGGL((k_gemm16<1, EPI>), dim3(a.n_tiles), dim3(512), 0, s, GEMM_VALUES(a, EPI));
   else if (gemm_takes_tile(EPI, a.N, max_rows)) launch_gemm_tile(EPI, a, max_rows, 1, s);
   else {
     // 17 .. 64 rows.  Two column tiles per wave, which share the activation fragments, where one would need a second round of
     // workgroups (one per compute unit): 4352 x 4096 (272 tiles) at 20 / 40 / 64 rows 15.8 / 19.1 / 23.3 us with one, 12.6 / 14.9 /
     // 17.6 with two; 4096 x 4096 (256) 10.0 / 12.1 / 14.5 and 12.6 / 14.9 / 17.5.
     constexpr bool DUAL = EPI == EPI_SWIGLU;
-#define SPRINTER_ROWS(MT_, NTW_) hipLaunchKernelGGL((k_gemm_rows<MT_, NTW_, EPI>), grid, dim3(512), 0, s, a)
+#define SPRINTER_ROWS(MT_, NTW_) hipLaunchKernelGGL((k_gemm_rows<MT_, NTW_, EPI>), grid, dim3(512), 0, s, GEMM_VALUES(a, EPI))
     const int mt = (max_rows + 15) / 16, ntw = !DUAL && a.n_tiles > 256 ? 2 : 1;
     const dim3 grid((a.n_tiles + ntw - 1) / ntw);
     if constexpr (!DUAL) {
@@ -535,8 +543,8 @@ int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, co
     while (sk > 1 && a.Kt / sk < 12) --sk;
     if (sk < 1) sk = 1;
     a.SK = sk;
-    if (two) hipLaunchKernelGGL((k_gemm16_part<2>), dim3(groups * sk), dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((k_gemm16_part<1>), dim3(groups * sk), dim3(512), 0, s, a);
+    if (two) hipLaunchKernelGGL((k_gemm16_part<2>), dim3(groups * sk), dim3(512), 0, s, a.W, a.X, a.Kt, a.N, a.rows_live, a.SK, a.part, a.n_rows, a.part_stride);
+    else hipLaunchKernelGGL((k_gemm16_part<1>), dim3(groups * sk), dim3(512), 0, s, a.W, a.X, a.Kt, a.N, a.rows_live, a.SK, a.part, a.n_rows, a.part_stride);
     return sk;
   }
   a.bias = bias; a.out_f32 = h;

@@ -4,6 +4,7 @@
 #include "gemm.h"
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 namespace sprinter {
 
@@ -21,6 +22,10 @@ __device__ __forceinline__ float last_lane(float v) { return __uint_as_float(__b
 // with no pass over the row: variance d = sum over the groups of theirs + cols (group mean - mean)^2, the update of Chan, Golub and LeVeque,
 // which loses nothing against two passes.
 
+// Column groups of the statistics: 16 / split columns each, at most 256 groups where a product reads them.  float32 rows hold their k side by side, so four columns
+// fill lines too: 512 x 2048, 1 row 5.0 -> 4.0 us, 8 rows 6.0 -> 5.4 but the norms behind it lose that again.
+static __host__ __device__ inline int resid_split(bool bf16, int N, int rows) { return N > 2048 ? 1 : !bf16 && N <= 1024 && rows <= 4 ? 4 : 2; }
+
 // A chain of short dependent launches is what a pass of few rows is, and the norm as a launch of its own two of a layer's seven: 3 - 4 us for a few KiB of
 // work.  Every workgroup of the product that follows can normalise the rows for itself, if that is cheap: here it reads them once, in one piece, with
 // at most 256 groups of statistics, and the weights it needs are requested behind them and arrive meanwhile.  (Before, it read residual rows and
@@ -33,14 +38,11 @@ __device__ __forceinline__ float last_lane(float v) { return __uint_as_float(__b
 // 4 rows 20.0 -> 17.4, 16 rows 21.6 -> 20.0; float32, 512 (2048), 1 row 22.1 -> 19.5, 8 rows 24.7 -> 22.4.
 // What bounds it: the weights at 4 - 5 TB/s and, of about 5.5 us at 15 MB, the start of a dependent launch, 1.6 us.
 // R = RT RG rows: RG groups of 512 / RG threads, a thread takes 8 columns of RT rows.  U: units of K in flight per wave.
-struct NormGemmArgs {
-  const float *h, *stat, *g, *b; const void *W, *W2; const float* bias; void* out;
-  int d, N, n_tiles, rows, groups; float eps, cols, inv_cols;   // groups of `cols` columns (a power of two) of the statistics
-  float* h_out; EmbedSource emb;                      // EMB: the rows are embeddings; workgroup 0 starts the residual stream with them
-};
-
+struct RowSource { EmbedSource emb; float* h_out; };    // EMB: the rows are embeddings; workgroup 0 starts the residual stream with them
+// second: the norm's offset b, or W2.  d / 16 * resid_split groups of statistics.
 template <typename AT, int ARCH, int RT, int RG, int NTW, int EPI, bool EMB>
-__global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
+__global__ __launch_bounds__(512) void k_norm_gemm(const float* h, const float* stat, const float* g, const void* second, const void* W, int d, int rows, int N, float eps,
+                                                   void* out, const float* bias, std::conditional_t<EMB, RowSource, Nothing> from) {
   constexpr bool BF = sizeof(AT) == 2;
   constexpr bool DUAL = EPI == EPI_SWIGLU, ACT_OUT = BF && EPI != EPI_F32;
   constexpr int R = RT * RG, CG = 512 / RG, WR = 8 / RG, NW = NTW * (DUAL ? 2 : 1), NI4 = NW * 4, SR = (R + 7) / 8;
@@ -50,22 +52,23 @@ __global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
   __shared__ float s_part[2][R][WR];
   __shared__ float red[8 * NI4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
-  const int nt0 = blockIdx.x * NTW, d = a.d, units = BF ? d >> 5 : d >> 4;
+  const int nt0 = blockIdx.x * NTW, n_tiles = (N + 15) >> 4, split = resid_split(BF, d, rows), groups = d / 16 * split, units = BF ? d >> 5 : d >> 4;
   if constexpr (EMB && ARCH == 1) {
-    if (__builtin_expect(nt0 >= a.n_tiles, 0)) {        // one workgroup more for the rows' rotary factors
-      const int half = a.emb.dh >> 1;
-      for (int i = tid; i < a.rows * half; i += 512) rope_factors(a.emb, i / half, i % half);
+    if (__builtin_expect(nt0 >= n_tiles, 0)) {        // one workgroup more for the rows' rotary factors
+      const int half = from.emb.dh >> 1;
+      for (int i = tid; i < rows * half; i += 512) rope_factors(from.emb, i / half, i % half);
       return;
     }
   }
+  const float cols = 16 / split, inv_cols = split / 16.f;                     // (a power of two)
   // ---- statistics, residual rows, gain and offset; then the weights
   float2 st[SR][NG];
   if constexpr (!EMB) {
 #pragma unroll
-    for (int j = 0; j < SR; ++j) if (w + 8 * j < a.rows) {   // (scalar; the first loads, so no later wait depends on it)
-      const float2* sp = (const float2*)a.stat + (size_t)min(w + 8 * j, a.rows - 1) * a.groups;
+    for (int j = 0; j < SR; ++j) if (w + 8 * j < rows) {   // (scalar; the first loads, so no later wait depends on it)
+      const float2* sp = (const float2*)stat + (size_t)min(w + 8 * j, rows - 1) * groups;
 #pragma unroll
-      for (int i = 0; i < NG; ++i) st[j][i] = sp[min(lane + 64 * i, a.groups - 1)];
+      for (int i = 0; i < NG; ++i) st[j][i] = sp[min(lane + 64 * i, groups - 1)];
     }
   }
   const int col = tid % CG, rg = w / WR, n_ch = d >> 3, c8 = min(col, n_ch - 1) * 8;
@@ -74,28 +77,28 @@ __global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
   if constexpr (EMB) {
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
-      const int r = min(rg * RT + i, a.rows - 1);
-      const int tok = min(max(a.emb.rd.tok[r], 0), a.emb.V - 1), pos = max(a.emb.rd.pos[r], 0);
-      load_row((const AT*)a.emb.tok_emb + (size_t)tok * d + c8, x[i]);
-      if (a.emb.pos_emb) {
+      const int r = min(rg * RT + i, rows - 1);
+      const int tok = min(max(from.emb.rd.tok[r], 0), from.emb.V - 1), pos = max(from.emb.rd.pos[r], 0);
+      load_row((const AT*)from.emb.tok_emb + (size_t)tok * d + c8, x[i]);
+      if (from.emb.pos_emb) {
         float p[8];
-        load_row((const AT*)a.emb.pos_emb + (size_t)min(pos, a.emb.max_pos - 1) * d + c8, p);
+        load_row((const AT*)from.emb.pos_emb + (size_t)min(pos, from.emb.max_pos - 1) * d + c8, p);
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[i][e] += p[e];
       }
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < RT; ++i) load_row(a.h + (size_t)min(rg * RT + i, a.rows - 1) * d + c8, x[i]);
+    for (int i = 0; i < RT; ++i) load_row(h + (size_t)min(rg * RT + i, rows - 1) * d + c8, x[i]);
   }
-  load_row(a.g + c8, gg);
-  if (ARCH == 0) load_row(a.b + c8, bb);
+  load_row(g + c8, gg);
+  if (ARCH == 0) load_row((const float*)second + c8, bb);
   __builtin_amdgcn_sched_barrier(0);
   const int w_lane = BF ? lane * 16 : (l16 * d + lq * 4) * 4;
   auto tile = [&](int j) {
     const int nt = nt0 + j % NTW;
-    const char* W = (const char*)(DUAL && j >= NTW ? a.W2 : a.W);
-    return bytes_at(W + (size_t)nt * 16 * d * sizeof(AT), nt < a.n_tiles ? (BF ? 16 : min(16, a.N - nt * 16)) * d * (int)sizeof(AT) : 0);
+    const char* m = (const char*)(DUAL && j >= NTW ? second : W);
+    return bytes_at(m + (size_t)nt * 16 * d * sizeof(AT), nt < n_tiles ? (BF ? 16 : min(16, N - nt * 16)) * d * (int)sizeof(AT) : 0);
   };
   u32x4 wv[U][NW];
   auto load_unit = [&](int u, int unit) {
@@ -108,15 +111,15 @@ __global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
   if (ACT_OUT) { m = (tid >> 3) & 15; c = (tid >> 7) * 8 + (tid & 7); }
   else { m = tid / (16 * NTW); c = tid % (16 * NTW); }
   const int n = nt0 * 16 + c;
-  const bool out_ok = tid < NTW * 256 && m < a.rows && n < a.N;
-  const float pbias = (out_ok && a.bias) ? a.bias[n] : 0.f;
+  const bool out_ok = tid < NTW * 256 && m < rows && n < N;
+  const float pbias = (out_ok && bias) ? bias[n] : 0.f;
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (EMB) {
     if (blockIdx.x == 0 && mine) {
 #pragma unroll
       for (int i = 0; i < RT; ++i)
-        if (rg * RT + i < a.rows) {
-          float4* o = reinterpret_cast<float4*>(a.h_out + (size_t)(rg * RT + i) * d + c8);
+        if (rg * RT + i < rows) {
+          float4* o = reinterpret_cast<float4*>(from.h_out + (size_t)(rg * RT + i) * d + c8);
           o[0] = make_float4(x[i][0], x[i][1], x[i][2], x[i][3]);
           o[1] = make_float4(x[i][4], x[i][5], x[i][6], x[i][7]);
         }
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
     totals(1);
     if (lane == 0) {
 #pragma unroll
-      for (int i = 0; i < RT; ++i) s_stat[rg * RT + i] = make_float2(mean[i], 1.0f / sqrtf(part[i] / (float)d + a.eps));
+      for (int i = 0; i < RT; ++i) s_stat[rg * RT + i] = make_float2(mean[i], 1.0f / sqrtf(part[i] / (float)d + eps));
     }
   } else {
 #pragma unroll
@@ -163,17 +166,17 @@ __global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
       float mean = 0.f, s = 0.f;
       if (ARCH == 0) {
 #pragma unroll
-        for (int i = 0; i < NG; ++i) s += lane + 64 * i < a.groups ? st[j][i].x : 0.f;
+        for (int i = 0; i < NG; ++i) s += lane + 64 * i < groups ? st[j][i].x : 0.f;
         mean = last_lane(wave_total(s)) / (float)d;
         s = 0.f;
       }
 #pragma unroll
       for (int i = 0; i < NG; ++i) {
         float q = st[j][i].y;
-        if (ARCH == 0) { const float t = st[j][i].x * a.inv_cols - mean; q += a.cols * (t * t); }
-        s += lane + 64 * i < a.groups ? q : 0.f;
+        if (ARCH == 0) { const float t = st[j][i].x * inv_cols - mean; q += cols * (t * t); }
+        s += lane + 64 * i < groups ? q : 0.f;
       }
-      const float rstd = 1.0f / sqrtf(last_lane(wave_total(s)) / (float)d + a.eps);
+      const float rstd = 1.0f / sqrtf(last_lane(wave_total(s)) / (float)d + eps);
       if (lane == 0 && w + 8 * j < R) s_stat[w + 8 * j] = make_float2(mean, rstd);
     }
   }
@@ -241,9 +244,9 @@ __global__ __launch_bounds__(512) void k_norm_gemm(NormGemmArgs a) {
     s1 += red[((size_t)q * NI4 + it) * 64 + sl];
     if (DUAL) s2 += red[((size_t)q * NI4 + NTW * 4 + it) * 64 + sl];
   }
-  if constexpr (EPI == EPI_F32) ((float*)a.out)[(size_t)m * a.N + n] = s1 + pbias;
-  else if constexpr (EPI == EPI_GELU) act_store<AT>((AT*)a.out, m, n, a.N, gelu_tanh(s1 + pbias));
-  else act_store<AT>((AT*)a.out, m, n, a.N, silu(s1) * s2);
+  if constexpr (EPI == EPI_F32) ((float*)out)[(size_t)m * N + n] = s1 + pbias;
+  else if constexpr (EPI == EPI_GELU) act_store<AT>((AT*)out, m, n, N, gelu_tanh(s1 + pbias));
+  else act_store<AT>((AT*)out, m, n, N, silu(s1) * s2);
 }
 
 template <int C>
@@ -261,25 +264,21 @@ __device__ __forceinline__ float columns_sum(float v) {   // over C = 4, 8 or 16
 // 2-norm, K in shares -> in order -> so: 1600 x 6400, 4 rows 8.7e-8 -> 9.5e-8 -> 6.9e-8; 4096 x 14336, 16 rows 1.58e-7 -> 2.13e-7 -> 1.19e-7).
 // us, K in shares over workgroups and the sum left to the norm -> this: 1600 x 6400, 4 rows 6.3 -> 6.7, 16 rows 7.1 -> 9.0; 1600 x 1600 3.8 -> 3.8;
 // 4096 x 14336 and 4096 x 4096 at 5 - 16 rows 24.7 -> 22.5 and 12.1 -> 8.1; the norms behind it 3.4 -> 2.9, or gone (above).
-struct ResidArgs {
-  const void *W, *X; float *h, *stat; const float* bias; int N, K, rows, groups;
-};
-
 // RP: rows an activation load carries (4, 8 or 16).  UG: groups of T = max(16 / RP, S) k tiles in flight per wave.
 template <typename AT, int ARCH, int S, int RP, int UG>
-__global__ __launch_bounds__(512) void k_gemm_resid(ResidArgs a) {
+__global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X, int K, int rows, float* h, const float* bias, float* stat, int N) {
   constexpr bool BF = sizeof(AT) == 2;
   constexpr int C = 16 / S, P = 16 / RP, T = P > S ? P : S, NX = T / P, NWL = T / S, NM = NX > NWL ? NX : NWL, KU = BF ? 32 : 16;
   constexpr int NA = P >= S ? P / S : S;                // accumulators: which of their elements are sums of matching k is below
   constexpr int D = NA < 4 ? 4 / NA : 1;                // each D times, for groups in turn
   __shared__ float red[8 * 4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
-  const int K = a.K, kt = (K + KU - 1) / KU, groups = (kt + T - 1) / T, n0 = blockIdx.x * C;
+  const int kt = (K + KU - 1) / KU, groups = (kt + T - 1) / T, n0 = blockIdx.x * C;
   const int ws = l16 / C, wc = l16 % C, xp = l16 / RP, xr = l16 % RP;
-  const auto rw = BF ? bytes_at((const char*)a.W + (size_t)(n0 >> 4) * kt * 1024, kt * 1024) : bytes_at((const char*)a.W + (size_t)n0 * K * 4, C * K * 4);
-  const auto rx = BF ? bytes_at(a.X, kt * 1024) : bytes_at(a.X, a.rows * K * 4);
+  const auto rw = BF ? bytes_at((const char*)W + (size_t)(n0 >> 4) * kt * 1024, kt * 1024) : bytes_at((const char*)W + (size_t)n0 * K * 4, C * K * 4);
+  const auto rx = BF ? bytes_at(X, kt * 1024) : bytes_at(X, rows * K * 4);
   const int w_lane = BF ? ws * 1024 + (lq * 16 + (n0 & 15) + wc) * 16 : wc * K * 4 + (ws * 16 + lq * 4) * 4;
-  const int x_lane = xr < a.rows ? (BF ? xp * 1024 + (lq * 16 + xr) * 16 : xr * K * 4 + (xp * 16 + lq * 4) * 4) : NOWHERE;
+  const int x_lane = xr < rows ? (BF ? xp * 1024 + (lq * 16 + xr) * 16 : xr * K * 4 + (xp * 16 + lq * 4) * 4) : NOWHERE;
   constexpr int TB = BF ? 1024 : 64;                    // bytes from one k tile to the next
   u32x4 wv[UG][NWL], xv[UG][NX];
   auto load_group = [&](int u, int g) {
@@ -298,9 +297,9 @@ __global__ __launch_bounds__(512) void k_gemm_resid(ResidArgs a) {
   for (int u = 0; u < UG; ++u) load_group(u, w + 8 * u);
   // this thread's output element: the row's columns in consecutive lanes
   const int m = tid / C, c = tid % C, n = n0 + c;
-  const bool out_ok = m < a.rows;
+  const bool out_ok = m < rows;
   float res = 0.f;
-  if (out_ok) { res = a.h[(size_t)m * a.N + n]; if (a.bias) res += a.bias[n]; }
+  if (out_ok) { res = h[(size_t)m * N + n]; if (bias) res += bias[n]; }
   f32x4 acc[NA][D];
 #pragma unroll
   for (int i = 0; i < NA; ++i)
@@ -359,13 +358,9 @@ __global__ __launch_bounds__(512) void k_gemm_resid(ResidArgs a) {
   if (ARCH == 0) { s1 = columns_sum<C>(v); mean = s1 * (1.0f / C); dv = v - mean; }
   const float s2 = columns_sum<C>(dv * dv);
   if (!out_ok) return;
-  a.h[(size_t)m * a.N + n] = v;
-  if (c == 0) reinterpret_cast<float2*>(a.stat)[(size_t)m * a.groups + blockIdx.x] = make_float2(s1, s2);
+  h[(size_t)m * N + n] = v;
+  if (c == 0) reinterpret_cast<float2*>(stat)[(size_t)m * (N / C) + blockIdx.x] = make_float2(s1, s2);
 }
-
-// Column groups of the statistics: 16 / split columns each, at most 256 groups where a product reads them.  float32 rows hold their k side by side, so four columns
-// fill lines too: 512 x 2048, 1 row 5.0 -> 4.0 us, 8 rows 6.0 -> 5.4 but the norms behind it lose that again.
-static int resid_split(int dtype, int N, int rows) { return N > 2048 ? 1 : dtype == 0 && N <= 1024 && rows <= 4 ? 4 : 2; }
 
 // The line: us per layer, seven launches / five.  1600 columns: 8 rows 34.2 / 30.6, 10 rows 35.9 / 35.7, 16 rows 38.4 / 38.9; 2048 (gate + up): 8 rows 43.6 / 38.6, 10 rows 44.1 / 44.6;
 // 4096: 4 rows 96.5 / 85.3, 5 rows 92.9 / 96.8; 768: 16 rows 25.6 / 23.4; 1024: 16 rows 28.8 / 27.2.  (Activations of more than 8 rows fill an operand; 5 rows of 4096 in
@@ -379,13 +374,17 @@ bool gemm_takes_norm(int dtype, int d, int rows) {
 // 5 rows 104.2 / 100.0, 16 rows 109.6 / 103.3; but 1600, 16 rows 38.3 / 38.8, 2048 44.6 / 46.4.
 bool gemm_adds_rows(int dtype, int d, int rows) { return gemm_takes_norm(dtype, d, rows) || (dtype != 0 && d > 2048 && rows <= 16); }
 
+struct NormGemmArgs { const float *h, *stat, *g; const void *second, *W; const float* bias; void* out; int d, N, n_tiles, rows; float eps; RowSource from; };
+
 template <typename AT, int ARCH, int NTW, int EPI, bool EMB>
 static void launch_norm_gemm_rows(const NormGemmArgs& a, hipStream_t s) {
+  std::conditional_t<EMB, RowSource, Nothing> from;
+  if constexpr (EMB) from = a.from;
   const dim3 grid((a.n_tiles + NTW - 1) / NTW + (EMB && ARCH == 1 ? 1 : 0));
 #define SPRINTER_NG(RT, RG)                                                                                  \
   do {                                                                                                       \
     const size_t lds = sizeof(AT) == 2 ? (size_t)RT * RG * a.d * 2 : (size_t)RT * RG * (a.d + 4) * 4;          \
-    hipLaunchKernelGGL((k_norm_gemm<AT, ARCH, RT, RG, NTW, EPI, EMB>), grid, dim3(512), lds, s, a);           \
+    hipLaunchKernelGGL((k_norm_gemm<AT, ARCH, RT, RG, NTW, EPI, EMB>), grid, dim3(512), lds, s, a.h, a.stat, a.g, a.second, a.W, a.d, a.rows, a.N, a.eps, a.out, a.bias, from);           \
   } while (0)
   constexpr bool BF = sizeof(AT) == 2;
   if constexpr (NTW == 1) {
@@ -424,20 +423,20 @@ void launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float*
                       float* h_out, const void* W, const void* W2, int N, int d, const float* bias, void* out, int rows, hipStream_t s) {
   NormGemmArgs a;
   memset(&a, 0, sizeof a);
-  const int S = resid_split(dtype, d, rows);
-  a.h = h; a.stat = stat; a.g = g; a.b = b; a.W = W; a.W2 = W2; a.bias = bias; a.out = out;
-  a.d = d; a.N = N; a.n_tiles = (N + 15) / 16; a.rows = rows; a.groups = d * S / 16; a.eps = eps; a.cols = 16 / S; a.inv_cols = S / 16.f;
-  a.h_out = h_out;
-  if (emb) a.emb = *emb;
+  a.h = h; a.stat = stat; a.g = g; a.second = arch == 0 ? (const void*)b : W2; a.W = W; a.bias = bias; a.out = out;   // (an offset and two matrices: no architecture has both)
+  a.d = d; a.N = N; a.n_tiles = (N + 15) / 16; a.rows = rows; a.eps = eps;
+  a.from.h_out = h_out;
+  if (emb) a.from.emb = *emb;
   if (dtype == 0) { if (arch == 0) launch_norm_gemm_arch<float, 0>(epi, emb, a, s); else launch_norm_gemm_arch<float, 1>(epi, emb, a, s); }
   else { if (arch == 0) launch_norm_gemm_arch<bf16_t, 0>(epi, emb, a, s); else launch_norm_gemm_arch<bf16_t, 1>(epi, emb, a, s); }
 }
 
+struct ResidArgs { const void *W, *X; float *h, *stat; const float* bias; int N, K, rows; };
 template <typename AT, int ARCH, int S>
 static void launch_gemm_resid_split(const ResidArgs& a, hipStream_t s) {
   const int ku = sizeof(AT) == 2 ? 32 : 16, kt = (a.K + ku - 1) / ku, rp = a.rows <= 4 ? 4 : a.rows <= 8 ? 8 : 16;
   const int T = std::max(16 / rp, S), per_wave = ((kt + T - 1) / T + 7) / 8, nwl = T / S;
-#define SPRINTER_RES(RP, UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG>), dim3(a.groups), dim3(512), 0, s, a)
+#define SPRINTER_RES(RP, UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N)
 // (up to 8 weight loads of 16 bytes per lane in flight; 16 where two of them make a group)
 #define SPRINTER_RES_U(RP) do { if (per_wave <= 2 || nwl == 4) SPRINTER_RES(RP, 2); else if (per_wave <= 4) SPRINTER_RES(RP, 4); else SPRINTER_RES(RP, 8); } while (0)
   if (rp == 4) SPRINTER_RES_U(4); else if (rp == 8) SPRINTER_RES_U(8); else SPRINTER_RES_U(16);
@@ -445,8 +444,8 @@ static void launch_gemm_resid_split(const ResidArgs& a, hipStream_t s) {
 #undef SPRINTER_RES
 }
 void launch_gemm_resid(int dtype, int arch, const void* W, const void* X, int N, int K, const float* bias, float* h, float* stat, int rows, hipStream_t s) {
-  const int S = resid_split(dtype, N, rows);
-  const ResidArgs a{W, X, h, stat, bias, N, K, rows, N * S / 16};
+  const int S = resid_split(dtype != 0, N, rows);
+  const ResidArgs a{W, X, h, stat, bias, N, K, rows};
 #define SPRINTER_RES(AT, ARCH) do { if (sizeof(AT) == 4 && S == 4) launch_gemm_resid_split<AT, ARCH, sizeof(AT) == 4 ? 4 : 2>(a, s); else if (S == 2) launch_gemm_resid_split<AT, ARCH, 2>(a, s); else launch_gemm_resid_split<AT, ARCH, 1>(a, s); } while (0)
   if (dtype == 0) { if (arch == 0) SPRINTER_RES(float, 0); else SPRINTER_RES(float, 1); }
   else { if (arch == 0) SPRINTER_RES(bf16_t, 0); else SPRINTER_RES(bf16_t, 1); }

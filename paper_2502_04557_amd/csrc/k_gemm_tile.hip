@@ -58,6 +58,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
   auto& ring = *reinterpret_cast<u32x4(*)[S][LT][64]>(lds);
   const int lane = threadIdx.x & 63, w = wave_index(), wm = w / WN, wn = w % WN;
   const int Kt = a.Kt;
+  const void *const w_lo = a.W, *const w_up = a.W2;
   // EPI_PART: the partial product goes to part[share] (summed by the norm that follows)
   const int k0 = (int)((long long)Kt * sk / SK), k1 = (int)((long long)Kt * (sk + 1) / SK);
   // this wave's PER operand tiles of a stage; tiles beyond the buffers are clamped, their products dropped by the epilogue
@@ -73,7 +74,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int x_tiles, int bm
     } else {
       const int j = l - TMT, jw = j / NT, jj = j % NT;
       const bool up = DUAL && jj >= COLS;
-      base = up ? a.W2 : a.W;
+      base = up ? w_up : w_lo;
       tile = min((bn * WN + jw) * COLS + (up ? jj - COLS : jj), a.n_tiles - 1);
     }
     src[i] = (const char*)base + (size_t)tile * Kt * 1024 + lane * 16;
@@ -347,20 +348,26 @@ __device__ __forceinline__ void tile_place(int t, int gm, int gn, int& bm, int& 
 }
 // whole: workgroups with a whole tile; those behind them (256 x 256 tile only) take half a tile each.
 template <typename T, int EPI>
-__global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(GemmArgs a, int x_tiles, int gm, int gn, int whole) {
+__global__ __launch_bounds__(T::waves * 64, T::pinned ? 1 : 2) void k_gemm_tile(const void* W_, const void* X_, const void* second_, int Kt_, int N_, int x_tiles, int gm, int gn, int whole,
+                                                                                  const int* n_rows_, void* out_, int ldo_, int rows_live_, int half_, int shares_, size_t part_stride_,
+                                                                                  GemmMore<EPI> more_) {
+  GemmArgs a;                                           // second: bias, or W2; out: EPI_PART: the shares' buffer; half_: workgroups with half a tile
+  a.W = W_; a.X = X_; a.W2 = second_; a.bias = EPI == EPI_SWIGLU ? nullptr : (const float*)second_; a.Kt = Kt_; a.N = N_; a.n_tiles = (N_ + 15) >> 4;
+  a.n_rows = n_rows_; a.out_f32 = a.part = (float*)out_; a.out_act = out_; a.ldo = a.out_K = ldo_; a.rows_live = rows_live_; a.part_stride = part_stride_;
+  if constexpr (EPI == EPI_QKV) a.kv = more_;
   __shared__ __attribute__((aligned(1024))) unsigned char lds[T::stages * (T::wm * T::mt + T::wn * T::nt) * 1024];
   const int id = blockIdx.x;
   int bm, bn;
   if constexpr (T::pinned && EPI != EPI_PART) {         // (partial products: several shares, never in halves)
     if (id >= whole) {                                  // (scalar)
-      const int t = xcd_run(id - whole, gridDim.x - whole);
+      const int t = xcd_run(id - whole, half_);
       tile_place<T>(whole + (t >> 1), gm, gn, bm, bn);
       gemm_tile<TileH, EPI>(a, x_tiles, bm, 2 * bn + (t & 1), 0, 1, lds);
       return;
     }
   }
   tile_place<T>(xcd_run(id, whole), gm, gn, bm, bn);
-  gemm_tile<T, EPI>(a, x_tiles, bm, bn, EPI == EPI_PART ? blockIdx.y : 0, EPI == EPI_PART ? gridDim.y : 1, lds);
+  gemm_tile<T, EPI>(a, x_tiles, bm, bn, EPI == EPI_PART ? blockIdx.y : 0, EPI == EPI_PART ? shares_ : 1, lds);
 }
 
 // Which tile, and how many K shares (partial products), for a shape: the one with the smallest estimate of
@@ -395,7 +402,9 @@ static void launch_tile(const GemmArgs& a, int rows, int sk, hipStream_t s) {
   constexpr int tm = T::wm * T::mt * 16, cols = T::wn * T::nt * 16 / (EPI == EPI_SWIGLU ? 2 : 1);
   const int x_tiles = (int)(a.x_elems / ((size_t)a.Kt * 512)), gm = (rows + tm - 1) / tm, gn = (a.N + cols - 1) / cols;
   const int tiles = gm * gn, rest = T::pinned && sk == 1 ? tiles_in_halves(tiles) : 0, whole = tiles - rest;
-  hipLaunchKernelGGL((k_gemm_tile<T, EPI>), dim3(whole + 2 * rest, sk), dim3(T::waves * 64), 0, s, a, x_tiles, gm, gn, whole);
+  hipLaunchKernelGGL((k_gemm_tile<T, EPI>), dim3(whole + 2 * rest, sk), dim3(T::waves * 64), 0, s, a.W, a.X, EPI == EPI_SWIGLU ? a.W2 : (const void*)a.bias, a.Kt, a.N,
+                     x_tiles, gm, gn, whole, a.n_rows, EPI == EPI_PART ? (void*)a.part : EPI == EPI_GELU || EPI == EPI_SWIGLU ? a.out_act : (void*)a.out_f32,
+                     EPI == EPI_GELU || EPI == EPI_SWIGLU ? a.out_K : a.ldo, a.rows_live, 2 * rest, sk, a.part_stride, gemm_more<EPI>(a));
 }
 
 int gemm_tile_choice(int epi, int rows, int N, int K, int max_shares) {

@@ -7,6 +7,7 @@
 #include "dev.h"
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 namespace sprinter {
 
@@ -79,10 +80,11 @@ __device__ __forceinline__ int norm_row(int id, int rows) {
   return id < (rows & ~127) ? (id & ~127) + (id & 7) * 16 + ((id >> 3) & 15) : id;
 }
 template <typename AT, int ARCH, int NI, int SH>
-__global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g,
-                                                   const float* __restrict__ b, float eps, int d,
-                                                   const int* __restrict__ n_rows, AT* __restrict__ act_out,
-                                                   float* __restrict__ f32_out, NormPending pend, EmbedSource emb, int n_rows_grid) {
+__global__ __launch_bounds__(256) void k_norm(const float* __restrict__ h, const float* __restrict__ g, const float* __restrict__ b,
+                                                   const float* __restrict__ part, const float* __restrict__ part_bias, int d, int n_rows_grid, int shares, float eps,
+                                                   const int* __restrict__ n_rows, AT* __restrict__ act_out, float* __restrict__ f32_out, size_t part_stride,
+                                                   std::conditional_t<(SH < 0), EmbedSource, Nothing> emb) {
+  const NormPending pend{part, part_stride, shares, part_bias};
   __shared__ float s_sum[4], s_sq[4];
   const int r = norm_row(blockIdx.x, n_rows_grid), tid = threadIdx.x;
   if constexpr (SH < 0 && ARCH == 1) {
@@ -290,8 +292,8 @@ static void launch_norm_ni(const float* h, const float* g, const float* b, float
     }
   }
   const int rope_wgs = es.rope ? (int)(((size_t)max_rows * (es.dh / 2) + 255) / 256) : 0;
-#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows + rope_wgs), dim3(256), 0, s, h, g, b, eps, d, n_rows, (AT*)act_out, f32_out, np, es, max_rows)
-  if (emb) SPRINTER_NORM(-1);
+#define SPRINTER_NORM(SH) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, SH>), dim3(max_rows), dim3(256), 0, s, h, g, b, np.part, np.bias, d, max_rows, np.shares, eps, n_rows, (AT*)act_out, f32_out, np.stride, Nothing{})
+  if (emb) hipLaunchKernelGGL((k_norm<AT, ARCH, NI, -1>), dim3(max_rows + rope_wgs), dim3(256), 0, s, h, g, b, nullptr, nullptr, d, max_rows, 0, eps, n_rows, (AT*)act_out, f32_out, 0, es);
   else if (np.shares <= 0) SPRINTER_NORM(0);
   else if (np.shares == 1) SPRINTER_NORM(1);
   else if (np.shares == 2) SPRINTER_NORM(2);
