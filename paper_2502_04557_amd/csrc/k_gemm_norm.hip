@@ -255,7 +255,7 @@ __device__ __forceinline__ float columns_sum(float v) {   // over C = 4, 8 or 16
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));           // quad_perm [1,0,3,2]
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));     // quad_perm [2,3,0,1]
 }
-// O-projection and FFN-down of at most 16 rows: h += bias + X W^T in place, and the statistics of what was written.  A workgroup has all of K for its columns, so
+// O-projection and FFN-down of at most 16 rows, of at most 32 from 2049 columns on: h += bias + X W^T in place, and the statistics of what was written.  A workgroup has all of K for its columns, so
 // that it can finish them, and 16 / S columns instead of 16 where that takes to fill the chip (N <= 2048): a weight load then carries S k
 // tiles of the columns - 128 bytes of each for S = 2, a line -, as many bytes per workgroup as K in S shares.  What that costs is the activations of
 // all of K in every workgroup, and the address unit takes 16 cycles per load whatever it brings: so where an operand's 16 rows are not all there, a load
@@ -264,28 +264,31 @@ __device__ __forceinline__ float columns_sum(float v) {   // over C = 4, 8 or 16
 // 2-norm, K in shares -> in order -> so: 1600 x 6400, 4 rows 8.7e-8 -> 9.5e-8 -> 6.9e-8; 4096 x 14336, 16 rows 1.58e-7 -> 2.13e-7 -> 1.19e-7).
 // us, K in shares over workgroups and the sum left to the norm -> this: 1600 x 6400, 4 rows 6.3 -> 6.7, 16 rows 7.1 -> 9.0; 1600 x 1600 3.8 -> 3.8;
 // 4096 x 14336 and 4096 x 4096 at 5 - 16 rows 24.7 -> 22.5 and 12.1 -> 8.1; the norms behind it 3.4 -> 2.9, or gone (above).
-// RP: rows an activation load carries (4, 8 or 16).  UG: groups of T = max(16 / RP, S) k tiles in flight per wave.
-template <typename AT, int ARCH, int S, int RP, int UG>
+// RP: rows an activation load carries (4, 8 or 16); MT: operands of 16 rows.  UG: groups of T = max(16 / RP, S) k tiles in flight per wave.
+template <typename AT, int ARCH, int S, int RP, int UG, int MT>
 __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X, int K, int rows, float* h, const float* bias, float* stat, int N) {
   constexpr bool BF = sizeof(AT) == 2;
   constexpr int C = 16 / S, P = 16 / RP, T = P > S ? P : S, NX = T / P, NWL = T / S, NM = NX > NWL ? NX : NWL, KU = BF ? 32 : 16;
   constexpr int NA = P >= S ? P / S : S;                // accumulators: which of their elements are sums of matching k is below
   constexpr int D = NA < 4 ? 4 / NA : 1;                // each D times, for groups in turn
-  __shared__ float red[8 * 4 * 64];
+  static_assert(MT == 1 || (BF && RP == 16), "");
+  __shared__ float red[8 * MT * 4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
   const int kt = (K + KU - 1) / KU, groups = (kt + T - 1) / T, n0 = blockIdx.x * C;
   const int ws = l16 / C, wc = l16 % C, xp = l16 / RP, xr = l16 % RP;
   const auto rw = BF ? bytes_at((const char*)W + (size_t)(n0 >> 4) * kt * 1024, kt * 1024) : bytes_at((const char*)W + (size_t)n0 * K * 4, C * K * 4);
-  const auto rx = BF ? bytes_at(X, kt * 1024) : bytes_at(X, rows * K * 4);
+  const auto rx = BF ? bytes_at(X, MT * kt * 1024) : bytes_at(X, rows * K * 4);
   const int w_lane = BF ? ws * 1024 + (lq * 16 + (n0 & 15) + wc) * 16 : wc * K * 4 + (ws * 16 + lq * 4) * 4;
   const int x_lane = xr < rows ? (BF ? xp * 1024 + (lq * 16 + xr) * 16 : xr * K * 4 + (xp * 16 + lq * 4) * 4) : NOWHERE;
+  const int x_lane2 = MT == 2 && 16 + l16 < rows ? kt * 1024 + lane * 16 : NOWHERE;   // (the second 16 rows: one operand tile row further)
   constexpr int TB = BF ? 1024 : 64;                    // bytes from one k tile to the next
-  u32x4 wv[UG][NWL], xv[UG][NX];
+  u32x4 wv[UG][NWL], xv[UG][NX], x2[UG][MT == 2 ? NX : 1];
   auto load_group = [&](int u, int g) {
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
       const int t = g * T + i * P;
       xv[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (BF || (t + xp) * KU + lq * 4 < K ? x_lane : NOWHERE) + t * TB, 0, 0);
+      if constexpr (MT == 2) x2[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, t < kt ? x_lane2 + t * TB : NOWHERE, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < NWL; ++i) {
@@ -300,16 +303,17 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
   const bool out_ok = m < rows;
   float res = 0.f;
   if (out_ok) { res = h[(size_t)m * N + n]; if (bias) res += bias[n]; }
-  f32x4 acc[NA][D];
+  f32x4 acc[NA][D], acc2[MT == 2 ? NA : 1][D];
 #pragma unroll
   for (int i = 0; i < NA; ++i)
 #pragma unroll
-    for (int v = 0; v < D; ++v) acc[i][v] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int v = 0; v < D; ++v) { acc[i][v] = (f32x4){0.f, 0.f, 0.f, 0.f}; if (MT == 2) acc2[i][v] = acc[i][v]; }
   auto use = [&](int u) {
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
       const u32x4 x = xv[u][i % NX], wt = wv[u][i % NWL];
       f32x4& sum = acc[i % NA][u % D];
+      if constexpr (MT == 2) { const u32x4 y = x2[u][i % NX]; acc2[i % NA][u % D] = mfma_f16(make_uint4(y.x, y.y, y.z, y.w), make_uint4(wt.x, wt.y, wt.z, wt.w), acc2[i % NA][u % D]); }
       if constexpr (BF) sum = mfma_f16(make_uint4(x.x, x.y, x.z, x.w), make_uint4(wt.x, wt.y, wt.z, wt.w), sum);
       else {
 #pragma unroll
@@ -331,23 +335,31 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
   for (int i = 0; i < NA; ++i) {
     if constexpr (D == 2) acc[i][0] += acc[i][1];
     if constexpr (D == 4) acc[i][0] = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+    if constexpr (MT == 2 && D == 2) acc2[i][0] += acc2[i][1];
+    if constexpr (MT == 2 && D == 4) acc2[i][0] = (acc2[i][0] + acc2[i][1]) + (acc2[i][2] + acc2[i][3]);
   }
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     float x = acc[0][0][v];
 #pragma unroll
     for (int i = 1; i < NA; ++i) x = mine == i ? acc[i][0][v] : x;
-    red[(w * 4 + v) * 64 + lane] = x;
+    red[(w * MT * 4 + v) * 64 + lane] = x;
+    if constexpr (MT == 2) {
+      float y = acc2[0][0][v];
+#pragma unroll
+      for (int i = 1; i < NA; ++i) y = mine == i ? acc2[i][0][v] : y;
+      red[(w * MT * 4 + 4 + v) * 64 + lane] = y;
+    }
   }
   __syncthreads();
-  if (tid >= RP * C) return;
+  if (tid >= MT * RP * C) return;
   float sum[8 * T];
 #pragma unroll
   for (int q = 0; q < 8; ++q)
 #pragma unroll
     for (int t = 0; t < T; ++t) {
-      const int row = (P == 1 ? 0 : t * RP) + m, s = t % S;
-      sum[q * T + t] = red[(q * 4 + (row & 3)) * 64 + (row >> 2) * 16 + s * C + c];
+      const int row = (P == 1 ? 0 : t * RP) + (m & (RP - 1)), s = t % S;
+      sum[q * T + t] = red[((q * MT + m / RP) * 4 + (row & 3)) * 64 + (row >> 2) * 16 + s * C + c];
     }
 #pragma unroll
   for (int half = 4 * T; half; half >>= 1)              // in pairs, always the same ones
@@ -369,10 +381,10 @@ bool gemm_takes_norm(int dtype, int d, int rows) {
   if (dtype == 0) return rows <= (d <= 512 ? 16 : d <= 1024 ? 8 : d <= 2048 ? 4 : 0);
   return rows <= (d <= 1024 ? 16 : d <= 2048 ? 8 : d <= 4096 ? 4 : 0);
 }
-// Whether O-projection and FFN-down add themselves to the residual rows: wherever the norms are in the products and, at most 16 rows, from 2049 columns on, where the
+// Whether O-projection and FFN-down add themselves to the residual rows: wherever the norms are in the products and, at most 32 rows, from 2049 columns on, where the
 // columns alone fill the chip.  us per layer with the norms as launches, partial products / this: 4096 (11008), 8 rows 98.6 / 92.9, 16 rows 110.6 / 104.6; 4096 (14336, 8 KV heads),
-// 5 rows 104.2 / 100.0, 16 rows 109.6 / 103.3; but 1600, 16 rows 38.3 / 38.8, 2048 44.6 / 46.4.
-bool gemm_adds_rows(int dtype, int d, int rows) { return gemm_takes_norm(dtype, d, rows) || (dtype != 0 && d > 2048 && rows <= 16); }
+// 5 rows 104.2 / 100.0, 16 rows 109.6 / 103.3, 17 rows 111.1 / 110.4, 24 rows 118.7 / 112.0, 32 rows 122.6 / 119.8; 4096 (11008) 17 rows 122.7 / 113.5, 32 rows 134.0 / 127.9; but 1600, 16 rows 38.3 / 38.8, 2048 44.6 / 46.4.
+bool gemm_adds_rows(int dtype, int d, int rows) { return gemm_takes_norm(dtype, d, rows) || (dtype != 0 && d > 2048 && rows <= 32); }
 
 struct NormGemmArgs { const float *h, *stat, *g; const void *second, *W; const float* bias; void* out; int d, N, n_tiles, rows; float eps; RowSource from; };
 
@@ -436,7 +448,9 @@ template <typename AT, int ARCH, int S>
 static void launch_gemm_resid_split(const ResidArgs& a, hipStream_t s) {
   const int ku = sizeof(AT) == 2 ? 32 : 16, kt = (a.K + ku - 1) / ku, rp = a.rows <= 4 ? 4 : a.rows <= 8 ? 8 : 16;
   const int T = std::max(16 / rp, S), per_wave = ((kt + T - 1) / T + 7) / 8, nwl = T / S;
-#define SPRINTER_RES(RP, UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N)
+  if constexpr (sizeof(AT) == 2 && S == 1)
+    if (a.rows > 16) { hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, 1, 16, 8, 2>), dim3(a.N / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N); return; }
+#define SPRINTER_RES(RP, UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG, 1>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N)
 // (up to 8 weight loads of 16 bytes per lane in flight; 16 where two of them make a group)
 #define SPRINTER_RES_U(RP) do { if (per_wave <= 2 || nwl == 4) SPRINTER_RES(RP, 2); else if (per_wave <= 4) SPRINTER_RES(RP, 4); else SPRINTER_RES(RP, 8); } while (0)
   if (rp == 4) SPRINTER_RES_U(4); else if (rp == 8) SPRINTER_RES_U(8); else SPRINTER_RES_U(16);

@@ -17,7 +17,7 @@ def _cases():
     # both sides of the lines in d (512, 1024, 2048) and of the rows a thread, a load or an operand takes; K: odd numbers of k tiles, a last one partly
     # filled, less than one round of the waves, several rounds of the loads in flight; columns beyond d: a part of a tile, two tiles per wave
     for d, K, rows in [(64, 64, (1, 9)), (512, 1344, (3, 8, 16)), (576, 72, (4, 5)), (768, 3072, (1, 4, 8, 9, 16)), (1024, 200, (12,)), (1088, 264, (1, 3, 8)),
-                       (1600, 6400, (1, 2, 4, 5, 8)), (2048, 8192, (7,)), (2112, 2112, (1, 2, 3)), (4096, 14336, (1, 4, 5, 16)), (8192, 96, (13,))]:
+                       (1600, 6400, (1, 2, 4, 5, 8)), (2048, 8192, (7,)), (2112, 2112, (1, 2, 3)), (4096, 14336, (1, 4, 5, 16, 17, 32)), (4160, 328, (25,)), (8192, 96, (13, 31))]:
         for r in rows:
             yield BF16, d, K, r, 40
     yield BF16, 1600, 1600, 4, 2520
