@@ -385,9 +385,9 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   // O-proj and FFN-down split K over workgroups and leave partial products; the norm that follows folds
   // them (and the bias) into the residual stream before it normalises the row.  A product in one piece adds itself.
   const size_t part_stride = (size_t)rows * md.d;
-  // a few rows: they always add themselves, and the norms before QKV and FFN-up are part of those launches (the rows' statistics lie in part,
+  // a few rows: they add themselves, and the norms before QKV and FFN-up are part of those launches (the rows' statistics lie in part,
   // which the attention only takes between a layer's QKV and its O-proj)
-  const bool adds = !shared_caches && gemm_adds_rows(dt, md.d, max_rows), fused = adds && gemm_takes_norm(dt, md.d, max_rows);
+  const bool fused = !shared_caches && gemm_takes_norm(dt, md.d, max_rows);
   // Short passes (work lists, speculative windows) of a model without rotary positions: the projection's epilogue puts keys and values
   // where the append launch would.  (A key's rotary partner is another workgroup's; and a prefill pass gathers 8 slots of a value column
   // into one store in that launch, where an epilogue would write 2 bytes at a time.)
@@ -395,7 +395,7 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   const bool append_in_qkv = shared_caches && run_len == 0 && dt == SPRINTER_BF16 && md.arch == SPRINTER_ARCH_GPT;
   NormPending pend{sc.part, part_stride, 0, nullptr};
   auto resid_gemm = [&](const void* W, const void* X, size_t plane, int K, const float* bias) {
-    if (adds) { launch_gemm_resid(dt, md.arch, W, X, md.d, K, bias, sc.h, sc.part, max_rows, s); return; }
+    if (fused || gemm_adds_rows(dt, md.d, K, max_rows)) { launch_gemm_resid(dt, md.arch, W, X, md.d, K, bias, sc.h, fused ? sc.part : nullptr, max_rows, s); return; }
     pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, PART_SHARES, bias, sc.h, max_rows, s);
     pend.bias = bias;
   };

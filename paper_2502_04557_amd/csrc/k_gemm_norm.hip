@@ -280,15 +280,16 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
   const auto rx = BF ? bytes_at(X, MT * kt * 1024) : bytes_at(X, rows * K * 4);
   const int w_lane = BF ? ws * 1024 + (lq * 16 + (n0 & 15) + wc) * 16 : wc * K * 4 + (ws * 16 + lq * 4) * 4;
   const int x_lane = xr < rows ? (BF ? xp * 1024 + (lq * 16 + xr) * 16 : xr * K * 4 + (xp * 16 + lq * 4) * 4) : NOWHERE;
-  const int x_lane2 = MT == 2 && 16 + l16 < rows ? kt * 1024 + lane * 16 : NOWHERE;   // (the second 16 rows: one operand tile row further)
   constexpr int TB = BF ? 1024 : 64;                    // bytes from one k tile to the next
-  u32x4 wv[UG][NWL], xv[UG][NX], x2[UG][MT == 2 ? NX : 1];
+  u32x4 wv[UG][NWL], xv[UG][NX][MT];
   auto load_group = [&](int u, int g) {
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
       const int t = g * T + i * P;
-      xv[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (BF || (t + xp) * KU + lq * 4 < K ? x_lane : NOWHERE) + t * TB, 0, 0);
-      if constexpr (MT == 2) x2[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rx, t < kt ? x_lane2 + t * TB : NOWHERE, 0, 0);
+      xv[u][i][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, (BF || (t + xp) * KU + lq * 4 < K ? x_lane : NOWHERE) + t * TB, 0, 0);
+#pragma unroll
+      for (int j = 1; j < MT; ++j)                      // (the next 16 rows are an operand tile row further)
+        xv[u][i][j] = __builtin_amdgcn_raw_buffer_load_b128(rx, t < kt && 16 * j + l16 < rows ? (j * kt + t) * 1024 + lane * 16 : NOWHERE, 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < NWL; ++i) {
@@ -298,28 +299,35 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
   };
 #pragma unroll
   for (int u = 0; u < UG; ++u) load_group(u, w + 8 * u);
-  // this thread's output element: the row's columns in consecutive lanes
-  const int m = tid / C, c = tid % C, n = n0 + c;
-  const bool out_ok = m < rows;
-  float res = 0.f;
-  if (out_ok) { res = h[(size_t)m * N + n]; if (bias) res += bias[n]; }
-  f32x4 acc[NA][D], acc2[MT == 2 ? NA : 1][D];
+  // this thread's output elements: a row's columns in consecutive lanes
+  constexpr int OUT = (MT * RP * C + 511) / 512;
+  float res[OUT];
 #pragma unroll
-  for (int i = 0; i < NA; ++i)
+  for (int o = 0; o < OUT; ++o) {
+    const int m = (o * 512 + tid) / C, n = n0 + tid % C;
+    res[o] = 0.f;
+    if (m < rows) { res[o] = h[(size_t)m * N + n]; if (bias) res[o] += bias[n]; }
+  }
+  f32x4 acc[MT][NA][D];
 #pragma unroll
-    for (int v = 0; v < D; ++v) { acc[i][v] = (f32x4){0.f, 0.f, 0.f, 0.f}; if (MT == 2) acc2[i][v] = acc[i][v]; }
+  for (int j = 0; j < MT; ++j)
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+      for (int v = 0; v < D; ++v) acc[j][i][v] = (f32x4){0.f, 0.f, 0.f, 0.f};
   auto use = [&](int u) {
 #pragma unroll
-    for (int i = 0; i < NM; ++i) {
-      const u32x4 x = xv[u][i % NX], wt = wv[u][i % NWL];
-      f32x4& sum = acc[i % NA][u % D];
-      if constexpr (MT == 2) { const u32x4 y = x2[u][i % NX]; acc2[i % NA][u % D] = mfma_f16(make_uint4(y.x, y.y, y.z, y.w), make_uint4(wt.x, wt.y, wt.z, wt.w), acc2[i % NA][u % D]); }
-      if constexpr (BF) sum = mfma_f16(make_uint4(x.x, x.y, x.z, x.w), make_uint4(wt.x, wt.y, wt.z, wt.w), sum);
-      else {
+    for (int i = 0; i < NM; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[e]), __uint_as_float(wt[e]), sum, 0, 0, 0);
+      for (int j = 0; j < MT; ++j) {
+        const u32x4 x = xv[u][i % NX][j], wt = wv[u][i % NWL];
+        f32x4& sum = acc[j][i % NA][u % D];
+        if constexpr (BF) sum = mfma_f16(make_uint4(x.x, x.y, x.z, x.w), make_uint4(wt.x, wt.y, wt.z, wt.w), sum);
+        else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[e]), __uint_as_float(wt[e]), sum, 0, 0, 0);
+        }
       }
-    }
   };
   int g = w;
   for (; g + 8 * UG < groups; g += 8 * UG) {            // (scalar)
@@ -332,46 +340,45 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
   // where p = S i + s (P >= S), or s = i (P = 1).
   const int mine = P >= S ? (lq * 4 / RP) / S : ws;
 #pragma unroll
-  for (int i = 0; i < NA; ++i) {
-    if constexpr (D == 2) acc[i][0] += acc[i][1];
-    if constexpr (D == 4) acc[i][0] = (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
-    if constexpr (MT == 2 && D == 2) acc2[i][0] += acc2[i][1];
-    if constexpr (MT == 2 && D == 4) acc2[i][0] = (acc2[i][0] + acc2[i][1]) + (acc2[i][2] + acc2[i][3]);
-  }
+  for (int j = 0; j < MT; ++j) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    float x = acc[0][0][v];
+    for (int i = 0; i < NA; ++i) {
+      if constexpr (D == 2) acc[j][i][0] += acc[j][i][1];
+      if constexpr (D == 4) acc[j][i][0] = (acc[j][i][0] + acc[j][i][1]) + (acc[j][i][2] + acc[j][i][3]);
+    }
 #pragma unroll
-    for (int i = 1; i < NA; ++i) x = mine == i ? acc[i][0][v] : x;
-    red[(w * MT * 4 + v) * 64 + lane] = x;
-    if constexpr (MT == 2) {
-      float y = acc2[0][0][v];
+    for (int v = 0; v < 4; ++v) {
+      float x = acc[j][0][0][v];
 #pragma unroll
-      for (int i = 1; i < NA; ++i) y = mine == i ? acc2[i][0][v] : y;
-      red[(w * MT * 4 + 4 + v) * 64 + lane] = y;
+      for (int i = 1; i < NA; ++i) x = mine == i ? acc[j][i][0][v] : x;
+      red[((w * MT + j) * 4 + v) * 64 + lane] = x;
     }
   }
   __syncthreads();
-  if (tid >= MT * RP * C) return;
-  float sum[8 * T];
 #pragma unroll
-  for (int q = 0; q < 8; ++q)
+  for (int o = 0; o < OUT; ++o) {
+    const int m = (o * 512 + tid) / C, c = tid % C, n = n0 + c;
+    if (m >= MT * RP) return;
+    float sum[8 * T];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int row = (P == 1 ? 0 : t * RP) + (m & (RP - 1)), s = t % S;
-      sum[q * T + t] = red[((q * MT + m / RP) * 4 + (row & 3)) * 64 + (row >> 2) * 16 + s * C + c];
-    }
+    for (int q = 0; q < 8; ++q)
 #pragma unroll
-  for (int half = 4 * T; half; half >>= 1)              // in pairs, always the same ones
+      for (int t = 0; t < T; ++t) {
+        const int row = (P == 1 ? 0 : t * RP) + (m & (RP - 1)), s = t % S;
+        sum[q * T + t] = red[((q * MT + m / RP) * 4 + (row & 3)) * 64 + (row >> 2) * 16 + s * C + c];
+      }
 #pragma unroll
-    for (int i = 0; i < half; ++i) sum[i] += sum[i + half];
-  const float v = res + sum[0];
-  float mean = 0.f, dv = v, s1 = 0.f;
-  if (ARCH == 0) { s1 = columns_sum<C>(v); mean = s1 * (1.0f / C); dv = v - mean; }
-  const float s2 = columns_sum<C>(dv * dv);
-  if (!out_ok) return;
-  h[(size_t)m * N + n] = v;
-  if (c == 0) reinterpret_cast<float2*>(stat)[(size_t)m * (N / C) + blockIdx.x] = make_float2(s1, s2);
+    for (int half = 4 * T; half; half >>= 1)            // in pairs, always the same ones
+#pragma unroll
+      for (int i = 0; i < half; ++i) sum[i] += sum[i + half];
+    const float v = res[o] + sum[0];
+    float mean = 0.f, dv = v, s1 = 0.f;
+    if (ARCH == 0) { s1 = columns_sum<C>(v); mean = s1 * (1.0f / C); dv = v - mean; }
+    const float s2 = columns_sum<C>(dv * dv);
+    if (m >= rows) return;
+    h[(size_t)m * N + n] = v;
+    if (stat && c == 0) reinterpret_cast<float2*>(stat)[(size_t)m * (N / C) + blockIdx.x] = make_float2(s1, s2);
+  }
 }
 
 // The line: us per layer, seven launches / five.  1600 columns: 8 rows 34.2 / 30.6, 10 rows 35.9 / 35.7, 16 rows 38.4 / 38.9; 2048 (gate + up): 8 rows 43.6 / 38.6, 10 rows 44.1 / 44.6;
@@ -381,10 +388,12 @@ bool gemm_takes_norm(int dtype, int d, int rows) {
   if (dtype == 0) return rows <= (d <= 512 ? 16 : d <= 1024 ? 8 : d <= 2048 ? 4 : 0);
   return rows <= (d <= 1024 ? 16 : d <= 2048 ? 8 : d <= 4096 ? 4 : 0);
 }
-// Whether O-projection and FFN-down add themselves to the residual rows: wherever the norms are in the products and, at most 32 rows, from 2049 columns on, where the
-// columns alone fill the chip.  us per layer with the norms as launches, partial products / this: 4096 (11008), 8 rows 98.6 / 92.9, 16 rows 110.6 / 104.6; 4096 (14336, 8 KV heads),
-// 5 rows 104.2 / 100.0, 16 rows 109.6 / 103.3, 17 rows 111.1 / 110.4, 24 rows 118.7 / 112.0, 32 rows 122.6 / 119.8; 4096 (11008) 17 rows 122.7 / 113.5, 32 rows 134.0 / 127.9; but 1600, 16 rows 38.3 / 38.8, 2048 44.6 / 46.4.
-bool gemm_adds_rows(int dtype, int d, int rows) { return gemm_takes_norm(dtype, d, rows) || (dtype != 0 && d > 2048 && rows <= 32); }
+// Whether a product of K adds itself to the residual rows although the norm behind it is a launch: at most 32 rows from 2049 columns on, where the columns alone fill
+// the chip, and 17 - 32 rows of a short K, whose activations (all of K in every workgroup) cost less than four and more partial products do in the norm.  us per layer, partial
+// products / so: 4096 (11008), 8 rows 98.6 / 92.9, 16 rows 110.6 / 104.6, 17 rows 122.7 / 113.5, 32 rows 134.0 / 127.9; 4096 (14336, 8 KV heads), 5 rows 104.2 / 100.0, 16 rows
+// 109.6 / 103.3, 24 rows 118.7 / 112.0, 32 rows 122.6 / 119.8.  O-projection of 1600 columns with its norm, 17 / 32 rows 10.3 / 10.0 us against 7.3 / 7.7, 40 rows 9.7 / 9.4; of 768, 24
+// rows 8.7 / 6.9; but FFN-down (6400) at 24 rows 12.6 / 13.1, both at 8 - 16 rows equal, and 256 columns 6.3 / 6.2.
+bool gemm_adds_rows(int dtype, int d, int K, int rows) { return dtype != 0 && rows <= 32 && (d > 2048 || (d > 512 && rows > 16 && K <= 2048)); }
 
 struct NormGemmArgs { const float *h, *stat, *g; const void *second, *W; const float* bias; void* out; int d, N, n_tiles, rows; float eps; RowSource from; };
 
@@ -448,8 +457,8 @@ template <typename AT, int ARCH, int S>
 static void launch_gemm_resid_split(const ResidArgs& a, hipStream_t s) {
   const int ku = sizeof(AT) == 2 ? 32 : 16, kt = (a.K + ku - 1) / ku, rp = a.rows <= 4 ? 4 : a.rows <= 8 ? 8 : 16;
   const int T = std::max(16 / rp, S), per_wave = ((kt + T - 1) / T + 7) / 8, nwl = T / S;
-  if constexpr (sizeof(AT) == 2 && S == 1)
-    if (a.rows > 16) { hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, 1, 16, 8, 2>), dim3(a.N / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N); return; }
+  if constexpr (sizeof(AT) == 2 && S <= 2)
+    if (a.rows > 16) { hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, 16, S == 1 ? 8 : 4, 2>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N); return; }
 #define SPRINTER_RES(RP, UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG, 1>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N)
 // (up to 8 weight loads of 16 bytes per lane in flight; 16 where two of them make a group)
 #define SPRINTER_RES_U(RP) do { if (per_wave <= 2 || nwl == 4) SPRINTER_RES(RP, 2); else if (per_wave <= 4) SPRINTER_RES(RP, 4); else SPRINTER_RES(RP, 8); } while (0)

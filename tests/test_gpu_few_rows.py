@@ -21,6 +21,9 @@ def _cases():
         for r in rows:
             yield BF16, d, K, r, 40
     yield BF16, 1600, 1600, 4, 2520
+    for r in (17, 24, 32):
+        yield BF16, 1600, 1600, r, 0
+        yield BF16, 576, 72, r, 0
     for d, K, rows in [(64, 72, (1, 16)), (256, 1024, (4, 5, 16)), (512, 2048, (1, 8)), (1024, 104, (3, 8)), (2048, 64, (4,))]:
         for r in rows:
             yield F32, d, K, r, 24
@@ -44,7 +47,7 @@ def test_residual_rows_and_their_norm(dtype, d, K, rows, more, arch):
     X = store(x)                                              # (operand tiles: the rows of a tile that do not exist must have no effect)
     if dtype == BF16:
         X.view(-1, X.shape[1], 4, 16, 8)[:, :, :, rows:] = float("nan")
-    hg, stat = h.clone(), torch.full((16 * d // 4,), float("nan"), device="cuda")
+    hg, stat = h.clone(), torch.full((32 * d // 4,), float("nan"), device="cuda")
     _lib()["_ZN8sprinter17launch_gemm_residEiiPKvS1_iiPKfPfS4_iP12ihipStream_t"](
         dtype, arch, _ptr(store(W)), _ptr(X), d, K, _ptr(bias), _ptr(hg), _ptr(stat), rows, stream)
     torch.cuda.synchronize()
@@ -54,7 +57,7 @@ def test_residual_rows_and_their_norm(dtype, d, K, rows, more, arch):
     bound = steps * 2.0 ** -24 * (h.double().abs() + x.double().abs() @ W.double().abs().T + (0 if bias is None else bias.double().abs()))
     assert ((hg.double() - want).abs() <= bound).all()
     if not _takes_norm(dtype, d, rows):
-        assert dtype == BF16 and d > 2048 and rows > 4
+        assert _lib()["_ZN8sprinter14gemm_adds_rowsEiiii"](dtype, d, K, rows) & 0xFF
         return
     # a unit matrix shows the normalised rows themselves; the columns behind it are products
     gain, off = 1 + 0.1 * rnd(d), 0.1 * rnd(d) if arch == 0 else None
