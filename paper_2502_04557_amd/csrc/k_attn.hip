@@ -209,8 +209,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // accumulator is done for NV registers instead of four: 2450 -> 790 cycles per step at 64 columns and one head.  us per launch in a chain,
 // with that, with the masks of the last block in two instructions a register and with loads only in the waves that use them: heads of 64,
 // 150 keys, 25 of them: 6 rows 6.15 -> 5.08, 16 rows 8.4 -> 7.5; 60 keys, 1 row 4.7 -> 3.1; of 128, 300 keys, 32: 3 rows 10.5 -> 8.7, 33 rows (162
-// MB) 41.9 -> 36.4; 8 KV heads, 540 keys, 17 rows 16.9 -> 13.1.  Long contexts and many rows: the cache, at 4.3 - 4.8 TB/s.  (8 waves from 140
-// keys on: 6 rows of 25 heads 5.08 -> 4.69, but 16 rows of 12 x 300 keys 6.6 -> 7.2 and 3 rows of 32 x 128 columns 8.7 -> 10.8.)
+// MB) 41.9 -> 36.4; 8 KV heads, 540 keys, 17 rows 16.9 -> 13.1.  Long contexts and many rows: the cache, at 4.3 - 4.8 TB/s.  (When eight waves: at the launch.)
 // The waves' partial results are merged through LDS at the end.  gridDim.z = extra > 1: that many workgroups share the keys (their waves
 // count on), each leaves its unnormalised result, maximum and sum in a.split, and k_attn_merge puts them together.
 template <int DH, int NW, int NV, bool ROPE>
@@ -1205,10 +1204,14 @@ static void launch_attn_bf16(const AttnArgs& a, int G, int max_rows, int ctx_bou
 #undef SPRINTER_RUNS
     return;
   }
+  // 64 columns and 129 - 256 keys: eight waves take one step where four take two, and one workgroup per compute unit leaves their loads alone.  us per launch, 4 / 8
+  // waves: 25 heads, 130 keys, 1 row 5.14 / 4.68, 190 keys, 5 rows 5.35 / 4.88, 12 heads, 150 keys, 16 rows 6.40 / 6.22, 8 KV heads, 230 keys, 1 row 5.12 / 4.66; but two
+  // steps for three, 300 keys, 8 KV heads, 4 rows 5.95 / 6.58, 16 rows 6.09 / 6.86, and at 128 columns 280 keys, 32 heads, 3 rows 7.90 / 8.84.
+  const bool one_step = DH == 64 && (long long)a.KVH * max_rows <= 256 && ctx_bound > 128 && ctx_bound <= 256;
   const int split = attn_split(DH, a.KVH, max_rows, ctx_bound);
   grid.z = split;
 #define SPRINTER_DEC(NW, NV, ROPE) hipLaunchKernelGGL((k_attn_dec_bf16<DH, NW, NV, ROPE>), grid, dim3(NW * 64), 0, s, ATTN_VALUES(a, split, 2), a.split)
-#define SPRINTER_DEC_NW(NV, ROPE) do { if (wide || split > 1) SPRINTER_DEC(8, NV, ROPE); else SPRINTER_DEC(4, NV, ROPE); } while (0)
+#define SPRINTER_DEC_NW(NV, ROPE) do { if (wide || one_step || split > 1) SPRINTER_DEC(8, NV, ROPE); else SPRINTER_DEC(4, NV, ROPE); } while (0)
   if (G <= 4) { if (a.use_rope) SPRINTER_DEC_NW(1, true); else SPRINTER_DEC_NW(1, false); }
   else { if (a.use_rope) SPRINTER_DEC_NW(2, true); else SPRINTER_DEC_NW(2, false); }
 #undef SPRINTER_DEC_NW
