@@ -461,10 +461,8 @@ static void launch_gemm_f32(const GemmArgs& a, int max_rows, int shares, hipStre
 template <int EPI>
 static void launch_gemm_bf16(const GemmArgs& a, int max_rows, hipStream_t s) {
   // Up to 16 rows: one 16-column tile per workgroup (two per wave for wide outputs), K split over its 8 waves.
-  // (Measured and dropped for that case: folding the layer norm into this kernel at 16 rows - every workgroup
-  // then normalises the whole activation matrix again, 13.6 us against 5.3 + 5.0 us for norm + GEMM at
-  // d = 1600; up to 4 rows it pays: k_gemm_norm.hip - and splitting K over workgroups with a last-arriver reduction - its two device-scope fences
-  // cost more than the 4 us they save; and a variant that requests all of a wave's weight and activation
+  // (Fewer rows of narrower models have the norm inside: k_gemm_norm.hip.  Measured and dropped: splitting K over workgroups with a last-arriver reduction - its two device-scope fences
+  // cost more than the 4 us they save; a variant that requests all of a wave's weight and activation
   // tiles up front (K <= 2048) - no faster.)
   // wide outputs with a short K: two column tiles per wave share the activation fragments (at K = 4096 one tile per
   // workgroup is faster: QKV 12288x4096 26 against 32 us, FFN-up 2x11008x4096 40 against 48 us)

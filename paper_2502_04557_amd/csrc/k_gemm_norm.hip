@@ -32,11 +32,11 @@ static __host__ __device__ inline int resid_split(bool bf16, int N, int rows) { 
 // up to four partial products, took the statistics in two passes through LDS and four barriers that waited for all weights in flight: 0.5 us a row
 // of 1600 columns, paid after the weights had arrived.)  The code is straight: buffers whose bounds make loads beyond them zeros instead of
 // branches, so that every wait counts the loads behind the one it is for; a barrier waits for LDS only.
-// A layer in a chain (graph over all layers, cold weights), us, before -> now: 1600 columns (25 heads, 6400), 1 row 28.0 -> 26.1, 4 rows 34.3 -> 28.5,
-// 8 rows (seven launches before) 34.2 -> 30.6; 768 (3072), 1 row 18.4 -> 16.3, 8 rows (seven) 24.5 -> 19.4, 16 rows (seven) 25.6 -> 23.4; 2048 (gate + up
-// 8192), 1 row 39.0 -> 35.4, 4 rows 42.3 -> 36.5, 8 rows (seven) 43.6 -> 38.6; 4096 (11008; seven), 2 rows 91.4 -> 83.2, 4 rows 96.5 -> 85.3; 512 (1344),
-// 4 rows 20.0 -> 17.4, 16 rows 21.6 -> 20.0; float32, 512 (2048), 1 row 22.1 -> 19.5, 8 rows 24.7 -> 22.4.
-// What bounds it: the weights at 4 - 5 TB/s and, of about 5.5 us at 15 MB, the start of a dependent launch, 1.6 us.
+// A layer in a chain (graph over all layers, cold weights), us, before -> with these two kernels -> and their arguments preloaded: 1600 columns (25 heads, 6400), 1 row
+// 28.0 -> 25.8 -> 24.6, 4 rows 34.3 -> 28.3 -> 27.0, 8 rows (seven launches before) 34.2 -> 30.6 -> 29.4; 768 (3072), 1 row 18.4 -> 16.3 -> 15.3, 16 rows (seven) 25.6 ->
+// 23.0 -> 22.4; 2048 (gate + up 8192), 1 row 39.0 -> 35.3 -> 34.0, 4 rows 42.3 -> 36.5 -> 36.0; 4096 (11008; seven), 3 rows 95.3 -> 84.3 -> 82.1; 4096 (14336; seven), 1 row 97.2 ->
+// 87.5 -> 85.6; 512 (1344), 4 rows 20.0 -> 17.4, 16 rows 21.6 -> 20.0; float32, 512 (2048), 1 row 22.1 -> 19.3 -> 18.3, 8 rows 24.7 -> 22.8 -> 22.0.
+// What bounds it: the weights at 4 - 5 TB/s and, of 5.4 us at 15 MB, the start of a dependent launch, 1.6 us.
 // R = RT RG rows: RG groups of 512 / RG threads, a thread takes 8 columns of RT rows.  U: units of K in flight per wave.
 struct RowSource { EmbedSource emb; float* h_out; };    // EMB: the rows are embeddings; workgroup 0 starts the residual stream with them
 // second: the norm's offset b, or W2.  d / 16 * resid_split groups of statistics.
@@ -255,7 +255,7 @@ __device__ __forceinline__ float columns_sum(float v) {   // over C = 4, 8 or 16
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));           // quad_perm [1,0,3,2]
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));     // quad_perm [2,3,0,1]
 }
-// O-projection and FFN-down of at most 16 rows, of at most 32 from 2049 columns on: h += bias + X W^T in place, and the statistics of what was written.  A workgroup has all of K for its columns, so
+// O-projection and FFN-down of at most 16 rows, some of at most 32 (gemm_adds_rows): h += bias + X W^T in place, and the statistics of what was written.  A workgroup has all of K for its columns, so
 // that it can finish them, and 16 / S columns instead of 16 where that takes to fill the chip (N <= 2048): a weight load then carries S k
 // tiles of the columns - 128 bytes of each for S = 2, a line -, as many bytes per workgroup as K in S shares.  What that costs is the activations of
 // all of K in every workgroup, and the address unit takes 16 cycles per load whatever it brings: so where an operand's 16 rows are not all there, a load
@@ -286,7 +286,8 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
       const int t = g * T + i * P;
-      xv[u][i][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, (BF || (t + xp) * KU + lq * 4 < K ? x_lane : NOWHERE) + t * TB, 0, 0);
+      // (beyond K zeros on both sides; with several operands the buffer goes on there: other rows, whose infinities must not meet a zero weight)
+      xv[u][i][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, ((BF ? MT == 1 || t < kt : (t + xp) * KU + lq * 4 < K) ? x_lane : NOWHERE) + t * TB, 0, 0);
 #pragma unroll
       for (int j = 1; j < MT; ++j)                      // (the next 16 rows are an operand tile row further)
         xv[u][i][j] = __builtin_amdgcn_raw_buffer_load_b128(rx, t < kt && 16 * j + l16 < rows ? (j * kt + t) * 1024 + lane * 16 : NOWHERE, 0, 0);

@@ -3,7 +3,7 @@ that normalises those rows with the statistics the first one left."""
 import ctypes as C
 import numpy as np
 import pytest
-from test_gpu_products import BF16, F32, _lib, _operand, _ptr
+from test_gpu_products import BF16, F32, _lib, _operand, _ptr, _rows
 
 pytestmark = pytest.mark.gpu
 EPS = 1e-5
@@ -44,12 +44,12 @@ def test_residual_rows_and_their_norm(dtype, d, K, rows, more, arch):
     # residual rows as deep models have them: a mean, a few columns far out, rows of different sizes
     h = (rnd(rows, d) * 3 + 2) * (1 + torch.arange(rows, device="cuda")[:, None])
     h[:, 5::61] += 150
-    X = store(x)                                              # (operand tiles: the rows of a tile that do not exist must have no effect)
+    Wd, X = store(W), store(x)                                              # (operand tiles: the rows of a tile that do not exist must have no effect)
     if dtype == BF16:
         X.view(-1, X.shape[1], 4, 16, 8)[:, :, :, rows:] = float("nan")
     hg, stat = h.clone(), torch.full((32 * d // 4,), float("nan"), device="cuda")
     _lib()["_ZN8sprinter17launch_gemm_residEiiPKvS1_iiPKfPfS4_iP12ihipStream_t"](
-        dtype, arch, _ptr(store(W)), _ptr(X), d, K, _ptr(bias), _ptr(hg), _ptr(stat), rows, stream)
+        dtype, arch, _ptr(Wd), _ptr(X), d, K, _ptr(bias), _ptr(hg), _ptr(stat), rows, stream)
     torch.cuda.synchronize()
     want = h.double() + x.double() @ W.double().T + (0 if bias is None else bias.double())
     # sums in float32: 32 products of an instruction, a wave's k tiles, 8 waves of at most 4 parts, residual and bias
@@ -64,10 +64,10 @@ def test_residual_rows_and_their_norm(dtype, d, K, rows, more, arch):
     V = torch.cat([torch.eye(d, device="cuda"), rnd(more, d)])
     if dtype == BF16:
         V = V.half().float()
-    N = d + more
+    N, Vd = d + more, store(V)
     y = torch.full((rows, N), float("nan"), device="cuda")
     _lib()["_ZN8sprinter16launch_norm_gemmEiiiPKfS1_S1_S1_fPKNS_11EmbedSourceEPfPKvS7_iiS1_PviP12ihipStream_t"](
-        dtype, arch, 0, _ptr(hg), _ptr(stat), _ptr(gain), _ptr(off), C.c_float(EPS), _ptr(None), _ptr(None), _ptr(store(V)), _ptr(None), N, d, _ptr(None),
+        dtype, arch, 0, _ptr(hg), _ptr(stat), _ptr(gain), _ptr(off), C.c_float(EPS), _ptr(None), _ptr(None), _ptr(Vd), _ptr(None), N, d, _ptr(None),
         _ptr(y), rows, stream)
     torch.cuda.synchronize()
     h64 = hg.double()
@@ -88,3 +88,53 @@ def test_residual_rows_and_their_norm(dtype, d, K, rows, more, arch):
     off_by = (scaled * (rstd * torch.sqrt(drop.sum(1, keepdim=True) / d + EPS)).reciprocal() - scaled).abs()
     if d <= 1024 or dtype == F32:
         assert (off_by > unit).any()
+
+
+@pytest.mark.parametrize("d,K,rows", [(4096, 96, 24), (1088, 96, 24), (576, 72, 18)])
+def test_rows_stay_apart(d, K, rows):
+    """A row of infinities (activations beyond float16) has no effect on other rows, whichever operand it lies in, at an odd number of k tiles and fewer than the loads in flight."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x, W, h = (torch.randn(*s, device="cuda", generator=g).half().float() for s in ((rows, K), (d, K), (rows, d)))
+    assert _lib()["_ZN8sprinter14gemm_adds_rowsEiiii"](BF16, d, K, rows) & 0xFF
+    out, Wd = [], _operand(W)
+    for bad in (None, 2, 16):
+        xb, hg = x.clone(), h.clone()
+        if bad is not None:
+            xb[bad] = float("inf")
+        Xd = _operand(xb)
+        _lib()["_ZN8sprinter17launch_gemm_residEiiPKvS1_iiPKfPfS4_iP12ihipStream_t"](
+            BF16, 0, _ptr(Wd), _ptr(Xd), d, K, _ptr(None), _ptr(hg), _ptr(None), rows, C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        out.append(hg)
+        if bad is not None:
+            assert not hg[bad].isfinite().any()
+            keep = torch.arange(rows, device="cuda") != bad
+            assert torch.equal(hg[keep], out[0][keep])
+
+
+# gate + up with the norm inside: one and two column tiles per wave, the largest LDS of each
+@pytest.mark.parametrize("d,N,rows", [(512, 1344, 16), (1024, 2816, 9), (2048, 4104, 8), (2048, 1000, 3), (4096, 520, 4)])
+def test_gate_and_up(d, N, rows):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(d + N)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    stream = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    h, gain, stat = rnd(rows, d) * 2, 1 + 0.1 * rnd(d), torch.zeros(8 * d, device="cuda")
+    W, W2 = ((rnd(N, d) * d ** -0.5).half().float() for _ in range(2))
+    Wd, W2d, Vd, none = _operand(W), _operand(W2), _operand(rnd(d, 64)), _operand(torch.zeros(rows, 64, device="cuda"))
+    _lib()["_ZN8sprinter17launch_gemm_residEiiPKvS1_iiPKfPfS4_iP12ihipStream_t"](
+        BF16, 1, _ptr(Vd), _ptr(none), d, 64, _ptr(None), _ptr(h), _ptr(stat), rows, stream)
+    out = _operand(torch.zeros(rows, N, device="cuda"))
+    _lib()["_ZN8sprinter16launch_norm_gemmEiiiPKfS1_S1_S1_fPKNS_11EmbedSourceEPfPKvS7_iiS1_PviP12ihipStream_t"](
+        BF16, 1, 3, _ptr(h), _ptr(stat), _ptr(gain), _ptr(None), C.c_float(EPS), _ptr(None), _ptr(None), _ptr(Wd), _ptr(W2d), N, d, _ptr(None),
+        _ptr(out), rows, stream)
+    torch.cuda.synchronize()
+    xn = h.double() * gain.double() / torch.sqrt((h.double() ** 2).mean(1, keepdim=True) + EPS)
+    a, b = xn @ W.double().T, xn @ W2.double().T
+    want, got = a / (1 + torch.exp(-a)) * b, _rows(out, rows, N).double()
+    # every input of the sums is rounded by at most 2^-11, 2^-11 / sqrt(3) in the mean square, independently: so are the sums, relative to their spread of about 1; the
+    # result moves by the factors' errors times at most 1.1 and 2.8 (SiLU's slope, and its values), then is rounded itself
+    assert ((got - want).norm() / want.norm()).item() <= 2.0 ** -10
+    spread = 2.0 ** -11 * 6 * (1.1 * b.abs() + a.abs() + 0.3)
+    assert ((got - want).abs() <= spread + 2.0 ** -11 * want.abs() + 2.0 ** -25).all()
