@@ -23,8 +23,8 @@ namespace sprinter {
 // prefill; then the epilogue, whose stores (float32) or activations no other wave hides.  In a loop of one launch, eight waves -> four, us:
 // FFN-up 2 x 14336 x 4096 746 -> 722, 2 x 11008 x 4096 603 -> 563, 2 x 8192 x 2048 227 -> 229, QKV 12288 x 4096 337 -> 311,
 // O-proj 4096 x 4096 113 -> 111, FFN-down 4096 x 14336 373 -> 347 (1.39 PFLOP/s).
-// GELU stays on eight waves: tanhf takes both of its branches for every element, which one wave per SIMD cannot hide (2032 x 6400 x 1600
-// 54 -> 66 us, 3528 x 3072 x 768 33 -> 44).
+// GELU stays on eight waves: one wave per SIMD does not hide its arithmetic (6400 x 1600 at 1811 / 2500 / 4096 rows 55.6 / 60.6 / 106.0 us;
+// four waves, the epilogue through LDS as for gate + up, 60.0 / 64.7 / 114.7).
 // Also measured: 32 x 32 x 16 instructions (8 - 20 % slower), a fifth stage (no faster), two fragment reads per row tile instead of
 // three and a later first one (equal), 256 x 128 tiles of four waves (10 - 20 % slower but where the last round is half empty).
 template <int WM, int WN, int MT, int NT, int S>
