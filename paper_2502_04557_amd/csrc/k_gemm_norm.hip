@@ -2,6 +2,7 @@
 // themselves to the residual rows and leave the statistics of what they wrote (k_gemm_resid); QKV projection and FFN-up normalise
 // those rows for themselves (k_norm_gemm).
 #include "gemm.h"
+#include "offsets.h"
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -14,7 +15,6 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 // A buffer of n bytes: loads beyond it give zeros and fetch nothing.
 __device__ __forceinline__ auto bytes_at(const void* p, int n) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, n, 0x00020000); }
-constexpr int NOWHERE = 0x7ffffff0;      // an offset beyond any buffer (and what is added to it stays below 2^32)
 __device__ __forceinline__ float last_lane(float v) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), 63)); }
 
 // Statistics of the residual rows: for every row and every `cols` consecutive columns {sum, sum of squared distances from their mean}
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(512) void k_norm_gemm(const float* h, const float* 
   load_row(g + c8, gg);
   if (ARCH == 0) load_row((const float*)second + c8, bb);
   __builtin_amdgcn_sched_barrier(0);
-  const int w_lane = BF ? lane * 16 : (l16 * d + lq * 4) * 4;
+  const unsigned w_lane = BF ? lane * 16 : (l16 * d + lq * 4) * 4;
   auto tile = [&](int j) {
     const int nt = nt0 + j % NTW;
     const char* m = (const char*)(DUAL && j >= NTW ? second : W);
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(512) void k_norm_gemm(const float* h, const float* 
   u32x4 wv[U][NW];
   auto load_unit = [&](int u, int unit) {
 #pragma unroll
-    for (int j = 0; j < NW; ++j) wv[u][j] = __builtin_amdgcn_raw_buffer_load_b128(tile(j), (BF || unit < units ? w_lane : NOWHERE) + unit * (BF ? 1024 : 64), 0, 0);
+    for (int j = 0; j < NW; ++j) wv[u][j] = __builtin_amdgcn_raw_buffer_load_b128(tile(j), unit_offset(BF || unit < units, w_lane, unit, BF ? 1024 : 64), 0, 0);
   };
 #pragma unroll
   for (int u = 0; u < U; ++u) load_unit(u, w + 8 * u);
@@ -278,8 +278,8 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
   const int ws = l16 / C, wc = l16 % C, xp = l16 / RP, xr = l16 % RP;
   const auto rw = BF ? bytes_at((const char*)W + (size_t)(n0 >> 4) * kt * 1024, kt * 1024) : bytes_at((const char*)W + (size_t)n0 * K * 4, C * K * 4);
   const auto rx = BF ? bytes_at(X, MT * kt * 1024) : bytes_at(X, rows * K * 4);
-  const int w_lane = BF ? ws * 1024 + (lq * 16 + (n0 & 15) + wc) * 16 : wc * K * 4 + (ws * 16 + lq * 4) * 4;
-  const int x_lane = xr < rows ? (BF ? xp * 1024 + (lq * 16 + xr) * 16 : xr * K * 4 + (xp * 16 + lq * 4) * 4) : NOWHERE;
+  const unsigned w_lane = BF ? ws * 1024 + (lq * 16 + (n0 & 15) + wc) * 16 : wc * K * 4 + (ws * 16 + lq * 4) * 4;
+  const unsigned x_lane = xr < rows ? (BF ? xp * 1024 + (lq * 16 + xr) * 16 : xr * K * 4 + (xp * 16 + lq * 4) * 4) : NOWHERE;
   constexpr int TB = BF ? 1024 : 64;                    // bytes from one k tile to the next
   u32x4 wv[UG][NWL], xv[UG][NX][MT];
   auto load_group = [&](int u, int g) {
@@ -287,15 +287,15 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
     for (int i = 0; i < NX; ++i) {
       const int t = g * T + i * P;
       // (beyond K zeros on both sides; with several operands the buffer goes on there: other rows, whose infinities must not meet a zero weight)
-      xv[u][i][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, ((BF ? MT == 1 || t < kt : (t + xp) * KU + lq * 4 < K) ? x_lane : NOWHERE) + t * TB, 0, 0);
+      xv[u][i][0] = __builtin_amdgcn_raw_buffer_load_b128(rx, unit_offset(BF ? MT == 1 || t < kt : (t + xp) * KU + lq * 4 < K, x_lane, t, TB), 0, 0);
 #pragma unroll
       for (int j = 1; j < MT; ++j)                      // (the next 16 rows are an operand tile row further)
-        xv[u][i][j] = __builtin_amdgcn_raw_buffer_load_b128(rx, t < kt && 16 * j + l16 < rows ? (j * kt + t) * 1024 + lane * 16 : NOWHERE, 0, 0);
+        xv[u][i][j] = __builtin_amdgcn_raw_buffer_load_b128(rx, unit_offset(t < kt && 16 * j + l16 < rows, lane * 16, j * kt + t, 1024), 0, 0);
     }
 #pragma unroll
     for (int i = 0; i < NWL; ++i) {
       const int t = g * T + i * S;
-      wv[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (BF || (t + ws) * KU + lq * 4 < K ? w_lane : NOWHERE) + t * TB, 0, 0);
+      wv[u][i] = __builtin_amdgcn_raw_buffer_load_b128(rw, unit_offset(BF || (t + ws) * KU + lq * 4 < K, w_lane, t, TB), 0, 0);
     }
   };
 #pragma unroll
