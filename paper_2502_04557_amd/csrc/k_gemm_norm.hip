@@ -23,7 +23,8 @@ __device__ __forceinline__ float last_lane(float v) { return __uint_as_float(__b
 // which loses nothing against two passes.
 
 // Column groups of the statistics: 16 / split columns each, at most 256 groups where a product reads them.  float32 rows hold their k side by side, so four columns
-// fill lines too: 512 x 2048, 1 row 5.0 -> 4.0 us, 8 rows 6.0 -> 5.4 but the norms behind it lose that again.
+// fill lines too: 512 x 2048, 1 row 5.0 -> 4.0 us, 8 rows 6.0 -> 5.4 but the norms behind it lose that again.  From 2049 columns on 16 stay ahead, also
+// where nobody reads the statistics: us per layer with 16 / 8 columns per workgroup, 2112 columns, 8 / 16 / 32 rows 47.3 / 52.6 / 65.8, 49.5 / 58.4 / 73.1; 3072 69.2 / 78.7 / 92.3, 72.9 / 84.6 / 103.6.
 static __host__ __device__ inline int resid_split(bool bf16, int N, int rows) { return N > 2048 ? 1 : !bf16 && N <= 1024 && rows <= 4 ? 4 : 2; }
 
 // A chain of short dependent launches is what a pass of few rows is, and the norm as a launch of its own two of a layer's seven: 3 - 4 us for a few KiB of
@@ -255,7 +256,7 @@ __device__ __forceinline__ float columns_sum(float v) {   // over C = 4, 8 or 16
   v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));           // quad_perm [1,0,3,2]
   return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));     // quad_perm [2,3,0,1]
 }
-// O-projection and FFN-down of at most 16 rows, some of at most 32 (gemm_adds_rows): h += bias + X W^T in place, and the statistics of what was written.  A workgroup has all of K for its columns, so
+// O-projection and FFN-down of at most 16 rows, some of at most 32 (gemm_takes_norm, gemm_adds_rows): h += bias + X W^T in place, and the statistics of what was written.  A workgroup has all of K for its columns, so
 // that it can finish them, and 16 / S columns instead of 16 where that takes to fill the chip (N <= 2048): a weight load then carries S k
 // tiles of the columns - 128 bytes of each for S = 2, a line -, as many bytes per workgroup as K in S shares.  What that costs is the activations of
 // all of K in every workgroup, and the address unit takes 16 cycles per load whatever it brings: so where an operand's 16 rows are not all there, a load
@@ -389,12 +390,24 @@ bool gemm_takes_norm(int dtype, int d, int rows) {
   if (dtype == 0) return rows <= (d <= 512 ? 16 : d <= 1024 ? 8 : d <= 2048 ? 4 : 0);
   return rows <= (d <= 1024 ? 16 : d <= 2048 ? 8 : d <= 4096 ? 4 : 0);
 }
-// Whether a product of K adds itself to the residual rows although the norm behind it is a launch: at most 32 rows from 2049 columns on, where the columns alone fill
-// the chip, and 17 - 32 rows of a short K, whose activations (all of K in every workgroup) cost less than four and more partial products do in the norm.  us per layer, partial
-// products / so: 4096 (11008), 8 rows 98.6 / 92.9, 16 rows 110.6 / 104.6, 17 rows 122.7 / 113.5, 32 rows 134.0 / 127.9; 4096 (14336, 8 KV heads), 5 rows 104.2 / 100.0, 16 rows
-// 109.6 / 103.3, 24 rows 118.7 / 112.0, 32 rows 122.6 / 119.8.  O-projection of 1600 columns with its norm, 17 / 32 rows 10.3 / 10.0 us against 7.3 / 7.7, 40 rows 9.7 / 9.4; of 768, 24
-// rows 8.7 / 6.9; but FFN-down (6400) at 24 rows 12.6 / 13.1, both at 8 - 16 rows equal, and 256 columns 6.3 / 6.2.
-bool gemm_adds_rows(int dtype, int d, int K, int rows) { return dtype != 0 && rows <= 32 && (d > 2048 || (d > 512 && rows > 16 && K <= 2048)); }
+// Whether a product of K adds itself to the residual rows although the norm behind it is a launch.  Its workgroups have all of K, and one of them fills a compute unit: what decides
+// is how many of those the last round of 16 columns per workgroup leaves idle, where K in shares would fill them, and how much K there is.  us per layer of a target pass of 4 to 16
+// layers, K in shares / added (O-projection and FFN-down changed one at a time; two runs of one side differ by 0.3 %):
+// - O-projection (K = d).  2112 columns, 8 / 16 / 32 rows 45.8 / 50.0 / 62.3 -> 45.2 / 49.1 / 61.2; 3072, 8 / 32 rows 73.0 / 88.7 -> 72.0 / 89.0; 4096, 17 rows 118.7 -> 117.7; 5120,
+//   4 / 16 / 24 rows 147.0 / 174.9 / 174.7 -> 144.9 / 173.7 / 178.4; 6144, 4 / 8 / 16 rows 197.8 / 206.1 / 227.4 -> 197.6 / 207.3 / 227.3; 8192, 8 / 16 / 24 rows 332.6 / 357.7 / 368.6 ->
+//   330.5 / 357.2 / 370.0.  17 - 32 rows of at most 2048 columns: 576 - 2048 columns 2 - 6 % ahead (1600, 17 / 32 rows 46.7 / 50.3 -> 44.8 / 48.8).
+// - FFN-down (K = 2.7 d - 4 d).  Up to 8 rows where the last round is 7/8 full: 2112, 8 rows 45.2 -> 46.6; 2560 57.7 -> 59.4; 3072 72.0 -> 71.9; 3584 86.4 -> 85.9; 3840 93.5 -> 92.0; 4096
+//   (14336) 117.4 -> 116.4; 5120, 4 / 8 rows 144.9 / 154.6 -> 149.2 / 157.4; 6144 207.3 -> 212.4; 8192 330.5 -> 326.9.  Beyond, only in one round that is full: 12 / 24 rows of 3584
+//   95.2 / 100.3 -> 96.8 / 102.4; 3840 102.1 / 107.8 -> 103.0 / 109.8; 4096 109.5 / 120.1 -> 109.4 / 118.2 (28 - 32 rows 1 % behind); 8192 347.1 / 370.0 -> 349.9 / 376.5; 5120, 24 rows 178.4 -> 194.6.
+// - K of at most 2048: 17 - 32 rows, FFN-down of 768 (2048), 24 rows 32.4 -> 32.0, of 640 (1728) 30.4 -> 29.8; 1600 columns, 6400 of K 12.6 -> 13.1; 256 columns 6.2 -> 6.3.
+bool gemm_adds_rows(int dtype, int d, int K, int rows) {
+  if (dtype == 0 || d <= 512 || rows > 32) return false;
+  if (K <= 2048) return d > 2048 || rows > 16;
+  if (d <= 2048) return false;
+  if (2 * K <= 3 * d) return rows <= (d <= 4096 ? 32 : d <= 5120 ? 16 : 8);
+  const int wgs = d / 16, idle = -wgs & 255;
+  return rows <= (wgs <= 256 && idle <= 4 ? 32 : 8 * idle <= wgs + idle ? 8 : 0);
+}
 
 struct NormGemmArgs { const float *h, *stat, *g; const void *second, *W; const float* bias; void* out; int d, N, n_tiles, rows; float eps; RowSource from; };
 

@@ -138,3 +138,29 @@ def test_gate_and_up(d, N, rows):
     assert ((got - want).norm() / want.norm()).item() <= 2.0 ** -10
     spread = 2.0 ** -11 * 6 * (1.1 * b.abs() + a.abs() + 0.3)
     assert ((got - want).abs() <= spread + 2.0 ** -11 * want.abs() + 2.0 ** -25).all()
+
+
+# widths and row counts at which the rule leaves the product in shares: one to eight of them, two column tiles per wave, tiles of 32 rows; workgroups for half the compute units and more than all
+@pytest.mark.parametrize("d,K,rows", [(2112, 8448, 5), (2112, 3200, 16), (2112, 8448, 17), (3072, 5000, 32), (4352, 4352, 24), (5120, 5120, 32), (5120, 9000, 4), (6144, 6144, 16)])
+def test_products_left_in_shares(d, K, rows):
+    import torch
+    assert not _lib()["_ZN8sprinter14gemm_adds_rowsEiiii"](BF16, d, K, rows) & 0xFF
+    g = torch.Generator(device="cuda").manual_seed(d + rows)
+    x, W = (torch.randn(*s, device="cuda", generator=g).half().float() for s in ((rows, K), (d, K)))
+    h, bias = torch.randn(rows, d, device="cuda", generator=g), torch.randn(d, device="cuda", generator=g)
+    X, Wd = torch.zeros(64, K, device="cuda"), _operand(W)                     # (activation buffers hold 64 rows)
+    X[:rows] = x
+    X, part, out = _operand(X), torch.full((8, rows, d), float("nan"), device="cuda"), h.clone()
+    n = torch.tensor([rows], dtype=torch.int32, device="cuda")
+    shares = _lib()["_ZN8sprinter16launch_gemm_partEiPKvS1_mPKiiiPfmiPKfS4_iP12ihipStream_t"](
+        BF16, _ptr(Wd), _ptr(X), C.c_size_t(X.numel()), _ptr(n), d, K, _ptr(part), C.c_size_t(rows * d), 8, _ptr(bias), _ptr(out), rows,
+        C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert 0 <= shares <= 8
+    got = out.double() if shares == 0 else h.double() + bias.double() + part[:shares].double().sum(0)
+    want = h.double() + bias.double() + x.double() @ W.double().T
+    bound = 2.0 ** -24 * ((K + 2) * (x.double().abs() @ W.double().abs().T) + 2 * (h.double().abs() + bias.double().abs()))   # any order of the sum
+    print(d, K, rows, "shares", shares, "worst share of the bound", float(((got - want).abs() / bound).max()), flush=True)
+    assert ((got - want).abs() <= bound).all()
+    # the bound tells a missing k tile
+    assert ((x[:, 32:64].double() @ W[:, 32:64].double().T).abs() > bound).double().mean() > 0.5
