@@ -109,6 +109,7 @@ struct sprinter_ctx {
   int B = 0, max_prompt_len = 0;
   long long steps_done = 0;
   bool prefilled = false;
+  const char* no_kernel = nullptr;             // a launch that a forward needed and no kernel was compiled for
   char err[512];
 };
 
@@ -395,7 +396,10 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   const bool append_in_qkv = shared_caches && run_len == 0 && dt == SPRINTER_BF16 && md.arch == SPRINTER_ARCH_GPT;
   NormPending pend{sc.part, part_stride, 0, nullptr};
   auto resid_gemm = [&](const void* W, const void* X, size_t plane, int K, const float* bias) {
-    if (fused || gemm_adds_rows(dt, md.d, K, max_rows)) { launch_gemm_resid(dt, md.arch, W, X, md.d, K, bias, sc.h, fused ? sc.part : nullptr, max_rows, s); return; }
+    if (fused || gemm_adds_rows(dt, md.d, K, max_rows)) {
+      if (!launch_gemm_resid(dt, md.arch, W, X, md.d, K, bias, sc.h, fused ? sc.part : nullptr, max_rows, s)) ctx->no_kernel = "a product that adds itself";
+      return;
+    }
     pend.shares = launch_gemm_part(dt, W, X, plane, rd.n_rows, md.d, K, sc.part, part_stride, PART_SHARES, bias, sc.h, max_rows, s);
     pend.bias = bias;
   };
@@ -596,6 +600,10 @@ int enqueue_step(sprinter_ctx* ctx, const sprinter_step_out* out, int n_tokens, 
 }
 
 int hip_status(sprinter_ctx* ctx, const char* what) {
+  if (const char* missing = ctx->no_kernel) {
+    ctx->no_kernel = nullptr;
+    return fail(ctx, SPRINTER_E_CONFIG, "%s: no kernel for %s", what, missing);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(ctx, SPRINTER_E_HIP, "%s: %s", what, hipGetErrorString(e));
   return SPRINTER_OK;

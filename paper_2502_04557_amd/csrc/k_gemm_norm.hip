@@ -273,6 +273,7 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
   constexpr int NA = P >= S ? P / S : S;                // accumulators: which of their elements are sums of matching k is below
   constexpr int D = NA < 4 ? 4 / NA : 1;                // each D times, for groups in turn
   static_assert(MT == 1 || (BF && RP == 16), "");
+  static_assert(P >= S || P == 1, "an accumulator for every tile s of a column, as they are matched below");
   __shared__ float red[8 * MT * 4 * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = wave_index(), l16 = lane & 15, lq = lane >> 4;
   const int kt = (K + KU - 1) / KU, groups = (kt + T - 1) / T, n0 = blockIdx.x * C;
@@ -467,26 +468,40 @@ void launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float*
 }
 
 struct ResidArgs { const void *W, *X; float *h, *stat; const float* bias; int N, K, rows; };
-template <typename AT, int ARCH, int S>
-static void launch_gemm_resid_split(const ResidArgs& a, hipStream_t s) {
-  const int ku = sizeof(AT) == 2 ? 32 : 16, kt = (a.K + ku - 1) / ku, rp = a.rows <= 4 ? 4 : a.rows <= 8 ? 8 : 16;
-  const int T = std::max(16 / rp, S), per_wave = ((kt + T - 1) / T + 7) / 8, nwl = T / S;
-  if constexpr (sizeof(AT) == 2 && S <= 2)
-    if (a.rows > 16) { hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, 16, S == 1 ? 8 : 4, 2>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N); return; }
-#define SPRINTER_RES(RP, UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG, 1>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N)
-// (up to 8 weight loads of 16 bytes per lane in flight; 16 where two of them make a group)
-#define SPRINTER_RES_U(RP) do { if (per_wave <= 2 || nwl == 4) SPRINTER_RES(RP, 2); else if (per_wave <= 4) SPRINTER_RES(RP, 4); else SPRINTER_RES(RP, 8); } while (0)
-  if (rp == 4) SPRINTER_RES_U(4); else if (rp == 8) SPRINTER_RES_U(8); else SPRINTER_RES_U(16);
-#undef SPRINTER_RES_U
+template <typename AT, int ARCH, int S, int RP>
+static void launch_gemm_resid_rows(const ResidArgs& a, hipStream_t s) {
+  constexpr int T = 16 / RP > S ? 16 / RP : S, KU = sizeof(AT) == 2 ? 32 : 16;
+#define SPRINTER_RES(UG) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S, RP, UG, 1>), dim3(a.N * S / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N)
+  // (up to 8 weight loads of 16 bytes per lane in flight; 16 where two of them make a group)
+  if constexpr (T / S == 4) SPRINTER_RES(2);
+  else {
+    const int per_wave = ((a.K + KU - 1) / KU + 8 * T - 1) / (8 * T);
+    if (per_wave <= 2) SPRINTER_RES(2); else if (per_wave <= 4) SPRINTER_RES(4); else SPRINTER_RES(8);
+  }
 #undef SPRINTER_RES
 }
-void launch_gemm_resid(int dtype, int arch, const void* W, const void* X, int N, int K, const float* bias, float* h, float* stat, int rows, hipStream_t s) {
-  const int S = resid_split(dtype != 0, N, rows);
-  const ResidArgs a{W, X, h, stat, bias, N, K, rows};
-#define SPRINTER_RES(AT, ARCH) do { if (sizeof(AT) == 4 && S == 4) launch_gemm_resid_split<AT, ARCH, sizeof(AT) == 4 ? 4 : 2>(a, s); else if (S == 2) launch_gemm_resid_split<AT, ARCH, 2>(a, s); else launch_gemm_resid_split<AT, ARCH, 1>(a, s); } while (0)
-  if (dtype == 0) { if (arch == 0) SPRINTER_RES(float, 0); else SPRINTER_RES(float, 1); }
-  else { if (arch == 0) SPRINTER_RES(bf16_t, 0); else SPRINTER_RES(bf16_t, 1); }
+template <typename AT, int ARCH, int S>
+static bool launch_gemm_resid_split(const ResidArgs& a, hipStream_t s) {
+  if (a.rows <= 4) launch_gemm_resid_rows<AT, ARCH, S, 4>(a, s);
+  else if (S == 4 || a.rows > 16) return false;
+  else if constexpr (S <= 2) { if (a.rows <= 8) launch_gemm_resid_rows<AT, ARCH, S, 8>(a, s); else launch_gemm_resid_rows<AT, ARCH, S, 16>(a, s); }
+  return true;
+}
+template <typename AT, int ARCH>
+static bool launch_gemm_resid_arch(const ResidArgs& a, hipStream_t s) {
+  const int S = resid_split(sizeof(AT) == 2, a.N, a.rows);
+  if constexpr (sizeof(AT) == 2) {
+#define SPRINTER_RES(S_) hipLaunchKernelGGL((k_gemm_resid<AT, ARCH, S_, 16, S_ == 1 ? 8 : 4, 2>), dim3(a.N * S_ / 16), dim3(512), 0, s, a.W, a.X, a.K, a.rows, a.h, a.bias, a.stat, a.N)
+    if (a.rows > 16 && a.rows <= 32) { if (S == 1) SPRINTER_RES(1); else SPRINTER_RES(2); return true; }
 #undef SPRINTER_RES
+    return S == 1 ? launch_gemm_resid_split<AT, ARCH, 1>(a, s) : launch_gemm_resid_split<AT, ARCH, 2>(a, s);
+  }
+  else return S == 4 ? launch_gemm_resid_split<AT, ARCH, 4>(a, s) : S == 2 && launch_gemm_resid_split<AT, ARCH, 2>(a, s);
+}
+bool launch_gemm_resid(int dtype, int arch, const void* W, const void* X, int N, int K, const float* bias, float* h, float* stat, int rows, hipStream_t s) {
+  const ResidArgs a{W, X, h, stat, bias, N, K, rows};
+  if (dtype == 0) return arch == 0 ? launch_gemm_resid_arch<float, 0>(a, s) : launch_gemm_resid_arch<float, 1>(a, s);
+  return arch == 0 ? launch_gemm_resid_arch<bf16_t, 0>(a, s) : launch_gemm_resid_arch<bf16_t, 1>(a, s);
 }
 
 }  // namespace sprinter

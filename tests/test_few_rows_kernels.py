@@ -1,0 +1,53 @@
+"""The compiled kernels of a pass of few rows are those that a rule can reach, and what has no kernel is refused, on the CPU."""
+import ctypes as C
+import re
+import subprocess
+import pytest
+from test_abi_cpu import lib  # noqa: F401
+
+F32, BF16 = 0, 1
+RESID, NORM_GEMM = "_ZN8sprinter17launch_gemm_residEiiPKvS1_iiPKfPfS4_iP12ihipStream_t", "_ZN8sprinter16launch_norm_gemmEiiiPKfS1_S1_S1_fPKNS_11EmbedSourceEPfPKvS7_iiS1_PviP12ihipStream_t"
+WIDTHS = range(64, 8193, 64)
+
+
+def _compiled(lib, kernel):
+    from paper_2502_04557_amd import binding
+    names = subprocess.run(["nm", "-C", binding.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    return {tuple(t.strip() for t in m.split(",")) for m in re.findall(r"sprinter::" + kernel + r"<([^<>]*)>\(", names)}
+
+
+def _takes_norm(lib, dtype, d, rows):
+    return bool(lib["_ZN8sprinter15gemm_takes_normEiii"](dtype, d, rows) & 0xFF)
+
+
+def _resid_kernel(dtype, N, K, rows):
+    """(type, S, RP, UG, MT): columns per workgroup 16 / S, rows per activation load, groups of k tiles in flight, operands of 16 rows."""
+    S = 1 if N > 2048 else 4 if dtype == F32 and N <= 1024 and rows <= 4 else 2
+    if rows > 16:
+        return "unsigned short", S, 16, 8 if S == 1 else 4, 2
+    RP = 4 if rows <= 4 else 8 if rows <= 8 else 16
+    T = max(16 // RP, S)
+    waves = -(-K // (32 if dtype == BF16 else 16) // (8 * T))                      # groups per wave
+    return "float" if dtype == F32 else "unsigned short", S, RP, 2 if waves <= 2 or T // S == 4 else 4 if waves <= 4 else 8, 1
+
+
+def test_every_residual_kernel_is_reached(lib):  # noqa: F811
+    adds = lib["_ZN8sprinter14gemm_adds_rowsEiiii"]
+    reached = set()
+    for dtype in (F32, BF16):
+        for d in WIDTHS:
+            for rows in range(1, 41):
+                for K in {d, 8, 264, 520, 1032, 2048, 4096, 4 * d, 32768}:
+                    if _takes_norm(lib, dtype, d, rows) or adds(dtype, d, K, rows) & 0xFF:
+                        reached.add(_resid_kernel(dtype, d, K, rows))
+    compiled = _compiled(lib, "k_gemm_resid")
+    # its accumulators hold every tile of a column only so
+    assert all(16 // int(rp) >= int(s) or rp == "16" for _, _, s, rp, _, _ in compiled)
+    assert compiled == {(t, arch, str(S), str(RP), str(UG), str(MT)) for t, S, RP, UG, MT in reached for arch in ("0", "1")}
+
+
+@pytest.mark.parametrize("dtype, N, rows", [(BF16, 1600, 33), (BF16, 4096, 40), (F32, 512, 17), (F32, 2112, 1), (F32, 4096, 4)])
+def test_products_without_a_kernel_are_refused(lib, dtype, N, rows):  # noqa: F811
+    null = C.c_void_p(None)
+    for arch in (0, 1):
+        assert not lib[RESID](dtype, arch, null, null, N, 64, null, null, null, rows, null) & 0xFF
