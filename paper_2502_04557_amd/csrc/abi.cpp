@@ -412,7 +412,8 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   auto norm_gemm = [&](const float* g, const float* b, int epi, const void* W, const void* W2, int N, const float* bias, float* out_f32,
                        void* out_act, const EmbedSource* src = nullptr) {
     if (fused) {
-      launch_norm_gemm(dt, md.arch, epi, sc.h, sc.part, g, b, md.eps, src, sc.h, W, W2, N, md.d, bias, out_f32 ? (void*)out_f32 : out_act, max_rows, s);
+      if (!launch_norm_gemm(dt, md.arch, epi, sc.h, sc.part, g, b, md.eps, src, sc.h, W, W2, N, md.d, bias, out_f32 ? (void*)out_f32 : out_act, max_rows, s))
+        ctx->no_kernel = "a product with the norm inside";
     } else {
       norm(g, b, sc.xn, nullptr, src);
       launch_gemm(dt, epi, W, W2, sc.xn, pl_d, rd.n_rows, N, md.d, bias, out_f32, N, out_act, N, max_rows, s);

@@ -99,10 +99,11 @@ void launch_gemm_qkv(const void* W, const void* X, size_t x_elems, const int* n_
 // A pass of few rows (k_gemm_norm.hip).  launch_gemm_resid adds bias + X W^T to the residual rows h[rows, N] and leaves the statistics of the new ones in stat (32 N bytes are enough;
 // NULL: nobody reads them).  gemm_takes_norm: O-projection and FFN-down go through it, QKV and FFN-up through launch_norm_gemm, out = epilogue(norm(h) W^T), which
 // reads them - or, with emb, the rows' embeddings, which it also writes to h_out.  gemm_adds_rows: a product goes through it although the norm behind it is a launch.
-// d, N of launch_gemm_resid: multiples of 64.  It launches nothing and returns false where there is no kernel: more than 32 rows; float32 more than 16, or columns from 2049 on.
+// d, N of launch_gemm_resid: multiples of 64.  Both launch nothing and return false where there is no kernel: outside gemm_takes_norm; launch_gemm_resid at more than 32
+// rows, in float32 at more than 16 or from 2049 columns on.
 bool gemm_takes_norm(int dtype, int d, int rows);
 bool gemm_adds_rows(int dtype, int d, int K, int rows);
-void launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float* stat, const float* g, const float* b, float eps, const EmbedSource* emb,
+bool launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float* stat, const float* g, const float* b, float eps, const EmbedSource* emb,
                       float* h_out, const void* W, const void* W2, int N, int d, const float* bias, void* out, int rows, hipStream_t s);
 bool launch_gemm_resid(int dtype, int arch, const void* W, const void* X, int N, int K, const float* bias, float* h, float* stat, int rows, hipStream_t s);
 

@@ -25,7 +25,28 @@ __device__ __forceinline__ float last_lane(float v) { return __uint_as_float(__b
 // Column groups of the statistics: 16 / split columns each, at most 256 groups where a product reads them.  float32 rows hold their k side by side, so four columns
 // fill lines too: 512 x 2048, 1 row 5.0 -> 4.0 us, 8 rows 6.0 -> 5.4 but the norms behind it lose that again.  From 2049 columns on 16 stay ahead, also
 // where nobody reads the statistics: us per layer with 16 / 8 columns per workgroup, 2112 columns, 8 / 16 / 32 rows 47.3 / 52.6 / 65.8, 49.5 / 58.4 / 73.1; 3072 69.2 / 78.7 / 92.3, 72.9 / 84.6 / 103.6.
-static __host__ __device__ inline int resid_split(bool bf16, int N, int rows) { return N > 2048 ? 1 : !bf16 && N <= 1024 && rows <= 4 ? 4 : 2; }
+static __host__ __device__ constexpr int resid_split(bool bf16, int N, int rows) { return N > 2048 ? 1 : !bf16 && N <= 1024 && rows <= 4 ? 4 : 2; }
+
+// What k_norm_gemm takes: rows per thread RT and groups of threads RG, 8 columns a thread; RT = 0: no kernel.  The rule of gemm_takes_norm is this one, so that no
+// row count is taken that a kernel does not hold.
+struct NormShape { int rt, rg; };
+static constexpr NormShape norm_shape(bool bf16, int d, int rows) {
+  const int rg = d <= 512 ? 8 : d <= 1024 ? 4 : d <= 2048 ? 2 : 1, most = d > (bf16 ? 4096 : 2048) ? 0 : bf16 && rg < 8 ? 4 : 2;
+  int rt = 1;
+  while (rt * rg < rows) rt *= 2;
+  return {rt <= most ? rt : 0, rg};
+}
+static __host__ __device__ constexpr int norm_stat_loads(bool bf16, int rg) { return bf16 ? (rg >= 2 ? 8 / rg : 4) : rg == 8 ? 2 : 4; }   // of 64 column groups, for a row's statistics
+static constexpr bool norm_shapes_hold() {
+  for (int bf16 = 0; bf16 < 2; ++bf16)
+    for (int d = 64; d <= 8192; d += 64)
+      for (int rows = 1; rows <= 40; ++rows) {
+        const NormShape f = norm_shape(bf16, d, rows);
+        if (f.rt && (f.rt * f.rg < rows || f.rt * f.rg > 16 || 512 / f.rg * 8 < d || d / 16 * resid_split(bf16, d, rows) > 64 * norm_stat_loads(bf16, f.rg))) return false;
+      }
+  return true;
+}
+static_assert(norm_shapes_hold(), "rows, columns or statistics that a kernel does not hold");
 
 // A chain of short dependent launches is what a pass of few rows is, and the norm as a launch of its own two of a layer's seven: 3 - 4 us for a few KiB of
 // work.  Every workgroup of the product that follows can normalise the rows for itself, if that is cheap: here it reads them once, in one piece, with
@@ -47,7 +68,7 @@ __global__ __launch_bounds__(512) void k_norm_gemm(const float* h, const float* 
   constexpr bool BF = sizeof(AT) == 2;
   constexpr bool DUAL = EPI == EPI_SWIGLU, ACT_OUT = BF && EPI != EPI_F32;
   constexpr int R = RT * RG, CG = 512 / RG, WR = 8 / RG, NW = NTW * (DUAL ? 2 : 1), NI4 = NW * 4, SR = (R + 7) / 8;
-  constexpr int U = (BF ? 1 : 2) * 16 / RG > 8 ? 8 : (BF ? 1 : 2) * 16 / RG, NG = BF ? (RG >= 2 ? 8 / RG : 4) : RG == 8 ? 2 : 4;   // units in flight; loads of a row's statistics
+  constexpr int U = (BF ? 1 : 2) * 16 / RG > 8 ? 8 : (BF ? 1 : 2) * 16 / RG, NG = norm_stat_loads(BF, RG);   // units in flight; loads of a row's statistics
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ float2 s_stat[R];
   __shared__ float s_part[2][R][WR];
@@ -387,10 +408,7 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
 // The line: us per layer, seven launches / five.  1600 columns: 8 rows 34.2 / 30.6, 10 rows 35.9 / 35.7, 16 rows 38.4 / 38.9; 2048 (gate + up): 8 rows 43.6 / 38.6, 10 rows 44.1 / 44.6;
 // 4096: 4 rows 96.5 / 85.3, 5 rows 92.9 / 96.8; 768: 16 rows 25.6 / 23.4; 1024: 16 rows 28.8 / 27.2.  (Activations of more than 8 rows fill an operand; 5 rows of 4096 in
 // every thread leave one workgroup per compute unit.)  float32 rows take twice the LDS.
-bool gemm_takes_norm(int dtype, int d, int rows) {
-  if (dtype == 0) return rows <= (d <= 512 ? 16 : d <= 1024 ? 8 : d <= 2048 ? 4 : 0);
-  return rows <= (d <= 1024 ? 16 : d <= 2048 ? 8 : d <= 4096 ? 4 : 0);
-}
+bool gemm_takes_norm(int dtype, int d, int rows) { return norm_shape(dtype != 0, d, rows).rt != 0; }
 // Whether a product of K adds itself to the residual rows although the norm behind it is a launch.  Its workgroups have all of K, and one of them fills a compute unit: what decides
 // is how many of those the last round of 16 columns per workgroup leaves idle, where K in shares would fill them, and how much K there is.  us per layer of a target pass of 4 to 16
 // layers, K in shares / added (O-projection and FFN-down changed one at a time; two runs of one side differ by 0.3 %):
@@ -413,49 +431,42 @@ bool gemm_adds_rows(int dtype, int d, int K, int rows) {
 struct NormGemmArgs { const float *h, *stat, *g; const void *second, *W; const float* bias; void* out; int d, N, n_tiles, rows; float eps; RowSource from; };
 
 template <typename AT, int ARCH, int NTW, int EPI, bool EMB>
-static void launch_norm_gemm_rows(const NormGemmArgs& a, hipStream_t s) {
+static bool launch_norm_gemm_rows(const NormGemmArgs& a, hipStream_t s) {
   std::conditional_t<EMB, RowSource, Nothing> from;
   if constexpr (EMB) from = a.from;
-  const dim3 grid((a.n_tiles + NTW - 1) / NTW + (EMB && ARCH == 1 ? 1 : 0));
-#define SPRINTER_NG(RT, RG)                                                                                  \
-  do {                                                                                                       \
-    const size_t lds = sizeof(AT) == 2 ? (size_t)RT * RG * a.d * 2 : (size_t)RT * RG * (a.d + 4) * 4;          \
-    hipLaunchKernelGGL((k_norm_gemm<AT, ARCH, RT, RG, NTW, EPI, EMB>), grid, dim3(512), lds, s, a.h, a.stat, a.g, a.second, a.W, a.d, a.rows, a.N, a.eps, a.out, a.bias, from);           \
-  } while (0)
   constexpr bool BF = sizeof(AT) == 2;
-  if constexpr (NTW == 1) {
-    if (a.d <= 512) { if (a.rows <= 8) SPRINTER_NG(1, 8); else SPRINTER_NG(2, 8); return; }
-    if (a.d <= 1024) {
-      if (a.rows <= 4) { SPRINTER_NG(1, 4); return; }
-      if (a.rows <= 8) { SPRINTER_NG(2, 4); return; }
-      if constexpr (BF) { SPRINTER_NG(4, 4); return; }
-    }
-    if constexpr (BF)
-      if (a.d > 2048) { if (a.rows <= 1) SPRINTER_NG(1, 1); else if (a.rows <= 2) SPRINTER_NG(2, 1); else SPRINTER_NG(4, 1); return; }
+  const dim3 grid((a.n_tiles + NTW - 1) / NTW + (EMB && ARCH == 1 ? 1 : 0));
+  const NormShape f = norm_shape(BF, a.d, a.rows);
+#define SPRINTER_NG(RT, RG)                                                                                  \
+  if (f.rt == RT && f.rg == RG) {                                                                            \
+    const size_t lds = BF ? (size_t)RT * RG * a.d * 2 : (size_t)RT * RG * (a.d + 4) * 4;                        \
+    hipLaunchKernelGGL((k_norm_gemm<AT, ARCH, RT, RG, NTW, EPI, EMB>), grid, dim3(512), lds, s, a.h, a.stat, a.g, a.second, a.W, a.d, a.rows, a.N, a.eps, a.out, a.bias, from);           \
+    return true;                                                                                             \
   }
-  if (a.rows <= 2) { SPRINTER_NG(1, 2); return; }
-  if (a.rows <= 4) { SPRINTER_NG(2, 2); return; }
-  if constexpr (BF) SPRINTER_NG(4, 2);
+  if constexpr (NTW == 1) {
+    SPRINTER_NG(1, 8) SPRINTER_NG(2, 8) SPRINTER_NG(1, 4) SPRINTER_NG(2, 4)
+    if constexpr (BF) { SPRINTER_NG(4, 4) SPRINTER_NG(1, 1) SPRINTER_NG(2, 1) SPRINTER_NG(4, 1) }
+  }
+  SPRINTER_NG(1, 2) SPRINTER_NG(2, 2)
+  if constexpr (BF) SPRINTER_NG(4, 2)
 #undef SPRINTER_NG
+  return false;
 }
 
 template <typename AT, int ARCH>
-static void launch_norm_gemm_arch(int epi, bool emb, const NormGemmArgs& a, hipStream_t s) {
+static bool launch_norm_gemm_arch(int epi, bool emb, const NormGemmArgs& a, hipStream_t s) {
   constexpr int ACT = ARCH == 0 ? EPI_GELU : EPI_SWIGLU;
   if constexpr (sizeof(AT) == 2) {
     if (a.n_tiles >= 256 && a.d > 1024 && a.d <= 2048) {   // two column tiles per wave, as k_gemm16
-      if (epi != EPI_F32) launch_norm_gemm_rows<AT, ARCH, 2, ACT, false>(a, s);
-      else if (emb) launch_norm_gemm_rows<AT, ARCH, 2, EPI_F32, true>(a, s);
-      else launch_norm_gemm_rows<AT, ARCH, 2, EPI_F32, false>(a, s);
-      return;
+      if (epi != EPI_F32) return launch_norm_gemm_rows<AT, ARCH, 2, ACT, false>(a, s);
+      return emb ? launch_norm_gemm_rows<AT, ARCH, 2, EPI_F32, true>(a, s) : launch_norm_gemm_rows<AT, ARCH, 2, EPI_F32, false>(a, s);
     }
   }
-  if (epi != EPI_F32) launch_norm_gemm_rows<AT, ARCH, 1, ACT, false>(a, s);
-  else if (emb) launch_norm_gemm_rows<AT, ARCH, 1, EPI_F32, true>(a, s);
-  else launch_norm_gemm_rows<AT, ARCH, 1, EPI_F32, false>(a, s);
+  if (epi != EPI_F32) return launch_norm_gemm_rows<AT, ARCH, 1, ACT, false>(a, s);
+  return emb ? launch_norm_gemm_rows<AT, ARCH, 1, EPI_F32, true>(a, s) : launch_norm_gemm_rows<AT, ARCH, 1, EPI_F32, false>(a, s);
 }
 
-void launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float* stat, const float* g, const float* b, float eps, const EmbedSource* emb,
+bool launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float* stat, const float* g, const float* b, float eps, const EmbedSource* emb,
                       float* h_out, const void* W, const void* W2, int N, int d, const float* bias, void* out, int rows, hipStream_t s) {
   NormGemmArgs a;
   memset(&a, 0, sizeof a);
@@ -463,8 +474,8 @@ void launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float*
   a.d = d; a.N = N; a.n_tiles = (N + 15) / 16; a.rows = rows; a.eps = eps;
   a.from.h_out = h_out;
   if (emb) a.from.emb = *emb;
-  if (dtype == 0) { if (arch == 0) launch_norm_gemm_arch<float, 0>(epi, emb, a, s); else launch_norm_gemm_arch<float, 1>(epi, emb, a, s); }
-  else { if (arch == 0) launch_norm_gemm_arch<bf16_t, 0>(epi, emb, a, s); else launch_norm_gemm_arch<bf16_t, 1>(epi, emb, a, s); }
+  if (dtype == 0) return arch == 0 ? launch_norm_gemm_arch<float, 0>(epi, emb, a, s) : launch_norm_gemm_arch<float, 1>(epi, emb, a, s);
+  return arch == 0 ? launch_norm_gemm_arch<bf16_t, 0>(epi, emb, a, s) : launch_norm_gemm_arch<bf16_t, 1>(epi, emb, a, s);
 }
 
 struct ResidArgs { const void *W, *X; float *h, *stat; const float* bias; int N, K, rows; };

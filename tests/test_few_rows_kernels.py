@@ -51,3 +51,31 @@ def test_products_without_a_kernel_are_refused(lib, dtype, N, rows):  # noqa: F8
     null = C.c_void_p(None)
     for arch in (0, 1):
         assert not lib[RESID](dtype, arch, null, null, N, 64, null, null, null, rows, null) & 0xFF
+
+
+def test_every_kernel_with_the_norm_inside_is_reached(lib):  # noqa: F811
+    reached = set()
+    for dtype in (F32, BF16):
+        for d in WIDTHS:
+            for rows in range(1, 41):
+                if not _takes_norm(lib, dtype, d, rows):
+                    continue
+                RG = 8 if d <= 512 else 4 if d <= 1024 else 2 if d <= 2048 else 1    # groups of 512 / RG threads of 8 columns
+                RT = 1 if rows <= RG else 2 if rows <= 2 * RG else 4
+                assert RT * RG >= rows and 4096 // RG >= d
+                for tiles in (1, 2) if dtype == BF16 and 1024 < d <= 2048 else (1,):   # column tiles per wave
+                    for arch in (0, 1):
+                        for epi, emb in ((2 + arch, "false"), (0, "false"), (0, "true")):
+                            reached.add(("float" if dtype == F32 else "unsigned short", str(arch), str(RT), str(RG), str(tiles), str(epi), emb))
+    assert _compiled(lib, "k_norm_gemm") == reached
+
+
+@pytest.mark.parametrize("dtype, d, rows", [(F32, 512, 17), (F32, 1024, 9), (F32, 2048, 5), (F32, 2112, 1), (BF16, 1024, 17), (BF16, 2048, 9), (BF16, 4096, 5), (BF16, 4160, 1)])
+def test_norms_without_a_kernel_are_refused(lib, dtype, d, rows):  # noqa: F811
+    """One row beyond each limit, and one column: nothing is launched, neither on fewer rows nor not at all without a word."""
+    assert not _takes_norm(lib, dtype, d, rows)
+    null = C.c_void_p(None)
+    for arch in (0, 1):
+        for epi in (0, 2 + arch):
+            for N in (192, 8192):
+                assert not lib[NORM_GEMM](dtype, arch, epi, null, null, null, null, C.c_float(1e-5), null, null, null, null, N, d, null, null, rows, null) & 0xFF
