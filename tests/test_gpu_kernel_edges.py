@@ -56,9 +56,9 @@ def test_float32_matrix_kernels(B, ff):
 @pytest.mark.parametrize("dtype", [W.DT_F32, W.DT_BF16])
 @pytest.mark.parametrize("B", [1, 2, 3, 4, 5])
 def test_norm_inside_the_product(B, dtype):
-    """A few rows: the norm folded into QKV / FFN-up, at its row counts and just beyond, with
-    both norms, gate + up and GELU, column tiles in pairs (>= 256 of them) and ragged; deep enough that both residual
-    buffers and K shares are used.  tau > 1: the target sees the same rows."""
+    """One to five rows: the norm folded into QKV / FFN-up, with both norms, gate + up and GELU and 257 - 265 column tiles (at 2048
+    columns in pairs), a last one that is not full; deep enough that a layer reads the statistics of the one before.  tau > 1: the target
+    sees the same rows.  (The ends of the row counts: test_norm_inside_the_product_at_its_limits.)"""
     _check(_gpt(2, 128, 200, 83), _llama(3, 512, 4, 2, 4104, 83), B, dtype, tau=1.5)
     _check(_llama(3, 640, 10, 5, 136, 83), _gpt(2, 2048 if B == 2 else 1024, 4232, 83), B, dtype, tau=1.5)
 
@@ -66,11 +66,26 @@ def test_norm_inside_the_product(B, dtype):
 @pytest.mark.parametrize("dtype", [W.DT_F32, W.DT_BF16])
 @pytest.mark.parametrize("B", [5, 8, 9, 12, 13, 16, 17])
 def test_norm_inside_the_product_of_narrow_models(B, dtype):
-    """Up to 512 columns the norm is folded in up to 16 rows, four groups of threads with 2, 3 or 4 rows each: the first and last row
+    """Up to 512 columns the norm is folded in up to 16 rows, eight groups of threads with one or two rows each: the first and last row
     counts of each, one row beyond, rows of 128 to 512 columns (a group's threads from a quarter to all in use), heads of 128
-    with rotary factors for 16 rows, column tiles in pairs."""
+    with rotary factors for 16 rows, 257 column tiles and more."""
     _check(_gpt(2, 128, 200, 83), _llama(3, 512, 4, 2, 4104, 83), B, dtype, tau=1.5)
     _check(_llama(2, 320, 5, 5, 136, 83), _gpt(2, 448, 4232, 83), B, dtype, tau=1.5)
+
+
+@pytest.mark.parametrize("dtype", [W.DT_F32, W.DT_BF16])
+@pytest.mark.parametrize("B", [4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("gpt_is_wide", [False, True])
+def test_norm_inside_the_product_at_its_limits(B, dtype, gpt_is_wide):
+    """Both sides of the last row counts with the norm inside: 1024 columns 8 in float32 and 16 in bf16, 2048 columns 4 and 8, each once with LayerNorm and
+    GELU, once with RMSNorm, gate + up and rotary factors.  tau > 1: the target sees the same rows."""
+    takes = lambda d: bool(_host("_ZN8sprinter15gemm_takes_normEiii", dtype, d, B) & 0xFF)
+    f32 = dtype == W.DT_F32
+    assert takes(1024) == (B <= (8 if f32 else 16)) and takes(2048) == (B <= (4 if f32 else 8))
+    if gpt_is_wide:
+        _check(_llama(2, 1024, 16, 4, 264, 83), _gpt(2, 2048, 520, 83), B, dtype, tau=1.5)
+    else:
+        _check(_gpt(2, 1024, 264, 83), _llama(2, 2048, 16, 4, 520, 83), B, dtype, tau=1.5)
 
 
 @pytest.mark.parametrize("B, prompt_len", [(7, 20), (9, 59), (8, 114)])
