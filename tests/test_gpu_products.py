@@ -72,8 +72,18 @@ def _silu(x):
 
 
 def _gelu(x):
+    """0.5 x (1 + tanh u) = x / (1 + exp(-2 u)), which does not cancel: 1 + tanh in 64 bits has no digit left from x = -6 on."""
     with np.errstate(over="ignore", invalid="ignore"):
-        return 0.5 * x * (1.0 + np.tanh(0.7978845608028654 * (x + 0.044715 * x ** 3)))
+        return x / (1.0 + np.exp(-2 * 0.7978845608028654 * (x + 0.044715 * x ** 3)))
+
+
+def _gelu_bound(s):
+    """Float32 error of x - x q (x > 0) or x q, q = e / (1 + e), e = exp(-|2 u|), 2 u = c (x + 0.044715 x^3).  Units of 2^-24: five roundings of 2 u are |2 u| times as much of
+    e, whose own end is within 2; the sum, quotient and product one each, so 5 |2 u| + 5 of x q, and one of the result.  Below 2^-126 e may be zero."""
+    with np.errstate(over="ignore", invalid="ignore"):
+        t = np.abs(1.5957691216057308 * (s + 0.044715 * s ** 3))
+        q = np.exp(-t) / (1 + np.exp(-t))
+        return 2.0 ** -24 * (np.abs(s) * q * (5 * np.minimum(t, 200.0) + 5) + np.abs(_gelu(s))) + np.abs(s) * 2.0 ** -126
 
 
 @pytest.mark.parametrize("rows, N, tile", [(4080, 2048, 0), (2032, 512, 2), (16, 512, None)])
@@ -100,8 +110,7 @@ def test_silu_is_rounded_once(rows, N, tile, lo, hi):
 
 @pytest.mark.parametrize("rows, N, tile", [(4080, 3072, 0), (4080, 2048, 1), (2032, 512, 3), (16, 512, None)])
 def test_gelu_stored_as_float16(rows, N, tile):
-    """GELU (tanh) with a bias, then one rounding to float16: 1 + tanh loses 2^-22 absolutely where tanh is near -1 (the sum's rounding and
-    1 ulp of tanh and its argument), times x / 2; half a float16 spacing (2^-25 below the normal numbers) on top."""
+    """GELU (tanh) with a bias in float32, then one rounding to float16: half a spacing (2^-25 below the normal numbers) on top."""
     import torch
     K = 2 * N + 32
     if tile is not None:
@@ -112,15 +121,15 @@ def test_gelu_stored_as_float16(rows, N, tile):
     bias = torch.empty(N, device="cuda").uniform_(-1, 1, generator=g)
     s = (exact.astype(np.float32) + bias.cpu().numpy()).astype(np.float64)
     got, want = _activation(BF16, EPI_GELU, x, W, None, bias, N, K).astype(np.float64), _gelu(s)
-    bound = np.abs(s) * 2.0 ** -22 + np.maximum(np.abs(want) * 2.0 ** -11, 2.0 ** -25)
+    bound = _gelu_bound(s) + np.maximum(np.abs(want) * 2.0 ** -11, 2.0 ** -25)
     print(rows, N, "worst share of the bound", float((np.abs(got - want) / bound).max()), flush=True)
     assert (np.abs(got - want) <= bound).all()
 
 
 @pytest.mark.parametrize("rows", [16, 48])
 def test_float32_activations_to_their_ends(rows):
-    """Float32 mode: SiLU within 2^-21 down to where its float32 values end (exp(-x) overflows below -88.7), GELU within the bound above;
-    infinities and NaN as the formulas give them."""
+    """Float32 mode: SiLU within 2^-21 down to where its float32 values end (exp(-x) overflows below -88.7), GELU within its own, which is
+    relative on the negative side as well; infinities and NaN as the formulas give them."""
     import torch
     N = 256
     K = N + 4
@@ -142,7 +151,10 @@ def test_float32_activations_to_their_ends(rows):
     got, want = _activation(F32, EPI_GELU, x, W, None, bias, N, K), _gelu(s)
     assert np.array_equal(got[:, :4], want[:, :4].astype(np.float32), equal_nan=True)
     got, want, s = got[:, 4:], want[:, 4:], s[:, 4:]
-    assert (np.abs(got - want) <= np.abs(s) * 2.0 ** -22 + np.abs(want) * 2.0 ** -22).all()
+    off, bound = np.abs(got - want), _gelu_bound(s)
+    low = (s > -6) & (s < -3)
+    print(rows, "GELU, worst share of the bound", float((off[bound > 0] / bound[bound > 0]).max()), "on -6 .. -3", float((off[low] / bound[low]).max()), flush=True)
+    assert (off <= bound).all()
     # x = 3e38 + 3e38 and the negative: infinite sums of the product itself, whose SiLU is infinity and NaN
     x[:, :N] = 0.0
     x[0, :2] = torch.tensor([3e38, -3e38], device="cuda")
