@@ -34,10 +34,11 @@ struct ModelDims {
   float eps, theta;
 };
 
-// Arguments of the kernels of decode steps are single values, not structs, and the 14 words a kernel needs first come first: the compiler marks those for
-// loading into registers with the dispatch (build flag -amdgpu-kernarg-preload-count), which takes a memory round trip, 0.35 us, off every launch in a chain.  They
-// are also few: the host writes them into device memory line by line (in some processes 2.7 us per launch up to 64 bytes, 3.4 - 3.7 from 128 on), and no
-// kernel asks for its grid's size, which brings 256 bytes of hidden arguments.
+// The layers' kernels of decode steps (products, norms, attention but for k_attn_merge) take single values, not structs, and the 14 words a kernel needs first come first: the
+// compiler marks those for loading into registers with the dispatch (build flag -amdgpu-kernarg-preload-count), which takes a memory round trip, 0.35 us, off every launch in a chain.
+// They are also few: the host writes them into device memory line by line (in some processes 2.7 us per launch up to 64 bytes, 3.4 - 3.7 from 128 on), and no such kernel asks for its
+// grid's size, which brings 256 bytes of hidden arguments.  The launches of once a step still take structs: LM heads (LmArgs), decide and finish (DecideArgs, FinishArgs), and the merge of a
+// split attention; so do the kernels of prefill and of speculative rounds.
 struct Nothing {};
 constexpr int PART_SHARES = 8;   // most K shares launch_gemm_part may use
 struct ModelScratch {  // per-model activation buffers, sized for max_batch rows

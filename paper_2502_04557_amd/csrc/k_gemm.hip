@@ -533,8 +533,9 @@ int launch_gemm_part(int dtype, const void* W, const void* X, size_t x_elems, co
     return sk;
   }
   if (max_rows <= 16) {
-    // shares: fill the 256 compute units, at least 12 k tiles per share; long K takes two column tiles per wave
-    const bool two = a.Kt >= 192 && a.n_tiles >= 64;   // (4096x4096: 8.2 us with one tile, 10.5 with two; 4096x11008: 24.1 / 19.8)
+    // shares: fill the 256 compute units, at least 12 k tiles per share; long K takes two column tiles per wave.  us per layer, FFN-down with one / two: 1088 x 4352, 16 rows 31.7 /
+    // 32.3; 2048 x 5504 45.3 / 46.2; 1600 x 6400 39.5 / 39.3; 2560 x 10240, 8 rows 61.2 / 57.9; 5120 x 13824 164.5 / 160.7; 5120 x 20480 162.4 / 154.8; 8192 x 32768, 16 rows 369.2 / 357.8.
+    const bool two = a.Kt >= 192 && a.n_tiles >= 64;
     const int groups = two ? (a.n_tiles + 1) / 2 : a.n_tiles;
     int sk = std::min(4, 256 / groups);              // (4: the norm kernel's smaller partial-sum variant)
     if (sk > max_shares) sk = max_shares;

@@ -65,8 +65,8 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t s) {
 // (bf16 mode: one 16-byte slot of a float16 operand tile), so the row, gain and offset are requested with six 16-byte
 // loads per thread before anything is waited for and the result leaves as one or two 16-byte stores.  d <= 8192.
 // NI = 2048-column blocks per row (1, 2 or 4); SH = 0, or the most partial products a pending update of the
-// residual stream may consist of (1, 2, 4 or 8; one share, which float32 mode and up to 16 rows bf16 mode leave, with the loads of four: 4096
-// columns, 8 rows 3.25 -> 3.70 us; two, which most O-projections leave: 1600 columns, 6 rows 3.0 -> 3.3, 4096 rows of 768 11.1 -> 12.6): the row is then h + bias + share 0 + share 1 + ..., added in that
+// residual stream may consist of (1, 2, 4 or 8; one share, which float32 mode leaves and bf16 mode at up to 16 rows of more than 4096 columns, with the loads of four:
+// 4096 columns, 8 rows 3.25 -> 3.70 us; two, which most O-projections of 9 - 16 rows leave: 1600 columns, 6 rows 3.0 -> 3.3, 4096 rows of 768 11.1 -> 12.6): the row is then h + bias + share 0 + share 1 + ..., added in that
 // order, written back and normalised.  The partial loads are issued with the others, before the row count
 // is known, with clamped share indices and the surplus selected away - no branch, no second memory round.
 // SH = -1: the first norm of a forward; the row is the token's embedding (+ the position's) and starts the residual stream
