@@ -388,7 +388,7 @@ void forward(sprinter_ctx* ctx, Model& m, const RowDesc& rd, int max_rows, bool 
   const size_t part_stride = (size_t)rows * md.d;
   // a few rows: they add themselves, and the norms before QKV and FFN-up are part of those launches (the rows' statistics lie in part,
   // which the attention only takes between a layer's QKV and its O-proj)
-  const bool fused = !shared_caches && gemm_takes_norm(dt, md.d, max_rows);
+  const bool fused = !shared_caches && md.ff <= FEW_ROWS_MAX_K && gemm_takes_norm(dt, md.d, max_rows);
   // Short passes (work lists, speculative windows) of a model without rotary positions: the projection's epilogue puts keys and values
   // where the append launch would.  (A key's rotary partner is another workgroup's; and a prefill pass gathers 8 slots of a value column
   // into one store in that launch, where an epilogue would write 2 bytes at a time.)

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stddef.h>
+#include "offsets.h"
 
 namespace sprinter {
 
@@ -101,7 +102,7 @@ void launch_gemm_qkv(const void* W, const void* X, size_t x_elems, const int* n_
 // NULL: nobody reads them).  gemm_takes_norm: O-projection and FFN-down go through it, QKV and FFN-up through launch_norm_gemm, out = epilogue(norm(h) W^T), which
 // reads them - or, with emb, the rows' embeddings, which it also writes to h_out.  gemm_adds_rows: a product goes through it although the norm behind it is a launch.
 // d, N of launch_gemm_resid: multiples of 64.  Both launch nothing and return false where there is no kernel: outside gemm_takes_norm; launch_gemm_resid at more than 32
-// rows, in float32 at more than 16 or from 2049 columns on.
+// rows or FEW_ROWS_MAX_K of K, in float32 at more than 16 rows or from 2049 columns on.
 bool gemm_takes_norm(int dtype, int d, int rows);
 bool gemm_adds_rows(int dtype, int d, int K, int rows);
 bool launch_norm_gemm(int dtype, int arch, int epi, const float* h, const float* stat, const float* g, const float* b, float eps, const EmbedSource* emb,

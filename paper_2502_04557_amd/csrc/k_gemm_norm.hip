@@ -2,7 +2,6 @@
 // themselves to the residual rows and leave the statistics of what they wrote (k_gemm_resid); QKV projection and FFN-up normalise
 // those rows for themselves (k_norm_gemm).
 #include "gemm.h"
-#include "offsets.h"
 #include <algorithm>
 #include <cstring>
 #include <type_traits>
@@ -420,7 +419,7 @@ bool gemm_takes_norm(int dtype, int d, int rows) { return norm_shape(dtype != 0,
 //   95.2 / 100.3 -> 96.8 / 102.4; 3840 102.1 / 107.8 -> 103.0 / 109.8; 4096 109.5 / 120.1 -> 109.4 / 118.2 (28 - 32 rows 1 % behind); 8192 347.1 / 370.0 -> 349.9 / 376.5; 5120, 24 rows 178.4 -> 194.6.
 // - K of at most 2048: 17 - 32 rows, FFN-down of 768 (2048), 24 rows 32.4 -> 32.0, of 640 (1728) 30.4 -> 29.8; 1600 columns, 6400 of K 12.6 -> 13.1; 256 columns 6.2 -> 6.3.
 bool gemm_adds_rows(int dtype, int d, int K, int rows) {
-  if (dtype == 0 || d <= 512 || rows > 32) return false;
+  if (dtype == 0 || d <= 512 || rows > 32 || K > FEW_ROWS_MAX_K) return false;
   if (K <= 2048) return d > 2048 || rows > 16;
   if (d <= 2048) return false;
   if (2 * K <= 3 * d) return rows <= (d <= 4096 ? 32 : d <= 5120 ? 16 : 8);
@@ -510,6 +509,7 @@ static bool launch_gemm_resid_arch(const ResidArgs& a, hipStream_t s) {
   else return S == 4 ? launch_gemm_resid_split<AT, ARCH, 4>(a, s) : S == 2 && launch_gemm_resid_split<AT, ARCH, 2>(a, s);
 }
 bool launch_gemm_resid(int dtype, int arch, const void* W, const void* X, int N, int K, const float* bias, float* h, float* stat, int rows, hipStream_t s) {
+  if (K > FEW_ROWS_MAX_K) return false;
   const ResidArgs a{W, X, h, stat, bias, N, K, rows};
   if (dtype == 0) return arch == 0 ? launch_gemm_resid_arch<float, 0>(a, s) : launch_gemm_resid_arch<float, 1>(a, s);
   return arch == 0 ? launch_gemm_resid_arch<bf16_t, 0>(a, s) : launch_gemm_resid_arch<bf16_t, 1>(a, s);

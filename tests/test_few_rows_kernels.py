@@ -79,3 +79,12 @@ def test_norms_without_a_kernel_are_refused(lib, dtype, d, rows):  # noqa: F811
         for epi in (0, 2 + arch):
             for N in (192, 8192):
                 assert not lib[NORM_GEMM](dtype, arch, epi, null, null, null, null, C.c_float(1e-5), null, null, null, null, N, d, null, null, rows, null) & 0xFF
+
+
+@pytest.mark.parametrize("dtype, d", [(F32, 64), (BF16, 64), (BF16, 4096)])
+def test_longer_k_than_the_offsets_hold_stays_in_shares(lib, dtype, d):  # noqa: F811
+    """d_ff has no limit of its own, and the buffers' sizes and offsets are 32 bits (16 float32 rows of 2^25 are 2^31 bytes)."""
+    adds, null = lib["_ZN8sprinter14gemm_adds_rowsEiiii"], C.c_void_p(None)
+    for K in ((1 << 20) + 8, 1 << 25, 1 << 28):
+        assert not adds(dtype, d, K, 5) & 0xFF
+        assert not lib[RESID](dtype, 0, null, null, d, K, null, null, null, 5, null) & 0xFF

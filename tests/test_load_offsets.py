@@ -14,7 +14,8 @@ constexpr bool beyond(int K, int ku, int bytes, unsigned lane, unsigned size) {
     if (unit_offset(false, lane, u, bytes) < size || unit_offset(true, NOWHERE, u, bytes) < size) return false;
   return true;
 }
-constexpr int KS[] = {8, 96, 8192, 32768, 1 << 20};
+constexpr int KS[] = {8, 96, 8192, 32768, FEW_ROWS_MAX_K};
+static_assert(64LL * FEW_ROWS_MAX_K < NOWHERE, "a buffer reaches NOWHERE");
 constexpr bool all() {
   for (int K : KS) {
     const int kt = (K + 31) / 32;
