@@ -406,7 +406,8 @@ __global__ __launch_bounds__(512) void k_gemm_resid(const void* W, const void* X
 
 // The line: us per layer, seven launches / five.  1600 columns: 8 rows 34.2 / 30.6, 10 rows 35.9 / 35.7, 16 rows 38.4 / 38.9; 2048 (gate + up): 8 rows 43.6 / 38.6, 10 rows 44.1 / 44.6;
 // 4096: 4 rows 96.5 / 85.3, 5 rows 92.9 / 96.8; 768: 16 rows 25.6 / 23.4; 1024: 16 rows 28.8 / 27.2.  (Activations of more than 8 rows fill an operand; 5 rows of 4096 in
-// every thread leave one workgroup per compute unit.)  float32 rows take twice the LDS.
+// every thread leave one workgroup per compute unit.)  float32 rows take twice the LDS: seven / five launches, 256 columns, 16 rows
+// 26.0 / 23.0, 512 30.8 / 27.8; 1024, 8 rows 40.0 / 35.5 (gate + up 40.5 / 37.5); 1536, 4 rows 65.4 / 53.5; 2048 72.6 / 67.0.  bf16, 2112 - 3584 columns, 4 rows: 46.6 / 45.5 to 85.0 / 79.1.
 bool gemm_takes_norm(int dtype, int d, int rows) { return norm_shape(dtype != 0, d, rows).rt != 0; }
 // Whether a product of K adds itself to the residual rows although the norm behind it is a launch.  Its workgroups have all of K, and one of them fills a compute unit: what decides
 // is how many of those the last round of 16 columns per workgroup leaves idle, where K in shares would fill them, and how much K there is.  us per layer of a target pass of 4 to 16
